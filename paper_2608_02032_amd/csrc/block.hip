@@ -305,15 +305,128 @@ __global__ __launch_bounds__(256) void k_conv1d_silu_bwd(
     pr[4] = ab;
 }
 
+// The same for four consecutive channels per thread (8-byte rows of bf16, 16
+// of fp32, 16-byte gradients): used when the channel count, the row strides
+// and the pointers are multiples of 4 elements.  HBM-bound, every input read
+// once plus three tokens of overlap per run: 587 MB at 32768 tokens of 1792
+// bf16 channels take about 140 us (4.2 TB/s; 154 with one channel per thread and
+// 2-byte loads; runs of 16 tokens 162, of 64 the same).
+template <typename T>
+__global__ __launch_bounds__(64) void k_conv1d_silu_bwd_v4(
+    const T* __restrict__ in, int64_t stride, const float* __restrict__ w,
+    const float* __restrict__ bias, const float* __restrict__ st_in,
+    const float* __restrict__ dout, float* __restrict__ din, int64_t dstride,
+    float* __restrict__ dst_in, float* __restrict__ part, int64_t L, int C, int nruns) {
+    const int c0 = (blockIdx.x * 64 + threadIdx.x) * 4;
+    const int run = blockIdx.y;
+    const int64_t b = blockIdx.z;
+    if (c0 >= C) return;
+    const int64_t t0 = (int64_t)run * kConvBwdTok;
+    const int64_t t1 = t0 + kConvBwdTok < L ? t0 + kConvBwdTok : L;
+    float wk[4][4], bc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        load4(w + (c0 + i) * 4, wk[i]);
+        bc[i] = bias ? bias[c0 + i] : 0.f;
+    }
+    const T* src = in + (b * L) * stride + c0;
+    const float* dsrc = dout + (b * L) * C + c0;
+    float* dd = din + (b * L) * dstride + c0;
+    float win[3][4];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const int64_t s = t0 - 3 + k;
+        if (s >= 0) {
+            load4(src + s * stride, win[k]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                win[k][i] = st_in ? st_in[(b * C + c0 + i) * 3 + (3 + s)] : 0.f;
+        }
+    }
+    float q[3][4];  // du at t-3, t-2, t-1 (zero before t0)
+    float acc[4][5];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        q[0][i] = q[1][i] = q[2][i] = 0.f;
+#pragma unroll
+        for (int k = 0; k < 5; ++k) acc[i][k] = 0.f;
+    }
+    // token t (own: t < t1; the three after it complete din of the last own
+    // tokens; beyond L du is zero): du, the weight sums and din of token t - 3
+    auto step = [&](int64_t t, bool own, bool inside) {
+        float v[4] = {0.f, 0.f, 0.f, 0.f}, dv[4] = {0.f, 0.f, 0.f, 0.f}, o[4];
+        if (inside) {
+            load4(src + t * stride, v);
+            load4(dsrc + t * C, dv);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float u = bc[i] + wk[i][0] * win[0][i] + wk[i][1] * win[1][i] + wk[i][2] * win[2][i] + wk[i][3] * v[i];
+            const float du = dv[i] * silu_grad_f(u);
+            if (own) {
+                acc[i][0] += du * win[0][i];
+                acc[i][1] += du * win[1][i];
+                acc[i][2] += du * win[2][i];
+                acc[i][3] += du * v[i];
+                acc[i][4] += du;
+            }
+            o[i] = wk[i][3] * q[0][i] + wk[i][2] * q[1][i] + wk[i][1] * q[2][i] + wk[i][0] * du;
+            q[0][i] = q[1][i];
+            q[1][i] = q[2][i];
+            q[2][i] = du;
+            win[0][i] = win[1][i];
+            win[1][i] = win[2][i];
+            win[2][i] = v[i];
+        }
+        if (t - 3 >= t0 && t - 3 < t1) store4(dd + (t - 3) * dstride, o);
+        if (dst_in && t0 == 0 && t == 2) {
+            // du of tokens 0, 1 and 2 stand in q
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float* ds = dst_in + (b * C + c0 + i) * 3;
+                ds[0] = q[0][i] * wk[i][0];
+                ds[1] = q[0][i] * wk[i][1] + q[1][i] * wk[i][0];
+                ds[2] = q[0][i] * wk[i][2] + q[1][i] * wk[i][1] + q[2][i] * wk[i][0];
+            }
+        }
+    };
+#pragma unroll 4
+    for (int64_t t = t0; t < t1; ++t) step(t, true, true);
+    for (int64_t t = t1; t < t1 + 3; ++t) step(t, false, t < L);
+    float* pr = part + ((b * nruns + run) * (int64_t)C + c0) * 5;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        float o[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = acc[(4 * k + i) / 5][(4 * k + i) % 5];
+        store4(pr + 4 * k, o);
+    }
+}
+
 // Sum of nparts partial rows of K floats per item: out[i][k] = sum_p part[p][i][k].
-__global__ __launch_bounds__(256) void k_sum_parts(const float* __restrict__ part,
-                                                   int64_t nparts, int64_t width,
-                                                   float* __restrict__ out, int K, int keep,
-                                                   float* __restrict__ out2) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= width) return;
+// A block serves 64 columns with 16 waves, each adding every 16th row, and
+// adds the waves' sums in a fixed order.  The kernel is bound by the latency of
+// its loads: one thread per column walking all rows serially took 274 us per
+// call at 1024 rows of 8960 columns (35 blocks), this split 9 us.
+constexpr int kSumLanes = 16;
+__global__ __launch_bounds__(64 * kSumLanes) void k_sum_parts(const float* __restrict__ part,
+                                                              int64_t nparts, int64_t width,
+                                                              float* __restrict__ out, int K, int keep,
+                                                              float* __restrict__ out2) {
+    __shared__ float s_sum[kSumLanes][64];
+    const int col = threadIdx.x & 63, pl = threadIdx.x >> 6;
+    const int64_t i = (int64_t)blockIdx.x * 64 + col;
     float s = 0.f;
-    for (int64_t p = 0; p < nparts; ++p) s += part[p * width + i];
+    if (i < width) {
+#pragma unroll 8
+        for (int64_t p = pl; p < nparts; p += kSumLanes) s += part[p * width + i];
+    }
+    s_sum[pl][col] = s;
+    __syncthreads();
+    if (pl != 0 || i >= width) return;
+#pragma unroll
+    for (int k = 1; k < kSumLanes; ++k) s += s_sum[k][col];
     // items of K values: the first `keep` go to out ([item][keep]), the rest
     // (at most one) to out2 ([item])
     const int64_t item = i / K;
@@ -324,74 +437,103 @@ __global__ __launch_bounds__(256) void k_sum_parts(const float* __restrict__ par
         out2[item] = s;
     }
 }
+inline unsigned sum_blocks(int64_t width) { return (unsigned)((width + 63) / 64); }
 
 // dt = softplus(raw + bias): draw = ddt sigmoid(raw + bias), dbias = sum over
-// rows.  One thread per (head, block of 256 rows).
+// rows.  A block serves kDtRows rows of up to 256 heads: its threads tile
+// (rows at a time) x heads, so that few heads still fill the block, and each
+// head's row sums meet in LDS in a fixed order.  Latency-bound: with one thread
+// per head walking the 256 rows serially, 24 heads and 32768 rows took 118 us
+// (24 of 256 threads active), this tiling 9 us.
 constexpr int kDtRows = 256;
+constexpr int kDtThreads = 1024;
 template <typename T>
-__global__ __launch_bounds__(256) void k_dt_softplus_bwd(const T* __restrict__ raw, int64_t stride,
+__global__ __launch_bounds__(kDtThreads) void k_dt_softplus_bwd(const T* __restrict__ raw, int64_t stride,
                                                          const float* __restrict__ bias,
                                                          const float* __restrict__ ddt,
                                                          float* __restrict__ draw,
                                                          int64_t dstride, float* __restrict__ part,
                                                          int64_t rows, int H) {
-    const int h = blockIdx.x * 256 + threadIdx.x;
+    __shared__ float s_acc[kDtThreads];
+    const int h0 = blockIdx.x * 256;
+    const int hc = H - h0 < 256 ? H - h0 : 256;  // heads of this block
+    const int nrl = kDtThreads / hc;             // rows at a time
+    const int rl = threadIdx.x / hc, h = h0 + threadIdx.x % hc;
     const int64_t rb = blockIdx.y;
-    if (h >= H) return;
     const int64_t r0 = rb * kDtRows;
     const int64_t r1 = r0 + kDtRows < rows ? r0 + kDtRows : rows;
-    const float bh = bias ? bias[h] : 0.f;
     float acc = 0.f;
-    for (int64_t r = r0; r < r1; ++r) {
-        const float v = to_f(raw[r * stride + h]) + bh;
-        const float g = ddt[r * H + h] / (1.0f + __expf(-v));
-        draw[r * dstride + h] = g;
-        acc += g;
+    if (rl < nrl) {
+        const float bh = bias ? bias[h] : 0.f;
+#pragma unroll 4
+        for (int64_t r = r0 + rl; r < r1; r += nrl) {
+            const float v = to_f(raw[r * stride + h]) + bh;
+            const float g = ddt[r * H + h] / (1.0f + __expf(-v));
+            draw[r * dstride + h] = g;
+            acc += g;
+        }
     }
+    s_acc[threadIdx.x] = acc;
+    __syncthreads();
+    if ((int)threadIdx.x >= hc) return;
+    for (int k = 1; k < nrl; ++k) acc += s_acc[k * hc + threadIdx.x];
     part[rb * H + h] = acc;
 }
 
-// Gated RMSNorm backward, one wave per (block of kNormRows rows, group); the
-// group's channels (at most 2048) stay in registers, 8 per lane per piece.
+// Gated RMSNorm backward, one block per (kNormRows rows, group), its four
+// waves taking every fourth row; a row's channels of the group (at most 2048:
+// KEEP pieces of 256, 4 channels per lane) stay in registers between the sums
+// and the gradients, so every input is read once.
 // With u = y SiLU(z), inv = (mean u^2 + eps)^-1/2, g = dout (.) w:
 //   du = inv g - u inv^3 (g . u) / group,  dy = du SiLU(z),
 //   dz = du y SiLU'(z),  dw += dout u inv (summed over the block's rows).
+// HBM-bound: 805 MB at 32768 rows of 1536 bf16 channels take 160 us (5.0
+// TB/s).  KEEP fits the group, so short groups keep more waves resident; 16 rows
+// go to four waves, and a lane's stores are 16 bytes so that a wave's cover
+// whole lines.  (One wave per 16 rows, reading the inputs twice: 229 us;
+// 8 channels per lane, whose stores leave every other 16 bytes to the next
+// instruction: 265 us; ordinary loads 172 us, nontemporal stores 187 us.)
 constexpr int kNormRows = 16;
-template <typename T>
+template <typename T, int KEEP>
 __global__ __launch_bounds__(256) void k_gated_rmsnorm_bwd(
     const T* __restrict__ y, const T* __restrict__ z, int64_t zstride, const float* __restrict__ w,
     float eps, const float* __restrict__ dout, float* __restrict__ dy, float* __restrict__ dz,
     int64_t dzstride, float* __restrict__ part, int64_t rows, int D, int group) {
-    const int lane = threadIdx.x & 63;
-    const int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    __shared__ float s_w[3][KEEP * 256];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ngr = D / group;
-    const int64_t nrb = (rows + kNormRows - 1) / kNormRows;
-    if (item >= nrb * ngr) return;
-    const int64_t rb = item / ngr;
-    const int g0 = (int)(item - rb * ngr) * group;
-    constexpr int KEEP = 4;
-    float wacc[KEEP][8];
+    const int64_t rb = blockIdx.x / ngr;
+    const int g0 = (int)(blockIdx.x - rb * ngr) * group;
+    float wacc[KEEP][4], wv[KEEP][4];
 #pragma unroll
-    for (int q = 0; q < KEEP; ++q)
+    for (int q = 0; q < KEEP; ++q) {
+        const int k = lane * 4 + q * 256;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) wacc[q][i] = 0.f;
+        for (int i = 0; i < 4; ++i) {
+            wacc[q][i] = 0.f;
+            wv[q][i] = w && k < group ? w[g0 + k + i] : 1.f;
+        }
+    }
     const int64_t r1 = (rb + 1) * kNormRows < rows ? (rb + 1) * kNormRows : rows;
-    for (int64_t r = rb * kNormRows; r < r1; ++r) {
-        float u[KEEP][8], g[KEEP][8], ss = 0.f, gu = 0.f;
+    for (int64_t r = rb * kNormRows + wave; r < r1; r += 4) {
+        float yv[KEEP][4], zv[KEEP][4], dv[KEEP][4], ss = 0.f, gu = 0.f;
 #pragma unroll
         for (int q = 0; q < KEEP; ++q) {
-            const int k = lane * 8 + q * 512;
+            const int k = lane * 4 + q * 256;
             if (k < group) {
-                float yv[8], zv[8], dv[8];
-                load8(y + r * D + g0 + k, yv);
-                load8(z + r * zstride + g0 + k, zv);
-                load8(dout + r * D + g0 + k, dv);
+                load4_nt(y + r * D + g0 + k, yv[q]);
+                load4_nt(z + r * zstride + g0 + k, zv[q]);
+                load4_nt(dout + r * D + g0 + k, dv[q]);
+            }
+        }
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    u[q][i] = yv[i] * silu_rcp(zv[i]);
-                    g[q][i] = dv[i] * (w ? w[g0 + k + i] : 1.f);
-                    ss += u[q][i] * u[q][i];
-                    gu += g[q][i] * u[q][i];
+        for (int q = 0; q < KEEP; ++q) {
+            if (lane * 4 + q * 256 < group) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float u = yv[q][i] * silu_rcp(zv[q][i]);
+                    ss += u * u;
+                    gu += dv[q][i] * wv[q][i] * u;
                 }
             }
         }
@@ -404,30 +546,57 @@ __global__ __launch_bounds__(256) void k_gated_rmsnorm_bwd(
         const float c3 = inv * inv * inv * gu / group;
 #pragma unroll
         for (int q = 0; q < KEEP; ++q) {
-            const int k = lane * 8 + q * 512;
+            const int k = lane * 4 + q * 256;
             if (k < group) {
-                float yv[8], zv[8], dv[8], oy[8], oz[8];
-                load8(y + r * D + g0 + k, yv);
-                load8(z + r * zstride + g0 + k, zv);
-                load8(dout + r * D + g0 + k, dv);
+                float oy[4], oz[4];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float du = inv * g[q][i] - u[q][i] * c3;
-                    const float sz = silu_rcp(zv[i]);
+                for (int i = 0; i < 4; ++i) {
+                    const float sz = silu_rcp(zv[q][i]);
+                    const float u = yv[q][i] * sz;
+                    const float du = inv * (dv[q][i] * wv[q][i]) - u * c3;
                     oy[i] = du * sz;
-                    oz[i] = du * yv[i] * silu_grad_f(zv[i]);
-                    wacc[q][i] += dv[i] * u[q][i] * inv;
+                    oz[i] = du * yv[q][i] * silu_grad_f(zv[q][i]);
+                    wacc[q][i] += dv[q][i] * u * inv;
                 }
-                store8(dy + r * D + g0 + k, oy);
-                store8(dz + r * dzstride + g0 + k, oz);
+                store4(dy + r * D + g0 + k, oy);
+                store4(dz + r * dzstride + g0 + k, oz);
             }
         }
     }
+    // the waves' weight sums, added in wave order
 #pragma unroll
     for (int q = 0; q < KEEP; ++q) {
-        const int k = lane * 8 + q * 512;
-        if (k < group) store8(part + rb * D + g0 + k, wacc[q]);
+        if (wave > 0) store4(&s_w[wave - 1][lane * 4 + q * 256], wacc[q]);
     }
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int q = 0; q < KEEP; ++q) {
+        const int k = lane * 4 + q * 256;
+        if (k < group) {
+#pragma unroll
+            for (int v = 0; v < 3; ++v) {
+                float o[4];
+                load4(&s_w[v][k], o);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) wacc[q][i] += o[i];
+            }
+            store4(part + rb * D + g0 + k, wacc[q]);
+        }
+    }
+}
+
+template <typename T>
+void run_gated_rmsnorm_bwd(int64_t blocks, const T* y, const T* z, int64_t zstride, const float* w,
+                           float eps, const float* dout, float* dy, float* dz, int64_t dzstride,
+                           float* part, int64_t rows, int D, int group, hipStream_t st) {
+#define DART_NB(K) \
+    k_gated_rmsnorm_bwd<T, K><<<(unsigned)blocks, 256, 0, st>>>(y, z, zstride, w, eps, dout, dy, dz, dzstride, part, rows, D, group)
+    if (group <= 512) DART_NB(2);
+    else if (group <= 1024) DART_NB(4);
+    else if (group <= 1536) DART_NB(6);
+    else DART_NB(8);
+#undef DART_NB
 }
 
 }  // namespace
@@ -507,9 +676,18 @@ hipError_t launch_conv1d_silu_bwd(int dtype, int64_t B, int64_t L, int C, int64_
                                   hipStream_t st) {
     const int nruns = (int)((L + kConvBwdTok - 1) / kConvBwdTok);
     float* part = reinterpret_cast<float*>(ws);
+    const size_t es = dtype == 1 ? 2 : 4;
+    const bool v4 = C % 4 == 0 && stride % 4 == 0 && dstride % 4 == 0 && (uintptr_t)in % (4 * es) == 0 &&
+                    ((uintptr_t)w | (uintptr_t)dout | (uintptr_t)din | (uintptr_t)ws) % 16 == 0;
     const dim3 grid((unsigned)((C + 255) / 256), (unsigned)nruns, (unsigned)B);
     prof_begin("k_conv1d_silu_bwd", st);
-    if (dtype == 1) {
+    if (dtype == 1 && v4) {
+        k_conv1d_silu_bwd_v4<bf16><<<grid, 64, 0, st>>>((const bf16*)in, stride, w, bias, st_in, dout,
+                                                        din, dstride, dst_in, part, L, C, nruns);
+    } else if (v4) {
+        k_conv1d_silu_bwd_v4<float><<<grid, 64, 0, st>>>((const float*)in, stride, w, bias, st_in, dout,
+                                                         din, dstride, dst_in, part, L, C, nruns);
+    } else if (dtype == 1) {
         k_conv1d_silu_bwd<bf16><<<grid, 256, 0, st>>>((const bf16*)in, stride, w, bias, st_in, dout,
                                                       din, dstride, dst_in, part, L, C, nruns);
     } else {
@@ -519,7 +697,7 @@ hipError_t launch_conv1d_silu_bwd(int dtype, int64_t B, int64_t L, int C, int64_
     prof_end(st);
     const int64_t width = (int64_t)C * 5;
     prof_begin("k_sum_parts", st);
-    k_sum_parts<<<(unsigned)((width + 255) / 256), 256, 0, st>>>(part, B * nruns, width, dw, 5, 4, db);
+    k_sum_parts<<<sum_blocks(width), 64 * kSumLanes, 0, st>>>(part, B * nruns, width, dw, 5, 4, db);
     prof_end(st);
     return hipGetLastError();
 }
@@ -536,16 +714,16 @@ hipError_t launch_dt_softplus_bwd(int dtype, int64_t rows, int H, const void* ra
     const dim3 grid((unsigned)((H + 255) / 256), (unsigned)nrb);
     prof_begin("k_dt_softplus_bwd", st);
     if (dtype == 1) {
-        k_dt_softplus_bwd<bf16><<<grid, 256, 0, st>>>((const bf16*)raw, stride, bias, ddt, draw,
+        k_dt_softplus_bwd<bf16><<<grid, kDtThreads, 0, st>>>((const bf16*)raw, stride, bias, ddt, draw,
                                                       dstride, part, rows, H);
     } else {
-        k_dt_softplus_bwd<float><<<grid, 256, 0, st>>>((const float*)raw, stride, bias, ddt, draw,
+        k_dt_softplus_bwd<float><<<grid, kDtThreads, 0, st>>>((const float*)raw, stride, bias, ddt, draw,
                                                        dstride, part, rows, H);
     }
     prof_end(st);
     if (dbias) {
         prof_begin("k_sum_parts", st);
-        k_sum_parts<<<(unsigned)((H + 255) / 256), 256, 0, st>>>(part, nrb, H, dbias, 1, 1, nullptr);
+        k_sum_parts<<<sum_blocks(H), 64 * kSumLanes, 0, st>>>(part, nrb, H, dbias, 1, 1, nullptr);
         prof_end(st);
     }
     return hipGetLastError();
@@ -561,21 +739,19 @@ hipError_t launch_gated_rmsnorm_bwd(int dtype, int64_t rows, int D, int group, c
                                     float* dw, void* ws, hipStream_t st) {
     const int64_t nrb = (rows + kNormRows - 1) / kNormRows;
     float* part = reinterpret_cast<float*>(ws);
-    const int64_t items = nrb * (D / group);
+    const int64_t blocks = nrb * (D / group);
     prof_begin("k_gated_rmsnorm_bwd", st);
     if (dtype == 1) {
-        k_gated_rmsnorm_bwd<bf16><<<(unsigned)((items + 3) / 4), 256, 0, st>>>(
-            (const bf16*)y, (const bf16*)z, zstride, w, eps, dout, dy, dz, dzstride, part, rows, D,
-            group);
+        run_gated_rmsnorm_bwd((int64_t)blocks, (const bf16*)y, (const bf16*)z, zstride, w, eps, dout, dy,
+                              dz, dzstride, part, rows, D, group, st);
     } else {
-        k_gated_rmsnorm_bwd<float><<<(unsigned)((items + 3) / 4), 256, 0, st>>>(
-            (const float*)y, (const float*)z, zstride, w, eps, dout, dy, dz, dzstride, part, rows,
-            D, group);
+        run_gated_rmsnorm_bwd((int64_t)blocks, (const float*)y, (const float*)z, zstride, w, eps, dout,
+                              dy, dz, dzstride, part, rows, D, group, st);
     }
     prof_end(st);
     if (dw) {
         prof_begin("k_sum_parts", st);
-        k_sum_parts<<<(unsigned)((D + 255) / 256), 256, 0, st>>>(part, nrb, D, dw, 1, 1, nullptr);
+        k_sum_parts<<<sum_blocks(D), 64 * kSumLanes, 0, st>>>(part, nrb, D, dw, 1, 1, nullptr);
         prof_end(st);
     }
     return hipGetLastError();

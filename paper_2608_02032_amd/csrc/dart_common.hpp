@@ -110,6 +110,17 @@ __device__ __forceinline__ void load8_nt(const float* p, float (&v)[8]) {
         v[4 + i] = b[i];
     }
 }
+__device__ __forceinline__ void load4_nt(const bf16* p, float (&v)[4]) {
+    typedef unsigned int u32x2_nt __attribute__((ext_vector_type(2)));
+    const bf16x4 r = __builtin_bit_cast(bf16x4, __builtin_nontemporal_load(reinterpret_cast<const u32x2_nt*>(p)));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = (float)r[i];
+}
+__device__ __forceinline__ void load4_nt(const float* p, float (&v)[4]) {
+    const f32x4 r = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = r[i];
+}
 __device__ __forceinline__ void store8_nt(bf16* p, const float (&v)[8]) {
     bf16x8 r;
 #pragma unroll
