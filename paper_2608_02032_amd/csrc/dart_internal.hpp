@@ -87,15 +87,19 @@ hipError_t launch_sma(const Shape& s, const SmaArgs& a, const void* q, const voi
                       const void* Cm, const void* mem, const void* z, const void* y_ssd, void* y,
                       float* lse, void* ws, hipStream_t st);
 
-// Generic SMA forward (no workspace).
-hipError_t launch_gsma(const Shape& s, const SmaArgs& a, const void* q, const void* e,
+// SMA forward on the fp32 matrix instructions (sma_f32.hip; no workspace):
+// fp32 storage, and bf16 storage at the shapes outside the bf16 kernels' set.
+hipError_t launch_fsma(const Shape& s, const SmaArgs& a, const void* q, const void* e,
                        const void* Cm, const void* mem, const void* z, const void* y_ssd, void* y,
                        float* lse, hipStream_t st);
+bool sma_bf16_shape(const Shape& s);  // the bf16 kernels' set
 
-// Workspace of the generic SMA backward: per (b, h, memory 0..M-2, token) the
-// logit (then g p_j) and dy . V_j (then dl_j) with row stride Ls; Dy per
-// (b, t, h); per-head token gradients [B][L][H][2N+P].
+// Workspace of its backward: Qbar and Ebar in float; per (b, h, memory
+// 0..M-2, token) the logit (then g p_j) and dy . V_j (then dl_j / sqrt(N)) with
+// row stride Ls; Dy per (b, t, h); per-head token gradients [B][L][H][2N+P].
 struct GenBwdWs {
+    float* qb;
+    float* eb;
     float* gp;
     float* dl;
     float* rdy;
@@ -103,9 +107,9 @@ struct GenBwdWs {
     int64_t Ls;
     size_t bytes;  // total workspace
 };
-// Token and memory sides of the generic SMA backward (the caller finishes
-// q, e, C and z gradients from part and rdy).
-hipError_t launch_gsma_bwd(const Shape& s, const SmaArgs& a, const void* q, const void* e,
+// Token and memory sides (the caller finishes q, e, C and z gradients from
+// part and rdy, which hold nothing for the tokens of chunk 0).
+hipError_t launch_fsma_bwd(const Shape& s, const SmaArgs& a, const void* q, const void* e,
                            const void* Cm, const void* mem, const void* z, const void* dy,
                            const GenBwdWs& w, float* dmem, hipStream_t st);
 

@@ -8,12 +8,12 @@
 // query tile fixed, historical memories streamed, online softmax, only R and
 // the log-sum-exp leave the chip).
 //
-// Both precisions run one workgroup per (b, group of heads, token block).
-// The block's 8 waves form 4 pairs; each pair owns 16*RT consecutive tokens
-// inside one chunk.  In a pair, the score wave holds Qbar and Ebar and the
-// value wave holds C and the output accumulator O, so each wave keeps only
+// bf16 storage (fp32: sma_f32.hip), one workgroup per (b, group of heads,
+// token block).  The block's 8 waves form 4 pairs; each pair owns 64
+// consecutive tokens inside one chunk.  In a pair, the score wave holds Qbar
+// and Ebar and the value wave holds C and the output accumulator O, so each wave keeps only
 // half of the per-token operands and every operand fragment it reads from LDS
-// feeds RT independent MFMA chains.  The block streams the memories of its
+// feeds four independent MFMA chains.  The block streams the memories of its
 // heads, head by head; per step:
 //   score waves   U^T = (r_s (.) dH_s)^T Qbar^T (P x tokens, MFMA), logits
 //                 l_t = sum_p U^T[p,t] Ebar[t,p], online softmax in base 2;
@@ -24,7 +24,7 @@
 // its softmax denominators and writes LSE = (m + log2 d) ln 2; the value wave
 // writes y = y_ssd + SiLU(z) O/d.
 //
-// bf16 (k_sma_prep, k_sma): a first kernel writes both sides of every attended
+// A first kernel (k_sma_prep) writes both sides of every attended
 // memory transposed to [P][N] (key side r (.) dH rounded to bf16, value side
 // dH), so every MFMA operand fragment is one 16-byte LDS read.  k_sma copies
 // the tiles by DMA (global_load_lds, no registers) into XOR-swizzled LDS
@@ -32,11 +32,6 @@
 // lag the score waves by two memories so neither waits on the other within a
 // step, and they copy each head's y_ssd rows and gates into LDS a step before
 // the head ends.
-//
-// fp32 (k_sma_keys, k_sma_regs): a first kernel writes the key side in the
-// cache's [N][P] layout; value tiles come straight from the cache, through
-// registers one step ahead when four LDS stages do not fit.  Operand fragments
-// are read with transposing LDS loads.
 #include <algorithm>
 #include <cstdlib>
 
@@ -57,62 +52,28 @@ constexpr int kHeadsPerBlock = 8;          // most heads of one group a block ca
 // itself cannot see the difference).
 constexpr int kFwdHeadsCap = 4;
 
-// 16-token column tiles per pair: 4 for bf16 (64 tokens), 2 for fp32 (its
-// operand fragments take twice the registers).
-template <typename T> constexpr int sma_rt() { return sizeof(T) == 2 ? 4 : 2; }
-template <typename T> constexpr int sma_tokens_per_block() { return 4 * 16 * sma_rt<T>(); }
-
-// 8 operand values of a token row vector v (length N) in the lane's k order:
-// k-group g holds elements 32 ks + 4 g + {0..3} and 32 ks + 16 + 4 g + {0..3},
-// the order in which frag_km hands out the rows of a k-major tile.
-template <typename T>
-__device__ __forceinline__ void load_kperm(const T* row, int ks, int grp, float (&v)[8]) {
-    float a[4], b[4];
-    load4(row + ks * 32 + 4 * grp, a);
-    load4(row + ks * 32 + 16 + 4 * grp, b);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        v[i] = a[i];
-        v[4 + i] = b[i];
-    }
-}
+constexpr int kTokensPerBlock = 4 * 64;  // 64 tokens (four 16-token column tiles) per pair
 
 // Four consecutive elements loaded as one vector (8 B for bf16, 16 B for fp32).
 template <typename T>
 using Vec4 = T __attribute__((ext_vector_type(4)));
 template <typename T>
 __device__ __forceinline__ Vec4<T> ld4(const T* p) { return *reinterpret_cast<const Vec4<T>*>(p); }
-template <typename T>
-__device__ __forceinline__ Frag<T> cat_frag(Vec4<T> a, Vec4<T> b) {
-    return Frag<T>{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-}
-
 // Sum of squares of the elements of one 16-byte piece, and the piece scaled.
-__device__ __forceinline__ float piece_sumsq(uint4 v, bf16) {
+__device__ __forceinline__ float piece_sumsq(uint4 v) {
     const bf16x8 h = __builtin_bit_cast(bf16x8, v);
     float s = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) s += (float)h[i] * (float)h[i];
     return s;
 }
-__device__ __forceinline__ float piece_sumsq(uint4 v, float) {
-    const f32x4 f = __builtin_bit_cast(f32x4, v);
-    return f[0] * f[0] + f[1] * f[1] + f[2] * f[2] + f[3] * f[3];
-}
-__device__ __forceinline__ uint4 piece_scale(uint4 v, float r, bf16) {
+__device__ __forceinline__ uint4 piece_scale(uint4 v, float r) {
     const bf16x8 h = __builtin_bit_cast(bf16x8, v);
     bf16x8 o;
 #pragma unroll
     for (int i = 0; i < 8; ++i) o[i] = (bf16)((float)h[i] * r);
     return __builtin_bit_cast(uint4, o);
 }
-__device__ __forceinline__ uint4 piece_scale(uint4 v, float r, float) {
-    f32x4 f = __builtin_bit_cast(f32x4, v);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) f[i] *= r;
-    return __builtin_bit_cast(uint4, f);
-}
-
 // The rounding residual of a scaled bf16 piece: lo = bf16(v r - bf16(v r)), so
 // that hi + lo carries v r to about 16 significant bits.
 __device__ __forceinline__ uint4 piece_scale_lo(uint4 v, float r) {
@@ -128,15 +89,15 @@ __device__ __forceinline__ uint4 piece_scale_lo(uint4 v, float r) {
 
 // Key side of one memory: kmem = r (.) dH, r[n] the inverse RMS of row n of
 // the stored values.  The RPC lanes holding one row's 16-byte pieces reduce
-// its sum of squares with DPP moves.  rinv (optional, [B][Mp][H][N]) receives
-// 1 / r[n]; klo (optional, bf16 only) the rounding residual of the bf16 key
-// side, so kmem + klo is r (.) dH to about 16 bits.
-template <typename T, int N>
-__global__ __launch_bounds__(256) void k_sma_keys(const T* __restrict__ mem, T* __restrict__ kmem,
-                                                  T* __restrict__ klo, float* __restrict__ rinv,
+// its sum of squares with DPP moves.  rinv ([B][Mp][H][N]) receives 1 / r[n],
+// klo the rounding residual of the key side, so kmem + klo is r (.) dH to
+// about 16 bits.
+template <int N>
+__global__ __launch_bounds__(256) void k_sma_keys(const bf16* __restrict__ mem, bf16* __restrict__ kmem,
+                                                  bf16* __restrict__ klo, float* __restrict__ rinv,
                                                   float eps, int normalize, int H, int64_t Mp,
                                                   int64_t Mcap) {
-    constexpr int RB = kP * (int)sizeof(T);
+    constexpr int RB = kP * 2;
     constexpr int PIECES = N * RB / 16;
     constexpr int RPC = RB / 16;
     static_assert(PIECES % 256 == 0, "pieces must tile the block");
@@ -146,618 +107,18 @@ __global__ __launch_bounds__(256) void k_sma_keys(const T* __restrict__ mem, T* 
     const uint4* src = reinterpret_cast<const uint4*>(mem + ((b * Mcap + j) * H + h) * (int64_t)N * kP);
     const int64_t obase = ((b * Mp + j) * H + h) * (int64_t)N * kP;
     uint4* dst = reinterpret_cast<uint4*>(kmem + obase);
+    uint4* lo = reinterpret_cast<uint4*>(klo + obase);
     uint4 v[PIECES / 256];
 #pragma unroll
     for (int i = 0; i < PIECES / 256; ++i) v[i] = src[threadIdx.x + i * 256];
 #pragma unroll
     for (int i = 0; i < PIECES / 256; ++i) {
-        const float ss = dpp_group_sum<RPC>(piece_sumsq(v[i], T()));
+        const float ss = dpp_group_sum<RPC>(piece_sumsq(v[i]));
         const float rn = normalize ? __builtin_amdgcn_rsqf(ss * (1.0f / kP) + eps) : 1.0f;
-        dst[threadIdx.x + i * 256] = piece_scale(v[i], rn, T());
-        if constexpr (sizeof(T) == 2) {
-            if (klo) reinterpret_cast<uint4*>(klo + obase)[threadIdx.x + i * 256] = piece_scale_lo(v[i], rn);
-        }
         const int q = threadIdx.x + i * 256;
-        if (rinv && q % RPC == 0) rinv[((b * Mp + j) * H + h) * (int64_t)N + q / RPC] = 1.0f / rn;
-    }
-}
-
-// The epilogue inputs of one head, for each of a lane's RT tokens: its gate
-// pre-activation z and its 4 x 4 y_ssd values (columns 16 pt + 4 (lane/16) ..
-// +3).  They are loaded inside one assembly block that also waits for them, so
-// the compiler tracks no load of these registers: loads it tracked here, in
-// the streaming loop, made it drain the tile copies in flight at later
-// register reuses in every step.  Called once per head, where the drain is
-// cheap.
-template <typename T, int RT>
-__device__ __forceinline__ void load_epilogue_inputs(const T* const (&zp)[RT],
-                                                     const T* const (&yp)[RT], float (&zz)[RT],
-                                                     Vec4<T> (&ys)[RT][4]);
-template <>
-__device__ __forceinline__ void load_epilogue_inputs<float, 2>(const float* const (&zp)[2],
-                                                               const float* const (&yp)[2],
-                                                               float (&zz)[2],
-                                                               Vec4<float> (&ys)[2][4]) {
-    asm volatile(
-        "global_load_dword %0, %10, off\n\t"
-        "global_load_dword %1, %11, off\n\t"
-        "global_load_dwordx4 %2, %12, off\n\t"
-        "global_load_dwordx4 %3, %12, off offset:64\n\t"
-        "global_load_dwordx4 %4, %12, off offset:128\n\t"
-        "global_load_dwordx4 %5, %12, off offset:192\n\t"
-        "global_load_dwordx4 %6, %13, off\n\t"
-        "global_load_dwordx4 %7, %13, off offset:64\n\t"
-        "global_load_dwordx4 %8, %13, off offset:128\n\t"
-        "global_load_dwordx4 %9, %13, off offset:192\n\t"
-        "s_waitcnt vmcnt(0)"
-        : "=&v"(zz[0]), "=&v"(zz[1]), "=&v"(ys[0][0]), "=&v"(ys[0][1]), "=&v"(ys[0][2]),
-          "=&v"(ys[0][3]), "=&v"(ys[1][0]), "=&v"(ys[1][1]), "=&v"(ys[1][2]), "=&v"(ys[1][3])
-        : "v"(zp[0]), "v"(zp[1]), "v"(yp[0]), "v"(yp[1])
-        : "memory");
-}
-
-// Copy of one swizzled [N][P] tile (MEMB bytes) from global memory into LDS by
-// DMA, issued from inline assembly with a scalar tile base and per-lane byte
-// offsets fixed at set-up, so the streaming loop does no vector address work.
-// Wave w copies the 1 KiB pieces w, w + 8, ... (or piece w alone when a tile
-// has fewer than 8); lane i of a piece lands at piece base + 16 i, which holds
-// global chunk (pos ^ (row & 7)) of its row (the tile swizzle is an XOR, its
-// own inverse).  Completion is tracked by the wave's vmcnt.
-template <int RB, int MEMB>
-struct TileDma {
-    static constexpr int CPR = RB / 16;
-    static constexpr int MASK = (CPR < 8 ? CPR : 8) - 1;
-    static constexpr int NI = MEMB / 1024;                      // pieces per tile
-    static constexpr int KPW = NI >= kWaves ? NI / kWaves : 1;  // pieces per wave
-    static_assert(NI >= kWaves ? NI % kWaves == 0 : true, "pieces must tile the waves");
-    uint32_t goff[KPW];
-    bool active;
-    int wave;
-    __device__ void init(int w, int lane) {
-        wave = __builtin_amdgcn_readfirstlane(w);
-        active = NI >= kWaves || w < NI;
-#pragma unroll
-        for (int k = 0; k < KPW; ++k) {
-            const int q = (w + k * kWaves) * 64 + lane;
-            const int row = q / CPR, pos = q % CPR;
-            goff[k] = (uint32_t)(row * RB + ((pos ^ (row & MASK)) << 4));
-            asm volatile("" : "+v"(goff[k]));
-        }
-    }
-    // copies issued by this wave per tile
-    __device__ int count() const { return active ? KPW : 0; }
-    __device__ __forceinline__ void issue(const char* gtile, char* ltile) const {
-        if (!active) return;
-        // readfirstlane returns a signed int: widen through uint32_t so the low
-        // half is zero-extended
-        const uint64_t gb = (uint64_t)(uintptr_t)gtile;
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(gb >> 32));
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)gb);
-        const uint64_t base = ((uint64_t)hi << 32) | (uint64_t)lo;
-        const uint32_t l0 = (uint32_t)__builtin_amdgcn_readfirstlane(
-            (int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)ltile);
-#pragma unroll
-        for (int k = 0; k < KPW; ++k) {
-            const uint32_t m0 =
-                (uint32_t)__builtin_amdgcn_readfirstlane((int)(l0 + (uint32_t)((wave + k * kWaves) * 1024)));
-            uint32_t save;
-            asm volatile(
-                "s_mov_b32 %0, m0\n\t"
-                "s_mov_b32 m0, %3\n\t"
-                "s_nop 0\n\t"
-                "global_load_lds_dwordx4 %1, %2\n\t"
-                "s_mov_b32 m0, %0"
-                : "=&s"(save)
-                : "v"(goff[k]), "s"(base), "s"(m0)
-                : "memory");
-        }
-    }
-};
-
-template <typename T, int N, int S>
-__global__ __launch_bounds__(kThreads) void k_sma_regs(
-    const T* __restrict__ q, const T* __restrict__ e, const T* __restrict__ Cm,
-    const T* __restrict__ mem, const T* __restrict__ kmem, const T* __restrict__ z,
-    const T* y_ssd, T* y,
-    float* __restrict__ lse, const float* __restrict__ qw, const float* __restrict__ ew, float eps,
-    int normalize, int z_per_head, int64_t L, int H, int G, int64_t Mcap, int64_t Mp, int nblk,
-    int hpb, int64_t BHC) {
-    constexpr int KS = N / 32;
-    constexpr int RT = sma_rt<T>();
-    constexpr int PT = 16 * RT;                  // tokens per pair
-    constexpr int TPB = sma_tokens_per_block<T>();
-    constexpr int RB = kP * (int)sizeof(T);      // bytes of one memory row (fixed n)
-    constexpr int MEMB = N * RB;                 // bytes of one memory
-    constexpr int PIECES = MEMB / 16;            // 16-byte pieces of one memory
-    constexpr int PPT = PIECES >= kThreads ? PIECES / kThreads : 1;
-    constexpr int RPC = RB / 16;                 // pieces per row
-    static_assert(PIECES < kThreads ? kThreads % PIECES == 0 : PIECES % kThreads == 0,
-                  "memory pieces must tile the block");
-    static_assert(PIECES >= kThreads || PIECES % 64 == 0, "partial copies must be whole waves");
-    static_assert(S >= PT, "a pair's tokens must lie in one chunk");
-    using Tl = SwzTile<RB>;
-
-    // A block serves `hpb` heads of one projection group (they share q, e and
-    // C, loaded once) for one token block, one head after another.
-    // Block order.  Workgroups are dealt to the 8 XCDs round-robin by block
-    // index, and each XCD has its own L2.  When the number of head groups
-    // B*H/hpb is a multiple of 8, XCD x runs only head groups x, x+8, ..., so
-    // all blocks reading one head group's memories share one L2.  With one or
-    // two groups per XCD they run one group after the other, heaviest first;
-    // with more, token blocks go heaviest first over all groups, so that the
-    // longest blocks start first and the short ones fill in behind them.
-    const int64_t bid = blockIdx.x;
-    int blk;
-    int64_t bhc;
-    if (BHC % 8 == 0) {
-        const int64_t slot = bid >> 3, ng8 = BHC >> 3;
-        if (ng8 <= 2) {
-            // one or two head groups per XCD: one group after the other (its
-            // blocks share the L2 while they run; the first group's light
-            // blocks meet the second's heavy ones)
-            blk = nblk - 1 - (int)(slot % nblk);
-            bhc = (slot / nblk) * 8 + (bid & 7);
-        } else {
-            blk = nblk - 1 - (int)(slot / ng8);
-            bhc = (slot % ng8) * 8 + (bid & 7);
-        }
-    } else {
-        blk = nblk - 1 - (int)(bid / BHC);
-        bhc = bid % BHC;
-    }
-    const int hgroups = H / hpb;
-    const int64_t b = bhc / hgroups;
-    const int h0 = (int)(bhc % hgroups) * hpb;
-    const int g = (int)((int64_t)h0 * G / H);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int col = lane & 15, grp = lane >> 4;
-    const bool scorer = wave < 4;
-    const int pair = wave & 3;
-
-    const int64_t blk0 = (int64_t)blk * TPB;
-    const int64_t pbase = blk0 + pair * PT;                  // first token of the pair
-    const int64_t blk_end = (blk0 + TPB < L) ? blk0 + TPB : L;
-    const int jmax = (int)((blk_end - 1) / S);              // memories any pair of the block needs
-    const bool active = pbase < L;
-    const int ip = (int)(pbase / S);                         // the pair's chunk
-    const int nj = active ? ip : 0;                          // memories the pair attends
-
-    // LDS: the streamed tiles (see below), the softmax weights (and rescale
-    // factors) of the last scored memory per pair, and the final
-    // denominators (by head parity).
-    constexpr bool kDma = 8 * MEMB + 8192 <= 160 * 1024;  // four (key, value) stages fit
-    __shared__ __attribute__((aligned(16))) char st0[2 * MEMB];
-    __shared__ __attribute__((aligned(16))) char st1[2 * MEMB];
-    __shared__ __attribute__((aligned(16))) char st2[kDma ? 2 * MEMB : 16];
-    __shared__ __attribute__((aligned(16))) char st3[kDma ? 2 * MEMB : 16];
-    __shared__ float xw[2][4][PT];
-    __shared__ float xa[2][4][PT];
-    __shared__ int xr[2][4];
-    __shared__ float xd[2][4][PT];
-
-    // ---- streaming helpers ---------------------------------------------------
-    // The block streams nmem = hpb * jmax memories: index J is memory
-    // J % jmax of head h0 + J / jmax.  Indices past the last re-read the last
-    // one, so copies are issued on every path and the per-wave count of
-    // copies in flight is the same at every wait.  A stage holds the key tile
-    // (bytes [0, MEMB)) and the value tile (bytes [MEMB, 2 MEMB)).
-    const int nmem = hpb * jmax;
-    const char* kbase0 = reinterpret_cast<const char*>(kmem) + (b * Mp * H + h0) * (int64_t)MEMB;
-    const char* vbase0 = reinterpret_cast<const char*>(mem) + (b * Mcap * H + h0) * (int64_t)MEMB;
-    const int64_t jstride = (int64_t)H * MEMB;
-    auto mem_off = [&](int J) {
-        const int jj = J < nmem ? J : nmem - 1;
-        const int hh = jj / jmax;
-        return (int64_t)hh * MEMB + (int64_t)(jj - hh * jmax) * jstride;
-    };
-    // operand fragments of one 16-column slice (P index pt) of a tile
-    auto read_slice = [&](const char* tile, int pt, Frag<T> (&f)[KS]) {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            f[ks] = frag_km<T, RB>(tile, ks * 32 + 4 * grp, ks * 32 + 16 + 4 * grp, pt * 16, lane);
-    };
-
-    // DMA streaming: step s scores memory s from stage s%4 and accumulates the
-    // values of memory s-1 from stage (s-1)%4, while memory s+2 is copied into
-    // stage (s+2)%4 (last read in step s-1).  The copies are issued untracked
-    // (the compiler would otherwise drain them before every LDS read), and
-    // each wave waits for its own copies of memory s+1 before the barrier:
-    // vector-memory operations complete in order, so allowing the latest
-    // dcnt operations to be outstanding leaves every older copy complete.
-    TileDma<RB, MEMB> tdma;
-    tdma.init(wave, lane);
-    const int dcnt = 2 * tdma.count();  // copies per memory issued by this wave
-    auto fetch = [&](int J, char* st) __attribute__((always_inline)) {
-        const int64_t off = mem_off(J);
-        tdma.issue(kbase0 + off, st);
-        tdma.issue(vbase0 + off, st + MEMB);
-    };
-    auto wait_older = [&]() __attribute__((always_inline)) {
-        if (dcnt >= 8) {
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(8));
-        } else if (dcnt >= 4) {
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));
-        } else if (dcnt >= 2) {
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(2));
-        }
-    };
-    static_assert(2 * TileDma<RB, MEMB>::KPW == 2 || 2 * TileDma<RB, MEMB>::KPW == 4 ||
-                      2 * TileDma<RB, MEMB>::KPW == 8,
-                  "per-wave copy count must be 2, 4 or 8");
-    auto stream_dma = [&](auto&& work) {
-        wait_older();
-        lds_barrier();
-        for (int s = 0;; s += 4) {
-            fetch(s + 2, st2);
-            work(s, st0, st3 + MEMB, 0);
-            wait_older();
-            lds_barrier();
-            if (s + 1 > nmem) break;
-            fetch(s + 3, st3);
-            work(s + 1, st1, st0 + MEMB, 1);
-            wait_older();
-            lds_barrier();
-            if (s + 2 > nmem) break;
-            fetch(s + 4, st0);
-            work(s + 2, st2, st1 + MEMB, 0);
-            wait_older();
-            lds_barrier();
-            if (s + 3 > nmem) break;
-            fetch(s + 5, st1);
-            work(s + 3, st3, st2 + MEMB, 1);
-            wait_older();
-            lds_barrier();
-            if (s + 4 > nmem) break;
-        }
-    };
-
-    // Register streaming (two stages): memory s+1 is loaded into registers
-    // during step s-1 and written to stage (s+1)%2 after step s's work.  Its
-    // key tile is needed in step s+1 and its value tile in step s+2, so the
-    // value copy of memory s is written one step later than its key copy.
-    const bool copier = PIECES >= kThreads || tid < PIECES;
-    struct Regs { uint4 k[PPT], v[PPT]; };
-    uint32_t loff[PPT];
-#pragma unroll
-    for (int i = 0; i < PPT; ++i) {
-        loff[i] = (uint32_t)(tid + i * kThreads) * 16u;
-        // each offset in its own register: every load is a scalar base plus a
-        // lane offset
-        asm volatile("" : "+v"(loff[i]));
-    }
-    auto load_regs = [&](int J) {
-        Regs r;
-        const int64_t off = mem_off(J);
-#pragma unroll
-        for (int i = 0; i < PPT; ++i) {
-            if (copier) {
-                r.k[i] = *reinterpret_cast<const uint4*>(kbase0 + off + loff[i]);
-                r.v[i] = *reinterpret_cast<const uint4*>(vbase0 + off + loff[i]);
-            }
-        }
-        return r;
-    };
-    auto put = [&](const uint4 (&src)[PPT], char* tile) {
-        if (!copier) return;
-#pragma unroll
-        for (int i = 0; i < PPT; ++i) {
-            const int pc = tid + i * kThreads;
-            *reinterpret_cast<uint4*>(tile + Tl::off(pc / RPC, (pc % RPC) * 16)) = src[i];
-        }
-    };
-    Regs r0, r1;
-    auto stream_regs = [&](auto&& work) {
-        put(r0.k, st0);
-        lds_barrier();
-        for (int s = 0;; s += 2) {
-            work(s, st0, st1 + MEMB, 0);
-            put(r0.v, st0 + MEMB);
-            put(r1.k, st1);
-            r0 = load_regs(s + 2);
-            lds_barrier();
-            if (s + 1 > nmem) break;
-            work(s + 1, st1, st0 + MEMB, 1);
-            put(r1.v, st1 + MEMB);
-            put(r0.k, st0);
-            r1 = load_regs(s + 3);
-            lds_barrier();
-            if (s + 2 > nmem) break;
-        }
-    };
-    // The first two memories are requested before the token operands, so
-    // their latency overlaps the prologue.
-    if (nmem > 0) {
-        if constexpr (kDma) {
-            fetch(0, st0);
-            fetch(1, st1);
-        } else {
-            r0 = load_regs(0);
-            r1 = load_regs(1);
-        }
-    }
-    // Both kinds of wave run steps s = 0..nmem and execute the same barriers.
-    // The prologue's loads are complete on entry (an explicit wait), so the
-    // compiler has no earlier load to wait for inside the loop, where such a
-    // wait would also drain the copies in flight.
-    auto stream = [&](auto&& work) {
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-        if constexpr (kDma) {
-            stream_dma(work);
-        } else {
-            stream_regs(work);
-        }
-    };
-
-    // token rows of the pair; rows past the end re-read the last token
-    // (their results are zeroed or discarded), so every load is issued up
-    // front without branches
-    int64_t trow[RT];
-    bool tvalid[RT];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        const int64_t t = pbase + rt * 16 + col;
-        tvalid[rt] = t < L;
-        trow[rt] = b * L + (t < L ? t : L - 1);
-    }
-    const bool hist = ip >= 1;
-
-    if (scorer) {
-        // ---- score wave: Qbar and Ebar of the pair's tokens -------------------
-        Vec4<T> qraw[RT][KS][2], eraw[RT][4];
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const T* qrow = q + (trow[rt] * G + g) * N;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                qraw[rt][ks][0] = ld4(qrow + ks * 32 + 4 * grp);
-                qraw[rt][ks][1] = ld4(qrow + ks * 32 + 16 + 4 * grp);
-            }
-#pragma unroll
-            for (int pt = 0; pt < 4; ++pt) eraw[rt][pt] = ld4(e + (trow[rt] * G + g) * kP + pt * 16 + grp * 4);
-        }
-        Frag<T> qf[RT][KS];
-        float ef[RT][4][4];
-        const float qscale = kLog2e / sqrtf((float)N);
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const float vmask = tvalid[rt] ? 1.0f : 0.0f;
-            float qv[KS][8];
-            float ss = 0.f;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    qv[ks][i] = to_f(qraw[rt][ks][0][i]) * vmask;
-                    qv[ks][4 + i] = to_f(qraw[rt][ks][1][i]) * vmask;
-                }
-#pragma unroll
-                for (int i = 0; i < 8; ++i) ss += qv[ks][i] * qv[ks][i];
-            }
-            ss += shfl_xor(ss, 16);
-            ss += shfl_xor(ss, 32);
-            const float qinv = (normalize ? 1.0f / sqrtf(ss * (1.0f / N) + eps) : 1.0f) * qscale;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) qv[ks][i] *= qinv;
-                if (qw) {
-                    float w[8];
-                    load_kperm(qw, ks, grp, w);
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) qv[ks][i] *= w[i];
-                }
-                qf[rt][ks] = make_frag<T>(qv[ks]);
-            }
-            float es = 0.f;
-#pragma unroll
-            for (int pt = 0; pt < 4; ++pt) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    ef[rt][pt][i] = to_f(eraw[rt][pt][i]) * vmask;
-                    es += ef[rt][pt][i] * ef[rt][pt][i];
-                }
-            }
-            es += shfl_xor(es, 16);
-            es += shfl_xor(es, 32);
-            const float einv = normalize ? 1.0f / sqrtf(es * (1.0f / kP) + eps) : 1.0f;
-#pragma unroll
-            for (int pt = 0; pt < 4; ++pt) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) ef[rt][pt][i] *= einv;
-                if (ew) {
-                    float w[4];
-                    load4(ew + pt * 16 + grp * 4, w);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) ef[rt][pt][i] *= w[i];
-                }
-            }
-        }
-        float m[RT], d[RT];
-        // LSE of one head, and its denominators for the value wave
-        auto finish_head = [&](int hh) __attribute__((always_inline)) {
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-                if (grp == 0) xd[hh & 1][pair][rt * 16 + col] = d[rt];
-                if (lse && grp == 0 && tvalid[rt])
-                    lse[trow[rt] * H + h0 + hh] = hist ? (m[rt] + log2f(d[rt])) * kLn2 : -INFINITY;
-            }
-        };
-        if (nmem == 0) {
-            // no history in this block: LSE = -inf for every head
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) d[rt] = 0.f;
-            for (int hh = 0; hh < hpb; ++hh) finish_head(hh);
-            return;
-        }
-        stream([&](int s, const char* kt, const char*, int buf) {
-            if (s >= nmem) return;
-            const int hh = s / jmax, j = s - hh * jmax;
-            if (j == 0) {
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt) {
-                    m[rt] = -INFINITY;
-                    d[rt] = 0.f;
-                }
-            }
-            if (j < nj) {
-                // U^T slices: fragments of slice pt+1 are requested before the
-                // MFMAs of slice pt
-                Frag<T> fb[2][KS];
-                read_slice(kt, 0, fb[0]);
-                float lp[RT];
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt) lp[rt] = 0.f;
-#pragma unroll
-                for (int pt = 0; pt < 4; ++pt) {
-                    if (pt < 3) read_slice(kt, pt + 1, fb[(pt + 1) & 1]);
-                        f32x4 u[RT];
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) u[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-                        for (int rt = 0; rt < RT; ++rt) u[rt] = mma16(u[rt], fb[pt & 1][ks], qf[rt][ks]);
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) lp[rt] += u[rt][i] * ef[rt][pt][i];
-                    }
-                // full logit of the lane's token: sum the 4 lanes sharing its
-                // column with one fp32 MFMA against a ones matrix
-                // (D[i][t] = sum_k B[k][t])
-                bool grow = false;
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt) {
-                    const f32x4 red = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                        1.0f, lp[rt], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-                    lp[rt] = red[0];
-                    grow |= lp[rt] > m[rt] + kRescaleLog2;
-                }
-                // lazy rescale: the reference maximum only moves when a logit
-                // exceeds it by more than 2^8, so weights stay <= 256 and O is
-                // rescaled rarely; R = O/d and LSE = m + log2 d do not depend on
-                // the choice of m
-                const bool rescale = __builtin_amdgcn_ballot_w64(grow) != 0;
-                if (rescale) {
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) {
-                        const float mn = fmaxf(m[rt], lp[rt]);
-                        const float al = fast_exp2(m[rt] - mn);
-                        d[rt] *= al;
-                        m[rt] = mn;
-                        if (grp == 0) xa[buf][pair][rt * 16 + col] = al;
-                    }
-                }
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt) {
-                    const float pw = fast_exp2(lp[rt] - m[rt]);
-                    d[rt] += pw;
-                    if (grp == 0) xw[buf][pair][rt * 16 + col] = pw;
-                }
-                if (lane == 0) xr[buf][pair] = rescale ? 1 : 0;
-            }
-            if (j == jmax - 1) finish_head(hh);
-        });
-    } else {
-        // ---- value wave: C of the pair's tokens, accumulator O ----------------
-        Frag<T> cf[RT][KS];
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const T* crow = Cm + (trow[rt] * G + g) * N;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                cf[rt][ks] = cat_frag<T>(ld4(crow + ks * 32 + 4 * grp), ld4(crow + ks * 32 + 16 + 4 * grp));
-        }
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            if (!tvalid[rt]) {
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) cf[rt][ks] = Frag<T>{};
-            }
-        }
-        f32x4 o[RT][4];
-        // y = y_ssd + SiLU(z) R of one head
-        auto finish_head = [&](int hh) __attribute__((always_inline)) {
-            const int h = h0 + hh;
-            const T* zp[RT];
-            const T* yp[RT];
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-                zp[rt] = z_per_head ? z + trow[rt] * H + h : z + trow[rt];
-                yp[rt] = y_ssd + (trow[rt] * H + h) * kP + grp * 4;
-            }
-            float zz[RT];
-            Vec4<T> ys[RT][4];
-            load_epilogue_inputs<T, RT>(zp, yp, zz, ys);
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-                if (!tvalid[rt]) continue;
-                const float gate = silu(zz[rt]);
-                const float invd = hist ? 1.0f / xd[hh & 1][pair][rt * 16 + col] : 0.f;
-#pragma unroll
-                for (int pt = 0; pt < 4; ++pt) {
-                    float yv[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) yv[i] = to_f(ys[rt][pt][i]);
-                    if (hist) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) yv[i] += gate * (o[rt][pt][i] * invd);
-                    }
-                    store4(y + (trow[rt] * H + h) * kP + pt * 16 + grp * 4, yv);
-                }
-            }
-        };
-        if (nmem == 0) {
-            // no history in this block: y = y_ssd for every head
-            for (int hh = 0; hh < hpb; ++hh) finish_head(hh);
-            return;
-        }
-        stream([&](int s, const char*, const char* vt, int buf) {
-            // memory s-1, scored in the previous step (weights in slot buf^1)
-            if (s < 1) return;
-            const int hh = (s - 1) / jmax, j = (s - 1) - hh * jmax;
-            if (j == 0) {
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                    for (int pt = 0; pt < 4; ++pt) o[rt][pt] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-            if (j < nj) {
-                const int wb = buf ^ 1;
-                // flag and weights first: LDS reads return in order, so the
-                // flag test does not wait for the fragment reads
-                const int rescale = __builtin_amdgcn_readfirstlane(xr[wb][pair]);
-                float pw[RT];
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt) pw[rt] = xw[wb][pair][rt * 16 + col];
-                Frag<T> fb[2][KS];
-                read_slice(vt, 0, fb[0]);
-                if (rescale) {
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) {
-                        const float al = xa[wb][pair][rt * 16 + col];
-#pragma unroll
-                        for (int pt = 0; pt < 4; ++pt) o[rt][pt] *= al;
-                    }
-                }
-#pragma unroll
-                for (int pt = 0; pt < 4; ++pt) {
-                    if (pt < 3) read_slice(vt, pt + 1, fb[(pt + 1) & 1]);
-                        f32x4 v[RT];
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) v[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-                        for (int rt = 0; rt < RT; ++rt) v[rt] = mma16(v[rt], fb[pt & 1][ks], cf[rt][ks]);
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) o[rt][pt] += pw[rt] * v[rt];
-                    }
-            }
-            // the head's last memory is in: its denominators were published
-            // in the previous step
-            if (j == jmax - 1) finish_head(hh);
-        });
+        dst[q] = piece_scale(v[i], rn);
+        lo[q] = piece_scale_lo(v[i], rn);
+        if (q % RPC == 0) rinv[((b * Mp + j) * H + h) * (int64_t)N + q / RPC] = 1.0f / rn;
     }
 }
 
@@ -848,7 +209,7 @@ __global__ __launch_bounds__(256) void k_sma_prep(const bf16* __restrict__ mem,
         const u32x4_nt vn = __builtin_nontemporal_load(src + q);
         const uint4 v = make_uint4(vn[0], vn[1], vn[2], vn[3]);
         const int n = q / RPC, pc = q % RPC;
-        const float ss = dpp_group_sum<RPC>(piece_sumsq(v, bf16()));
+        const float ss = dpp_group_sum<RPC>(piece_sumsq(v));
         if (pc == 0) rs[n] = normalize ? __builtin_amdgcn_rsqf(ss * (1.0f / kP) + eps) : 1.0f;
         *reinterpret_cast<uint4*>(t + Tl::off(n, pc * 16)) = v;
     }
@@ -947,7 +308,7 @@ __global__ __launch_bounds__(kThreads) void k_sma(
     static_assert(NF >= 4, "at least one fragment per slice");
     using Dma = TileDmaPN<N, 4>;  // the score waves issue all copies
 
-    // block order: as in k_sma_regs (XCD-aware, heaviest token block first)
+    // block order: XCD-aware, heaviest token block first
     const int64_t bid = blockIdx.x;
     int blk;
     int64_t bhc;
@@ -1565,69 +926,39 @@ int sma_block_heads(int64_t B, int H, int G, int64_t L, int S, int tpb, int hmax
 
 namespace {
 
-template <typename T, int N, int S>
+template <int N, int S>
 hipError_t run_sma(const Shape& s, const SmaArgs& a, const void* q, const void* e, const void* Cm,
                    const void* mem, const void* z, const void* y_ssd, void* y, float* lse,
                    void* ws, hipStream_t st) {
-    constexpr int TPB = sma_tokens_per_block<T>();
-    const int nblk = (int)((s.L + TPB - 1) / TPB);
-    const int hpb = sma_block_heads(s.B, s.H, s.G, s.L, s.S, TPB, kFwdHeadsCap, false);
+    const int nblk = (int)((s.L + kTokensPerBlock - 1) / kTokensPerBlock);
+    const int hpb = sma_block_heads(s.B, s.H, s.G, s.L, s.S, kTokensPerBlock, kFwdHeadsCap, false);
     const int64_t BHC = s.B * (s.H / hpb);
     const int64_t Mp = s.M > 1 ? s.M - 1 : 0;  // memories any token attends to
-    T* kmem = reinterpret_cast<T*>(ws);
-    if constexpr (sizeof(T) == 2) {
-        // bf16: transposed key and value sides ([P][N]) of memories 0..M-2
-        T* vT = kmem + (size_t)s.B * Mp * s.H * N * kP;
-        if (Mp > 0) {
-            prof_begin("k_sma_prep", st);
-            k_sma_prep<N><<<dim3((unsigned)Mp, (unsigned)s.H, (unsigned)s.B), 256, 0, st>>>(
-                (const T*)mem, kmem, vT, a.eps, a.normalize, s.H, Mp, s.Mcap);
-            prof_end(st);
-        }
-        prof_begin("k_sma", st);
-        k_sma<N, S><<<dim3((unsigned)(BHC * nblk)), kThreads, 0, st>>>(
-            (const T*)q, (const T*)e, (const T*)Cm, vT, kmem, (const T*)z, (const T*)y_ssd,
-            (T*)y, lse, a.qw, a.ew, a.eps, a.normalize, a.z_per_head, s.L, s.H, s.G, Mp, nblk,
-            hpb, BHC);
+    // transposed key and value sides ([P][N]) of memories 0..M-2
+    bf16* kmem = reinterpret_cast<bf16*>(ws);
+    bf16* vT = kmem + (size_t)s.B * Mp * s.H * N * kP;
+    if (Mp > 0) {
+        prof_begin("k_sma_prep", st);
+        k_sma_prep<N><<<dim3((unsigned)Mp, (unsigned)s.H, (unsigned)s.B), 256, 0, st>>>(
+            (const bf16*)mem, kmem, vT, a.eps, a.normalize, s.H, Mp, s.Mcap);
         prof_end(st);
-        return hipGetLastError();
-    } else {
-        if (Mp > 0) {
-            prof_begin("k_sma_keys", st);
-            k_sma_keys<T, N><<<dim3((unsigned)Mp, (unsigned)s.H, (unsigned)s.B), 256, 0, st>>>(
-                (const T*)mem, kmem, nullptr, nullptr, a.eps, a.normalize, s.H, Mp, s.Mcap);
-            prof_end(st);
-        }
-        prof_begin("k_sma", st);
-        k_sma_regs<T, N, S><<<dim3((unsigned)(BHC * nblk)), kThreads, 0, st>>>(
-            (const T*)q, (const T*)e, (const T*)Cm, (const T*)mem, kmem, (const T*)z,
-            (const T*)y_ssd, (T*)y, lse, a.qw, a.ew, a.eps, a.normalize, a.z_per_head, s.L, s.H,
-            s.G, s.Mcap, Mp, nblk, hpb, BHC);
-        prof_end(st);
-        return hipGetLastError();
     }
+    prof_begin("k_sma", st);
+    k_sma<N, S><<<dim3((unsigned)(BHC * nblk)), kThreads, 0, st>>>(
+        (const bf16*)q, (const bf16*)e, (const bf16*)Cm, vT, kmem, (const bf16*)z, (const bf16*)y_ssd,
+        (bf16*)y, lse, a.qw, a.ew, a.eps, a.normalize, a.z_per_head, s.L, s.H, s.G, Mp, nblk, hpb, BHC);
+    prof_end(st);
+    return hipGetLastError();
 }
 
-template <typename T, int N>
+template <int N>
 hipError_t run_sma_s(const Shape& s, const SmaArgs& a, const void* q, const void* e,
                      const void* Cm, const void* mem, const void* z, const void* ys, void* y,
                      float* lse, void* ws, hipStream_t st) {
     switch (s.S) {
-        case 64: return run_sma<T, N, 64>(s, a, q, e, Cm, mem, z, ys, y, lse, ws, st);
-        case 128: return run_sma<T, N, 128>(s, a, q, e, Cm, mem, z, ys, y, lse, ws, st);
-        case 256: return run_sma<T, N, 256>(s, a, q, e, Cm, mem, z, ys, y, lse, ws, st);
-    }
-    return hipErrorInvalidValue;
-}
-
-template <typename T>
-hipError_t run_sma_n(const Shape& s, const SmaArgs& a, const void* q, const void* e,
-                     const void* Cm, const void* mem, const void* z, const void* ys, void* y,
-                     float* lse, void* ws, hipStream_t st) {
-    switch (s.N) {
-        case 32: return run_sma_s<T, 32>(s, a, q, e, Cm, mem, z, ys, y, lse, ws, st);
-        case 64: return run_sma_s<T, 64>(s, a, q, e, Cm, mem, z, ys, y, lse, ws, st);
-        case 128: return run_sma_s<T, 128>(s, a, q, e, Cm, mem, z, ys, y, lse, ws, st);
+        case 64: return run_sma<N, 64>(s, a, q, e, Cm, mem, z, ys, y, lse, ws, st);
+        case 128: return run_sma<N, 128>(s, a, q, e, Cm, mem, z, ys, y, lse, ws, st);
+        case 256: return run_sma<N, 256>(s, a, q, e, Cm, mem, z, ys, y, lse, ws, st);
     }
     return hipErrorInvalidValue;
 }
@@ -1640,40 +971,37 @@ hipError_t launch_sma_keys(const Shape& s, const SmaArgs& a, const void* mem, vo
     if (Mp == 0) return hipSuccess;
     const dim3 grid((unsigned)Mp, (unsigned)s.H, (unsigned)s.B);
     prof_begin("k_sma_keys", st);
-#define DART_KEYS(T, NN)                                                                      \
-    k_sma_keys<T, NN><<<grid, 256, 0, st>>>((const T*)mem, (T*)kmem, (T*)klo, rinv, a.eps, \
-                                            a.normalize, s.H, Mp, s.Mcap)
-    if (s.dtype == 1) {
-        switch (s.N) {
-            case 32: DART_KEYS(bf16, 32); break;
-            case 64: DART_KEYS(bf16, 64); break;
-            case 128: DART_KEYS(bf16, 128); break;
-        }
-    } else {
-        switch (s.N) {
-            case 32: DART_KEYS(float, 32); break;
-            case 64: DART_KEYS(float, 64); break;
-            case 128: DART_KEYS(float, 128); break;
-        }
+#define DART_KEYS(NN)                                                                           \
+    k_sma_keys<NN><<<grid, 256, 0, st>>>((const bf16*)mem, (bf16*)kmem, (bf16*)klo, rinv, a.eps, \
+                                         a.normalize, s.H, Mp, s.Mcap)
+    switch (s.N) {
+        case 32: DART_KEYS(32); break;
+        case 64: DART_KEYS(64); break;
+        case 128: DART_KEYS(128); break;
     }
 #undef DART_KEYS
     prof_end(st);
     return hipGetLastError();
 }
 
+bool sma_bf16_shape(const Shape& s) { return s.dtype == 1 && tuned_shape(s); }
+
 size_t sma_workspace_bytes(const Shape& s) {
-    if (!tuned_shape(s)) return 0;  // the generic kernel stages memories itself
+    if (!sma_bf16_shape(s)) return 0;  // the fp32 kernel stages memories itself
     const int64_t Mp = s.M > 1 ? s.M - 1 : 0;
-    // bf16: key and value sides; fp32: key side only
-    return (s.dtype == 1 ? 2 : 1) * elem_bytes(s.dtype) * s.B * Mp * s.H * (size_t)s.N * s.P;
+    return 2 * sizeof(bf16) * s.B * Mp * s.H * (size_t)s.N * s.P;  // key and value sides
 }
 
 hipError_t launch_sma(const Shape& s, const SmaArgs& a, const void* q, const void* e,
                       const void* Cm, const void* mem, const void* z, const void* y_ssd, void* y,
                       float* lse, void* ws, hipStream_t st) {
-    if (!tuned_shape(s)) return launch_gsma(s, a, q, e, Cm, mem, z, y_ssd, y, lse, st);
-    if (s.dtype == 1) return run_sma_n<bf16>(s, a, q, e, Cm, mem, z, y_ssd, y, lse, ws, st);
-    return run_sma_n<float>(s, a, q, e, Cm, mem, z, y_ssd, y, lse, ws, st);
+    if (!sma_bf16_shape(s)) return launch_fsma(s, a, q, e, Cm, mem, z, y_ssd, y, lse, st);
+    switch (s.N) {
+        case 32: return run_sma_s<32>(s, a, q, e, Cm, mem, z, y_ssd, y, lse, ws, st);
+        case 64: return run_sma_s<64>(s, a, q, e, Cm, mem, z, y_ssd, y, lse, ws, st);
+        case 128: return run_sma_s<128>(s, a, q, e, Cm, mem, z, y_ssd, y, lse, ws, st);
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace dart

@@ -20,7 +20,8 @@
 // values; r = 1 and no such term without normalisation).  q and e gradients
 // follow through RMSNorm with the weights held constant.
 //
-// Kernels, in launch order:
+// Kernels for bf16 storage at the tuned shapes (the others: sma_f32.hip, then
+// k_bwd_finish), in launch order:
 //   k_sma_keys          key side Kh_j (cache layout, bf16 as hi + lo) and 1 / r_j
 //   k_bwd_prep          Qbar' = Qbar log2(e)/sqrt(N) (storage dtype, the
 //                       forward's operand exactly), q (.) w as hi + lo and its
@@ -69,11 +70,6 @@ __device__ __forceinline__ float wave_sum(float v) { return row4_sum(dpp_group_s
 // An empty use of every register of a fragment, so the compiler waits for its
 // loads at this point (operands of at most 128 bits each).
 __device__ __forceinline__ void keep(const bf16x8& f) { asm volatile("" ::"v"(f)); }
-__device__ __forceinline__ void keep(const f32x8& f) {
-    const f32x4 a{f[0], f[1], f[2], f[3]}, b{f[4], f[5], f[6], f[7]};
-    asm volatile("" ::"v"(a), "v"(b));
-}
-
 __device__ __forceinline__ float silu_grad(float z) {
     const float sg = 1.0f / (1.0f + __expf(-z));
     return sg * (1.0f + z * (1.0f - sg));
@@ -169,7 +165,7 @@ __global__ __launch_bounds__(256) void k_bwd_prep(const T* __restrict__ q, const
             qb[row * N + n] = from_f<T>(qwv * qinv);
             const T hi = from_f<T>(qwv);
             qh[row * N + n] = hi;
-            if (ql) ql[row * N + n] = (bf16)(qwv - to_f(hi));
+            ql[row * N + n] = (bf16)(qwv - to_f(hi));
         }
     }
     if (lane == 0) qsc[row] = qinv;
@@ -179,7 +175,7 @@ __global__ __launch_bounds__(256) void k_bwd_prep(const T* __restrict__ q, const
     float v = ev * einv;
     if (ew) v *= ew[lane];
     eb[row * kP + lane] = v;
-    if (ebt) ebt[row * kP + lane] = from_f<T>(v);
+    ebt[row * kP + lane] = from_f<T>(v);
 }
 
 // Block order shared by the two token kernels.  Workgroups are dealt to the
@@ -261,8 +257,7 @@ __global__ __launch_bounds__(512) void k_bwd_scores(
     const T* __restrict__ dy, float* __restrict__ lw, float* __restrict__ dwv,
     float* __restrict__ lsep, float* __restrict__ rdy, int use_ql, int64_t L, int64_t Ls, int H,
     int G, int S, int64_t Mp, int hpb, int blk0, int nblk, int64_t BHC) {
-    constexpr bool LO = sizeof(T) == 2;
-    constexpr int NTL = LO ? 2 : 1;  // tiles per stage: key side (and its residual)
+    constexpr int NTL = 2;  // tiles per stage: key side and its residual
     constexpr int RB = kP * (int)sizeof(T);
     constexpr int TILE = N * RB;
     constexpr int NT = N / 16;
@@ -305,20 +300,18 @@ __global__ __launch_bounds__(512) void k_bwd_scores(
     }
 
     Frag<T> qf[RT][KQ];
-    Frag<bf16> qlf[RT][LO ? KQ : 1];
+    Frag<bf16> qlf[RT][KQ];
     float qs[RT], ea[RT][2][4];
     typedef T T4 __attribute__((ext_vector_type(4)));
     T4 ca[RT][NTH];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
         load_row_frags<T, T, N>(qh + (bt[rt] * G + g) * N, grp, qf[rt]);
-        if constexpr (LO) {
-            if (use_ql) {
-                load_row_frags<bf16, bf16, N>(ql + (bt[rt] * G + g) * N, grp, qlf[rt]);
-            } else {
+        if (use_ql) {
+            load_row_frags<bf16, bf16, N>(ql + (bt[rt] * G + g) * N, grp, qlf[rt]);
+        } else {
 #pragma unroll
-                for (int ks = 0; ks < KQ; ++ks) qlf[rt][ks] = bf16x8{};
-            }
+            for (int ks = 0; ks < KQ; ++ks) qlf[rt][ks] = bf16x8{};
         }
         qs[rt] = qsc[bt[rt] * G + g];
         const float* erow = eb + (bt[rt] * G + g) * kP;
@@ -345,7 +338,7 @@ __global__ __launch_bounds__(512) void k_bwd_scores(
         if (!copier) return;
         const int64_t hj = (b * Mp + j) * H + h0 + hh;
         copy.issue(kmem + hj * N * kP, ring[k % NS][0]);
-        if constexpr (LO) copy.issue(klo + hj * N * kP, ring[k % NS][NTL - 1]);
+        copy.issue(klo + hj * N * kP, ring[k % NS][NTL - 1]);
         if (lane < RPW)
             lds_dma16_untracked_at(rinv + hj * N + (tg * RPW + lane) * 4,
                                    lds_addr(&rring[k % NS][0]) + tg * RPW * 16);
@@ -400,14 +393,11 @@ __global__ __launch_bounds__(512) void k_bwd_scores(
                 const Frag<T> a = frag_km<T, RB>(kt, r0, r1, cb, lane);
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) w[rt][q] = mma16(w[rt][q], a, qf[rt][ks]);
-                if constexpr (LO) {
-                    const char* kl = ring[k % NS][NTL - 1];
-                    const Frag<T> al = frag_km<T, RB>(kl, r0, r1, cb, lane);
+                const Frag<T> al = frag_km<T, RB>(ring[k % NS][NTL - 1], r0, r1, cb, lane);
 #pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) {
-                        w[rt][q] = mma16(w[rt][q], al, qf[rt][ks]);
-                        if (use_ql) w[rt][q] = mma16(w[rt][q], a, qlf[rt][ks]);
-                    }
+                for (int rt = 0; rt < RT; ++rt) {
+                    w[rt][q] = mma16(w[rt][q], al, qf[rt][ks]);
+                    if (use_ql) w[rt][q] = mma16(w[rt][q], a, qlf[rt][ks]);
                 }
             }
         }
@@ -658,18 +648,16 @@ __global__ __launch_bounds__(512) void k_bwd_tokens(
         int ln = lane;
         asm volatile("" : "+v"(ln));
         const int col = ln & 15, grp = ln >> 4;
-        // bf16: the step's fragment offsets, once per step: the transposing
+        // the step's fragment offsets, once per step: the transposing
         // reads of W' (column tile pt0 + q; k blocks move by 32 rows, an
         // immediate) and the row reads of X and Z (k half ks; n tiles move by
         // 16 rows, an immediate)
         KmOffBf16<RB> kofs[2];
         uint32_t xofs[2];
-        if constexpr (sizeof(T) == 2) {
 #pragma unroll
-            for (int q = 0; q < 2; ++q) kofs[q].init(4 * grp, 16 + 4 * grp, 16 * (pt0 + q), ln);
+        for (int q = 0; q < 2; ++q) kofs[q].init(4 * grp, 16 + 4 * grp, 16 * (pt0 + q), ln);
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) xofs[ks] = (uint32_t)SwzTile<RB>::off(col, (32 * ks + 8 * grp) * 2);
-        }
+        for (int ks = 0; ks < 2; ++ks) xofs[ks] = (uint32_t)SwzTile<RB>::off(col, (32 * ks + 8 * grp) * 2);
         float gp[RT], dl[RT];
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
@@ -685,12 +673,7 @@ __global__ __launch_bounds__(512) void k_bwd_tokens(
             for (int rt = 0; rt < RT; ++rt) w[rt] = zero4;
 #pragma unroll
             for (int ks = 0; ks < KQ; ++ks) {
-                Frag<T> a;
-                if constexpr (sizeof(T) == 2) {
-                    a = kofs[q].read(kt, ks * 32 * RB);
-                } else {
-                    a = frag_km<T, RB>(kt, 32 * ks + 4 * grp, 32 * ks + 16 + 4 * grp, 16 * (pt0 + q), ln);
-                }
+                const Frag<T> a = kofs[q].read(kt, ks * 32 * RB);
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) {
                     if constexpr (RT > 1) {
@@ -713,12 +696,7 @@ __global__ __launch_bounds__(512) void k_bwd_tokens(
             for (int rt = 0; rt < RT; ++rt) x[rt] = zz[rt] = zero4;
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                Frag<T> a;
-                if constexpr (sizeof(T) == 2) {
-                    a = *reinterpret_cast<const bf16x8*>(kt + xofs[ks] + 16 * nt * RB);
-                } else {
-                    a = frag_rowmajor<T, RB>(kt, 16 * nt + col, 32 * ks + 8 * grp);
-                }
+                const Frag<T> a = *reinterpret_cast<const bf16x8*>(kt + xofs[ks] + 16 * nt * RB);
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) {
                     x[rt] = mma16(x[rt], a, dyf[rt][ks]);
@@ -774,18 +752,15 @@ __global__ __launch_bounds__(512) void k_bwd_tokens(
 // tokens per step are copied into LDS by DMA one step ahead, and the
 // per-(memory, token) factors g p_j and ln2 dl_j (zero where memory j is not
 // attended) scale the dy and Ebar fragments in registers.  Wave w owns the
-// output columns p = 16 (w % 4) .. + 15; for bf16 it takes two of the four
-// memories (2 (w / 4), + 1) over every n tile, so each scaled fragment feeds
-// N/16 MFMAs of each product and no two waves scale the same fragment; for
-// fp32 (operands twice as wide) it takes every memory over half the n tiles.
-// The token
+// output columns p = 16 (w % 4) .. + 15 of two of the four memories
+// (2 (w / 4), + 1) over every n tile, so each scaled fragment feeds N/16 MFMAs
+// of each product and no two waves scale the same fragment.  The token
 // tiles stream through a 3-stage LDS ring, two steps ahead: waves 0-3 issue
 // the DMA copies (and wait for their own with exact counts), waves 4-7 load
 // the factors of the step two ahead and write them to LDS at the end of the
 // current one, so the ordinary loads never make a copying wave drain its
 // copies.  Memories j >= M - 1 (attended by no token) are written as zeros.
-template <typename T>
-constexpr int mem_tb() { return sizeof(T) == 2 ? 64 : 32; }
+constexpr int kMemTok = 64;  // tokens per k_bwd_mem step
 
 template <typename T>
 __device__ __forceinline__ Frag<T> scale_frag(Frag<T> f, const f32x4& s0, const f32x4& s1) {
@@ -811,15 +786,14 @@ __global__ __launch_bounds__(512) void k_bwd_mem(const T* __restrict__ qb,
                                                  int64_t Mcap, int64_t Mp, int64_t BH) {
     constexpr int J = kMemJ;
     constexpr int ES = (int)sizeof(T);
-    constexpr int TB = mem_tb<T>();
+    constexpr int TB = kMemTok;
     constexpr int RBN = N * ES, RBP = kP * ES;
     constexpr int CT = TB * RBN, DT = TB * RBP;
     // C and Qbar' tiles: pair-spread swizzle where their rows span 256 bytes
-    using SwN = std::conditional_t<(ES == 2 && RBN >= 256), SwzTilePair<RBN>, SwzTile<RBN>>;
+    using SwN = std::conditional_t<(RBN >= 256), SwzTilePair<RBN>, SwzTile<RBN>>;
     constexpr int STAGE = 2 * CT + 2 * DT;
-    constexpr bool MSPLIT = ES == 2;           // waves split the memories (else the n tiles)
-    constexpr int NT = MSPLIT ? N / 16 : N / 32;  // n tiles per wave
-    constexpr int JW = MSPLIT ? J / 2 : J;        // memories per wave
+    constexpr int NT = N / 16;  // n tiles per wave
+    constexpr int JW = J / 2;   // memories per wave
     static_assert(NT >= 1 && J % 2 == 0, "whole n tiles, memories in two halves");
     constexpr int NS = 3;
     // DMA copies per copying wave per step (every tile is a multiple of 256 pieces)
@@ -832,8 +806,7 @@ __global__ __launch_bounds__(512) void k_bwd_mem(const T* __restrict__ qb,
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
     const int col = lane & 15, grp = lane >> 4;
     const int pt = wave & 3;                       // p tile of the wave
-    const int jh = MSPLIT ? (wave >> 2) * JW : 0;  // its first memory
-    const int nt0 = MSPLIT ? 0 : (wave >> 2) * NT; // its first n tile
+    const int jh = (wave >> 2) * JW;               // its first memory
     const int64_t jb = (int64_t)blockIdx.x / BH;
     const int64_t bh = (int64_t)blockIdx.x - jb * BH;
     const int64_t b = bh / H;
@@ -962,8 +935,8 @@ __global__ __launch_bounds__(512) void k_bwd_mem(const T* __restrict__ qb,
             }
 #pragma unroll
             for (int k = 0; k < NT; ++k) {
-                const Frag<T> ac = frag_km<T, RBN, SwN>(cs, r0, r1, 16 * (nt0 + k), lane);
-                const Frag<T> aq = frag_km<T, RBN, SwN>(qs, r0, r1, 16 * (nt0 + k), lane);
+                const Frag<T> ac = frag_km<T, RBN, SwN>(cs, r0, r1, 16 * k, lane);
+                const Frag<T> aq = frag_km<T, RBN, SwN>(qs, r0, r1, 16 * k, lane);
 #pragma unroll
                 for (int jw = 0; jw < JW; ++jw) {
                     m1[jw][k] = mma16(m1[jw][k], ac, bdj[jw]);
@@ -992,7 +965,7 @@ __global__ __launch_bounds__(512) void k_bwd_mem(const T* __restrict__ qb,
         for (int k = 0; k < NT; ++k)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int n = 16 * (nt0 + k) + 4 * grp + i;
+                const int n = 16 * k + 4 * grp + i;
                 const float hv = to_f(hsrc[n * kP + p]);
                 const float s2 = dpp_group_sum<16>(hv * hv);
                 const float d2 = dpp_group_sum<16>(hv * m2[jw][k][i]);
@@ -1014,7 +987,7 @@ __global__ __launch_bounds__(512) void k_bwd_mem(const T* __restrict__ qb,
         for (int k = 0; k < NT; ++k)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int n = 16 * (nt0 + k) + 4 * grp + i;
+                const int n = 16 * k + 4 * grp + i;
                 float o = 0.f;
                 if (j < Mp) {
                     o = m1[jw][k][i];
@@ -1115,22 +1088,22 @@ __global__ __launch_bounds__(256) void k_bwd_finish(
 }
 
 // Heads per block of the token kernels (and so of the per-token partials the
-// finishing kernel sums): the token blocks are 128 tokens for bf16 at S >= 128,
+// finishing kernel sums): the token blocks are 128 tokens at S >= 128,
 // else kTokBlock, and the first chunk's blocks are not launched.
 int bwd_heads_per_block(const Shape& s) {
-    const int tpb = (s.dtype == 1 && s.S >= 128) ? 2 * kTokBlock : kTokBlock;
+    const int tpb = s.S >= 128 ? 2 * kTokBlock : kTokBlock;
     return sma_block_heads(s.B, s.H, s.G, s.L, s.S, tpb, kHeadsPerBlock, true);
 }
 
 struct BwdWs {
     void* kmem;
-    void* klo;    // rounding residual of the bf16 key side (bf16 only)
+    void* klo;    // rounding residual of the key side
     void* qb;     // Qbar' in the storage dtype
     void* qh;     // q (.) w in the storage dtype
-    void* ql;     // its bf16 rounding residual (bf16 only)
+    void* ql;     // its rounding residual
     float* qsc;   // per-row scale: Qbar' = (q (.) w) qsc
     float* eb;
-    void* ebt;    // Ebar in the storage dtype (eb itself for fp32)
+    void* ebt;    // Ebar in the storage dtype
     float* rinv;  // 1 / r of every attended memory row, [B][M-1][H][N]
     float* gp;    // per (b, h, memory, token): the exact logit, then g p
     float* gd;    // per (b, h, memory, token): dwy
@@ -1150,8 +1123,7 @@ inline int64_t bwd_row_stride(const Shape& s) {
 
 BwdWs bwd_layout(const Shape& s, void* base) {
     const int64_t Mp = s.M > 1 ? s.M - 1 : 0;
-    const size_t es = elem_bytes(s.dtype);
-    const bool lo = s.dtype == 1;
+    constexpr size_t es = sizeof(bf16);
     const int nhb = s.H / bwd_heads_per_block(s);
     const size_t Ls = (size_t)bwd_row_stride(s);
     size_t o = 0;
@@ -1163,14 +1135,14 @@ BwdWs bwd_layout(const Shape& s, void* base) {
         return r;
     };
     w.kmem = take(es * s.B * Mp * s.H * (size_t)s.N * s.P);
-    w.klo = lo ? take(es * s.B * Mp * s.H * (size_t)s.N * s.P) : nullptr;
+    w.klo = take(es * s.B * Mp * s.H * (size_t)s.N * s.P);
     w.rinv = (float*)take(4 * s.B * Mp * s.H * (size_t)s.N);
     w.qb = take(es * s.B * s.L * s.G * (size_t)s.N);
     w.qh = take(es * s.B * s.L * s.G * (size_t)s.N);
-    w.ql = lo ? take(2 * s.B * s.L * s.G * (size_t)s.N) : nullptr;
+    w.ql = take(es * s.B * s.L * s.G * (size_t)s.N);
     w.qsc = (float*)take(4 * s.B * s.L * (size_t)s.G);
     w.eb = (float*)take(4 * s.B * s.L * s.G * (size_t)s.P);
-    w.ebt = lo ? take(es * s.B * s.L * s.G * (size_t)s.P) : (void*)w.eb;
+    w.ebt = take(es * s.B * s.L * s.G * (size_t)s.P);
     w.gp = (float*)take(4 * s.B * s.H * Mp * Ls);
     w.gd = (float*)take(4 * s.B * s.H * Mp * Ls);
     w.part = (float*)take(4 * s.B * s.L * nhb * (size_t)(2 * s.N + s.P));
@@ -1188,7 +1160,6 @@ hipError_t run_bwd(const Shape& s, const SmaArgs& a, const void* q, const void* 
     const BwdWs w = bwd_layout(s, ws);
     const int hpb = bwd_heads_per_block(s);
     const int64_t Ls = bwd_row_stride(s);
-    constexpr bool LO = sizeof(T) == 2;
     hipError_t err;
     if (Mp > 0) {
         err = launch_sma_keys(s, a, mem, w.kmem, w.klo, w.rinv, st);
@@ -1199,7 +1170,7 @@ hipError_t run_bwd(const Shape& s, const SmaArgs& a, const void* q, const void* 
     prof_begin("k_bwd_prep", st);
     k_bwd_prep<T, N><<<rblocks, 256, 0, st>>>((const T*)q, (const T*)e, a.qw, a.ew, (T*)w.qb,
                                               (T*)w.qh, (bf16*)w.ql, w.qsc, w.eb,
-                                              LO ? (T*)w.ebt : nullptr, a.eps, a.normalize, rows);
+                                              (T*)w.ebt, a.eps, a.normalize, rows);
     prof_end(st);
     const int blk0 = s.S / kTokBlock;
     const int64_t nblk = (s.L + kTokBlock - 1) / kTokBlock - blk0;
@@ -1207,50 +1178,33 @@ hipError_t run_bwd(const Shape& s, const SmaArgs& a, const void* q, const void* 
         const int64_t BHC = s.B * (s.H / hpb);
         // the query operand needs its residual only when a norm weight makes
         // q (.) w inexact in bf16
-        const int use_ql = LO && a.qw != nullptr;
-        prof_begin("k_bwd_scores", st);
-        bool two = false;
-        if constexpr (sizeof(T) == 2) {
-            if (s.S >= 128) {
-                // bf16: 128 tokens per workgroup (S is a multiple of 128, so a
-                // block never straddles chunks)
-                constexpr int TB2 = 2 * kTokBlock;
-                const int sb0 = s.S / TB2;
-                const int64_t snblk = (s.L + TB2 - 1) / TB2 - sb0;
-                k_bwd_scores<T, N, 2><<<(unsigned)(BHC * snblk), 512, 0, st>>>(
-                    (const T*)w.qh, (const bf16*)w.ql, w.qsc, w.eb, (const T*)Cm, w.rinv,
-                    (const T*)w.kmem, (const T*)w.klo, lse, (const T*)dy, w.gp, w.gd, w.lsep, w.rdy,
-                    use_ql, s.L, Ls, s.H, s.G, s.S, Mp, hpb, sb0, (int)snblk, BHC);
-                two = true;
-            }
-        }
-        if (!two) {
-            k_bwd_scores<T, N, 1><<<(unsigned)(BHC * nblk), 512, 0, st>>>(
+        const int use_ql = a.qw != nullptr;
+        // at S >= 128 128 tokens per workgroup (S is a multiple of 128, so a
+        // block never straddles chunks)
+        constexpr int TB2 = 2 * kTokBlock;
+        const bool two = s.S >= 128;
+        const int tb0 = two ? s.S / TB2 : blk0;
+        const int64_t tnblk = two ? (s.L + TB2 - 1) / TB2 - tb0 : nblk;
+        const unsigned tgrid = (unsigned)(BHC * tnblk);
+        auto scores = [&](auto rt) {
+            k_bwd_scores<T, N, decltype(rt)::value><<<tgrid, 512, 0, st>>>(
                 (const T*)w.qh, (const bf16*)w.ql, w.qsc, w.eb, (const T*)Cm, w.rinv,
                 (const T*)w.kmem, (const T*)w.klo, lse, (const T*)dy, w.gp, w.gd, w.lsep, w.rdy,
-                use_ql, s.L, Ls, s.H, s.G, s.S, Mp, hpb, blk0, (int)nblk, BHC);
-        }
-        prof_end(st);
-        prof_begin("k_bwd_tokens", st);
-        two = false;
-        if constexpr (sizeof(T) == 2) {
-            if (s.S >= 128) {
-                constexpr int TB2 = 2 * kTokBlock;
-                const int sb0 = s.S / TB2;
-                const int64_t snblk = (s.L + TB2 - 1) / TB2 - sb0;
-                k_bwd_tokens<T, N, 2><<<(unsigned)(BHC * snblk), 512, 0, st>>>(
-                    (const T*)w.qb, w.eb, w.rinv, (const T*)w.kmem, (const T*)z, w.lsep, w.rdy,
-                    (const T*)dy, w.gp, w.gd, w.part, a.z_per_head, s.L, Ls, s.H, s.G, s.S, Mp, hpb,
-                    sb0, (int)snblk, BHC);
-                two = true;
-            }
-        }
-        if (!two) {
-            k_bwd_tokens<T, N, 1><<<(unsigned)(BHC * nblk), 512, 0, st>>>(
+                use_ql, s.L, Ls, s.H, s.G, s.S, Mp, hpb, tb0, (int)tnblk, BHC);
+        };
+        auto tokens = [&](auto rt) {
+            k_bwd_tokens<T, N, decltype(rt)::value><<<tgrid, 512, 0, st>>>(
                 (const T*)w.qb, w.eb, w.rinv, (const T*)w.kmem, (const T*)z, w.lsep, w.rdy,
                 (const T*)dy, w.gp, w.gd, w.part, a.z_per_head, s.L, Ls, s.H, s.G, s.S, Mp, hpb,
-                blk0, (int)nblk, BHC);
-        }
+                tb0, (int)tnblk, BHC);
+        };
+        using One = std::integral_constant<int, 1>;
+        using Two = std::integral_constant<int, 2>;
+        prof_begin("k_bwd_scores", st);
+        if (two) scores(Two()); else scores(One());
+        prof_end(st);
+        prof_begin("k_bwd_tokens", st);
+        if (two) tokens(Two()); else tokens(One());
         prof_end(st);
     }
     const int64_t BH = s.B * s.H;
@@ -1268,8 +1222,8 @@ hipError_t run_bwd(const Shape& s, const SmaArgs& a, const void* q, const void* 
     return hipGetLastError();
 }
 
-// The generic path: token and memory sides from generic.hip, then the same
-// finishing kernel with one head per partial.
+// The fp32 kernels' path: token and memory sides from sma_f32.hip, then the
+// same finishing kernel with one head per partial.
 GenBwdWs gbwd_layout(const Shape& s, void* base) {
     const int64_t Mp = s.M > 1 ? s.M - 1 : 0;
     const size_t Ls = (size_t)bwd_row_stride(s);
@@ -1281,6 +1235,8 @@ GenBwdWs gbwd_layout(const Shape& s, void* base) {
         return r;
     };
     GenBwdWs w;
+    w.qb = take(4 * s.B * s.L * s.G * (size_t)s.N);
+    w.eb = take(4 * s.B * s.L * s.G * (size_t)s.P);
     w.gp = take(4 * s.B * s.H * (Mp > 0 ? Mp : 1) * Ls);
     w.dl = take(4 * s.B * s.H * (Mp > 0 ? Mp : 1) * Ls);
     w.rdy = take(4 * s.B * s.L * (size_t)s.H);
@@ -1295,9 +1251,9 @@ hipError_t run_gbwd(const Shape& s, const SmaArgs& a, const void* q, const void*
                     const void* Cm, const void* mem, const void* z, const float* lse,
                     const void* dy, float* dq, float* de, float* dC, float* dmem, float* dz,
                     void* ws, hipStream_t st) {
-    (void)lse;  // the generic backward forms the exact log-sum-exp itself
+    (void)lse;  // the fp32 token kernel forms the exact log-sum-exp itself
     const GenBwdWs w = gbwd_layout(s, ws);
-    hipError_t err = launch_gsma_bwd(s, a, q, e, Cm, mem, z, dy, w, dmem, st);
+    hipError_t err = launch_fsma_bwd(s, a, q, e, Cm, mem, z, dy, w, dmem, st);
     if (err != hipSuccess) return err;
     const int64_t rows = s.B * s.L * s.G;
     prof_begin("k_bwd_finish", st);
@@ -1338,7 +1294,7 @@ hipError_t run_bwd_n(const Shape& s, const SmaArgs& a, const void* q, const void
 }  // namespace
 
 size_t sma_bwd_workspace_bytes(const Shape& s) {
-    if (!tuned_shape(s)) return gbwd_layout(s, nullptr).bytes;
+    if (!sma_bf16_shape(s)) return gbwd_layout(s, nullptr).bytes;
     return bwd_layout(s, nullptr).bytes;
 }
 
@@ -1346,12 +1302,11 @@ hipError_t launch_sma_bwd(const Shape& s, const SmaArgs& a, const void* q, const
                           const void* Cm, const void* mem, const void* z, const float* lse,
                           const void* dy, float* dq, float* de, float* dC, float* dmem, float* dz,
                           void* ws, hipStream_t st) {
-    if (!tuned_shape(s)) {
+    if (!sma_bf16_shape(s)) {
         if (s.dtype == 1) return run_gbwd_n<bf16>(s, a, q, e, Cm, mem, z, lse, dy, dq, de, dC, dmem, dz, ws, st);
         return run_gbwd_n<float>(s, a, q, e, Cm, mem, z, lse, dy, dq, de, dC, dmem, dz, ws, st);
     }
-    if (s.dtype == 1) return run_bwd_n<bf16>(s, a, q, e, Cm, mem, z, lse, dy, dq, de, dC, dmem, dz, ws, st);
-    return run_bwd_n<float>(s, a, q, e, Cm, mem, z, lse, dy, dq, de, dC, dmem, dz, ws, st);
+    return run_bwd_n<bf16>(s, a, q, e, Cm, mem, z, lse, dy, dq, de, dC, dmem, dz, ws, st);
 }
 
 }  // namespace dart

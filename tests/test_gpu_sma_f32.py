@@ -1,0 +1,46 @@
+"""The attention kernels on the fp32 matrix instructions, forward and backward,
+at the edges of their tiles: 16 tokens of a wave in several chunks, blocks of 64
+tokens cut by the end of the sequence, every N, chunk sizes around 16 and 64,
+and both block shapes of the memory side (one memory of up to 64 rows per
+block; as many memories as the registers hold when that leaves two blocks per
+CU), against the oracle with the metrics of the other attention tests."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2608_02032_amd import synth
+from tests.helpers import TOL, assert_close_slices, assert_lse_close, to_np
+from tests import test_gpu_sma_bwd as MB
+from tests.test_gpu_parity import run_sma, sma_case
+
+pytestmark = pytest.mark.gpu
+
+# B, L, H, G, N, S, dtype, z_per_head
+SHAPES = [
+    (1, 66, 2, 1, 16, 5, "fp32", True),      # a wave spans four chunks
+    (2, 129, 3, 1, 32, 17, "fp32", False),   # chunks of 16 tokens and one
+    (1, 127, 4, 2, 64, 63, "bf16", True),
+    (1, 193, 2, 2, 128, 65, "bf16", False),
+    (1, 257, 3, 1, 128, 64, "fp32", True),   # fp32 storage at a tuned chunk size
+    (1, 65, 2, 1, 64, 64, "fp32", True),     # one token with a memory
+    (32, 256, 4, 1, 64, 16, "fp32", True),   # full memory blocks: four memories
+    (8, 200, 4, 1, 128, 12, "fp32", True),   # ... two memories of 128 rows, the last block half empty
+    (64, 100, 4, 1, 16, 5, "fp32", True),    # ... sixteen memories
+    (64, 120, 4, 1, 32, 7, "bf16", True),    # ... eight memories
+]
+
+
+@pytest.mark.parametrize("c", SHAPES, ids=lambda c: "B%d_L%d_H%d_G%d_N%d_S%d_%s" % c[:7])
+def test_sma_f32_forward_and_backward(c):
+    B, L, H, G, N, S, dtype, zh = c
+    w = synth.Workload("f32_%d_%d" % (N, S), B, L, H, 64, N, S, dtype, ngroups=G, z_per_head=zh)
+    print("\n[gpu-case] sma f32 %s" % (w,), flush=True)
+    d, mem, y_ssd, dy = MB.bwd_case(w, seed=L)
+    y, lse = run_sma(w, d, mem, y_ssd)
+    y_ref, lse_ref = oracle.sma(d["q"], d["e"], d["Cm"], mem, d["z"], y_ssd, S)
+    # fp32 sums whatever the storage; outputs are rounded to it
+    assert_close_slices(to_np(y), y_ref, TOL[dtype] if dtype == "fp32" else 2.0 ** -8, what="y")
+    assert_lse_close(to_np(lse), lse_ref, "fp32")
+    np.testing.assert_array_equal(to_np(y)[:, :S], y_ssd[:, :S].astype(np.float64))
+    got = MB.run_gpu(w, d, mem, y_ssd, dy)
+    MB.check(w, got, d, mem, dy)
