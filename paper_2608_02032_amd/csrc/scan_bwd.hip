@@ -1,42 +1,56 @@
-// scan_bwd.hip -- backward of the chunked SSD scan and of its chunk memories.
+// scan_bwd.hip -- backward of the chunked SSD scan and of its chunk memories on
+// the fp32 matrix instructions: fp32 storage at every shape, and either storage
+// at the shapes outside the bf16 kernels' set (scan_bwd_mfma.hip).
 //
 // Paper: Sec. 2 (the recurrence H_t = a_t H_{t-1} + dt_t B_t^T x_t,
 // y_t = C_t H_t, a_t = exp(dt_t A_h)) and Sec. 3 / App. A (the chunk memory
 // dH_[c], the chunk's own contribution).  Gradients of
 //   loss = sum_t dy_t . y_t + sum_c <dmem_c, dH_[c]> + <dh_last, H_{L-1}>
-// with respect to x, dt, A, B, C and h0.  With Lam_t the adjoint of the
-// token's input term u_t = dt_t B_t^T x_t (through later outputs, through
-// H_{L-1} and through its own chunk's memory):
-//   Lam_t = C_t^T dy_t + a_{t+1} Lam_{t+1} inside chunk c, starting at the
-//           chunk's last token from W_c = R_c + dmem_c, where R_c is the
-//           adjoint entering chunk c's end from the later chunks:
-//           R_{M-1} = dh_last, R_{c-1} = e^{cs_e(c)} R_c + dR_c,
-//           dR_c = sum_{s in c} e^{cs_s} C_s^T dy_s (cs inclusive within c),
-//           dh0 = R_{-1};
-//   dx_t = dt_t B_t Lam_t,  dB_t = dt_t Lam_t x_t,  dC_t = H_t dy_t;
-//   the decay gradient, per (b, h) a reverse cumulative sum of scalars
-//   (a_t <G_t, H_{t-1}> = <G_t, H_t> - <G_t, u_t> telescopes):
-//     g_t = sum_{s >= t} (y_s . dy_s - dx_s . x_s) + <dh_last, H_{L-1}>
-//           + sum_{c' >= c(t)} <dmem_c', dH_[c']>,
-//   ddt_t = dx_t . x_t / dt_t + A_h g_t,  dA_h = sum_{b,t} dt_t g_t.
+// with respect to x, dt, A, B, C and h0.
 //
-// Kernels, in launch order (after a forward scan into the workspace, which
-// gives y_ssd, the memories, H_{L-1} and every chunk's entry state):
-//   k_sbwd_chunk   per (b, c, h): dR_c and the chunk's total decay;
-//   k_sbwd_pass    per (b, h, 1024 elements): the reverse chunk pass -> R_c,
-//                  dh0;
-//   k_sbwd_tokens  per (b, c, block of heads of one group): for each head a
-//                  forward sweep over the chunk's tokens (H_t from the entry
-//                  state, dC) and a reverse one (Lam_t, dx, dB).  Each of the
-//                  4 waves holds N/4 rows of the N x P state, each lane N/16
-//                  rows by 4 columns, so the sums over p are short in-lane
-//                  sums plus a reduce-scatter over 16 lanes, and the sum over
-//                  n of dx meets in LDS once per 16 tokens.  The same sweeps give
-//                  the pieces of the decay gradient (y.dy, (B Lam).x and the
-//                  memory terms) on one consistent trajectory;
-//   k_sbwd_decay   per (b, h): the reverse cumulative sum -> ddt, dA partials;
-//   k_sbwd_finish  per (b, t, g): dB, dC summed over the group's head blocks;
-//                  dA summed over the batch.
+// The sequence is cut into pieces of at most 64 tokens that nest with the
+// memory chunks: a chunk of S >= 64 tokens is ceil(S / 64) pieces, and for
+// S < 64 a piece is floor(64 / S) whole chunks.  With cs the inclusive
+// cumulative log decay inside a piece (e its last token), H the state entering
+// it and R the adjoint of the state leaving it, M1[s,t] = e^{cs_s - cs_t} C_s.B_t
+// and M2[s,t] = e^{cs_s - cs_t} dy_s.x_t for t <= s:
+//   dx_t = dt_t [sum_s M1[s,t] dy_s + e^{cs_e - cs_t} B_t W + B_t D_t],
+//   dB_t = dt_t [sum_s M2[s,t] C_s + e^{cs_e - cs_t} W x_t + D_t x_t],
+//   dC_s = sum_t M2[s,t] dt_t B_t + e^{cs_s} H dy_s,
+// where a chunk's dmem reaches its own tokens only: for S >= 64 decayed from
+// the chunk's end to the piece's end and added to R (W = R + D, D_t = 0), for
+// S < 64 inside the piece (W = R, D_t = e^{cs_ce - cs_t} dmem_c(t), ce the
+// chunk's last token).  The decay gradient dL/dl_t (l_t = dt_t A_h) is the sum
+// over the (input s', output s) pairs with s' < t <= s, from piece-local parts
+// only, so no sum runs (and cancels) over the whole sequence:
+//   inside the piece: sum_{s >= t} (r_s - c_s), r and c the row and column sums
+//     of P[s,t] = M1[s,t] (dy_s . x_t) dt_t;
+//   input inside, leaving: sum_{s' < t} dt_s' x_s' . (e^{cs_e - cs_s'} B_s' W),
+//     and the same with D_s' over the tokens s' of t's own chunk;
+//   entering, output inside: sum_{s >= t} e^{cs_s} C_s . (H dy_s);
+//   entering and leaving: e^{cs_e} (<R, H> + <D, H_own>), H_own the part of H
+//     from the piece's own chunk.
+// ddt_t = x_t . (dx_t / dt_t) + A_h dL/dl_t, dA_h = sum_{b,t} dt_t dL/dl_t.
+//
+// Kernels, in launch order:
+//   k_fs_contract  per (b, piece, h): dH = sum_s (B_s dt_s e^{cs_e - cs_s})^T x_s,
+//                  dR = sum_s (C_s e^{cs_s})^T dy_s and the piece's log decay;
+//   k_fs_pass      per (b, h, 1024 elements): forward over the pieces, dH becomes
+//                  the entering state H; then backward, dR becomes W (and dh0),
+//                  with the sums of the entering-and-leaving terms;
+//   k_fs_tokens    per (b, piece, block of heads of one group): everything else.
+//                  C_s . B_t depends on the group only: its tiles are formed once
+//                  per block, and the heads' dt_t M2 are summed before the two
+//                  contractions over C and B, also once per block;
+//   k_fs_finish    dB, dC summed over a group's head blocks, dA over pieces.
+//
+// All products are v_mfma_f32_16x16x4_f32, whose rate (32 cycles each) bounds
+// k_fs_tokens; operand layouts as in sma_f32.hip: lane (m, g) = (lane % 16,
+// lane / 16), tiles of 64-float rows in LDS in 16-byte chunks.  An accumulator
+// tile (rows s = 4 g + r, column t = m) is the next product's operand as it
+// stands: at step r its k index g means s = 4 g + r.
+#include <type_traits>
+
 #include "dart_common.hpp"
 #include "dart_internal.hpp"
 
@@ -44,502 +58,738 @@ namespace dart {
 namespace {
 
 constexpr int kP = 64;
-constexpr int kHpb = 4;  // heads per k_sbwd_tokens workgroup (at most)
+constexpr int kBT = 256;  // threads: 4 waves
+constexpr int kQ = 64;    // tokens per piece at most, 16 a wave
 
-__device__ __forceinline__ float block_sum(float v, float* red) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane == 0) red[wave] = v;
-    __syncthreads();
-    float s = 0.f;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += red[w];
-    return s;
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
+__device__ __forceinline__ f32x4 lds4(const char* p) { return *reinterpret_cast<const f32x4*>(p); }
 
-// ---- per (b, c, h): chunk adjoint and total decay -------------------------------
-// Thread (n, slice of P/TPR columns); the running product e^{cs_s} advances
-// token by token.
-template <typename T, int N>
-__global__ __launch_bounds__(256) void k_sbwd_chunk(const T* __restrict__ Cm,
-                                                    const T* __restrict__ dy,
-                                                    const float* __restrict__ dt,
-                                                    const float* __restrict__ A,
-                                                    float* __restrict__ dR,
-                                                    float* __restrict__ dec, int64_t L, int H,
-                                                    int G, int S, int64_t M) {
-    constexpr int TPR = 256 / N;
-    constexpr int PPT = kP / TPR;
-    const int64_t c = blockIdx.x;
-    const int h = blockIdx.y;
-    const int64_t b = blockIdx.z;
-    const int g = h / (H / G);
-    const int tid = threadIdx.x;
-    const int n = tid / TPR, p0 = (tid % TPR) * PPT;
-    const int64_t a0 = c * S;
-    const int64_t e = (c + 1) * S < L ? (c + 1) * S - 1 : L - 1;
-    const float Ah = A[h];
-    float acc[PPT];
-#pragma unroll
-    for (int i = 0; i < PPT; ++i) acc[i] = 0.f;
-    float w = 1.f;
-    for (int64_t s = a0; s <= e; ++s) {
-        w *= __expf(dt[(b * L + s) * H + h] * Ah);
-        const float cw = w * to_f(Cm[((b * L + s) * G + g) * N + n]);
-        const T* dyr = dy + ((b * L + s) * H + h) * kP + p0;
-#pragma unroll
-        for (int i = 0; i < PPT; i += 4) {
-            float d4[4];
-            load4(dyr + i, d4);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) acc[i + k] += cw * d4[k];
-        }
-    }
-    float* out = dR + ((b * M + c) * H + h) * (int64_t)N * kP + n * kP + p0;
-#pragma unroll
-    for (int i = 0; i < PPT; i += 4) {
-        float v4[4] = {acc[i], acc[i + 1], acc[i + 2], acc[i + 3]};
-        store4(out + i, v4);
-    }
-    if (tid == 0) dec[(b * H + h) * M + c] = w;
-}
-
-// ---- per (b, h, element block): reverse chunk pass ----------------------------
-__global__ __launch_bounds__(256) void k_sbwd_pass(const float* __restrict__ dR,
-                                                   const float* __restrict__ dec,
-                                                   const float* __restrict__ dhl,
-                                                   float* __restrict__ Rs, float* __restrict__ dh0,
-                                                   int H, int NP, int64_t M) {
-    const int h = blockIdx.y;
-    const int64_t b = blockIdx.z;
-    const int e0 = (blockIdx.x * 256 + threadIdx.x) * 4;
-    if (e0 >= NP) return;
-    float r[4] = {0.f, 0.f, 0.f, 0.f};
-    if (dhl) load4(dhl + (b * H + h) * (int64_t)NP + e0, r);
-    for (int64_t c = M - 1; c >= 0; --c) {
-        const int64_t ch = (b * M + c) * H + h;
-        store4(Rs + ch * NP + e0, r);
-        float d[4];
-        load4(dR + ch * NP + e0, d);
-        const float dc = dec[(b * H + h) * M + c];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) r[i] = dc * r[i] + d[i];
-    }
-    if (dh0) store4(dh0 + (b * H + h) * (int64_t)NP + e0, r);
-}
-
-template <int K>
-__device__ __forceinline__ void load_k(const bf16* p, float (&v)[K]) {
-    if constexpr (K % 8 == 0) {
-#pragma unroll
-        for (int i = 0; i < K; i += 8) {
-            float t[8];
-            load8(p + i, t);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[i + k] = t[k];
-        }
-    } else if constexpr (K == 4) {
-        load4(p, v);
-    } else {
-#pragma unroll
-        for (int i = 0; i < K; ++i) v[i] = (float)p[i];
-    }
-}
-template <int K>
-__device__ __forceinline__ void load_k(const float* p, float (&v)[K]) {
-    if constexpr (K % 4 == 0) {
-#pragma unroll
-        for (int i = 0; i < K; i += 4) {
-            float t[4];
-            load4(p + i, t);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) v[i + k] = t[k];
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < K; ++i) v[i] = p[i];
-    }
-}
-
-// K storage elements kept raw in registers (converted where used), so that a
-// load issued one token ahead is not waited for at once.
-template <typename T, int K>
-struct alignas(sizeof(T) * K >= 16 ? 16 : sizeof(T) * K) RawVec {
-    T v[K];
+// The pieces of a sequence.
+struct Pieces {
+    int64_t L, nk;
+    int S, nq, Q;  // nq pieces per chunk (S >= 64), or Q tokens per piece
 };
-template <typename T, int K>
-__device__ __forceinline__ RawVec<T, K> raw_load(const T* p) {
-    return *reinterpret_cast<const RawVec<T, K>*>(p);
+inline Pieces pieces_of(const Shape& s) {
+    Pieces p;
+    p.L = s.L;
+    p.S = s.S;
+    if (s.S >= kQ) {
+        p.nq = (s.S + kQ - 1) / kQ;
+        p.Q = kQ;
+        p.nk = (s.M - 1) * p.nq + (s.L - (s.M - 1) * s.S + kQ - 1) / kQ;
+    } else {
+        p.nq = 1;
+        p.Q = kQ / s.S * s.S;
+        p.nk = (s.L + p.Q - 1) / p.Q;
+    }
+    return p;
+}
+__device__ __forceinline__ void piece_range(const Pieces& p, int64_t k, int64_t& t0, int64_t& t1) {
+    if (p.S >= kQ) {
+        const int64_t c = k / p.nq, end = (c + 1) * p.S < p.L ? (c + 1) * p.S : p.L;
+        t0 = c * p.S + (k - c * p.nq) * kQ;
+        t1 = t0 + kQ < end ? t0 + kQ : end;
+    } else {
+        t0 = k * p.Q;
+        t1 = t0 + p.Q < p.L ? t0 + p.Q : p.L;
+    }
 }
 
-// ---- per (b, c, head block): the two sweeps ----------------------------------------
-// Wave w holds state rows n0 = w N/4 .. n0 + N/4 - 1; inside the wave lane
-// (ng, pg) = (lane / 16, lane % 16) holds the RL = N/16 rows n0 + ng RL + i and
-// the 4 columns 4 pg + c.  Sums over p (dC, dB) are then 4-term in-lane sums
-// followed by a reduce-scatter over the 16 pg lanes; the sum over n of dx is an
-// in-lane sum over RL rows, a reduce-scatter over the 4 ng lanes and an LDS
-// exchange between the waves once per 16 tokens.
-// Besides dx, dB and dC this records, per wave, the pieces of the decay
-// gradient that the same recomputed trajectory gives: y_t . dy_t
-// (= C_t . dC_t), (B_t Lam_t) . x_t, and <dmem_c, dH_[c]> (+ <dh_last, H_{L-1}>
-// in the last chunk), so that the reverse cumulative sum telescopes exactly.
+// This lane's token of the piece: dt (0 past its end) and the inclusive
+// cumulative log decay in log2 units, by one wave.
+__device__ __forceinline__ float piece_decay(const float* __restrict__ dt, float Ah, int64_t b,
+                                             int64_t L, int H, int h, int64_t t0, int64_t t1,
+                                             int lane, float& d) {
+    d = t0 + lane < t1 ? dt[(b * L + t0 + lane) * H + h] : 0.f;
+    float cs = d * Ah * kLog2e;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const float u = __shfl_up(cs, o, 64);
+        if (lane >= o) cs += u;
+    }
+    return cs;
+}
+
+// A grid of any length along x and y (a launch takes at most 2^32 threads
+// along x).
+inline dim3 flat_grid(int64_t blocks) {
+    const int64_t x = blocks < (1 << 23) ? blocks : (1 << 23);
+    return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
+}
+__device__ __forceinline__ int64_t flat_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
+// ---- per (b, piece, h): the piece's contributions ---------------------------------
+// The four waves split the N rows (WN of them, NTW row tiles each) and, for
+// N < 64, the column tiles.  Rows arrive 16 tokens at a time.  HBM-bound: 2 N P
+// floats are written per 64 tokens of a head.
 template <typename T, int N>
-__global__ __launch_bounds__(256) void k_sbwd_tokens(
+__global__ __launch_bounds__(kBT, 2) void k_fs_contract(
     const T* __restrict__ x, const float* __restrict__ dt, const float* __restrict__ A,
     const T* __restrict__ Bm, const T* __restrict__ Cm, const T* __restrict__ dy,
-    const float* __restrict__ states, const float* __restrict__ Rs, const float* __restrict__ dmem,
-    const float* __restrict__ dhl, float* __restrict__ dx, float* __restrict__ bxl,
-    float* __restrict__ ydyp, float* __restrict__ mdp, float* __restrict__ dBp,
-    float* __restrict__ dCp, int64_t L, int H, int G, int S, int64_t M, int64_t Mcap, int hpb) {
-    constexpr int RL = N / 16;       // rows per lane
-    constexpr int GRP = 16 / RL;     // pg lanes that share one row sum
-    constexpr int TB = 16;           // tokens per dx exchange
-    __shared__ float xpart[2][TB][4][kP];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int ng = lane >> 4, pg = lane & 15;
-    const int64_t c = blockIdx.x;
-    const int hb = blockIdx.y;
-    const int64_t b = blockIdx.z;
-    const int nhb = H / hpb;
-    const int h0 = hb * hpb;
-    const int g = h0 / (H / G);
-    const int nl = wave * (N / 4) + ng * RL;  // first row of this lane
-    const int pl = pg * 4;                    // first column of this lane
-    const int64_t a0 = c * S;
-    const int64_t e = (c + 1) * S < L ? (c + 1) * S - 1 : L - 1;
-    const int nsum = wave * (N / 4) + ng * RL + pg / GRP;  // row of this lane's sum
-    const bool writer = pg % GRP == 0;
+    float* __restrict__ dH, float* __restrict__ dR, float* __restrict__ lda, Pieces pc, int H, int G,
+    int64_t blocks) {
+    constexpr int WN = N / 16 < 4 ? N / 16 : 4, NTW = N / 16 / WN, PT = WN;  // column tiles per wave
+    constexpr int TT = 16, RN = N + 16, RP = kP + 16;
+    constexpr int CN = (TT * N / 4 + kBT - 1) / kBT;
+    __shared__ __attribute__((aligned(16))) float s_b[2][TT][RN], s_c[2][TT][RN], s_x[2][TT][RP], s_y[2][TT][RP];
+    __shared__ float s_f[2][kQ];
+    const int64_t blk = flat_block();
+    if (blk >= blocks) return;
+    const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave % WN, p0 = wave / WN * PT;
+    const int h = (int)(blk % H);
+    const int64_t bk = blk / H, b = bk / pc.nk, k = bk - b * pc.nk;
+    const int grp = (int)((int64_t)h * G / H);
+    int64_t t0, t1;
+    piece_range(pc, k, t0, t1);
+    if (wave == 0) {
+        float d;
+        const float cs = piece_decay(dt, A[h], b, pc.L, H, h, t0, t1, lane, d);
+        const float ce = __shfl(cs, 63, 64);
+        s_f[0][lane] = fast_exp2(ce - cs) * d;
+        s_f[1][lane] = t0 + lane < t1 ? fast_exp2(cs) : 0.f;
+        if (lane == 0) lda[(b * H + h) * pc.nk + k] = ce;
+    }
+    float rb[CN][4], rc[CN][4], rx[4], ry[4];
+    auto load = [&](int64_t tt) {
+#pragma unroll
+        for (int q = 0; q < CN; ++q) {
+            const int i = tid + q * kBT;
+            if (i < TT * N / 4) {
+                const int64_t t = tt + i / (N / 4) < t1 ? tt + i / (N / 4) : t1 - 1;
+                const int64_t o = ((b * pc.L + t) * G + grp) * N + 4 * (i % (N / 4));
+                load4(Bm + o, rb[q]);
+                load4(Cm + o, rc[q]);
+            }
+        }
+        const int64_t t = tt + (tid >> 4) < t1 ? tt + (tid >> 4) : t1 - 1;
+        const int64_t o = ((b * pc.L + t) * H + h) * kP + 4 * (tid & 15);
+        load4(x + o, rx);
+        load4(dy + o, ry);
+    };
+    auto store = [&](int buf) {
+#pragma unroll
+        for (int q = 0; q < CN; ++q) {
+            const int i = tid + q * kBT;
+            if (i < TT * N / 4) {
+                store4(&s_b[buf][i / (N / 4)][4 * (i % (N / 4))], rb[q]);
+                store4(&s_c[buf][i / (N / 4)][4 * (i % (N / 4))], rc[q]);
+            }
+        }
+        store4(&s_x[buf][tid >> 4][4 * (tid & 15)], rx);
+        store4(&s_y[buf][tid >> 4][4 * (tid & 15)], ry);
+    };
+    f32x4 mh[NTW][PT], mr[NTW][PT];
+#pragma unroll
+    for (int n = 0; n < NTW; ++n)
+#pragma unroll
+        for (int p = 0; p < PT; ++p) mh[n][p] = mr[n][p] = f32x4{0.f, 0.f, 0.f, 0.f};
+    load(t0);
+    store(0);
+    int buf = 0;
+    for (int64_t tt = t0; tt < t1; tt += TT, buf ^= 1) {
+        __syncthreads();
+        const bool more = tt + TT < t1;
+        if (more) load(tt + TT);
+#pragma unroll
+        for (int ks = 0; ks < TT / 4; ++ks) {
+            const int t = 4 * ks + g;
+            const float fx = s_f[0][(int)(tt - t0) + t], fy = s_f[1][(int)(tt - t0) + t];
+            float ab[NTW], ac[NTW];
+#pragma unroll
+            for (int n = 0; n < NTW; ++n) {
+                ab[n] = s_b[buf][t][wn * 16 * NTW + NTW * m + n] * fx;
+                ac[n] = s_c[buf][t][wn * 16 * NTW + NTW * m + n] * fy;
+            }
+            const f32x4 vx = *reinterpret_cast<const f32x4*>(&s_x[buf][t][4 * m]);
+            const f32x4 vy = *reinterpret_cast<const f32x4*>(&s_y[buf][t][4 * m]);
+#pragma unroll
+            for (int n = 0; n < NTW; ++n)
+#pragma unroll
+                for (int p = 0; p < PT; ++p) {
+                    // the wave's column tiles (all four for N >= 64)
+                    const float px = PT == 4 ? vx[p] : vx[p0 + p], py = PT == 4 ? vy[p] : vy[p0 + p];
+                    mh[n][p] = mfma4(ab[n], px, mh[n][p]);
+                    mr[n][p] = mfma4(ac[n], py, mr[n][p]);
+                }
+        }
+        if (more) store(buf ^ 1);
+    }
+    const int64_t base = blk * (int64_t)(N * kP);
+#pragma unroll
+    for (int n = 0; n < NTW; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int64_t o = base + (wn * 16 * NTW + NTW * (4 * g + r) + n) * kP + 4 * m + p0;
+            if constexpr (PT == 4) {
+                const float vh[4] = {mh[n][0][r], mh[n][1][r], mh[n][2][r], mh[n][3][r]};
+                const float vr[4] = {mr[n][0][r], mr[n][1][r], mr[n][2][r], mr[n][3][r]};
+                store4(dH + o, vh);
+                store4(dR + o, vr);
+            } else {
+#pragma unroll
+                for (int p = 0; p < PT; ++p) {
+                    dH[o + p] = mh[n][p][r];
+                    dR[o + p] = mr[n][p][r];
+                }
+            }
+        }
+}
 
+// ---- per (b, h, 1024 elements): the passes over the pieces --------------------------
+// In place: dH -> H (the state entering each piece), dR -> W.  kpart [b][h][k]
+// [waves]: each wave's part of e^{cs_e} (<R, H> + <D, H_own>).  suf [b][h][k]:
+// the decay from a piece's end to its chunk's end (every block of a (b, h)
+// writes the same values and reads its own).
+template <bool OWN>
+__global__ __launch_bounds__(256) void k_fs_pass(float* __restrict__ dH, float* __restrict__ dR,
+                                                 const float* __restrict__ lda, const float* __restrict__ h0,
+                                                 const float* __restrict__ dhl, const float* __restrict__ dmem,
+                                                 float* __restrict__ dh0, float* __restrict__ kpart,
+                                                 float* suf, Pieces pc, int H, int NP, int64_t Mcap) {
+    const int h = blockIdx.y;
+    const int64_t b = blockIdx.z, bh = b * H + h;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int e0 = (blockIdx.x * 256 + tid) * 4;
+    const int nw = gridDim.x * 4, wv = blockIdx.x * 4 + (tid >> 6);
+    const float* ld = lda + bh * pc.nk;
+    float* kp = kpart + bh * pc.nk * nw + wv;
+    const int64_t step = (int64_t)H * NP;
+    float* ph = dH + (b * pc.nk * H + h) * (int64_t)NP + e0;
+    float* pr = dR + (b * pc.nk * H + h) * (int64_t)NP + e0;
+    const float* pm = dmem ? dmem + (b * Mcap * H + h) * (int64_t)NP + e0 : nullptr;
+    if (OWN) {
+        // one thread per chunk
+        for (int64_t k = (int64_t)tid * pc.nq; k < pc.nk; k += 256 * pc.nq) {
+            const int64_t last = (k + pc.nq < pc.nk ? k + pc.nq : pc.nk) - 1;
+            float a = 1.f;
+            for (int64_t q = last; q >= k; --q) {
+                suf[bh * pc.nk + q] = a;
+                a *= fast_exp2(ld[q]);
+            }
+        }
+        __syncthreads();
+    }
+    const bool in = e0 < NP;
+    float hc[4] = {0.f, 0.f, 0.f, 0.f}, ho[4] = {0.f, 0.f, 0.f, 0.f}, dm[4] = {0.f, 0.f, 0.f, 0.f};
+    if (h0 && in) load4(h0 + bh * (int64_t)NP + e0, hc);
+    for (int64_t k = 0, i = 0; k < pc.nk; ++k, i = i + 1 == pc.nq ? 0 : i + 1) {
+        const float a = fast_exp2(ld[k]);
+        float d4[4] = {0.f, 0.f, 0.f, 0.f};
+        if (in) {
+            load4(ph + k * step, d4);
+            store4(ph + k * step, hc);
+        }
+        if (OWN) {
+            if (i == 0) {
+                if (pm && in) load4(pm + k / pc.nq * step, dm);
+                ho[0] = ho[1] = ho[2] = ho[3] = 0.f;
+            }
+            float s = (ho[0] * dm[0] + ho[1] * dm[1]) + (ho[2] * dm[2] + ho[3] * dm[3]);
+            s = row4_sum(dpp_group_sum<16>(s));
+            if (lane == 0) kp[k * nw] = a * suf[bh * pc.nk + k] * s;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) ho[q] = a * ho[q] + d4[q];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) hc[q] = a * hc[q] + d4[q];
+    }
+    float r[4] = {0.f, 0.f, 0.f, 0.f}, dd[4] = {0.f, 0.f, 0.f, 0.f};
+    if (dhl && in) load4(dhl + bh * (int64_t)NP + e0, r);
+    const bool nest = pc.S >= kQ;  // a chunk's dmem leaves with its pieces
+    for (int64_t k = pc.nk - 1; k >= 0; --k) {
+        const float a = fast_exp2(ld[k]);
+        float d4[4] = {0.f, 0.f, 0.f, 0.f}, h4[4] = {0.f, 0.f, 0.f, 0.f}, w4[4];
+        if (in) {
+            load4(pr + k * step, d4);
+            load4(ph + k * step, h4);
+        }
+        if (nest && pm && in) {
+            const int64_t c = k / pc.nq;
+            if (k == pc.nk - 1 || (k + 1) / pc.nq != c) load4(pm + c * step, dd);
+        }
+        float s = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            w4[q] = r[q] + dd[q];
+            s += r[q] * h4[q];
+            r[q] = a * r[q] + d4[q];
+            dd[q] *= a;
+        }
+        if (in) store4(pr + k * step, w4);
+        s = row4_sum(dpp_group_sum<16>(s)) * a;
+        if (lane == 0) kp[k * nw] = OWN ? kp[k * nw] + s : s;
+    }
+    if (dh0 && in) store4(dh0 + bh * (int64_t)NP + e0, r);
+}
+
+// ---- per (b, piece, block of heads): the token gradients ----------------------------
+// A wave owns 16 tokens, as columns t of the tiles with s >= t and as rows of
+// dB, dC and dx.  Rows n of the N-row products come in the order
+// n = 16 NV q + NV m + i (tile (q, i), NV = min(4, N / 16)), so that NV
+// consecutive n of a B or C row are one load for NV tiles; a state's chunk c of
+// row n is at c ^ ((n / NV) & 15), without bank conflicts in either reading.
+// 36 + N / 4 KB of LDS, 256 registers: two blocks per CU.  SMALL: S < 64.
+template <typename T, int N, bool SMALL>
+__global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
+    const T* __restrict__ x, const float* __restrict__ dt, const float* __restrict__ A,
+    const T* __restrict__ Bm, const T* __restrict__ Cm, const T* __restrict__ dy,
+    const float* __restrict__ Hs, const float* __restrict__ Ws, const float* __restrict__ dmem,
+    const float* __restrict__ kpart, float* __restrict__ dx, float* __restrict__ ddt,
+    float* __restrict__ dBp, float* __restrict__ dCp, float* __restrict__ dAp, Pieces pc, int H, int G,
+    int64_t Mcap, int hpb, int nkp, int64_t blocks) {
+    constexpr int K = N / 16, NV = K < 4 ? K : 4, NQ = K / NV;
+    constexpr int MP = kQ + 4;  // row pitch of the summed M2, in floats
+    __shared__ __attribute__((aligned(16))) char s_xy[2 * kQ * 256], s_w[N * 256];
+    __shared__ __attribute__((aligned(16))) float s_cs[kQ], s_dt[kQ];
+    __shared__ float s_r[4][kQ], s_c[kQ], s_v[kQ], s_d[kQ], s_u[kQ], s_bx[kQ];
+    static_assert(kQ * MP * 4 <= 2 * kQ * 256, "the summed M2 takes the place of x and dy");
+    const int64_t blk = flat_block();
+    if (blk >= blocks) return;
+    char* s_x = s_xy;
+    char* s_y = s_xy + kQ * 256;
+    const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nhb = H / hpb;
+    const int64_t bk = blk / nhb, b = bk / pc.nk, k = bk - b * pc.nk;
+    const int hb = (int)(blk - bk * nhb), h0 = hb * hpb;
+    const int grp = (int)((int64_t)h0 * G / H);
+    int64_t t0, t1;
+    piece_range(pc, k, t0, t1);
+    const int nt = (int)(t1 - t0);
+    const int tl = 16 * w + m;  // this lane's token
+    const bool valid = tl < nt;
+    const bool used = 16 * w < nt;  // any token in the wave
+    // a row of the piece, clamped to its last token (whose x, dy and dt are
+    // taken as zero, so that it adds nothing)
+    auto row = [&](int s) { return b * pc.L + t0 + (s < nt ? s : nt - 1); };
+    const int64_t bt = row(tl);
+    float bv[K][4];
+#pragma unroll
+    for (int q = 0; q < K; ++q) load4(Bm + (bt * G + grp) * N + 16 * q + 4 * g, bv[q]);
+    // C_s . B_t of the tiles s >= t
+    f32x4 g1[4], mb[4], aB[K], aC[K];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        g1[j] = mb[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (j >= w && 16 * j < nt) {
+            const T* cr = Cm + (row(16 * j + m) * G + grp) * N + 4 * g;
+#pragma unroll
+            for (int q = 0; q < K; ++q) {
+                float c4[4];
+                load4(cr + 16 * q, c4);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) g1[j] = mfma4(c4[s], bv[q][s], g1[j]);
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < K; ++q) aB[q] = aC[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // NV consecutive elements
+    auto vec = [&](const T* p, float (&v)[NV]) {
+        if constexpr (NV == 4) {
+            load4(p, v);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NV; ++i) v[i] = to_f(p[i]);
+        }
+    };
+    // byte offsets of this lane's LDS reads: chunk 4 q + g of row m (oc, without
+    // the row), chunk m of row 4 g + r, and the two readings of a state
+    int oc[4], op[4], on[4], ow[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        oc[q] = m * 256 + (((4 * q + g) ^ m) << 4);
+        op[q] = (4 * g + q) * 256 + ((m ^ (4 * g + q)) << 4);
+        on[q] = NV * m * 256 + (((4 * q + g) ^ m) << 4);
+        // rows 16 q' + 4 g + s: key 4 q' + g for NV = 4 (by q' mod 4), 8 q' + 2 g +
+        // s / 2 for NV = 2, 4 g + s for NV = 1
+        ow[q] = NV == 4 ? g * 1024 + (((4 * q + g) ^ m) << 4)
+              : NV == 2 ? g * 1024 + ((((8 * (q >> 1) + 2 * g + (q & 1)) & 15) ^ m) << 4)
+                        : g * 1024 + (((4 * g + q) ^ m) << 4);
+    }
+    auto state_p = [&](int q, int s) {  // row 16 q + 4 g + s, columns 4 m ..
+        return lds4(s_w + ow[NV == 4 ? q & 3 : NV == 2 ? 2 * q + (s >> 1) : s] + (16 * q + s) * 256);
+    };
+    auto state_n = [&](int tile, int q) {  // the tile's row m, columns 16 q + 4 g ..
+        return lds4(s_w + on[q] + (16 * NV * (tile / NV) + tile % NV) * 256);
+    };
+    char* const xr = s_x + w * 4096;  // the wave's rows of x and dy
+    char* const yr = s_y + w * 4096;
+    // one state into s_w
+    auto stage_state = [&](const float* src) {
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+            const int i = tid + q * kBT, n = i >> 4, c = (i & 15) ^ ((n / NV) & 15);
+            lds_dma16(src + n * kP + 4 * c, s_w + (w * 64 + q * kBT) * 16);
+        }
+    };
     for (int hh = 0; hh < hpb; ++hh) {
         const int h = h0 + hh;
         const float Ah = A[h];
-        const int64_t ch = (b * M + c) * H + h;
-        const int64_t sm = ((b * Mcap + c) * H + h) * (int64_t)N * kP;
-        // forward sweep: H_t from the entry state; dC_t = H_t dy_t; the
-        // chunk's own contribution dH accumulates beside it
-        float st[RL][4], dh[RL][4];
+        const int64_t st = ((b * pc.nk + k) * H + h) * (int64_t)(N * kP);
+        __syncthreads();  // the last head's reads are done
+        stage_state(Ws + st);
 #pragma unroll
-        for (int i = 0; i < RL; ++i) {
-            float t4[4];
-            load4(states + ch * (int64_t)N * kP + (nl + i) * kP + pl, t4);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                st[i][k] = t4[k];
-                dh[i][k] = 0.f;
+        for (int q = 0; q < 4; ++q) {
+            const int s = (tid >> 4) + 16 * q, c = tid & 15;
+            float x4[4] = {0.f, 0.f, 0.f, 0.f}, y4[4] = {0.f, 0.f, 0.f, 0.f};
+            if (s < nt) {
+                load4(x + (row(s) * H + h) * kP + 4 * c, x4);
+                load4(dy + (row(s) * H + h) * kP + 4 * c, y4);
             }
+            const int o = s * 256 + ((c ^ (s & 15)) << 4);
+            *reinterpret_cast<f32x4*>(s_x + o) = f32x4{x4[0], x4[1], x4[2], x4[3]};
+            *reinterpret_cast<f32x4*>(s_y + o) = f32x4{y4[0], y4[1], y4[2], y4[3]};
         }
-        // the next token's rows are loaded while this one is swept
-        RawVec<T, 4> xr, yr;
-        RawVec<T, RL> br;
-        float dn, on = 0.f;  // on: the previous heads' partial of the row sum
-        const bool rmw = hh > 0 && writer;
-        auto fetch_f = [&](int64_t t) {
-            const int64_t th = (b * L + t) * H + h;
-            dn = dt[th];
-            if (rmw) on = dCp[((b * L + t) * nhb + hb) * (int64_t)N + nsum];
-            xr = raw_load<T, 4>(x + th * kP + pl);
-            yr = raw_load<T, 4>(dy + th * kP + pl);
-            br = raw_load<T, RL>(Bm + ((b * L + t) * G + g) * N + nl);
-        };
-        fetch_f(a0);
-        for (int64_t t = a0; t <= e; ++t) {
-            const int64_t th = (b * L + t) * H + h;
-            const float d = dn, oc = on;
-            const RawVec<T, 4> xc = xr, yc = yr;
-            const RawVec<T, RL> bc = br;
-            if (t < e) fetch_f(t + 1);
-            const float a = __expf(d * Ah);
-            float xv[4], dyv[4], bv[RL];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                xv[k] = to_f(xc.v[k]);
-                dyv[k] = to_f(yc.v[k]);
-            }
-#pragma unroll
-            for (int i = 0; i < RL; ++i) bv[i] = to_f(bc.v[i]);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) xv[k] *= d;
-            float v[RL];
-#pragma unroll
-            for (int i = 0; i < RL; ++i) {
-                float acc = 0.f;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const float u = bv[i] * xv[k];
-                    st[i][k] = a * st[i][k] + u;
-                    dh[i][k] = a * dh[i][k] + u;
-                    acc += st[i][k] * dyv[k];
-                }
-                v[i] = acc;
-            }
-            const float sc = lane_sums<RL, 16>(v, lane);
-            if (writer) dCp[((b * L + t) * nhb + hb) * (int64_t)N + nsum] = oc + sc;
-            // y_t . dy_t over this wave's rows: C_n dC_n summed over the rows
-            float yd = writer ? to_f(Cm[((b * L + t) * G + g) * N + nsum]) * sc : 0.f;
-#pragma unroll
-            for (int m = 32; m >= 1; m >>= 1) yd += __shfl_xor(yd, m, 64);
-            if (lane == 0) ydyp[th * 4 + wave] = yd;
+        if (w == 0) {
+            float d;
+            const float cs = piece_decay(dt, Ah, b, pc.L, H, h, t0, t1, lane, d);
+            s_cs[lane] = cs;
+            s_dt[lane] = d;
         }
-        float md = 0.f;
-        if (dmem) {
-#pragma unroll
-            for (int i = 0; i < RL; ++i) {
-                float t4[4];
-                load4(dmem + sm + (nl + i) * kP + pl, t4);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) md += t4[k] * dh[i][k];
-            }
-        }
-        if (dhl && c == M - 1) {
-            const float* hr = dhl + (b * H + h) * (int64_t)N * kP;
-#pragma unroll
-            for (int i = 0; i < RL; ++i) {
-                float t4[4];
-                load4(hr + (nl + i) * kP + pl, t4);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) md += t4[k] * st[i][k];
-            }
-        }
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) md += __shfl_xor(md, m, 64);
-        if (lane == 0) mdp[((b * H + h) * M + c) * 4 + wave] = md;
-
-        // reverse sweep: Lam from W_c = R_c + dmem_c; dx, dB
-        float lam[RL][4];
-#pragma unroll
-        for (int i = 0; i < RL; ++i) {
-            const int64_t o = (nl + i) * kP + pl;
-            float r4[4], m4[4] = {0.f, 0.f, 0.f, 0.f};
-            load4(Rs + ch * (int64_t)N * kP + o, r4);
-            if (dmem) load4(dmem + sm + o, m4);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) lam[i][k] = r4[k] + m4[k];
-        }
-        const int ntok = (int)(e - a0 + 1);
-        RawVec<T, RL> cr;
-        auto fetch_r = [&](int64_t t) {
-            const int64_t th = (b * L + t) * H + h;
-            dn = dt[th];
-            if (rmw) on = dBp[((b * L + t) * nhb + hb) * (int64_t)N + nsum];
-            xr = raw_load<T, 4>(x + th * kP + pl);
-            yr = raw_load<T, 4>(dy + th * kP + pl);
-            br = raw_load<T, RL>(Bm + ((b * L + t) * G + g) * N + nl);
-            cr = raw_load<T, RL>(Cm + ((b * L + t) * G + g) * N + nl);
-        };
-        fetch_r(e);
-        for (int k = 0; k < ntok; ++k) {
-            const int64_t t = e - k;
-            const float d = dn, ob = on;
-            const RawVec<T, 4> xc = xr, yc = yr;
-            const RawVec<T, RL> bc = br, cc = cr;
-            if (k + 1 < ntok) fetch_r(t - 1);
-            float xv[4], dyv[4], bv[RL], cv[RL];
+        __syncthreads();
+        const float cst = s_cs[tl], dtt = s_dt[tl], cse = s_cs[kQ - 1];
+        if (used) {
+            f32x4 xt[4], di[4], bw[4], bd[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                xv[q] = to_f(xc.v[q]);
-                dyv[q] = to_f(yc.v[q]);
+                xt[q] = lds4(xr + oc[q]);
+                di[q] = bw[q] = bd[q] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
 #pragma unroll
-            for (int i = 0; i < RL; ++i) {
-                bv[i] = to_f(bc.v[i]);
-                cv[i] = to_f(cc.v[i]);
-            }
-            float px[4] = {0.f, 0.f, 0.f, 0.f}, v[RL];
+            for (int j = 0; j < 4; ++j) {
+                if (j >= w && 16 * j < nt) {
+                    f32x4 g2 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int i = 0; i < RL; ++i) {
-                float acc = 0.f;
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 a = lds4(s_y + j * 4096 + oc[q]);
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) g2 = mfma4(a[s], xt[q][s], g2);
+                    }
+                    const f32x4 css = *reinterpret_cast<const f32x4*>(s_cs + 16 * j + 4 * g);
+                    f32x4 m1, ps;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        float e = fast_exp2(fminf(css[r] - cst, 0.f));
+                        if (j == w && 4 * g + r < m) e = 0.f;
+                        m1[r] = e * g1[j][r];
+                        mb[j][r] += dtt * (e * g2[r]);
+                        ps[r] = dpp_group_sum<16>(m1[r] * (g2[r] * dtt));
+                    }
+                    if (m == 0) *reinterpret_cast<f32x4*>(&s_r[w][16 * j + 4 * g]) = ps;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const f32x4 a = lds4(s_y + j * 4096 + op[r]);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) di[i] = mfma4(a[i], m1[r], di[i]);
+                    }
+                }
+            }
+            // B_t W
+#pragma unroll
+            for (int q = 0; q < K; ++q)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const f32x4 a = state_p(q, s);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) bw[i] = mfma4(a[i], bv[q][s], bw[i]);
+                }
+            const float fw = fast_exp2(cse - cst);
+            // the chunks of the wave's tokens, each dmem_c for its own tokens only
+            const int64_t c0 = (t0 + 16 * w) / pc.S;
+            const int nc = SMALL && dmem ? (int)((t0 + (16 * w + 15 < nt ? 16 * w + 15 : nt - 1)) / pc.S - c0) + 1 : 0;
+            auto own = [&](int c) {  // e^{cs_ce - cs_t}, zero for the others
+                const int lo = (int)((c0 + c) * pc.S - t0), hi = lo + pc.S < nt ? lo + pc.S : nt;
+                return tl >= lo && tl < hi ? fast_exp2(s_cs[hi - 1] - cst) : 0.f;
+            };
+            auto dmem_of = [&](int c) { return dmem + ((b * Mcap + c0 + c) * H + h) * (int64_t)(N * kP); };
+            if constexpr (SMALL) {
+                for (int c = 0; c < nc; ++c) {
+                    const float fd = own(c);
+                    const float* dm = dmem_of(c) + 4 * g * kP + 4 * m;
+#pragma unroll
+                    for (int q = 0; q < K; ++q)
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) {
+                            const f32x4 a = *reinterpret_cast<const f32x4*>(dm + (16 * q + s) * kP);
+                            const float bq = bv[q][s] * fd;
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) bd[i] = mfma4(a[i], bq, bd[i]);
+                        }
+                }
+            }
+            // dx, and x_t . of its three parts
+            float si = 0.f, sw = 0.f, sd = 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const f32x4 xv = lds4(xr + m * 256 + (((4 * g + r) ^ m) << 4));
+                float o[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float wv = fw * bw[i][r];
+                    si += xv[i] * di[i][r];
+                    sw += xv[i] * wv;
+                    if constexpr (SMALL) sd += xv[i] * bd[i][r];
+                    o[i] = dtt * (SMALL ? di[i][r] + wv + bd[i][r] : di[i][r] + wv);
+                }
+                if (valid) store4(dx + (bt * H + h) * kP + 16 * g + 4 * r, o);
+            }
+            si = row4_sum(si);
+            sw = row4_sum(sw);
+            if constexpr (SMALL) sd = row4_sum(sd);
+            if (g == 0) {
+                s_c[tl] = dtt * si;
+                s_v[tl] = dtt * sw;
+                s_d[tl] = dtt * sd;
+                s_bx[tl] = si + sw + sd;
+            }
+            // dB += dt (e^{cs_e - cs_t} W + D_t) x_t
+            f32x4 xs[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) xs[q] = xt[q] * (dtt * fw);
+#pragma unroll
+            for (int tile = 0; tile < K; ++tile)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    lam[i][q] += cv[i] * dyv[q];
-                    px[q] += bv[i] * lam[i][q];
-                    acc += lam[i][q] * xv[q];
+                    const f32x4 a = state_n(tile, q);
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) aB[tile] = mfma4(a[s], xs[q][s], aB[tile]);
                 }
-                v[i] = acc;
-            }
-            const float sb = lane_sums<RL, 16>(v, lane);
-            if (writer) dBp[((b * L + t) * nhb + hb) * (int64_t)N + nsum] = ob + d * sb;
-            // sum of px over the 4 ng lanes: lane (ng, pg) keeps column 4 pg + ng
-            rs_step<4, 4, 32>(px, lane);
-            const int slot = k % TB, buf = (k / TB) & 1;
-            xpart[buf][slot][wave][pl + ng] = px[0];
-            // carry to t - 1: Lam_{t-1} = C_{t-1}^T dy_{t-1} + a_t Lam_t
-            const float a = __expf(d * Ah);
+            if constexpr (SMALL) {
+                for (int c = 0; c < nc; ++c) {
+                    const float fx = dtt * own(c);
+                    const float* dm = dmem_of(c) + NV * m * kP + 4 * g;
 #pragma unroll
-            for (int i = 0; i < RL; ++i)
+                    for (int q = 0; q < 4; ++q) xs[q] = xt[q] * fx;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) lam[i][q] *= a;
-            if (slot == TB - 1 || k == ntok - 1) {
-                __syncthreads();
-                // wave w finishes tokens w, w + 4, ... of this batch
-                const int kb = k - slot;
-                for (int q = wave; q <= slot; q += 4) {
-                    const int64_t tq = (b * L + (e - (kb + q))) * H + h;
-                    const float s4 = xpart[buf][q][0][lane] + xpart[buf][q][1][lane] +
-                                     xpart[buf][q][2][lane] + xpart[buf][q][3][lane];
-                    dx[tq * kP + lane] = dt[tq] * s4;
-                    float pr = s4 * to_f(x[tq * kP + lane]);
+                    for (int tile = 0; tile < K; ++tile)
 #pragma unroll
-                    for (int o = 32; o >= 1; o >>= 1) pr += __shfl_xor(pr, o, 64);
-                    if (lane == 0) bxl[tq] = pr;
+                        for (int q = 0; q < 4; ++q) {
+                            const f32x4 a = *reinterpret_cast<const f32x4*>(
+                                dm + (16 * NV * (tile / NV) + tile % NV) * kP + 16 * q);
+#pragma unroll
+                            for (int s = 0; s < 4; ++s) aB[tile] = mfma4(a[s], xs[q][s], aB[tile]);
+                        }
                 }
             }
+        }
+        __syncthreads();  // W is read
+        stage_state(Hs + st);
+        __syncthreads();
+        if (used) {
+            // dC += e^{cs_s} H dy_s, and its dot with C_s
+            f32x4 ys[4];
+            const float ec = valid ? fast_exp2(cst) : 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) ys[q] = lds4(yr + oc[q]) * ec;
+            float u = 0.f;
+#pragma unroll
+            for (int qn = 0; qn < NQ; ++qn) {
+                f32x4 acc[NV];
+#pragma unroll
+                for (int i = 0; i < NV; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int i = 0; i < NV; ++i) {
+                        const f32x4 a = state_n(qn * NV + i, q);
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) acc[i] = mfma4(a[s], ys[q][s], acc[i]);
+                    }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float c4[NV];
+                    vec(Cm + (bt * G + grp) * N + 16 * NV * qn + NV * (4 * g + r), c4);
+#pragma unroll
+                    for (int i = 0; i < NV; ++i) u += acc[i][r] * c4[i];
+                }
+#pragma unroll
+                for (int i = 0; i < NV; ++i) aC[qn * NV + i] += acc[i];
+            }
+            u = row4_sum(u);
+            if (g == 0) s_u[tl] = u;
         }
         __syncthreads();
-    }
-}
-
-// ---- per (b, h): the decay gradient by a reverse cumulative sum -------------------
-// g_t = sum_{s >= t} (y_s . dy_s - dt_s (B_s Lam_s) . x_s) + sum_{c' >= c(t)} md_c',
-// ddt_t = (B_t Lam_t) . x_t + A_h g_t, dA partial = sum_t dt_t g_t.
-__global__ __launch_bounds__(256) void k_sbwd_decay(
-    const float* __restrict__ dt, const float* __restrict__ A, const float* __restrict__ bxl,
-    const float* __restrict__ ydyp, const float* __restrict__ mdp, float* __restrict__ ddt,
-    float* __restrict__ dAp, float* __restrict__ mdsuf, int64_t L, int H, int S, int64_t M) {
-    __shared__ float red[4];
-    __shared__ float carry_s;
-    const int h = blockIdx.x;
-    const int64_t b = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const float Ah = A[h];
-    // suffix sums over chunks of the memory (and final-state) terms
-    float* suf = mdsuf + (b * H + h) * M;
-    if (tid == 0) {
-        float s = 0.f;
-        for (int64_t c = M - 1; c >= 0; --c) {
-            const float* m4 = mdp + ((b * H + h) * M + c) * 4;
-            s += (m4[0] + m4[1]) + (m4[2] + m4[3]);
-            suf[c] = s;
+        if (w == 0) {
+            // the decay gradient: lane = token
+            const bool ok = lane < nt;
+            float F = 0.f, v = 0.f, vd = 0.f;
+            if (ok) {
+                for (int ww = 0; ww <= lane >> 4; ++ww) F += s_r[ww][lane];
+                F += s_u[lane] - s_c[lane];
+                v = s_v[lane];
+                vd = s_d[lane];
+            }
+            // first token of this token's chunk inside the piece
+            const int seg = pc.S < kQ ? lane - (int)((t0 + lane) % pc.S) : 0;
+            float sv = v, svd = vd;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const float dn = __shfl_down(F, o, 64), up = __shfl_up(sv, o, 64), ud = __shfl_up(svd, o, 64);
+                if (lane + o < 64) F += dn;
+                if (lane >= o) sv += up;
+                if (lane - o >= seg) svd += ud;
+            }
+            const float pv = __shfl_up(sv, 1, 64), pd = __shfl_up(svd, 1, 64);
+            float Kt = 0.f;
+            const float* kp = kpart + ((b * H + h) * pc.nk + k) * nkp;
+            for (int q = lane; q < nkp; q += 64) Kt += kp[q];
+            Kt = row4_sum(dpp_group_sum<16>(Kt));
+            const float dl = F + Kt + (lane > 0 ? pv : 0.f) + (lane > seg ? pd : 0.f);
+            float da = 0.f;
+            if (ok) {
+                ddt[(b * pc.L + t0 + lane) * H + h] = s_bx[lane] + Ah * dl;
+                da = s_dt[lane] * dl;
+            }
+            da = row4_sum(dpp_group_sum<16>(da));
+            if (lane == 0) dAp[(b * pc.nk + k) * H + h] = da;
         }
-        carry_s = 0.f;
     }
+    // the heads' sum of dt_t M2: rows t in LDS for the products over t
     __syncthreads();
-    float dA = 0.f;
-    const int64_t nblk = (L + 255) / 256;
-    for (int64_t blk = 0; blk < nblk; ++blk) {
-        // thread i takes token t = L - 1 - (256 blk + i): a suffix in token order
-        const int64_t t = L - 1 - (blk * 256 + tid);
-        float v = 0.f, d = 0.f, bx = 0.f;
-        if (t >= 0) {
-            const int64_t th = (b * L + t) * H + h;
-            const float* y4 = ydyp + th * 4;
-            d = dt[th];
-            bx = bxl[th];
-            v = (y4[0] + y4[1]) + (y4[2] + y4[3]) - d * bx;
-        }
-        float sc = v;
+    float* s_m = reinterpret_cast<float*>(s_xy);
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const float u = __shfl_up(sc, o, 64);
-            if (lane >= o) sc += u;
+    for (int j = 0; j < 4; ++j)
+        if (j >= w) *reinterpret_cast<f32x4*>(s_m + tl * MP + 16 * j + 4 * g) = mb[j];
+    __syncthreads();
+    if (!used) return;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if (j >= w && 16 * j < nt) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int qn = 0; qn < NQ; ++qn) {
+                    float a[NV];
+                    vec(Cm + (row(16 * j + 4 * g + r) * G + grp) * N + 16 * NV * qn + NV * m, a);
+#pragma unroll
+                    for (int i = 0; i < NV; ++i) aB[qn * NV + i] = mfma4(a[i], mb[j][r], aB[qn * NV + i]);
+                }
         }
-        if (lane == 63) red[wave] = sc;
-        __syncthreads();
-        float add = carry_s;
-        for (int w2 = 0; w2 < wave; ++w2) add += red[w2];
-        const float total = carry_s + red[0] + red[1] + red[2] + red[3];
-        sc += add;
-        if (t >= 0) {
-            const float gsum = sc + suf[t / S];
-            ddt[(b * L + t) * H + h] = bx + Ah * gsum;
-            dA += d * gsum;
+        if (j <= w) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float mt = s_m[(16 * j + 4 * g + r) * MP + tl];
+#pragma unroll
+                for (int qn = 0; qn < NQ; ++qn) {
+                    float a[NV];
+                    vec(Bm + (row(16 * j + 4 * g + r) * G + grp) * N + 16 * NV * qn + NV * m, a);
+#pragma unroll
+                    for (int i = 0; i < NV; ++i) aC[qn * NV + i] = mfma4(a[i], mt, aC[qn * NV + i]);
+                }
+            }
         }
-        __syncthreads();
-        if (tid == 0) carry_s = total;
-        __syncthreads();
     }
-    dA = block_sum(dA, red);
-    if (tid == 0) dAp[b * H + h] = dA;
+    if (!valid) return;
+    float* outB = dBp + (bt * nhb + hb) * (int64_t)N;
+    float* outC = dCp + (bt * nhb + hb) * (int64_t)N;
+#pragma unroll
+    for (int qn = 0; qn < NQ; ++qn)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int n = 16 * NV * qn + NV * (4 * g + r);
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                outB[n + i] = aB[qn * NV + i][r];
+                outC[n + i] = aC[qn * NV + i][r];
+            }
+        }
 }
 
-// ---- per (b, t, g): group sums of dB, dC; dA over the batch -----------------------
+// ---- group sums of dB, dC; dA over batch and pieces ----------------------------------
+// The first H blocks sum dA of one head each, the others dB and dC.
 template <int N>
-__global__ __launch_bounds__(256) void k_sbwd_finish(const float* __restrict__ dBp,
-                                                     const float* __restrict__ dCp,
-                                                     const float* __restrict__ dAp,
-                                                     float* __restrict__ dB, float* __restrict__ dC,
-                                                     float* __restrict__ dA, int64_t rows, int H,
-                                                     int G, int hpb, int64_t B) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__global__ __launch_bounds__(256) void k_fs_finish(const float* __restrict__ dBp,
+                                                   const float* __restrict__ dCp,
+                                                   const float* __restrict__ dAp,
+                                                   float* __restrict__ dB, float* __restrict__ dC,
+                                                   float* __restrict__ dA, int64_t rows, int H,
+                                                   int G, int hpb, int64_t arows) {
+    if ((int)blockIdx.x < H) {
+        __shared__ float red[4];
+        float s = 0.f;
+        for (int64_t r = threadIdx.x; r < arows; r += 256) s += dAp[r * H + blockIdx.x];
+        s = row4_sum(dpp_group_sum<16>(s));
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+        __syncthreads();
+        if (threadIdx.x == 0) dA[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+        return;
+    }
+    const int64_t i = ((int64_t)(blockIdx.x - H) * 256 + threadIdx.x) * 4;
+    if (i >= rows * N) return;
     const int nhb = H / hpb, per = (H / G) / hpb;
-    if (i < rows * N) {
-        const int64_t row = i / N;  // (b, t, g)
-        const int n = (int)(i - row * N);
-        const int g = (int)(row % G);
-        const int64_t bt = row / G;
-        float sb = 0.f, sc = 0.f;
-        for (int k = 0; k < per; ++k) {
-            const int hb = g * per + k;
-            sb += dBp[(bt * nhb + hb) * (int64_t)N + n];
-            sc += dCp[(bt * nhb + hb) * (int64_t)N + n];
-        }
-        dB[i] = sb;
-        dC[i] = sc;
-    }
-    if (blockIdx.x == 0) {
-        for (int h = threadIdx.x; h < H; h += 256) {
-            float s = 0.f;
-            for (int64_t b = 0; b < B; ++b) s += dAp[b * H + h];
-            dA[h] = s;
+    const int64_t row = i / N;  // (b, t, g)
+    const int n = (int)(i - row * N);
+    const int64_t bt = row / G;
+    const int g = (int)(row - bt * G);
+    float sb[4] = {0.f, 0.f, 0.f, 0.f}, sc[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int q = 0; q < per; ++q) {
+        const int64_t o = (bt * nhb + g * per + q) * (int64_t)N + n;
+        float vb[4], vc[4];
+        load4(dBp + o, vb);
+        load4(dCp + o, vc);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            sb[j] += vb[j];
+            sc[j] += vc[j];
         }
     }
+    store4(dB + i, sb);
+    store4(dC + i, sc);
 }
 
-int sbwd_heads_per_block(const Shape& s) {
+// Heads per k_fs_tokens block: the more, the fewer partials and repeats of the
+// per-group products, while two blocks per CU remain.
+int fs_heads_per_block(const Shape& s, int64_t nk) {
     const int per = s.H / s.G;
-    for (int c = kHpb; c > 1; --c)
-        if (per % c == 0) return c;
-    return 1;
+    int best = 1;
+    for (int c = 2; c <= 8; ++c)
+        if (per % c == 0 && s.B * nk * (s.H / c) >= 2 * device_cu_count()) best = c;
+    return best;
 }
 
 struct SbwdWs {
     float* lda;
-    float* dh32;
-    float* st32;
+    float* dH;
     float* dR;
-    float* Rs;
-    float* dec;
-    float* mdp;
-    float* mdsuf;
-    float* bxl;
-    float* ydyp;
+    float* kpart;
+    float* suf;
     float* dBp;
     float* dCp;
     float* dAp;
     size_t total;
 };
 
-// Workspace: the chunk log decays, chunk contributions and entry states of
-// the forward recomputed in float, then the backward's: chunk adjoints dR
-// and R, chunk decays, per-wave memory terms [B][H][M][4] and their suffix
-// sums, per-token (B Lam) . x [B][L][H] and per-wave y . dy [B][L][H][4],
-// per-head-block dB / dC partials [B][L][H/hpb][N], per-batch dA partials.
+// Workspace: the pieces' log decays [B][H][nk]; their contributions, then
+// entering states, and adjoint contributions, then leaving adjoints
+// [B][nk][H][N][P]; per-wave entering-and-leaving sums [B][H][nk][N P / 256];
+// decays to the chunk's end [B][H][nk]; per-head-block dB, dC partials
+// [B][L][H / hpb][N]; dA partials [B][nk][H].  All float.
 SbwdWs sbwd_layout(const Shape& s, void* base) {
+    const Pieces pc = pieces_of(s);
     const size_t NP = (size_t)s.N * s.P;
-    const size_t BLH = (size_t)s.B * s.L * s.H;
-    const size_t BHM = (size_t)s.B * s.H * s.M;
-    const int nhb = s.H / sbwd_heads_per_block(s);
+    const size_t BHK = (size_t)s.B * s.H * pc.nk;
+    const int nhb = s.H / fs_heads_per_block(s, pc.nk);
     SbwdWs w;
     size_t o = 0;
     char* p = reinterpret_cast<char*>(base);
     auto take = [&](size_t bytes) {
-        char* r = p ? p + o : nullptr;
+        float* r = p ? reinterpret_cast<float*>(p + o) : nullptr;
         o += align256(bytes);
         return r;
     };
-    w.lda = (float*)take(4 * BHM);
-    w.dh32 = (float*)take(4 * BHM * NP);
-    w.st32 = (float*)take(4 * BHM * NP);
-    w.dR = (float*)take(4 * BHM * NP);
-    w.Rs = (float*)take(4 * BHM * NP);
-    w.dec = (float*)take(4 * BHM);
-    w.mdp = (float*)take(16 * BHM);
-    w.mdsuf = (float*)take(4 * BHM);
-    w.bxl = (float*)take(4 * BLH);
-    w.ydyp = (float*)take(16 * BLH);
-    w.dBp = (float*)take(4 * (size_t)s.B * s.L * nhb * s.N);
-    w.dCp = (float*)take(4 * (size_t)s.B * s.L * nhb * s.N);
-    w.dAp = (float*)take(4 * (size_t)s.B * s.H);
+    w.lda = take(4 * BHK);
+    w.dH = take(4 * BHK * NP);
+    w.dR = take(4 * BHK * NP);
+    w.kpart = take(4 * BHK * ((NP + 1023) / 1024 * 4));
+    w.suf = take(4 * BHK);
+    w.dBp = take(4 * (size_t)s.B * s.L * nhb * s.N);
+    w.dCp = take(4 * (size_t)s.B * s.L * nhb * s.N);
+    w.dAp = take(4 * BHK);
     w.total = o;
     return w;
 }
@@ -550,32 +800,35 @@ hipError_t run_sbwd(const Shape& s, const void* x, const float* dt, const float*
                     const float* dmem, const float* dhl, float* dx, float* ddt, float* dA,
                     float* dB, float* dC, float* dh0, void* ws, hipStream_t st) {
     const SbwdWs w = sbwd_layout(s, ws);
-    // the forward again, in float, for every chunk's entry state
-    hipError_t err = launch_scan_states_f32(s, x, dt, A, Bm, h0, w.lda, w.dh32, w.st32, st);
-    if (err != hipSuccess) return err;
-    const int hpb = sbwd_heads_per_block(s);
-    const int NP = s.N * s.P;
-    prof_begin("k_sbwd_chunk", st);
-    k_sbwd_chunk<T, N><<<dim3((unsigned)s.M, (unsigned)s.H, (unsigned)s.B), 256, 0, st>>>(
-        (const T*)Cm, (const T*)dy, dt, A, w.dR, w.dec, s.L, s.H, s.G, s.S, s.M);
+    const Pieces pc = pieces_of(s);
+    constexpr int NP = N * kP;
+    const int64_t units = s.B * pc.nk * s.H;
+    prof_begin("k_sbwd_contract", st);
+    k_fs_contract<T, N><<<flat_grid(units), kBT, 0, st>>>((const T*)x, dt, A, (const T*)Bm, (const T*)Cm,
+                                                          (const T*)dy, w.dH, w.dR, w.lda, pc, s.H, s.G, units);
     prof_end(st);
+    const dim3 pg((unsigned)((NP + 1023) / 1024), (unsigned)s.H, (unsigned)s.B);
     prof_begin("k_sbwd_pass", st);
-    k_sbwd_pass<<<dim3((unsigned)((NP / 4 + 255) / 256), (unsigned)s.H, (unsigned)s.B), 256, 0, st>>>(
-        w.dR, w.dec, dhl, w.Rs, dh0, s.H, NP, s.M);
+    if (pc.nq > 1) {
+        k_fs_pass<true><<<pg, 256, 0, st>>>(w.dH, w.dR, w.lda, h0, dhl, dmem, dh0, w.kpart, w.suf, pc, s.H, NP, s.Mcap);
+    } else {
+        k_fs_pass<false><<<pg, 256, 0, st>>>(w.dH, w.dR, w.lda, h0, dhl, dmem, dh0, w.kpart, w.suf, pc, s.H, NP, s.Mcap);
+    }
     prof_end(st);
+    const int hpb = fs_heads_per_block(s, pc.nk);
+    const int64_t blocks = s.B * pc.nk * (s.H / hpb);
     prof_begin("k_sbwd_tokens", st);
-    k_sbwd_tokens<T, N><<<dim3((unsigned)s.M, (unsigned)(s.H / hpb), (unsigned)s.B), 256, 0, st>>>(
-        (const T*)x, dt, A, (const T*)Bm, (const T*)Cm, (const T*)dy, w.st32, w.Rs, dmem, dhl, dx,
-        w.bxl, w.ydyp, w.mdp, w.dBp, w.dCp, s.L, s.H, s.G, s.S, s.M, s.Mcap, hpb);
-    prof_end(st);
-    prof_begin("k_sbwd_decay", st);
-    k_sbwd_decay<<<dim3((unsigned)s.H, (unsigned)s.B), 256, 0, st>>>(
-        dt, A, w.bxl, w.ydyp, w.mdp, ddt, w.dAp, w.mdsuf, s.L, s.H, s.S, s.M);
+    auto tokens = [&](auto small) {
+        k_fs_tokens<T, N, decltype(small)::value><<<flat_grid(blocks), kBT, 0, st>>>(
+            (const T*)x, dt, A, (const T*)Bm, (const T*)Cm, (const T*)dy, w.dH, w.dR, dmem, w.kpart, dx, ddt,
+            w.dBp, w.dCp, w.dAp, pc, s.H, s.G, s.Mcap, hpb, (int)pg.x * 4, blocks);
+    };
+    if (s.S < kQ) tokens(std::true_type()); else tokens(std::false_type());
     prof_end(st);
     const int64_t rows = s.B * s.L * s.G;
     prof_begin("k_sbwd_finish", st);
-    k_sbwd_finish<N><<<(unsigned)((rows * N + 255) / 256), 256, 0, st>>>(
-        w.dBp, w.dCp, w.dAp, dB, dC, dA, rows, s.H, s.G, hpb, s.B);
+    k_fs_finish<N><<<(unsigned)(s.H + (rows * N / 4 + 255) / 256), 256, 0, st>>>(
+        w.dBp, w.dCp, w.dAp, dB, dC, dA, rows, s.H, s.G, hpb, s.B * pc.nk);
     prof_end(st);
     return hipGetLastError();
 }
