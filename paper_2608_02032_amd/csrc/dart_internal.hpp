@@ -16,45 +16,25 @@ struct Shape {
     int dtype;     // 0 fp32, 1 bf16
 };
 
-// Workspace of the scan: per-chunk log decay [B][H][M] (float), the
-// chunk-entry states [B][M][H][N][P] (storage dtype), the within-chunk
-// cumulative log decay [B][H][M][S] and the causal Gram tiles of every chunk
-// and group (float).
+// The scan; its workspace holds per-chunk log decays, the chunk-entry states
+// and the per-token decays.
 size_t scan_workspace_bytes(const Shape& s);
 hipError_t launch_scan(const Shape& s, const void* x, const float* dt, const float* A,
                        const void* Bm, const void* Cm, const float* h0, void* y_ssd, void* mem,
                        float* h_last, void* ws, hipStream_t st);
 
-// The tuned kernels serve N in {32, 64, 128} with S in {64, 128, 256}; every
-// other supported shape (N in {16, 32, 64, 128}, any S) takes the generic
-// kernels of generic.hip.
-bool tuned_shape(const Shape& s);
+// The bf16 kernels (scan.hip, sma.hip, sma_bwd.hip, scan_bwd_mfma.hip) serve
+// bf16 storage with N in {32, 64, 128} and S in {64, 128, 256}; everything else
+// (fp32 storage; N = 16; any other S) takes the kernels on the fp32 matrix
+// instructions (scan_f32.hip, sma_f32.hip, scan_bwd.hip).
+inline bool bf16_shape(const Shape& s) {
+    return s.dtype == 1 && (s.N == 32 || s.N == 64 || s.N == 128) && (s.S == 64 || s.S == 128 || s.S == 256);
+}
 
-// Workspace pieces of the generic scan: per-chunk log decay [B][H][M], the
-// chunk-entry states in the storage dtype (where the tuned scan keeps them),
-// the chunk contributions and the entry states in float, [B][M][H][N][P].
-struct GenScanWs {
-    float* lda;
-    void* states;
-    float* dh32;
-    float* st32;
-};
-hipError_t launch_gscan(const Shape& s, const void* x, const float* dt, const float* A,
-                        const void* Bm, const void* Cm, const float* h0, void* y_ssd, void* mem,
-                        float* h_last, const GenScanWs& w, hipStream_t st);
-
-// The chunk-entry states H_[c-1] a scan left in its workspace,
-// [B][M][H][N][P] in the storage dtype (H_[-1] = h0 or 0).
-const void* scan_entry_states(const Shape& s, const void* ws);
-// Every chunk's entry state in float for a backward pass: the chunk
-// contributions dH32 [B][M][H][N][P] run token by token in float, the chunk
-// log decays lda [B][H][M], and st32 [B][M][H][N][P] = H_[c-1] (h0 or 0 for
-// c = 0), accumulated in float from dH32 -- the trajectory the backward's
-// own token sweeps reproduce, so the decay gradient telescopes across chunk
-// boundaries without a storage-dtype rounding at each.
-hipError_t launch_scan_states_f32(const Shape& s, const void* x, const float* dt, const float* A,
-                                  const void* Bm, const float* h0, float* lda, float* dh32,
-                                  float* st32, hipStream_t st);
+size_t fscan_workspace_bytes(const Shape& s);
+hipError_t launch_fscan(const Shape& s, const void* x, const float* dt, const float* A, const void* Bm,
+                        const void* Cm, const float* h0, void* y_ssd, void* mem, float* h_last, void* ws,
+                        hipStream_t st);
 
 // Backward of the scan and its memories (scan_bwd.hip).
 size_t ssd_bwd_workspace_bytes(const Shape& s);
@@ -63,9 +43,7 @@ hipError_t launch_ssd_bwd(const Shape& s, const void* x, const float* dt, const 
                           const float* dmem, const float* dh_last, float* dx, float* ddt, float* dA,
                           float* dB, float* dC, float* dh0, void* ws, hipStream_t st);
 
-// The chunked-matrix scan backward on MFMA (scan_bwd_mfma.hip): bf16 storage
-// and the tuned shapes; launch_ssd_bwd dispatches to it.
-bool sbwd_mfma_shape(const Shape& s);
+// The bf16 kernels' scan backward; launch_ssd_bwd dispatches to it.
 size_t sbwd_mfma_workspace_bytes(const Shape& s);
 hipError_t launch_ssd_bwd_mfma(const Shape& s, const void* x, const float* dt, const float* A,
                                const void* Bm, const void* Cm, const float* h0, const void* dy,
@@ -80,8 +58,8 @@ struct SmaArgs {
     int z_per_head;
 };
 
-// Workspace of the SMA forward: the key side r (.) dH of memories 0..M-2,
-// [B][M-1][H][N][P] in the storage dtype.
+// Workspace of the SMA forward: the key and value sides of memories 0..M-2
+// (bf16 kernels only).
 size_t sma_workspace_bytes(const Shape& s);
 hipError_t launch_sma(const Shape& s, const SmaArgs& a, const void* q, const void* e,
                       const void* Cm, const void* mem, const void* z, const void* y_ssd, void* y,
@@ -92,7 +70,6 @@ hipError_t launch_sma(const Shape& s, const SmaArgs& a, const void* q, const voi
 hipError_t launch_fsma(const Shape& s, const SmaArgs& a, const void* q, const void* e,
                        const void* Cm, const void* mem, const void* z, const void* y_ssd, void* y,
                        float* lse, hipStream_t st);
-bool sma_bf16_shape(const Shape& s);  // the bf16 kernels' set
 
 // Workspace of its backward: Qbar and Ebar in float; per (b, h, memory
 // 0..M-2, token) the logit (then g p_j) and dy . V_j (then dl_j / sqrt(N)) with
@@ -113,10 +90,8 @@ hipError_t launch_fsma_bwd(const Shape& s, const SmaArgs& a, const void* q, cons
                            const void* Cm, const void* mem, const void* z, const void* dy,
                            const GenBwdWs& w, float* dmem, hipStream_t st);
 
-// Key side r (.) dH of memories 0..M-2 in the cache layout [B][M-1][H][N][P]
-// (storage dtype), as the fp32 forward stages it; klo (optional, bf16 only,
-// same layout) receives its rounding residual; rinv (optional,
-// [B][M-1][H][N] float) receives 1 / r.
+// bf16 key side r (.) dH of memories 0..M-2 in the cache layout
+// [B][M-1][H][N][P], its rounding residual klo and 1 / r as rinv [B][M-1][H][N].
 hipError_t launch_sma_keys(const Shape& s, const SmaArgs& a, const void* mem, void* kmem,
                            void* klo, float* rinv, hipStream_t st);
 

@@ -1,0 +1,154 @@
+// f32_tiles.hpp -- shared pieces of the kernels on the fp32 matrix instructions
+// (sma_f32.hip, scan_f32.hip, scan_bwd.hip).
+#pragma once
+
+#include "dart_common.hpp"
+#include "dart_internal.hpp"
+
+namespace dart {
+
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 lds4(const char* p) { return *reinterpret_cast<const f32x4*>(p); }
+
+// A grid of any length along x and y (a launch takes at most 2^32 threads
+// along x), and the block's place in it.
+inline dim3 flat_grid(int64_t blocks) {
+    const int64_t x = blocks < (1 << 23) ? blocks : (1 << 23);
+    return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
+}
+__device__ __forceinline__ int64_t flat_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
+// The scan's pieces of a sequence: at most kQ tokens, nested with the memory
+// chunks (a chunk of S >= kQ tokens is nq pieces, the last one shorter; for
+// S < kQ a piece is Q / S whole chunks).
+constexpr int kQ = 64;
+struct Pieces {
+    int64_t L, nk;
+    int S, nq, Q;
+};
+inline Pieces pieces_of(const Shape& s) {
+    Pieces p;
+    p.L = s.L;
+    p.S = s.S;
+    if (s.S >= kQ) {
+        p.nq = (s.S + kQ - 1) / kQ;
+        p.Q = kQ;
+        p.nk = (s.M - 1) * p.nq + (s.L - (s.M - 1) * s.S + kQ - 1) / kQ;
+    } else {
+        p.nq = 1;
+        p.Q = kQ / s.S * s.S;
+        p.nk = (s.L + p.Q - 1) / p.Q;
+    }
+    return p;
+}
+__device__ __forceinline__ void piece_range(const Pieces& p, int64_t k, int64_t& t0, int64_t& t1) {
+    if (p.S >= kQ) {
+        const int64_t c = k / p.nq, end = (c + 1) * p.S < p.L ? (c + 1) * p.S : p.L;
+        t0 = c * p.S + (k - c * p.nq) * kQ;
+        t1 = t0 + kQ < end ? t0 + kQ : end;
+    } else {
+        t0 = k * p.Q;
+        t1 = t0 + p.Q < p.L ? t0 + p.Q : p.L;
+    }
+}
+
+// The decays of one piece, lane = token: dt (0 past the piece's end), the
+// inclusive cumulative log decay cl inside its 16-token tile (log2 units) and
+// the four tiles' totals T.  The decay between two tokens is then the
+// difference of two small numbers inside a tile, and a sum of non-positive
+// terms across tiles: cumulative sums over longer ranges would lose their last
+// bits in the difference.
+struct PieceDecay {
+    float d, cl;
+    f32x4 T;
+    __device__ __forceinline__ void load(const float* __restrict__ dt, float Ah, int64_t b, int64_t L, int H,
+                                         int h, int64_t t0, int64_t t1, int lane) {
+        d = t0 + lane < t1 ? dt[(b * L + t0 + lane) * H + h] : 0.f;
+        cl = d * Ah * kLog2e;
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) {
+            const float u = __shfl_up(cl, o, 64);
+            if ((lane & 15) >= o) cl += u;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) T[i] = __shfl(cl, 16 * i + 15, 64);
+    }
+};
+// Sum of the tile totals between tiles a and b (exclusive).
+__device__ __forceinline__ float tiles_between(const f32x4& T, int a, int b) {
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s += i > a && i < b ? T[i] : 0.f;
+    return s;
+}
+// Log decay from token t (tile jt, cl ct) to token s >= t (tile js, cl cs).
+__device__ __forceinline__ float log_decay(const f32x4& T, int js, float cs, int jt, float ct) {
+    return js == jt ? cs - ct : (T[jt & 3] - ct) + tiles_between(T, jt, js) + cs;
+}
+// ... from token t to the piece's end, and from its start to token s.
+__device__ __forceinline__ float log_to_end(const f32x4& T, int jt, float ct) {
+    return (T[jt & 3] - ct) + tiles_between(T, jt, 4);
+}
+__device__ __forceinline__ float log_from_start(const f32x4& T, int js, float cs) {
+    return tiles_between(T, -1, js) + cs;
+}
+
+// Heads per block of the per-piece output kernels: the more, the fewer repeats
+// of the per-group products (and partials), while two blocks per CU remain.
+inline int piece_heads_per_block(const Shape& s, int64_t nk) {
+    const int per = s.H / s.G;
+    int best = 1;
+    for (int c = 2; c <= 8; ++c)
+        if (per % c == 0 && s.B * nk * (s.H / c) >= 2 * device_cu_count()) best = c;
+    return best;
+}
+
+// Byte offsets of a lane's LDS reads of tiles of 64-float rows in 16-byte
+// chunks, (m, g) = (lane % 16, lane / 16): rows of x or dy hold chunk c of row
+// s at c ^ (s & 15); a state's row n holds chunk c at c ^ ((n / NV) & 15) with
+// NV = min(4, N / 16), and its N-row products take the rows in the order
+// n = 16 NV q + NV m + i (tile q NV + i), so that NV consecutive n of a B or C
+// row are one load for NV tiles.  Both readings of either are free of bank
+// conflicts.
+template <int N>
+struct PieceOff {
+    static constexpr int K = N / 16, NV = K < 4 ? K : 4, NQ = K / NV;
+    int oc[4];  // row m, chunk 4 q + g
+    int op[4];  // row 4 g + q, chunk m
+    int on[4];  // a state tile's row m, chunk 4 q + g
+    int ow[4];  // a state's rows 16 q + 4 g + s, chunk m
+    __device__ __forceinline__ void init(int m, int g) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            oc[q] = m * 256 + (((4 * q + g) ^ m) << 4);
+            op[q] = (4 * g + q) * 256 + ((m ^ (4 * g + q)) << 4);
+            on[q] = NV * m * 256 + (((4 * q + g) ^ m) << 4);
+            // key 4 q + g for NV = 4 (by q mod 4), 8 q + 2 g + s / 2 for NV = 2,
+            // 4 g + s for NV = 1
+            ow[q] = NV == 4 ? g * 1024 + (((4 * q + g) ^ m) << 4)
+                  : NV == 2 ? g * 1024 + ((((8 * (q >> 1) + 2 * g + (q & 1)) & 15) ^ m) << 4)
+                            : g * 1024 + (((4 * g + q) ^ m) << 4);
+        }
+    }
+    // row 16 q + 4 g + s, columns 4 m ..
+    __device__ __forceinline__ f32x4 state_p(const char* tile, int q, int s) const {
+        return lds4(tile + ow[NV == 4 ? q & 3 : NV == 2 ? 2 * q + (s >> 1) : s] + (16 * q + s) * 256);
+    }
+    // the tile's row m, columns 16 q + 4 g ..
+    __device__ __forceinline__ f32x4 state_n(const char* state, int tile, int q) const {
+        return lds4(state + on[q] + (16 * NV * (tile / NV) + tile % NV) * 256);
+    }
+    // DMA of one state [N][64] into its tile by the block's 256 threads
+    __device__ __forceinline__ static void stage(const float* src, char* tile, int tid) {
+        const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+            const int i = tid + q * 256, n = i >> 4, c = (i & 15) ^ ((n / NV) & 15);
+            lds_dma16(src + n * 64 + 4 * c, tile + (w * 64 + q * 256) * 16);
+        }
+    }
+};
+
+}  // namespace dart

@@ -51,74 +51,13 @@
 // stands: at step r its k index g means s = 4 g + r.
 #include <type_traits>
 
-#include "dart_common.hpp"
-#include "dart_internal.hpp"
+#include "f32_tiles.hpp"
 
 namespace dart {
 namespace {
 
 constexpr int kP = 64;
 constexpr int kBT = 256;  // threads: 4 waves
-constexpr int kQ = 64;    // tokens per piece at most, 16 a wave
-
-__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f32x4 lds4(const char* p) { return *reinterpret_cast<const f32x4*>(p); }
-
-// The pieces of a sequence.
-struct Pieces {
-    int64_t L, nk;
-    int S, nq, Q;  // nq pieces per chunk (S >= 64), or Q tokens per piece
-};
-inline Pieces pieces_of(const Shape& s) {
-    Pieces p;
-    p.L = s.L;
-    p.S = s.S;
-    if (s.S >= kQ) {
-        p.nq = (s.S + kQ - 1) / kQ;
-        p.Q = kQ;
-        p.nk = (s.M - 1) * p.nq + (s.L - (s.M - 1) * s.S + kQ - 1) / kQ;
-    } else {
-        p.nq = 1;
-        p.Q = kQ / s.S * s.S;
-        p.nk = (s.L + p.Q - 1) / p.Q;
-    }
-    return p;
-}
-__device__ __forceinline__ void piece_range(const Pieces& p, int64_t k, int64_t& t0, int64_t& t1) {
-    if (p.S >= kQ) {
-        const int64_t c = k / p.nq, end = (c + 1) * p.S < p.L ? (c + 1) * p.S : p.L;
-        t0 = c * p.S + (k - c * p.nq) * kQ;
-        t1 = t0 + kQ < end ? t0 + kQ : end;
-    } else {
-        t0 = k * p.Q;
-        t1 = t0 + p.Q < p.L ? t0 + p.Q : p.L;
-    }
-}
-
-// This lane's token of the piece: dt (0 past its end) and the inclusive
-// cumulative log decay in log2 units, by one wave.
-__device__ __forceinline__ float piece_decay(const float* __restrict__ dt, float Ah, int64_t b,
-                                             int64_t L, int H, int h, int64_t t0, int64_t t1,
-                                             int lane, float& d) {
-    d = t0 + lane < t1 ? dt[(b * L + t0 + lane) * H + h] : 0.f;
-    float cs = d * Ah * kLog2e;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const float u = __shfl_up(cs, o, 64);
-        if (lane >= o) cs += u;
-    }
-    return cs;
-}
-
-// A grid of any length along x and y (a launch takes at most 2^32 threads
-// along x).
-inline dim3 flat_grid(int64_t blocks) {
-    const int64_t x = blocks < (1 << 23) ? blocks : (1 << 23);
-    return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
-}
-__device__ __forceinline__ int64_t flat_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
 
 // ---- per (b, piece, h): the piece's contributions ---------------------------------
 // The four waves split the N rows (WN of them, NTW row tiles each) and, for
@@ -146,12 +85,12 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_contract(
     int64_t t0, t1;
     piece_range(pc, k, t0, t1);
     if (wave == 0) {
-        float d;
-        const float cs = piece_decay(dt, A[h], b, pc.L, H, h, t0, t1, lane, d);
-        const float ce = __shfl(cs, 63, 64);
-        s_f[0][lane] = fast_exp2(ce - cs) * d;
-        s_f[1][lane] = t0 + lane < t1 ? fast_exp2(cs) : 0.f;
-        if (lane == 0) lda[(b * H + h) * pc.nk + k] = ce;
+        PieceDecay pd;
+        pd.load(dt, A[h], b, pc.L, H, h, t0, t1, lane);
+        const bool in = t0 + lane < t1;
+        s_f[0][lane] = in ? fast_exp2(log_to_end(pd.T, lane >> 4, pd.cl)) * pd.d : 0.f;
+        s_f[1][lane] = in ? fast_exp2(log_from_start(pd.T, lane >> 4, pd.cl)) : 0.f;
+        if (lane == 0) lda[(b * H + h) * pc.nk + k] = tiles_between(pd.T, -1, 4);
     }
     float rb[CN][4], rc[CN][4], rx[4], ry[4];
     auto load = [&](int64_t tt) {
@@ -241,11 +180,11 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_contract(
 
 // ---- per (b, h, 1024 elements): the passes over the pieces --------------------------
 // In place: dH -> H (the state entering each piece), dR -> W.  kpart [b][h][k]
-// [waves]: each wave's part of e^{cs_e} (<R, H> + <D, H_own>).  suf [b][h][k]:
+// [nkp]: each wave's parts of e^{cs_e} <R, H> and, OWN, of e^{cs_e} <D, H_own>.  suf [b][h][k]:
 // the decay from a piece's end to its chunk's end (every block of a (b, h)
 // writes the same values and reads its own).
 template <bool OWN>
-__global__ __launch_bounds__(256) void k_fs_pass(float* __restrict__ dH, float* __restrict__ dR,
+__global__ __launch_bounds__(256) void k_fs_pass(float* dH, float* dR,
                                                  const float* __restrict__ lda, const float* __restrict__ h0,
                                                  const float* __restrict__ dhl, const float* __restrict__ dmem,
                                                  float* __restrict__ dh0, float* __restrict__ kpart,
@@ -254,9 +193,9 @@ __global__ __launch_bounds__(256) void k_fs_pass(float* __restrict__ dH, float* 
     const int64_t b = blockIdx.z, bh = b * H + h;
     const int tid = threadIdx.x, lane = tid & 63;
     const int e0 = (blockIdx.x * 256 + tid) * 4;
-    const int nw = gridDim.x * 4, wv = blockIdx.x * 4 + (tid >> 6);
+    const int nw = gridDim.x * 4, wv = blockIdx.x * 4 + (tid >> 6), nkp = OWN ? 2 * nw : nw;
     const float* ld = lda + bh * pc.nk;
-    float* kp = kpart + bh * pc.nk * nw + wv;
+    float* kp = kpart + bh * pc.nk * nkp + wv;
     const int64_t step = (int64_t)H * NP;
     float* ph = dH + (b * pc.nk * H + h) * (int64_t)NP + e0;
     float* pr = dR + (b * pc.nk * H + h) * (int64_t)NP + e0;
@@ -274,64 +213,83 @@ __global__ __launch_bounds__(256) void k_fs_pass(float* __restrict__ dH, float* 
         __syncthreads();
     }
     const bool in = e0 < NP;
+    // four pieces' values are loaded before the first is replaced: the chains
+    // over the pieces are short, the loads' latency is what bounds them
+    constexpr int U = 4;
     float hc[4] = {0.f, 0.f, 0.f, 0.f}, ho[4] = {0.f, 0.f, 0.f, 0.f}, dm[4] = {0.f, 0.f, 0.f, 0.f};
     if (h0 && in) load4(h0 + bh * (int64_t)NP + e0, hc);
-    for (int64_t k = 0, i = 0; k < pc.nk; ++k, i = i + 1 == pc.nq ? 0 : i + 1) {
-        const float a = fast_exp2(ld[k]);
-        float d4[4] = {0.f, 0.f, 0.f, 0.f};
-        if (in) {
-            load4(ph + k * step, d4);
-            store4(ph + k * step, hc);
+    int i = 0;  // piece of its chunk
+    for (int64_t k0 = 0; k0 < pc.nk; k0 += U) {
+        float d4[U][4], a[U], sf[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t k = k0 + u < pc.nk ? k0 + u : pc.nk - 1;
+            if (in) load4(ph + k * step, d4[u]);
+            a[u] = fast_exp2(ld[k]);
+            if (OWN) sf[u] = suf[bh * pc.nk + k];
         }
-        if (OWN) {
-            if (i == 0) {
-                if (pm && in) load4(pm + k / pc.nq * step, dm);
-                ho[0] = ho[1] = ho[2] = ho[3] = 0.f;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t k = k0 + u;
+            if (k >= pc.nk) break;
+            if (in) store4(ph + k * step, hc);
+            if (OWN) {
+                if (i == 0) {
+                    if (pm && in) load4(pm + k / pc.nq * step, dm);
+                    ho[0] = ho[1] = ho[2] = ho[3] = 0.f;
+                }
+                float s = (ho[0] * dm[0] + ho[1] * dm[1]) + (ho[2] * dm[2] + ho[3] * dm[3]);
+                s = row4_sum(dpp_group_sum<16>(in ? s : 0.f));
+                if (lane == 0) kp[k * nkp + nw] = a[u] * sf[u] * s;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) ho[q] = a[u] * ho[q] + d4[u][q];
+                if (++i == pc.nq) i = 0;
             }
-            float s = (ho[0] * dm[0] + ho[1] * dm[1]) + (ho[2] * dm[2] + ho[3] * dm[3]);
-            s = row4_sum(dpp_group_sum<16>(s));
-            if (lane == 0) kp[k * nw] = a * suf[bh * pc.nk + k] * s;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) ho[q] = a * ho[q] + d4[q];
+            for (int q = 0; q < 4; ++q) hc[q] = a[u] * hc[q] + d4[u][q];
         }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) hc[q] = a * hc[q] + d4[q];
     }
     float r[4] = {0.f, 0.f, 0.f, 0.f}, dd[4] = {0.f, 0.f, 0.f, 0.f};
     if (dhl && in) load4(dhl + bh * (int64_t)NP + e0, r);
     const bool nest = pc.S >= kQ;  // a chunk's dmem leaves with its pieces
-    for (int64_t k = pc.nk - 1; k >= 0; --k) {
-        const float a = fast_exp2(ld[k]);
-        float d4[4] = {0.f, 0.f, 0.f, 0.f}, h4[4] = {0.f, 0.f, 0.f, 0.f}, w4[4];
-        if (in) {
-            load4(pr + k * step, d4);
-            load4(ph + k * step, h4);
-        }
-        if (nest && pm && in) {
-            const int64_t c = k / pc.nq;
-            if (k == pc.nk - 1 || (k + 1) / pc.nq != c) load4(pm + c * step, dd);
-        }
-        float s = 0.f;
+    for (int64_t k0 = pc.nk - 1; k0 >= 0; k0 -= U) {
+        float d4[U][4], h4[U][4], a[U];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            w4[q] = r[q] + dd[q];
-            s += r[q] * h4[q];
-            r[q] = a * r[q] + d4[q];
-            dd[q] *= a;
+        for (int u = 0; u < U; ++u) {
+            const int64_t k = k0 - u > 0 ? k0 - u : 0;
+            if (in) {
+                load4(pr + k * step, d4[u]);
+                load4(ph + k * step, h4[u]);
+            }
+            a[u] = fast_exp2(ld[k]);
         }
-        if (in) store4(pr + k * step, w4);
-        s = row4_sum(dpp_group_sum<16>(s)) * a;
-        if (lane == 0) kp[k * nw] = OWN ? kp[k * nw] + s : s;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t k = k0 - u;
+            if (k < 0) break;
+            if (nest && pm && in) {
+                const int64_t c = k / pc.nq;
+                if (k == pc.nk - 1 || (k + 1) / pc.nq != c) load4(pm + c * step, dd);
+            }
+            float s = 0.f, w4[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                w4[q] = r[q] + dd[q];
+                s += r[q] * h4[u][q];
+                r[q] = a[u] * r[q] + d4[u][q];
+                dd[q] *= a[u];
+            }
+            if (in) store4(pr + k * step, w4);
+            s = row4_sum(dpp_group_sum<16>(in ? s : 0.f)) * a[u];
+            if (lane == 0) kp[k * nkp] = s;
+        }
     }
     if (dh0 && in) store4(dh0 + bh * (int64_t)NP + e0, r);
 }
 
 // ---- per (b, piece, block of heads): the token gradients ----------------------------
 // A wave owns 16 tokens, as columns t of the tiles with s >= t and as rows of
-// dB, dC and dx.  Rows n of the N-row products come in the order
-// n = 16 NV q + NV m + i (tile (q, i), NV = min(4, N / 16)), so that NV
-// consecutive n of a B or C row are one load for NV tiles; a state's chunk c of
-// row n is at c ^ ((n / NV) & 15), without bank conflicts in either reading.
+// dB, dC and dx.
 // 36 + N / 4 KB of LDS, 256 registers: two blocks per CU.  SMALL: S < 64.
 template <typename T, int N, bool SMALL>
 __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
@@ -344,7 +302,8 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
     constexpr int K = N / 16, NV = K < 4 ? K : 4, NQ = K / NV;
     constexpr int MP = kQ + 4;  // row pitch of the summed M2, in floats
     __shared__ __attribute__((aligned(16))) char s_xy[2 * kQ * 256], s_w[N * 256];
-    __shared__ __attribute__((aligned(16))) float s_cs[kQ], s_dt[kQ];
+    __shared__ __attribute__((aligned(16))) float s_cl[kQ], s_dt[kQ];
+    __shared__ f32x4 s_T;
     __shared__ float s_r[4][kQ], s_c[kQ], s_v[kQ], s_d[kQ], s_u[kQ], s_bx[kQ];
     static_assert(kQ * MP * 4 <= 2 * kQ * 256, "the summed M2 takes the place of x and dy");
     const int64_t blk = flat_block();
@@ -397,42 +356,16 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
             for (int i = 0; i < NV; ++i) v[i] = to_f(p[i]);
         }
     };
-    // byte offsets of this lane's LDS reads: chunk 4 q + g of row m (oc, without
-    // the row), chunk m of row 4 g + r, and the two readings of a state
-    int oc[4], op[4], on[4], ow[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        oc[q] = m * 256 + (((4 * q + g) ^ m) << 4);
-        op[q] = (4 * g + q) * 256 + ((m ^ (4 * g + q)) << 4);
-        on[q] = NV * m * 256 + (((4 * q + g) ^ m) << 4);
-        // rows 16 q' + 4 g + s: key 4 q' + g for NV = 4 (by q' mod 4), 8 q' + 2 g +
-        // s / 2 for NV = 2, 4 g + s for NV = 1
-        ow[q] = NV == 4 ? g * 1024 + (((4 * q + g) ^ m) << 4)
-              : NV == 2 ? g * 1024 + ((((8 * (q >> 1) + 2 * g + (q & 1)) & 15) ^ m) << 4)
-                        : g * 1024 + (((4 * g + q) ^ m) << 4);
-    }
-    auto state_p = [&](int q, int s) {  // row 16 q + 4 g + s, columns 4 m ..
-        return lds4(s_w + ow[NV == 4 ? q & 3 : NV == 2 ? 2 * q + (s >> 1) : s] + (16 * q + s) * 256);
-    };
-    auto state_n = [&](int tile, int q) {  // the tile's row m, columns 16 q + 4 g ..
-        return lds4(s_w + on[q] + (16 * NV * (tile / NV) + tile % NV) * 256);
-    };
+    PieceOff<N> off;
+    off.init(m, g);
     char* const xr = s_x + w * 4096;  // the wave's rows of x and dy
     char* const yr = s_y + w * 4096;
-    // one state into s_w
-    auto stage_state = [&](const float* src) {
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-            const int i = tid + q * kBT, n = i >> 4, c = (i & 15) ^ ((n / NV) & 15);
-            lds_dma16(src + n * kP + 4 * c, s_w + (w * 64 + q * kBT) * 16);
-        }
-    };
     for (int hh = 0; hh < hpb; ++hh) {
         const int h = h0 + hh;
         const float Ah = A[h];
         const int64_t st = ((b * pc.nk + k) * H + h) * (int64_t)(N * kP);
         __syncthreads();  // the last head's reads are done
-        stage_state(Ws + st);
+        PieceOff<N>::stage(Ws + st, s_w, tid);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int s = (tid >> 4) + 16 * q, c = tid & 15;
@@ -446,18 +379,20 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
             *reinterpret_cast<f32x4*>(s_y + o) = f32x4{y4[0], y4[1], y4[2], y4[3]};
         }
         if (w == 0) {
-            float d;
-            const float cs = piece_decay(dt, Ah, b, pc.L, H, h, t0, t1, lane, d);
-            s_cs[lane] = cs;
-            s_dt[lane] = d;
+            PieceDecay pd;
+            pd.load(dt, Ah, b, pc.L, H, h, t0, t1, lane);
+            s_cl[lane] = pd.cl;
+            s_dt[lane] = pd.d;
+            if (lane == 0) s_T = pd.T;
         }
         __syncthreads();
-        const float cst = s_cs[tl], dtt = s_dt[tl], cse = s_cs[kQ - 1];
+        const f32x4 tt = s_T;
+        const float ct = s_cl[tl], dtt = s_dt[tl];
         if (used) {
             f32x4 xt[4], di[4], bw[4], bd[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                xt[q] = lds4(xr + oc[q]);
+                xt[q] = lds4(xr + off.oc[q]);
                 di[q] = bw[q] = bd[q] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
 #pragma unroll
@@ -466,15 +401,15 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
                     f32x4 g2 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const f32x4 a = lds4(s_y + j * 4096 + oc[q]);
+                        const f32x4 a = lds4(s_y + j * 4096 + off.oc[q]);
 #pragma unroll
                         for (int s = 0; s < 4; ++s) g2 = mfma4(a[s], xt[q][s], g2);
                     }
-                    const f32x4 css = *reinterpret_cast<const f32x4*>(s_cs + 16 * j + 4 * g);
+                    const f32x4 cs = *reinterpret_cast<const f32x4*>(s_cl + 16 * j + 4 * g);
                     f32x4 m1, ps;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        float e = fast_exp2(fminf(css[r] - cst, 0.f));
+                        float e = fast_exp2(fminf(log_decay(tt, j, cs[r], w, ct), 0.f));
                         if (j == w && 4 * g + r < m) e = 0.f;
                         m1[r] = e * g1[j][r];
                         mb[j][r] += dtt * (e * g2[r]);
@@ -483,7 +418,7 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
                     if (m == 0) *reinterpret_cast<f32x4*>(&s_r[w][16 * j + 4 * g]) = ps;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const f32x4 a = lds4(s_y + j * 4096 + op[r]);
+                        const f32x4 a = lds4(s_y + j * 4096 + off.op[r]);
 #pragma unroll
                         for (int i = 0; i < 4; ++i) di[i] = mfma4(a[i], m1[r], di[i]);
                     }
@@ -494,17 +429,17 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
             for (int q = 0; q < K; ++q)
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
-                    const f32x4 a = state_p(q, s);
+                    const f32x4 a = off.state_p(s_w, q, s);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) bw[i] = mfma4(a[i], bv[q][s], bw[i]);
                 }
-            const float fw = fast_exp2(cse - cst);
+            const float fw = fast_exp2(log_to_end(tt, w, ct));
             // the chunks of the wave's tokens, each dmem_c for its own tokens only
             const int64_t c0 = (t0 + 16 * w) / pc.S;
             const int nc = SMALL && dmem ? (int)((t0 + (16 * w + 15 < nt ? 16 * w + 15 : nt - 1)) / pc.S - c0) + 1 : 0;
             auto own = [&](int c) {  // e^{cs_ce - cs_t}, zero for the others
                 const int lo = (int)((c0 + c) * pc.S - t0), hi = lo + pc.S < nt ? lo + pc.S : nt;
-                return tl >= lo && tl < hi ? fast_exp2(s_cs[hi - 1] - cst) : 0.f;
+                return tl >= lo && tl < hi ? fast_exp2(log_decay(tt, (hi - 1) >> 4, s_cl[hi - 1], w, ct)) : 0.f;
             };
             auto dmem_of = [&](int c) { return dmem + ((b * Mcap + c0 + c) * H + h) * (int64_t)(N * kP); };
             if constexpr (SMALL) {
@@ -555,7 +490,7 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
             for (int tile = 0; tile < K; ++tile)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const f32x4 a = state_n(tile, q);
+                    const f32x4 a = off.state_n(s_w, tile, q);
 #pragma unroll
                     for (int s = 0; s < 4; ++s) aB[tile] = mfma4(a[s], xs[q][s], aB[tile]);
                 }
@@ -578,14 +513,14 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
             }
         }
         __syncthreads();  // W is read
-        stage_state(Hs + st);
+        PieceOff<N>::stage(Hs + st, s_w, tid);
         __syncthreads();
         if (used) {
             // dC += e^{cs_s} H dy_s, and its dot with C_s
             f32x4 ys[4];
-            const float ec = valid ? fast_exp2(cst) : 0.f;
+            const float ec = valid ? fast_exp2(log_from_start(tt, w, ct)) : 0.f;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) ys[q] = lds4(yr + oc[q]) * ec;
+            for (int q = 0; q < 4; ++q) ys[q] = lds4(yr + off.oc[q]) * ec;
             float u = 0.f;
 #pragma unroll
             for (int qn = 0; qn < NQ; ++qn) {
@@ -596,7 +531,7 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
                 for (int q = 0; q < 4; ++q)
 #pragma unroll
                     for (int i = 0; i < NV; ++i) {
-                        const f32x4 a = state_n(qn * NV + i, q);
+                        const f32x4 a = off.state_n(s_w, qn * NV + i, q);
 #pragma unroll
                         for (int s = 0; s < 4; ++s) acc[i] = mfma4(a[s], ys[q][s], acc[i]);
                     }
@@ -742,16 +677,6 @@ __global__ __launch_bounds__(256) void k_fs_finish(const float* __restrict__ dBp
     store4(dC + i, sc);
 }
 
-// Heads per k_fs_tokens block: the more, the fewer partials and repeats of the
-// per-group products, while two blocks per CU remain.
-int fs_heads_per_block(const Shape& s, int64_t nk) {
-    const int per = s.H / s.G;
-    int best = 1;
-    for (int c = 2; c <= 8; ++c)
-        if (per % c == 0 && s.B * nk * (s.H / c) >= 2 * device_cu_count()) best = c;
-    return best;
-}
-
 struct SbwdWs {
     float* lda;
     float* dH;
@@ -766,14 +691,14 @@ struct SbwdWs {
 
 // Workspace: the pieces' log decays [B][H][nk]; their contributions, then
 // entering states, and adjoint contributions, then leaving adjoints
-// [B][nk][H][N][P]; per-wave entering-and-leaving sums [B][H][nk][N P / 256];
+// [B][nk][H][N][P]; per-wave entering-and-leaving sums [B][H][nk][nkp];
 // decays to the chunk's end [B][H][nk]; per-head-block dB, dC partials
 // [B][L][H / hpb][N]; dA partials [B][nk][H].  All float.
 SbwdWs sbwd_layout(const Shape& s, void* base) {
     const Pieces pc = pieces_of(s);
     const size_t NP = (size_t)s.N * s.P;
     const size_t BHK = (size_t)s.B * s.H * pc.nk;
-    const int nhb = s.H / fs_heads_per_block(s, pc.nk);
+    const int nhb = s.H / piece_heads_per_block(s, pc.nk);
     SbwdWs w;
     size_t o = 0;
     char* p = reinterpret_cast<char*>(base);
@@ -785,7 +710,7 @@ SbwdWs sbwd_layout(const Shape& s, void* base) {
     w.lda = take(4 * BHK);
     w.dH = take(4 * BHK * NP);
     w.dR = take(4 * BHK * NP);
-    w.kpart = take(4 * BHK * ((NP + 1023) / 1024 * 4));
+    w.kpart = take(4 * BHK * ((NP + 1023) / 1024 * 4) * (pc.nq > 1 ? 2 : 1));
     w.suf = take(4 * BHK);
     w.dBp = take(4 * (size_t)s.B * s.L * nhb * s.N);
     w.dCp = take(4 * (size_t)s.B * s.L * nhb * s.N);
@@ -815,13 +740,13 @@ hipError_t run_sbwd(const Shape& s, const void* x, const float* dt, const float*
         k_fs_pass<false><<<pg, 256, 0, st>>>(w.dH, w.dR, w.lda, h0, dhl, dmem, dh0, w.kpart, w.suf, pc, s.H, NP, s.Mcap);
     }
     prof_end(st);
-    const int hpb = fs_heads_per_block(s, pc.nk);
+    const int hpb = piece_heads_per_block(s, pc.nk);
     const int64_t blocks = s.B * pc.nk * (s.H / hpb);
     prof_begin("k_sbwd_tokens", st);
     auto tokens = [&](auto small) {
         k_fs_tokens<T, N, decltype(small)::value><<<flat_grid(blocks), kBT, 0, st>>>(
             (const T*)x, dt, A, (const T*)Bm, (const T*)Cm, (const T*)dy, w.dH, w.dR, dmem, w.kpart, dx, ddt,
-            w.dBp, w.dCp, w.dAp, pc, s.H, s.G, s.Mcap, hpb, (int)pg.x * 4, blocks);
+            w.dBp, w.dCp, w.dAp, pc, s.H, s.G, s.Mcap, hpb, (int)pg.x * (pc.nq > 1 ? 8 : 4), blocks);
     };
     if (s.S < kQ) tokens(std::true_type()); else tokens(std::false_type());
     prof_end(st);
@@ -850,14 +775,14 @@ hipError_t run_sbwd_n(const Shape& s, const void* x, const float* dt, const floa
 }  // namespace
 
 size_t ssd_bwd_workspace_bytes(const Shape& s) {
-    return sbwd_mfma_shape(s) ? sbwd_mfma_workspace_bytes(s) : sbwd_layout(s, nullptr).total;
+    return bf16_shape(s) ? sbwd_mfma_workspace_bytes(s) : sbwd_layout(s, nullptr).total;
 }
 
 hipError_t launch_ssd_bwd(const Shape& s, const void* x, const float* dt, const float* A,
                           const void* Bm, const void* Cm, const float* h0, const void* dy,
                           const float* dmem, const float* dh_last, float* dx, float* ddt, float* dA,
                           float* dB, float* dC, float* dh0, void* ws, hipStream_t st) {
-    if (sbwd_mfma_shape(s))
+    if (bf16_shape(s))
         return launch_ssd_bwd_mfma(s, x, dt, A, Bm, Cm, h0, dy, dmem, dh_last, dx, ddt, dA, dB, dC, dh0, ws, st);
     if (s.dtype == 1)
         return run_sbwd_n<bf16>(s, x, dt, A, Bm, Cm, h0, dy, dmem, dh_last, dx, ddt, dA, dB, dC, dh0, ws, st);

@@ -1142,7 +1142,6 @@ hipError_t run_mfma_s(const Shape& s, const bf16* x, const float* dt, const floa
 
 }  // namespace
 
-bool sbwd_mfma_shape(const Shape& s) { return s.dtype == 1 && s.P == kP && tuned_shape(s); }
 
 size_t sbwd_mfma_workspace_bytes(const Shape& s) { return mfma_layout(s, nullptr).total; }
 

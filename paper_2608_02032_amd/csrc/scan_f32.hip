@@ -1,0 +1,382 @@
+// scan_f32.hip -- the chunked SSD scan with its memories on the fp32 matrix
+// instructions: fp32 storage at every shape, and either storage at the shapes
+// outside the bf16 kernels' set (any chunk size S >= 1, N in {16, 32, 64, 128},
+// P = 64).
+//
+// Paper: Sec. 2 (recurrence H_t = a_t H_{t-1} + dt_t B_t^T x_t, y_t = C_t H_t),
+// Sec. 3 / App. A (the memory dH_[c] of every chunk).  The sequence is cut into
+// pieces of at most 64 tokens that nest with the memory chunks (f32_tiles.hpp):
+// a state product costs the same per token at any piece length, the products
+// inside a piece grow with it, and short pieces keep the decays' exponents (and
+// their rounding) small.
+//   k_fs_state  per (b, piece, h): for S <= 64 each chunk's memory, and the
+//               piece's contribution to the state, on MFMA;
+//   k_fs_states per (b, h, 1024 elements): the pass over the pieces; a
+//               contribution becomes the state entering its piece, and for
+//               S > 64 the contributions of a chunk's pieces its memory;
+//   k_fs_out    per (b, piece, block of heads of one group): y = (decay o
+//               C B^T)(dt x) + e^{cs} C H, the tiles of C B^T formed once per
+//               block for all its heads.
+// Operand layouts as in scan_bwd.hip.
+//
+// Measured, with the kernels these replaced: B 2, L 2048, 24 heads, N 128,
+// S 256, fp32 (three MFMA kernels with the Gram tiles through memory, and the
+// state pass) 136 -> 105 us; B 64, L 512, 4 heads, N 64, S 16, fp32 (token by
+// token) 258 -> 107; B 2, L 2048, 8 heads, N 128, S 32, bf16 104 -> 58.
+#include "f32_tiles.hpp"
+
+namespace dart {
+namespace {
+
+constexpr int kP = 64;
+constexpr int kFT = 256;
+
+// The waves split the N rows (WN of them, NTW row tiles each) and, for N < 64,
+// the column tiles (PT each).  HBM-bound: N P floats are written per piece.
+template <typename T, int N>
+__global__ __launch_bounds__(kFT) void k_fs_state(const T* __restrict__ x, const float* __restrict__ dt,
+                                                  const float* __restrict__ A, const T* __restrict__ Bm,
+                                                  T* __restrict__ mem, float* __restrict__ dH,
+                                                  float* __restrict__ lda, Pieces pc, int H, int G,
+                                                  int64_t Mcap, int64_t blocks) {
+    constexpr int WN = N / 16 < 4 ? N / 16 : 4, NTW = N / 16 / WN, PT = WN;
+    __shared__ __attribute__((aligned(16))) float s_b[kQ][N + 16], s_x[kQ][kP + 16];
+    __shared__ float s_f[kQ], s_cl[kQ];
+    __shared__ f32x4 s_T;
+    const int64_t blk = flat_block();
+    if (blk >= blocks) return;
+    const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave % WN, p0 = wave / WN * PT;
+    const int h = (int)(blk % H);
+    const int64_t bk = blk / H, b = bk / pc.nk, k = bk - b * pc.nk;
+    const int grp = (int)((int64_t)h * G / H);
+    int64_t t0, t1;
+    piece_range(pc, k, t0, t1);
+    const int nt = (int)(t1 - t0);
+    float rb[N / 16][4], rx[4][4];
+#pragma unroll
+    for (int q = 0; q < N / 16; ++q) {
+        const int i = tid + q * kFT, s = i / (N / 4);
+        const int64_t t = t0 + (s < nt ? s : nt - 1);
+        load4(Bm + ((b * pc.L + t) * G + grp) * N + 4 * (i % (N / 4)), rb[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int s = (tid >> 4) + 16 * q;
+        const int64_t t = t0 + (s < nt ? s : nt - 1);
+        load4(x + ((b * pc.L + t) * H + h) * kP + 4 * (tid & 15), rx[q]);
+    }
+    if (wave == 0) {
+        PieceDecay pd;
+        pd.load(dt, A[h], b, pc.L, H, h, t0, t1, lane);
+        // to the last token of this token's chunk inside the piece
+        float to = log_to_end(pd.T, lane >> 4, pd.cl);
+        if (pc.S < kQ) {
+            int e = lane - (int)((t0 + lane) % pc.S) + pc.S - 1;
+            e = e < nt ? e : nt - 1;
+            const float ce = __shfl(pd.cl, e, 64);
+            to = log_decay(pd.T, e >> 4, ce, lane >> 4, pd.cl);
+        }
+        s_f[lane] = lane < nt ? fast_exp2(to) * pd.d : 0.f;
+        s_cl[lane] = pd.cl;
+        if (lane == 0) {
+            s_T = pd.T;
+            lda[(b * H + h) * pc.nk + k] = tiles_between(pd.T, -1, 4);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < N / 16; ++q) {
+        const int i = tid + q * kFT;
+        store4(&s_b[i / (N / 4)][4 * (i % (N / 4))], rb[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) store4(&s_x[(tid >> 4) + 16 * q][4 * (tid & 15)], rx[q]);
+    __syncthreads();
+    f32x4 sum[NTW][PT];
+#pragma unroll
+    for (int n = 0; n < NTW; ++n)
+#pragma unroll
+        for (int p = 0; p < PT; ++p) sum[n][p] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int per = pc.S < kQ ? pc.S : kQ;  // tokens of one memory in the piece
+    for (int lo = 0; lo < nt; lo += per) {
+        const int hi = lo + per < nt ? lo + per : nt;
+        f32x4 acc[NTW][PT];
+#pragma unroll
+        for (int n = 0; n < NTW; ++n)
+#pragma unroll
+            for (int p = 0; p < PT; ++p) acc[n][p] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int k16 = lo & ~15; k16 < hi; k16 += 16) {
+#pragma unroll
+            for (int ks = 0; ks < 16; ks += 4) {
+                if (k16 + ks >= hi || k16 + ks + 4 <= lo) continue;
+                const int t = k16 + ks + g;
+                const float f = t >= lo && t < hi ? s_f[t] : 0.f;
+                float ab[NTW];
+#pragma unroll
+                for (int n = 0; n < NTW; ++n) ab[n] = s_b[t][wn * 16 * NTW + NTW * m + n] * f;
+                const f32x4 vx = *reinterpret_cast<const f32x4*>(&s_x[t][4 * m]);
+#pragma unroll
+                for (int n = 0; n < NTW; ++n)
+#pragma unroll
+                    for (int p = 0; p < PT; ++p) acc[n][p] = mfma4(ab[n], PT == 4 ? vx[p] : vx[p0 + p], acc[n][p]);
+            }
+        }
+        const float a = lo > 0 ? fast_exp2(log_decay(s_T, (hi - 1) >> 4, s_cl[hi - 1], (lo - 1) >> 4, s_cl[lo - 1])) : 0.f;
+        T* mo = pc.S <= kQ ? mem + ((b * Mcap + (t0 + lo) / pc.S) * H + h) * (int64_t)(N * kP) : nullptr;
+#pragma unroll
+        for (int n = 0; n < NTW; ++n) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (!mo) break;
+                T* o = mo + (wn * 16 * NTW + NTW * (4 * g + r) + n) * kP + 4 * m + p0;
+                if constexpr (PT == 4) {
+                    const float v[4] = {acc[n][0][r], acc[n][1][r], acc[n][2][r], acc[n][3][r]};
+                    store4(o, v);
+                } else {
+#pragma unroll
+                    for (int p = 0; p < PT; ++p) o[p] = from_f<T>(acc[n][p][r]);
+                }
+            }
+#pragma unroll
+            for (int p = 0; p < PT; ++p) sum[n][p] = sum[n][p] * a + acc[n][p];
+        }
+    }
+    const int64_t base = blk * (int64_t)(N * kP);
+#pragma unroll
+    for (int n = 0; n < NTW; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float* o = dH + base + (wn * 16 * NTW + NTW * (4 * g + r) + n) * kP + 4 * m + p0;
+            if constexpr (PT == 4) {
+                const float v[4] = {sum[n][0][r], sum[n][1][r], sum[n][2][r], sum[n][3][r]};
+                store4(o, v);
+            } else {
+#pragma unroll
+                for (int p = 0; p < PT; ++p) o[p] = sum[n][p][r];
+            }
+        }
+}
+
+// In place: a piece's contribution becomes the state entering it.  Four pieces'
+// contributions are loaded before the first is replaced: the chain over the
+// pieces is short, the loads' latency is what bounds it.
+template <typename T>
+__global__ __launch_bounds__(256) void k_fs_states(float* dH, const float* __restrict__ lda,
+                                                   const float* __restrict__ h0, float* __restrict__ h_last,
+                                                   T* __restrict__ mem, Pieces pc, int H, int NP, int64_t Mcap) {
+    const int h = blockIdx.y;
+    const int64_t b = blockIdx.z, bh = b * H + h;
+    const int e0 = (blockIdx.x * 256 + threadIdx.x) * 4;
+    if (e0 >= NP) return;
+    const float* ld = lda + bh * pc.nk;
+    const int64_t step = (int64_t)H * NP;
+    float* ph = dH + (b * pc.nk * H + h) * (int64_t)NP + e0;
+    T* pm = pc.S > kQ ? mem + (b * Mcap * H + h) * (int64_t)NP + e0 : nullptr;
+    float hc[4] = {0.f, 0.f, 0.f, 0.f}, own[4] = {0.f, 0.f, 0.f, 0.f};
+    if (h0) load4(h0 + bh * (int64_t)NP + e0, hc);
+    int i = 0;  // piece of its chunk
+    for (int64_t k0 = 0; k0 < pc.nk; k0 += 4) {
+        float d4[4][4], a[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (k0 + u < pc.nk) {
+                load4(ph + (k0 + u) * step, d4[u]);
+                a[u] = fast_exp2(ld[k0 + u]);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t k = k0 + u;
+            if (k >= pc.nk) break;
+            store4(ph + k * step, hc);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                hc[q] = a[u] * hc[q] + d4[u][q];
+                own[q] = (i == 0 ? 0.f : a[u] * own[q]) + d4[u][q];
+            }
+            if (++i == pc.nq || k == pc.nk - 1) {
+                if (pm) store4(pm + k / pc.nq * step, own);
+                i = 0;
+            }
+        }
+    }
+    if (h_last) store4(h_last + bh * (int64_t)NP + e0, hc);
+}
+
+// A wave owns 16 tokens s, as columns of the tiles with t <= s and of y.
+template <typename T, int N>
+__global__ __launch_bounds__(kFT, 2) void k_fs_out(const T* __restrict__ x, const float* __restrict__ dt,
+                                                   const float* __restrict__ A, const T* __restrict__ Bm,
+                                                   const T* __restrict__ Cm, const float* __restrict__ Hs,
+                                                   T* __restrict__ y, Pieces pc, int H, int G, int hpb,
+                                                   int64_t blocks) {
+    constexpr int K = N / 16;
+    __shared__ __attribute__((aligned(16))) char s_x[kQ * 256], s_w[N * 256];
+    __shared__ __attribute__((aligned(16))) float s_cl[kQ], s_dt[kQ];
+    __shared__ f32x4 s_T;
+    const int64_t blk = flat_block();
+    if (blk >= blocks) return;
+    const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nhb = H / hpb;
+    const int64_t bk = blk / nhb, b = bk / pc.nk, k = bk - b * pc.nk;
+    const int h0 = (int)(blk - bk * nhb) * hpb;
+    const int grp = (int)((int64_t)h0 * G / H);
+    int64_t t0, t1;
+    piece_range(pc, k, t0, t1);
+    const int nt = (int)(t1 - t0), tl = 16 * w + m;
+    const bool used = 16 * w < nt;
+    // a row of the piece, clamped to its last token (tokens past the end have
+    // x and dt zero and are not stored)
+    auto row = [&](int s) { return b * pc.L + t0 + (s < nt ? s : nt - 1); };
+    const int64_t bt = row(tl);
+    float cv[K][4];
+#pragma unroll
+    for (int q = 0; q < K; ++q) load4(Cm + (bt * G + grp) * N + 16 * q + 4 * g, cv[q]);
+    f32x4 g1[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        g1[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (j <= w && 16 * j < nt) {
+            const T* br = Bm + (row(16 * j + m) * G + grp) * N + 4 * g;
+#pragma unroll
+            for (int q = 0; q < K; ++q) {
+                float b4[4];
+                load4(br + 16 * q, b4);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) g1[j] = mfma4(b4[s], cv[q][s], g1[j]);
+            }
+        }
+    }
+    PieceOff<N> off;
+    off.init(m, g);
+    for (int hh = 0; hh < hpb; ++hh) {
+        const int h = h0 + hh;
+        if (hh > 0) __syncthreads();
+        PieceOff<N>::stage(Hs + ((b * pc.nk + k) * H + h) * (int64_t)(N * kP), s_w, tid);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int s = (tid >> 4) + 16 * q, c = tid & 15;
+            float x4[4] = {0.f, 0.f, 0.f, 0.f};
+            if (s < nt) load4(x + (row(s) * H + h) * kP + 4 * c, x4);
+            *reinterpret_cast<f32x4*>(s_x + s * 256 + ((c ^ (s & 15)) << 4)) = f32x4{x4[0], x4[1], x4[2], x4[3]};
+        }
+        if (w == 0) {
+            PieceDecay pd;
+            pd.load(dt, A[h], b, pc.L, H, h, t0, t1, lane);
+            s_cl[lane] = pd.cl;
+            s_dt[lane] = pd.d;
+            if (lane == 0) s_T = pd.T;
+        }
+        __syncthreads();
+        if (!used) continue;
+        const f32x4 tt = s_T;
+        const float cs = s_cl[tl];
+        f32x4 yi[4], yw[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) yi[i] = yw[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < K; ++q)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const f32x4 a = off.state_p(s_w, q, s);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) yw[i] = mfma4(a[i], cv[q][s], yw[i]);
+            }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (j <= w && 16 * j < nt) {
+                const f32x4 ct = *reinterpret_cast<const f32x4*>(s_cl + 16 * j + 4 * g);
+                const f32x4 dtt = *reinterpret_cast<const f32x4*>(s_dt + 16 * j + 4 * g);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float e = fast_exp2(fminf(log_decay(tt, w, cs, j, ct[r]), 0.f)) * dtt[r];
+                    if (j == w && 4 * g + r > m) e = 0.f;
+                    const float bq = e * g1[j][r];
+                    const f32x4 a = lds4(s_x + j * 4096 + off.op[r]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) yi[i] = mfma4(a[i], bq, yi[i]);
+                }
+            }
+        }
+        if (tl < nt) {
+            const float ec = fast_exp2(log_from_start(tt, w, cs));
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float o[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[i] = yi[i][r] + ec * yw[i][r];
+                store4(y + (bt * H + h) * kP + 16 * g + 4 * r, o);
+            }
+        }
+    }
+}
+
+struct FScanWs {
+    float* lda;  // [B][H][nk]
+    float* dH;   // [B][nk][H][N][P]: contributions, then entering states
+    size_t total;
+};
+FScanWs fscan_ws(const Shape& s, void* base) {
+    const size_t BHK = (size_t)s.B * s.H * pieces_of(s).nk;
+    char* p = reinterpret_cast<char*>(base);
+    FScanWs w;
+    w.lda = reinterpret_cast<float*>(p);
+    w.dH = p ? reinterpret_cast<float*>(p + align256(4 * BHK)) : nullptr;
+    w.total = align256(4 * BHK) + align256(4 * BHK * s.N * (size_t)s.P);
+    return w;
+}
+
+template <typename T, int N>
+hipError_t run_fscan(const Shape& s, const void* x, const float* dt, const float* A, const void* Bm,
+                     const void* Cm, const float* h0, void* y, void* mem, float* hl, void* ws, hipStream_t st) {
+    const Pieces pc = pieces_of(s);
+    const FScanWs w = fscan_ws(s, ws);
+    constexpr int NP = N * kP;
+    const int64_t units = s.B * pc.nk * s.H;
+    prof_begin("k_chunk_state", st);
+    k_fs_state<T, N><<<flat_grid(units), kFT, 0, st>>>((const T*)x, dt, A, (const T*)Bm, (T*)mem, w.dH,
+                                                       w.lda, pc, s.H, s.G, s.Mcap, units);
+    prof_end(st);
+    prof_begin("k_state_pass", st);
+    k_fs_states<T><<<dim3((NP + 1023) / 1024, (unsigned)s.H, (unsigned)s.B), 256, 0, st>>>(
+        w.dH, w.lda, h0, hl, (T*)mem, pc, s.H, NP, s.Mcap);
+    prof_end(st);
+    const int hpb = piece_heads_per_block(s, pc.nk);
+    const int64_t blocks = s.B * pc.nk * (s.H / hpb);
+    prof_begin("k_chunk_out", st);
+    k_fs_out<T, N><<<flat_grid(blocks), kFT, 0, st>>>((const T*)x, dt, A, (const T*)Bm, (const T*)Cm, w.dH,
+                                                      (T*)y, pc, s.H, s.G, hpb, blocks);
+    prof_end(st);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+size_t fscan_workspace_bytes(const Shape& s) { return fscan_ws(s, nullptr).total; }
+
+hipError_t launch_fscan(const Shape& s, const void* x, const float* dt, const float* A, const void* Bm,
+                        const void* Cm, const float* h0, void* y_ssd, void* mem, float* h_last, void* ws,
+                        hipStream_t st) {
+#define DART_FS(T, NN) run_fscan<T, NN>(s, x, dt, A, Bm, Cm, h0, y_ssd, mem, h_last, ws, st)
+    if (s.dtype == 1) {
+        switch (s.N) {
+            case 16: return DART_FS(bf16, 16);
+            case 32: return DART_FS(bf16, 32);
+            case 64: return DART_FS(bf16, 64);
+            case 128: return DART_FS(bf16, 128);
+        }
+    } else {
+        switch (s.N) {
+            case 16: return DART_FS(float, 16);
+            case 32: return DART_FS(float, 32);
+            case 64: return DART_FS(float, 64);
+            case 128: return DART_FS(float, 128);
+        }
+    }
+#undef DART_FS
+    return hipErrorInvalidValue;
+}
+
+}  // namespace dart

@@ -984,10 +984,8 @@ hipError_t launch_sma_keys(const Shape& s, const SmaArgs& a, const void* mem, vo
     return hipGetLastError();
 }
 
-bool sma_bf16_shape(const Shape& s) { return s.dtype == 1 && tuned_shape(s); }
-
 size_t sma_workspace_bytes(const Shape& s) {
-    if (!sma_bf16_shape(s)) return 0;  // the fp32 kernel stages memories itself
+    if (!bf16_shape(s)) return 0;  // the fp32 kernel stages memories itself
     const int64_t Mp = s.M > 1 ? s.M - 1 : 0;
     return 2 * sizeof(bf16) * s.B * Mp * s.H * (size_t)s.N * s.P;  // key and value sides
 }
@@ -995,7 +993,7 @@ size_t sma_workspace_bytes(const Shape& s) {
 hipError_t launch_sma(const Shape& s, const SmaArgs& a, const void* q, const void* e,
                       const void* Cm, const void* mem, const void* z, const void* y_ssd, void* y,
                       float* lse, void* ws, hipStream_t st) {
-    if (!sma_bf16_shape(s)) return launch_fsma(s, a, q, e, Cm, mem, z, y_ssd, y, lse, st);
+    if (!bf16_shape(s)) return launch_fsma(s, a, q, e, Cm, mem, z, y_ssd, y, lse, st);
     switch (s.N) {
         case 32: return run_sma_s<32>(s, a, q, e, Cm, mem, z, y_ssd, y, lse, ws, st);
         case 64: return run_sma_s<64>(s, a, q, e, Cm, mem, z, y_ssd, y, lse, ws, st);

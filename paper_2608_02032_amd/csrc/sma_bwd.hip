@@ -1294,7 +1294,7 @@ hipError_t run_bwd_n(const Shape& s, const SmaArgs& a, const void* q, const void
 }  // namespace
 
 size_t sma_bwd_workspace_bytes(const Shape& s) {
-    if (!sma_bf16_shape(s)) return gbwd_layout(s, nullptr).bytes;
+    if (!bf16_shape(s)) return gbwd_layout(s, nullptr).bytes;
     return bwd_layout(s, nullptr).bytes;
 }
 
@@ -1302,7 +1302,7 @@ hipError_t launch_sma_bwd(const Shape& s, const SmaArgs& a, const void* q, const
                           const void* Cm, const void* mem, const void* z, const float* lse,
                           const void* dy, float* dq, float* de, float* dC, float* dmem, float* dz,
                           void* ws, hipStream_t st) {
-    if (!sma_bf16_shape(s)) {
+    if (!bf16_shape(s)) {
         if (s.dtype == 1) return run_gbwd_n<bf16>(s, a, q, e, Cm, mem, z, lse, dy, dq, de, dC, dmem, dz, ws, st);
         return run_gbwd_n<float>(s, a, q, e, Cm, mem, z, lse, dy, dq, de, dC, dmem, dz, ws, st);
     }

@@ -47,8 +47,7 @@
 //               through r_j.
 #include <type_traits>
 
-#include "dart_common.hpp"
-#include "dart_internal.hpp"
+#include "f32_tiles.hpp"
 
 namespace dart {
 namespace {
@@ -56,10 +55,6 @@ namespace {
 constexpr int kP = 64;
 constexpr int kFT = 256;   // threads: 4 waves
 constexpr int kFTok = 64;  // tokens per block, 16 a wave
-
-__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
 
 // One memory on its way from HBM to LDS: thread (row tid / 16 + 16 k, chunk
 // tid % 16), loaded a memory ahead of its use and stored with its row scales
@@ -96,7 +91,6 @@ struct TileOff {
         }
     }
 };
-__device__ __forceinline__ f32x4 lds4(const char* p) { return *reinterpret_cast<const f32x4*>(p); }
 
 // Row pieces of one token in operand order: v[k][s] = row[16 k + 4 g + s].
 template <typename T, int K>
@@ -155,14 +149,6 @@ __device__ __forceinline__ float col_dot(const f32x4 (&U)[4], const float (&e)[4
     return row4_sum((s[0] + s[1]) + (s[2] + s[3]));
 }
 
-// A one-dimensional grid of any length: a launch takes at most 2^32 threads
-// along x, so long grids continue along y.
-inline dim3 flat_grid(int64_t blocks) {
-    const int64_t x = blocks < (1 << 23) ? blocks : (1 << 23);
-    return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
-}
-__device__ __forceinline__ unsigned flat_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
-
 // ---- forward -----------------------------------------------------------------------
 // Block order: heaviest (latest) tokens first, and blockIdx % (B H) = (b, h), so
 // that for a multiple of eight (b, h) the blocks that read the same memories
@@ -178,7 +164,7 @@ __global__ __launch_bounds__(kFT, 2) void k_fsma(
     __shared__ __attribute__((aligned(16))) float s_r[2][N];
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const unsigned blk = flat_block(), bq = blk / (unsigned)BH;
+    const unsigned blk = (unsigned)flat_block(), bq = blk / (unsigned)BH;
     if (bq >= (unsigned)used) return;
     const int bh = (int)(blk % (unsigned)BH);
     const int64_t tb = (int64_t)(nblk - 1 - (int)bq) * kFTok;
@@ -292,7 +278,7 @@ __global__ __launch_bounds__(kFT, 2) void k_fbwd_tok(
     __shared__ __attribute__((aligned(16))) float s_r[2][N];
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const unsigned blk = flat_block(), bq = blk / (unsigned)BH;
+    const unsigned blk = (unsigned)flat_block(), bq = blk / (unsigned)BH;
     if (bq >= (unsigned)used) return;
     const int bh = (int)(blk % (unsigned)BH);
     const int64_t tb = (int64_t)(nblk - 1 - (int)bq) * kFTok;
@@ -463,7 +449,7 @@ __global__ __launch_bounds__(kFT, 2) void k_fbwd_mem(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave % WN, wj = wave / WN;
     // heaviest memories first
-    const unsigned blk = flat_block(), per = (unsigned)BH * (N / NR);
+    const unsigned blk = (unsigned)flat_block(), per = (unsigned)BH * (N / NR);
     const int64_t j0 = (int64_t)(blk / per) * JJ;
     const int bh = (int)(blk % per % (unsigned)BH);
     const int n0 = (int)(blk % per / (unsigned)BH) * NR;

@@ -1,11 +1,14 @@
-"""The scan backward on the fp32 matrix instructions at the edges of its pieces
+"""The scan and its backward on the fp32 matrix instructions at the edges of its pieces
 (at most 64 tokens, nested with the memory chunks): chunks one token longer than
 a piece, chunks of several pieces with a short last one, several short chunks
 in a piece, chunk sizes that leave a piece ragged, every N, with and without
-the optional inputs, against the oracle's reverse recurrence."""
+the optional inputs, against the oracle's recurrence and its reverse."""
+import numpy as np
 import pytest
 
-from paper_2608_02032_amd import synth
+import oracle
+from paper_2608_02032_amd import dart, synth
+from tests.helpers import assert_close_slices, f32_dev, to_dev, to_np
 from tests import test_gpu_scan_bwd as SB
 
 pytestmark = pytest.mark.gpu
@@ -29,3 +32,26 @@ def test_scan_f32_backward(c, extras):
     B, L, H, G, N, S, dtype = c
     w = synth.Workload("f32_%d_%d" % (N, S), B, L, H, 64, N, S, dtype, ngroups=G)
     SB.run_case(w, seed=L + S, with_dmem=True, with_dhl=extras, with_h0=extras, mcap=w.nchunks + 2 if extras else 0)
+
+
+@pytest.mark.parametrize("c", SHAPES, ids=lambda c: "B%d_L%d_H%d_G%d_N%d_S%d_%s" % c)
+def test_scan_f32_forward(c):
+    import torch
+    B, L, H, G, N, S, dtype = c
+    w = synth.Workload("f32_%d_%d" % (N, S), B, L, H, 64, N, S, dtype, ngroups=G)
+    print("\n[gpu-case] scan f32 %s" % (w,), flush=True)
+    d = synth.forward_inputs(w, seed=L)
+    h0 = (np.random.default_rng(L).standard_normal((B, H, N, 64)) * 0.05).astype(np.float32)
+    x, Bm, Cm = (to_dev(d[k], dtype) for k in ("x", "Bm", "Cm"))
+    M = w.nchunks
+    mem = torch.full((B, M + 1, H, N, 64), 7.0, dtype=x.dtype, device="cuda")
+    y, _, hl = dart.ssd_chunk_scan(x, f32_dev(d["dt"]), f32_dev(d["A"]), Bm, Cm, S, h0=f32_dev(h0), mem=mem)
+    torch.cuda.synchronize()
+    y_ref, hl_ref = oracle.ssd_recurrence(d["x"], d["dt"], d["A"], d["Bm"], d["Cm"], h0)
+    mem_ref = oracle.chunk_memories(d["x"], d["dt"], d["A"], d["Bm"], S)
+    # fp32 sums whatever the storage; outputs are rounded to it
+    tol = 1e-5 if dtype == "fp32" else 2.0 ** -8
+    assert_close_slices(to_np(y), y_ref, tol, what="y_ssd")
+    assert_close_slices(to_np(mem)[:, :M], mem_ref, tol, axes_keep=(0, 1, 2), what="mem")
+    assert_close_slices(to_np(hl), hl_ref, 1e-5, axes_keep=(0, 1), what="h_last")
+    assert np.all(to_np(mem)[:, M:] == 7.0)
