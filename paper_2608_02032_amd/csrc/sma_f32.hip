@@ -4,7 +4,7 @@
 // 64, 128}, P = 64).  The paper trains at S = 16, N in {16, 64} (MQAR,
 // App. D.1) and evaluates one checkpoint at S = 64 and 32 (Sec. 5.2).
 //
-// Every product runs on v_mfma_f32_16x16x4_f32 (32 cycles of a SIMD each), so
+// Every product but k_bsma's runs on v_mfma_f32_16x16x4_f32 (32 cycles of a SIMD each), so
 // operands, sums and probabilities are fp32 throughout, as the definitions
 // have them.  What bounds these kernels is that instruction's rate (154 TFLOP/s
 // measured on a large matrix product): a wave's vector work per memory is about
@@ -34,6 +34,8 @@
 //               V = dH^T C from the same reads, l = U . Ebar, the online
 //               softmax of Alg. 1, the gated residual.  Tokens of a wave may
 //               belong to different chunks (each is masked by its own).
+//   k_bsma      the forward for bf16 storage and N >= 32, on the bf16
+//               instructions with exact or split operands (comment there).
 //   k_fbwd_prep Qbar and Ebar of every token (float).
 //   k_fbwd_tok  per (64 tokens, b, h): pass 1 over the memories for the logits,
 //               dy . V_j, the exact log-sum-exp of these logits and
@@ -234,6 +236,206 @@ __global__ __launch_bounds__(kFT, 2) void k_fsma(
             for (int i = 0; i < 4; ++i) v[i] += f * O[i][r];
         }
         store4(y + yi + 4 * r, v);
+    }
+    if (lse && g == 0) lse[bt * H + h] = jt > 0 ? (mx + log2f(d)) * kLn2 : -INFINITY;
+}
+
+// ---- forward, bf16 storage ------------------------------------------------------------
+// The same with the products on the bf16 matrix instructions, eight times the
+// fp32 ones' rate, at the precision of the kernel above: a stored memory and C
+// are bf16 as they stand, so V = dH^T C^T is exact in its operands, and the
+// logit contracts over p first, W = dH Ebar^T with Ebar as hi + lo bf16 (16
+// bits), then l = sum_n Qbar_n r_n W_n in float.  (The other order would round
+// r . dH or Qbar.)  Rows of 128 bytes in LDS, 16-byte chunks swizzled by row.
+// Eight waves: four take the even memories of the block's 64 tokens, four the
+// odd ones, and their softmax states merge at the end, so that the heaviest
+// blocks of a small problem are half as long (B 2, L 2048, 8 heads, N 128,
+// S 32: 466 us with the fp32 instructions, 141 with four waves, 84 here; at 32
+// heads 332).  Bound by the vector work beside the 48 MFMAs per 16 tokens and
+// memory (two operations per W element, and the staging).
+template <int N>
+struct MemStage16 {
+    static constexpr int K = N / 32;  // 16-byte pieces per thread
+    uint4 v[K];
+    __device__ __forceinline__ void load(const bf16* __restrict__ src, int tid) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] = reinterpret_cast<const uint4*>(src)[tid + k * kFT];
+    }
+    __device__ __forceinline__ void store(char* tile, float* r, float eps, int normalize, int tid) const {
+        const int row = tid >> 3, c = tid & 7;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            *reinterpret_cast<uint4*>(tile + SwzTile<128>::off(row, c * 16) + k * 4096) = v[k];
+            const uint32_t w[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+            float ss = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const bf16x2 h = __builtin_bit_cast(bf16x2, w[i]);
+                ss = __builtin_amdgcn_fdot2_f32_bf16(h, h, ss, false);
+            }
+            ss = dpp_group_sum<8>(ss);
+            if (c == 0) r[row + 32 * k] = normalize ? __builtin_amdgcn_rsqf(ss * (1.0f / kP) + eps) : 1.0f;
+        }
+    }
+};
+
+template <int N>
+__global__ __launch_bounds__(2 * kFT, N < 128 ? 4 : 2) void k_bsma(
+    const bf16* __restrict__ q, const bf16* __restrict__ e, const bf16* __restrict__ Cm,
+    const bf16* __restrict__ mem, const bf16* __restrict__ z, const bf16* y_ssd, bf16* y,
+    float* __restrict__ lse, const float* __restrict__ qw, const float* __restrict__ ew, float eps,
+    int normalize, int z_per_head, int64_t L, int H, int G, int S, int64_t Mcap, int BH, int nblk,
+    int used) {
+    constexpr int NT = N / 16, KS = N / 32;
+    __shared__ __attribute__((aligned(16))) char s_h[2][2][N < 64 ? 64 * 128 : N * 128];  // [buffer][memory of the step]
+    __shared__ __attribute__((aligned(16))) float s_r[2][2][N];
+    const int tid = threadIdx.x & (kFT - 1), lane = tid & 63, m = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int odd = __builtin_amdgcn_readfirstlane(threadIdx.x / kFT);
+    const unsigned blk = (unsigned)flat_block(), bq = blk / (unsigned)BH;
+    if (bq >= (unsigned)used) return;
+    const int bh = (int)(blk % (unsigned)BH);
+    const int64_t tb = (int64_t)(nblk - 1 - (int)bq) * kFTok;
+    const int64_t b = bh / H;
+    const int h = bh % H;
+    const int grp = (int)((int64_t)h * G / H);
+    const int64_t tw = tb + wave * 16, t = tw + m;
+    const int64_t tc = t < L ? t : L - 1;
+    const int64_t last = tb + kFTok - 1 < L ? tb + kFTok - 1 : L - 1;
+    const int64_t jb = last / S;
+    const int64_t jw = tw < L ? (tw + 15 < last ? tw + 15 : last) / S : 0;
+    const int64_t jt = t < L ? t / S : 0;
+    const int64_t row = (b * L + tc) * G + grp;
+    const bf16* mh = mem + (b * Mcap * H + h) * (int64_t)(N * kP);
+    const int64_t mstep = (int64_t)H * N * kP;
+    MemStage16<N> st;  // memory 2 s + odd of step s
+    if (odd < jb) st.load(mh + odd * mstep, tid);
+    float qv[NT][4];
+    load_row<bf16, NT>(q + row * N, g, qv);
+    if (normalize) norm_pieces<NT>(qv, qw, 4 * g, 16, eps);
+    bf16x8 eh[2], el[2], cf[KS];
+    {
+        // Ebar in operand order: elements 32 ks + 8 g + 0 .. 7
+        float ev[4][4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) load4(e + row * kP + 32 * (k >> 1) + 8 * g + 4 * (k & 1), ev[k]);
+        float ss = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) ss += ev[k][i] * ev[k][i];
+        const float inv = normalize ? 1.0f / sqrtf(row4_sum(ss) * (1.0f / kP) + eps) : 1.0f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int p = 32 * (k >> 1) + 8 * g + 4 * (k & 1) + i;
+                const float v = ev[k][i] * (inv * (normalize && ew ? ew[p] : 1.0f));
+                const bf16 hi = (bf16)v;
+                eh[k >> 1][4 * (k & 1) + i] = hi;
+                el[k >> 1][4 * (k & 1) + i] = (bf16)(v - (float)hi);
+            }
+    }
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+        const bf16x4 c0 = *reinterpret_cast<const bf16x4*>(Cm + row * N + 32 * k + 4 * g);
+        const bf16x4 c1 = *reinterpret_cast<const bf16x4*>(Cm + row * N + 32 * k + 16 + 4 * g);
+        cf[k] = bf16x8{c0[0], c0[1], c0[2], c0[3], c1[0], c1[1], c1[2], c1[3]};
+    }
+    if (odd < jb) st.store(s_h[0][odd], s_r[0][odd], eps, normalize, tid);
+    // lane offsets of the two readings: rows n (k steps of 32 p), and the
+    // transposing reads of column tile pt (k steps of 32 n: 32 rows further)
+    uint32_t on[2];
+    KmOffBf16<128> ot[4];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) on[k] = (uint32_t)SwzTile<128>::off(m, (32 * k + 8 * g) * 2);
+#pragma unroll
+    for (int pt = 0; pt < 4; ++pt) ot[pt].init(4 * g, 16 + 4 * g, 16 * pt, lane);
+    const float sc = kLog2e / sqrtf((float)N);
+    float mx = -INFINITY, d = 0.f;
+    f32x4 O[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) O[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int64_t j = odd; j - odd < jb; j += 2) {
+        const int buf = (int)((j >> 1) & 1);
+        __syncthreads();
+        if (j + 2 < jb) st.load(mh + (j + 2) * mstep, tid);
+        if (j < jw) {
+            const char* tile = s_h[buf][odd];
+            float l4[2] = {0.f, 0.f};
+#pragma unroll
+            for (int n = 0; n < NT; ++n) {
+                f32x4 w = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const bf16x8 a = *reinterpret_cast<const bf16x8*>(tile + on[k] + 2048 * n);
+                    w = mma16(w, a, eh[k]);
+                    w = mma16(w, a, el[k]);
+                }
+                const f32x4 rn = *reinterpret_cast<const f32x4*>(&s_r[buf][odd][16 * n + 4 * g]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) l4[n & 1] += qv[n][i] * rn[i] * w[i];
+            }
+            f32x4 V[4];
+#pragma unroll
+            for (int pt = 0; pt < 4; ++pt) {
+                V[pt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int k = 0; k < KS; ++k) V[pt] = mma16(V[pt], ot[pt].read(tile, 4096 * k), cf[k]);
+            }
+            const float l = row4_sum(l4[0] + l4[1]) * sc;
+            const bool at = j < jt, grow = at && l > mx;
+            if (__builtin_amdgcn_ballot_w64(grow)) {  // (rare after the first memories)
+                const float mn = grow ? l : mx, al = grow ? fast_exp2(mx - mn) : 1.f;
+                mx = mn;
+                d *= al;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) O[i] *= al;
+            }
+            const float pw = at ? fast_exp2(l - mx) : 0.f;
+            d += pw;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) O[i] += V[i] * pw;
+        }
+        if (j + 2 < jb) st.store(s_h[buf ^ 1][odd], s_r[buf ^ 1][odd], eps, normalize, tid);
+    }
+    // the two halves of a token's memories meet in the waves of the even ones
+    // (O, maximum and sum where the memories were)
+    static_assert(sizeof(s_h) >= 18 * 256 * 4, "room for 256 lanes");
+    float* so = reinterpret_cast<float*>(&s_h[0][0][0]) + (wave * 64 + lane) * 18;
+    __syncthreads();
+    if (odd) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) so[4 * i + r] = O[i][r];
+        so[16] = mx;
+        so[17] = d;
+    }
+    __syncthreads();
+    if (odd || t >= L) return;
+    if (jt > 1) {
+        const float m1 = so[16], mn = fmaxf(mx, m1);
+        const float a0 = fast_exp2(mx - mn), a1 = fast_exp2(m1 - mn);
+        mx = mn;
+        d = d * a0 + so[17] * a1;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) O[i][r] = O[i][r] * a0 + so[4 * i + r] * a1;
+    }
+    const int64_t bt = b * L + t;
+    const int64_t yi = (bt * H + h) * kP + 4 * g;
+    const float f = jt > 0 ? silu(to_f(z[z_per_head ? bt * H + h : bt])) / d : 0.f;
+#pragma unroll
+    for (int pt = 0; pt < 4; ++pt) {
+        float v[4];
+        load4(y_ssd + yi + 16 * pt, v);
+        if (jt > 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] += f * O[pt][i];
+        }
+        store4(y + yi + 16 * pt, v);
     }
     if (lse && g == 0) lse[bt * H + h] = jt > 0 ? (mx + log2f(d)) * kLn2 : -INFINITY;
 }
@@ -584,11 +786,19 @@ template <typename T, int N>
 hipError_t run_fsma(const Shape& s, const SmaArgs& a, const void* q, const void* e, const void* Cm,
                     const void* mem, const void* z, const void* ys, void* y, float* lse, hipStream_t st) {
     const int BH = (int)(s.B * s.H);
-    const int64_t nblk = (s.L + kFTok - 1) / kFTok;
+    const int nblk = (int)((s.L + kFTok - 1) / kFTok);
+    const dim3 grid = flat_grid((int64_t)BH * nblk);
     prof_begin("k_sma", st);
-    k_fsma<T, N><<<flat_grid(BH * nblk), kFT, 0, st>>>(
-        (const T*)q, (const T*)e, (const T*)Cm, (const T*)mem, (const T*)z, (const T*)ys, (T*)y, lse,
-        a.qw, a.ew, a.eps, a.normalize, a.z_per_head, s.L, s.H, s.G, s.S, s.Mcap, BH, (int)nblk, (int)nblk);
+    // (at N = 16 a bf16 k step of 32 would be half empty)
+    if constexpr (sizeof(T) == 2 && N >= 32) {
+        k_bsma<N><<<grid, 2 * kFT, 0, st>>>(
+            (const T*)q, (const T*)e, (const T*)Cm, (const T*)mem, (const T*)z, (const T*)ys, (T*)y, lse,
+            a.qw, a.ew, a.eps, a.normalize, a.z_per_head, s.L, s.H, s.G, s.S, s.Mcap, BH, nblk, nblk);
+    } else {
+        k_fsma<T, N><<<grid, kFT, 0, st>>>(
+            (const T*)q, (const T*)e, (const T*)Cm, (const T*)mem, (const T*)z, (const T*)ys, (T*)y, lse,
+            a.qw, a.ew, a.eps, a.normalize, a.z_per_head, s.L, s.H, s.G, s.S, s.Mcap, BH, nblk, nblk);
+    }
     prof_end(st);
     return hipGetLastError();
 }
