@@ -7,21 +7,30 @@
 // cached memory: the step is a stream over B*H*m*N*P storage elements and is
 // bound by HBM bandwidth.
 //
-//   k_decode_partial      grid (split, head, batch): each block streams up to
+//   k_decode_partial      a block per (split, head, batch) streams up to
 //                         decode_mps() memories, one wave per memory at a time;
 //                         lanes own 8 consecutive p of N/8 rows.  Each wave
 //                         keeps the next memory's rows in flight while it
 //                         reduces the current one (r, the logit and C dH on
 //                         the fly; online softmax (m, d, O[P])).  Waves merge
 //                         in LDS; one partial per split goes to the workspace.
-//   k_decode_state_merge  grid (head, batch): recurrent update of h_state and
-//                         of the running chunk contribution, y_ssd = C h_state,
-//                         the append of the running contribution when the
-//                         token closes its chunk (slot m, never read by this
-//                         step), the deterministic LSE merge of the split
-//                         partials and y = y_ssd + SiLU(z) R.
-// Keeping the state traffic out of the streaming kernel measured faster than
-// giving it to one split per head (that split then lags the others).
+//                         After these (or, for a long stream, in
+//                         k_decode_state_merge), a block per (head, batch) makes
+//                         the recurrent update of h_state and of the running chunk
+//                         contribution, y_ssd = C h_state, and the append of
+//                         the running contribution when the token closes its
+//                         chunk (slot m, never read by this step).
+//   k_decode_merge        a wave per (head, batch): the deterministic LSE merge
+//                         of the split partials and y = y_ssd + SiLU(z) R.
+//   k_decode_one          both in one launch, a block of eight waves per (head,
+//                         batch), where the context is short and the blocks few.
+// A block's first memory rows are requested before anything else, so that their
+// latency covers the set-up (row norms of q and e, C).  Measured, N 128, S 256,
+// bf16, against the state update in the merging kernel, the first loads after
+// the set-up and the split index fastest: B 16, 24 heads, ragged contexts up to 16384: 72 -> 57 us (state blocks
+// among the streaming ones 59 there, but 1500 against 1270 at B 64, 32 heads,
+// context 65536); B 64, 32 heads, ragged up to 32768: 436 -> 374; B 1, context
+// 4095: 12.1 -> 10.5 (and one launch instead of two).
 #include "dart_common.hpp"
 #include "dart_internal.hpp"
 
@@ -85,137 +94,92 @@ inline size_t decode_part_floats(int64_t B, int H, int nsplit) {
     return (size_t)B * H * nsplit * (kP + 2);
 }
 
-template <typename T, int N>
+// By a block of 64 WAVES threads; s_y holds a row per wave.
+template <typename T, int N, int WAVES>
 __device__ __forceinline__ void state_update(const T* __restrict__ x, const float* __restrict__ dt,
                                              const float* __restrict__ A, const T* __restrict__ Bm,
                                              const T* __restrict__ Cm, float* __restrict__ h_state,
                                              float* __restrict__ chunk_acc, T* __restrict__ mem,
-                                             float* __restrict__ yssd, int H, int G, int S,
-                                             int64_t Mcap, int64_t pos, int64_t m, int64_t b, int h,
-                                             int g, float* s_x, float* s_B, float* s_C,
-                                             float (*s_y)[kP]) {
+                                             int H, int G, int S, int64_t Mcap, int64_t pos,
+                                             int64_t m, int64_t b, int h, int g, float (*s_y)[kP]) {
+    constexpr int RG = 4 * WAVES, K = (N + RG - 1) / RG;  // row groups, rows per thread
     const int tid = threadIdx.x;
     const int pq = tid & 15, rg = tid >> 4;  // p quad, row group
     const bool reset = (pos % S) == 0;
     const bool append = (pos % S) == S - 1;
-    if (tid < kP) s_x[tid] = to_f(x[(b * H + h) * kP + tid]);
-    if (tid < N) {
-        s_B[tid] = to_f(Bm[(b * G + g) * N + tid]);
-        s_C[tid] = to_f(Cm[(b * G + g) * N + tid]);
+    const int64_t sbase = (b * H + h) * (int64_t)N * kP;
+    float hs[K][4], ca[K][4], xv[4], yp[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int n = rg + RG * k;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ca[k][i] = 0.f;
+        if (n >= N) continue;
+        load4(h_state + sbase + n * kP + 4 * pq, hs[k]);
+        if (!reset) load4(chunk_acc + sbase + n * kP + 4 * pq, ca[k]);
     }
-    __syncthreads();
+    load4(x + (b * H + h) * kP + 4 * pq, xv);
     const float dtv = dt[b * H + h];
     const float a = __expf(dtv * A[h]);
-    float yp[4] = {0.f, 0.f, 0.f, 0.f};
-    const int64_t sbase = (b * H + h) * (int64_t)N * kP;
     T* mdst = mem + ((b * Mcap + m) * H + h) * (int64_t)N * kP;
-#pragma unroll 4
-    for (int k = 0; k < N / 16; ++k) {
-        const int n = rg + 16 * k;
-        const int64_t off = sbase + n * kP + 4 * pq;
-        float hs[4], ca[4];
-        load4(h_state + off, hs);
-        if (reset) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) ca[i] = 0.f;
-        } else {
-            load4(chunk_acc + off, ca);
-        }
+    for (int k = 0; k < K; ++k) {
+        const int n = rg + RG * k;
+        if (n >= N) continue;
+        const float bn = dtv * to_f(Bm[(b * G + g) * N + n]), cn = to_f(Cm[(b * G + g) * N + n]);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float u = dtv * s_B[n] * s_x[4 * pq + i];
-            hs[i] = a * hs[i] + u;
-            ca[i] = a * ca[i] + u;
-            yp[i] += s_C[n] * hs[i];
+            const float u = bn * xv[i];
+            hs[k][i] = a * hs[k][i] + u;
+            ca[k][i] = a * ca[k][i] + u;
+            yp[i] += cn * hs[k][i];
         }
-        store4(h_state + off, hs);
-        store4(chunk_acc + off, ca);
-        if (append) store4(mdst + n * kP + 4 * pq, ca);
+        store4(h_state + sbase + n * kP + 4 * pq, hs[k]);
+        store4(chunk_acc + sbase + n * kP + 4 * pq, ca[k]);
+        if (append) store4(mdst + n * kP + 4 * pq, ca[k]);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s_y[rg][4 * pq + i] = yp[i];
-    __syncthreads();
-    if (tid < kP) {
-        float ys = 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) ys += s_y[r][tid];
-        yssd[(b * H + h) * kP + tid] = ys;
-    }
+    for (int i = 0; i < 4; ++i) yp[i] = row4_sum(yp[i]);
+    if ((tid & 63) < 16) store4(&s_y[tid >> 6][4 * pq], yp);
 }
 
+// One token's attention over memories, a wave at a time: lanes own 8
+// consecutive p (po) of rows n = rg + 8 k.
 template <typename T, int N>
-__global__ __launch_bounds__(kThreads) void k_decode_partial(
-    const T* __restrict__ mem_rd, const T* __restrict__ q, const T* __restrict__ e,
-    const T* __restrict__ Cm, const float* __restrict__ qw, const float* __restrict__ ew,
-    float* __restrict__ part, float eps, int normalize, int H, int G, int S, int64_t Mcap,
-    int64_t m, const int64_t* __restrict__ pos_rows, int64_t pos_lim, int nsplit, int mps) {
-    constexpr int R = N / 8;  // rows per lane (row n = rg + 8 k)
-    const int s = blockIdx.x, h = blockIdx.y;
-    const int64_t b = blockIdx.z;
-    const int g = (int)((int64_t)h * G / H);
-    if (pos_rows) {
-        // ragged batch: this row's own position; rows outside [0, pos_lim]
-        // take no part in the step
-        const int64_t pb = pos_rows[b];
-        if (pb < 0 || pb > pos_lim) return;
-        m = pb / S;
-    }
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int po = lane & 7, rg = lane >> 3;
-
-    __shared__ float s_q[N];
-    __shared__ float s_e[kP];
-    __shared__ float s_part[4][kP + 2];
-
-    const int64_t j0 = (int64_t)s * mps;
-    const int64_t j1 = (j0 + mps < m) ? j0 + mps : m;
-    if (j0 >= j1) return;  // block-uniform: no cached memory in this split
-
-    if (wave == 0) {
-        const float v0 = lane < N ? to_f(q[(b * G + g) * N + lane]) : 0.f;
-        const float v1 = lane + 64 < N ? to_f(q[(b * G + g) * N + lane + 64]) : 0.f;
-        float ss = v0 * v0 + v1 * v1;
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) ss += shfl_xor(ss, o);
-        const float inv = (normalize ? 1.0f / sqrtf(ss * (1.0f / N) + eps) : 1.0f) *
-                          (kLog2e / sqrtf((float)N));
-        if (lane < N) s_q[lane] = v0 * inv * (qw ? qw[lane] : 1.0f);
-        if (lane + 64 < N) s_q[lane + 64] = v1 * inv * (qw ? qw[lane + 64] : 1.0f);
-    } else if (wave == 1) {
-        const float v = to_f(e[(b * G + g) * kP + lane]);
-        float ss = v * v;
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) ss += shfl_xor(ss, o);
-        const float inv = normalize ? 1.0f / sqrtf(ss * (1.0f / kP) + eps) : 1.0f;
-        s_e[lane] = v * inv * (ew ? ew[lane] : 1.0f);
-    }
-    __syncthreads();
-
+struct Attend {
+    static constexpr int R = N / 8;
+    using Rows = RowChunk<T>[R];
     float eb[8], qb[R], cb[R];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) eb[i] = s_e[po * 8 + i];
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-        qb[k] = s_q[rg + 8 * k];
-        cb[k] = to_f(Cm[(b * G + g) * N + rg + 8 * k]);
-    }
-    // packed bf16 copies for the dot2 path
-    uint32_t ebp[4], cbp[R / 2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) ebp[i] = pack_bf2(eb[2 * i], eb[2 * i + 1]);
-#pragma unroll
-    for (int k = 0; k < R / 2; ++k) cbp[k] = pack_bf2(cb[2 * k], cb[2 * k + 1]);
+    uint32_t ebp[4], cbp[R / 2];  // packed bf16 copies for the dot2 path
+    float mx, den, o[8];
+    float eps;
+    int normalize, po, rg;
 
-    float mx = -INFINITY, den = 0.f, o[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) o[i] = 0.f;
-
-    auto load_mem = [&](int64_t j, RowChunk<T>(&xr)[R]) {
-        const T* src = mem_rd + ((b * Mcap + j) * H + h) * (int64_t)N * kP;
+    __device__ __forceinline__ void load(const T* src, Rows& xr) const {
 #pragma unroll
         for (int k = 0; k < R; ++k) load_row(src + (rg + 8 * k) * kP + po * 8, xr[k]);
-    };
-    auto reduce_mem = [&](const RowChunk<T>(&xr)[R]) {
+    }
+    // s_q, s_e: Qbar log2(e)/sqrt(N) and Ebar in LDS
+    __device__ __forceinline__ void init(const float* s_q, const float* s_e) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            eb[i] = s_e[po * 8 + i];
+            o[i] = 0.f;
+        }
+#pragma unroll
+        for (int k = 0; k < R; ++k) qb[k] = s_q[rg + 8 * k];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ebp[i] = pack_bf2(eb[2 * i], eb[2 * i + 1]);
+#pragma unroll
+        for (int k = 0; k < R / 2; ++k) cbp[k] = pack_bf2(cb[2 * k], cb[2 * k + 1]);
+        mx = -INFINITY;
+        den = 0.f;
+    }
+    __device__ __forceinline__ void load_c(const T* crow) {
+#pragma unroll
+        for (int k = 0; k < R; ++k) cb[k] = to_f(crow[rg + 8 * k]);
+    }
+    __device__ __forceinline__ void reduce(const Rows& xr) {
         float lsum = 0.f, v[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] = 0.f;
@@ -270,35 +234,122 @@ __global__ __launch_bounds__(kThreads) void k_decode_partial(
 #pragma unroll
         for (int i = 0; i < 8; ++i) o[i] = o[i] * al + pw * v[i];
         mx = mn;
-    };
+    }
+    // the wave's (O, m, d) into its row of s_part
+    __device__ __forceinline__ void publish(float* row) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            o[i] += shfl_xor(o[i], 8);
+            o[i] += shfl_xor(o[i], 16);
+            o[i] += shfl_xor(o[i], 32);
+        }
+        if (rg == 0) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) row[po * 8 + i] = o[i];
+        }
+        if (po == 0 && rg == 0) {
+            row[kP] = mx;
+            row[kP + 1] = den;
+        }
+    }
+};
+
+// Qbar log2(e)/sqrt(N) by wave 0, Ebar by wave 1, into LDS.
+template <typename T, int N>
+__device__ __forceinline__ void norm_q_e(const T* __restrict__ qrow, const T* __restrict__ erow,
+                                         const float* __restrict__ qw, const float* __restrict__ ew,
+                                         float eps, int normalize, float* s_q, float* s_e) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (wave == 0) {
+        const float v0 = lane < N ? to_f(qrow[lane]) : 0.f;
+        const float v1 = lane + 64 < N ? to_f(qrow[lane + 64]) : 0.f;
+        float ss = v0 * v0 + v1 * v1;
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) ss += shfl_xor(ss, o);
+        const float inv = (normalize ? 1.0f / sqrtf(ss * (1.0f / N) + eps) : 1.0f) *
+                          (kLog2e / sqrtf((float)N));
+        if (lane < N) s_q[lane] = v0 * inv * (qw ? qw[lane] : 1.0f);
+        if (lane + 64 < N) s_q[lane + 64] = v1 * inv * (qw ? qw[lane + 64] : 1.0f);
+    } else if (wave == 1) {
+        const float v = to_f(erow[lane]);
+        float ss = v * v;
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) ss += shfl_xor(ss, o);
+        const float inv = normalize ? 1.0f / sqrtf(ss * (1.0f / kP) + eps) : 1.0f;
+        s_e[lane] = v * inv * (ew ? ew[lane] : 1.0f);
+    }
+}
+
+template <typename T, int N>
+__global__ __launch_bounds__(kThreads) void k_decode_partial(
+    const T* __restrict__ x, const float* __restrict__ dt, const float* __restrict__ A,
+    const T* __restrict__ Bm, float* __restrict__ h_state, float* __restrict__ chunk_acc,
+    T* mem, float* __restrict__ yssd, const T* __restrict__ q, const T* __restrict__ e,
+    const T* __restrict__ Cm, const float* __restrict__ qw, const float* __restrict__ ew,
+    float* __restrict__ part, float eps, int normalize, int H, int G, int S, int64_t Mcap,
+    int64_t pos, const int64_t* __restrict__ pos_rows, int64_t pos_lim, int nsplit, int mps, int ns,
+    int64_t BH) {
+    const int64_t id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, nstream = BH * ns;
+    if (id >= nstream + BH) return;  // (the grid may end with the stream)
+    // A (b, h)'s splits one after the other (1253 us against 1265 with (b, h)
+    // fastest at B 64, context 65536), except in a ragged batch: its short rows
+    // leave the later splits empty, and with the split index fastest (8 splits, 8
+    // XCDs, workgroups dealt in turn) some XCDs would get the empty ones.  The
+    // state blocks come last and overlap the stream's end.
+    const bool state = id >= nstream;
+    const int64_t bh = state ? id - nstream : pos_rows ? id % BH : id / ns;
+    const int s = (int)(state ? 0 : pos_rows ? id / BH : id % ns);
+    const int64_t b = bh / H;
+    const int h = (int)(bh - b * H);
+    const int g = (int)((int64_t)h * G / H);
+    if (pos_rows) {
+        // ragged batch: this row's own position; rows outside [0, pos_lim]
+        // take no part in the step
+        pos = pos_rows[b];
+        if (pos < 0 || pos > pos_lim) return;
+    }
+    const int64_t m = pos / S;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ float s_q[N];
+    __shared__ float s_e[kP];
+    __shared__ __attribute__((aligned(16))) float s_part[4][kP + 4];
+    if (state) {
+        float(*s_y)[kP] = reinterpret_cast<float(*)[kP]>(&s_part[0][0]);
+        state_update<T, N, 4>(x, dt, A, Bm, Cm, h_state, chunk_acc, mem, H, G, S, Mcap, pos, m, b, h, g, s_y);
+        __syncthreads();
+        if (tid < kP) yssd[(b * H + h) * kP + tid] = (s_y[0][tid] + s_y[1][tid]) + (s_y[2][tid] + s_y[3][tid]);
+        return;
+    }
+    const int64_t j0 = (int64_t)s * mps;
+    const int64_t j1 = (j0 + mps < m) ? j0 + mps : m;
+    if (j0 >= j1) return;  // block-uniform: no cached memory in this split
+
     // wave w takes memories j0 + w, j0 + w + 4, ...; the next one's rows are
     // loaded before the current one is reduced (two register buffers)
-    RowChunk<T> xa[R], xb[R];
+    const T* src = mem + (b * Mcap * H + h) * (int64_t)N * kP;
+    const int64_t step = (int64_t)H * N * kP;
+    Attend<T, N> at;
+    at.po = lane & 7;
+    at.rg = lane >> 3;
+    at.eps = eps;
+    at.normalize = normalize;
+    typename Attend<T, N>::Rows xa, xb;
     int64_t j = j0 + wave;
-    if (j < j1) load_mem(j, xa);
+    if (j < j1) at.load(src + j * step, xa);
+    at.load_c(Cm + (b * G + g) * N);
+    norm_q_e<T, N>(q + (b * G + g) * N, e + (b * G + g) * kP, qw, ew, eps, normalize, s_q, s_e);
+    lds_barrier();  // (the first rows stay in flight)
+    at.init(s_q, s_e);
     while (j < j1) {
-        if (j + 4 < j1) load_mem(j + 4, xb);
-        reduce_mem(xa);
+        if (j + 4 < j1) at.load(src + (j + 4) * step, xb);
+        at.reduce(xa);
         j += 4;
         if (j >= j1) break;
-        if (j + 4 < j1) load_mem(j + 4, xa);
-        reduce_mem(xb);
+        if (j + 4 < j1) at.load(src + (j + 4) * step, xa);
+        at.reduce(xb);
         j += 4;
     }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        o[i] += shfl_xor(o[i], 8);
-        o[i] += shfl_xor(o[i], 16);
-        o[i] += shfl_xor(o[i], 32);
-    }
-    if (rg == 0) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) s_part[wave][po * 8 + i] = o[i];
-    }
-    if (lane == 0) {
-        s_part[wave][kP] = mx;
-        s_part[wave][kP + 1] = den;
-    }
+    at.publish(s_part[wave]);
     __syncthreads();
     if (tid < kP) {
         float M = -INFINITY;
@@ -322,47 +373,141 @@ __global__ __launch_bounds__(kThreads) void k_decode_partial(
     }
 }
 
-// Recurrent update (h_state, running chunk contribution, y_ssd, append), then
-// the deterministic LSE merge of the split partials and the gate.
+// The LSE merge of a (b, h)'s split partials, the gate and y, by one wave
+// (lane = p); ys: y_ssd of the lane's column.
+template <typename T>
+__device__ __forceinline__ void merge_splits(const T* __restrict__ z, T* __restrict__ y,
+                                             const float* __restrict__ part, float ys, int64_t bh,
+                                             int64_t b, int64_t m, int nsplit, int z_per_head, int mps) {
+    const int p = threadIdx.x & 63;
+    float R = 0.f;
+    if (m > 0) {
+        const int ns = (int)((m + mps - 1) / mps);
+        const float* pb = part + bh * nsplit * (int64_t)(kP + 2);
+        // maximum and sum with a split per lane, O with a column per lane
+        float M = -INFINITY, D = 0.f, O = 0.f;
+        for (int s = p; s < ns; s += 64) M = fmaxf(M, pb[s * (kP + 2) + kP]);
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) M = fmaxf(M, shfl_xor(M, o));
+        for (int s = p; s < ns; s += 64) D += pb[s * (kP + 2) + kP + 1] * fast_exp2(pb[s * (kP + 2) + kP] - M);
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) D += shfl_xor(D, o);
+#pragma unroll 8
+        for (int s = 0; s < ns; ++s) O += pb[s * (kP + 2) + p] * fast_exp2(pb[s * (kP + 2) + kP] - M);
+        R = O / D;
+    }
+    const float zz = to_f(z_per_head ? z[bh] : z[b]);
+    y[bh * kP + p] = from_f<T>(ys + silu(zz) * R);
+}
+
+// After a stream that made the state updates: one wave per (b, h).
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_decode_merge(
+    const T* __restrict__ z, T* __restrict__ y, const float* __restrict__ part,
+    const float* __restrict__ yssd, int H, int S, int64_t pos, const int64_t* __restrict__ pos_rows,
+    int64_t pos_lim, int nsplit, int z_per_head, int mps, int64_t BH) {
+    const int64_t bh = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (bh >= BH) return;
+    const int64_t b = bh / H;
+    if (pos_rows) {
+        pos = pos_rows[b];
+        if (pos < 0 || pos > pos_lim) return;  // the row takes no part in the step
+    }
+    merge_splits(z, y, part, yssd[bh * kP + (threadIdx.x & 63)], bh, b, pos / S, nsplit, z_per_head, mps);
+}
+
+// After a stream that did not: a block per (b, h) makes the state update, then
+// its first wave merges.
 template <typename T, int N>
 __global__ __launch_bounds__(kThreads) void k_decode_state_merge(
     const T* __restrict__ x, const float* __restrict__ dt, const float* __restrict__ A,
     const T* __restrict__ Bm, const T* __restrict__ Cm, const T* __restrict__ z,
     float* __restrict__ h_state, float* __restrict__ chunk_acc, T* __restrict__ mem,
-    T* __restrict__ y, const float* __restrict__ part, float* __restrict__ yssd, int H, int G,
-    int S, int64_t Mcap, int64_t pos, int64_t m, const int64_t* __restrict__ pos_rows,
-    int64_t pos_lim, int nsplit, int z_per_head, int mps) {
+    T* __restrict__ y, const float* __restrict__ part, int H, int G, int S, int64_t Mcap, int64_t pos,
+    const int64_t* __restrict__ pos_rows, int64_t pos_lim, int nsplit, int z_per_head, int mps) {
+    const int h = blockIdx.x;
+    const int64_t b = blockIdx.y;
+    if (pos_rows) {
+        pos = pos_rows[b];
+        if (pos < 0 || pos > pos_lim) return;
+    }
+    __shared__ __attribute__((aligned(16))) float s_y[4][kP];
+    const int tid = threadIdx.x;
+    state_update<T, N, 4>(x, dt, A, Bm, Cm, h_state, chunk_acc, mem, H, G, S, Mcap, pos, pos / S, b, h,
+                          (int)((int64_t)h * G / H), s_y);
+    __syncthreads();
+    if (tid >= kP) return;
+    const float ys = (s_y[0][tid] + s_y[1][tid]) + (s_y[2][tid] + s_y[3][tid]);
+    merge_splits(z, y, part, ys, b * H + h, b, pos / S, nsplit, z_per_head, mps);
+}
+
+// The whole step of one (b, h) in one block of eight waves: wave w takes
+// memories w, w + 8, ..., after its part of the state update.
+constexpr int kOneWaves = 8;
+template <typename T, int N>
+__global__ __launch_bounds__(64 * kOneWaves, 2) void k_decode_one(
+    const T* __restrict__ x, const float* __restrict__ dt, const float* __restrict__ A,
+    const T* __restrict__ Bm, float* __restrict__ h_state, float* __restrict__ chunk_acc, T* mem,
+    const T* __restrict__ q, const T* __restrict__ e, const T* __restrict__ Cm,
+    const T* __restrict__ z, T* __restrict__ y, const float* __restrict__ qw,
+    const float* __restrict__ ew, float eps, int normalize, int H, int G, int S, int64_t Mcap,
+    int64_t pos, const int64_t* __restrict__ pos_rows, int64_t pos_lim, int z_per_head) {
     const int h = blockIdx.x;
     const int64_t b = blockIdx.y;
     const int g = (int)((int64_t)h * G / H);
     if (pos_rows) {
         pos = pos_rows[b];
-        if (pos < 0 || pos > pos_lim) return;  // the row takes no part in the step
-        m = pos / S;
+        if (pos < 0 || pos > pos_lim) return;
     }
-    __shared__ float s_x[kP], s_B[N], s_C[N];
-    __shared__ float s_y[16][kP];
-    state_update<T, N>(x, dt, A, Bm, Cm, h_state, chunk_acc, mem, yssd, H, G, S, Mcap, pos, m, b,
-                       h, g, s_x, s_B, s_C, s_y);
-    const int p = threadIdx.x;
-    if (p >= kP) return;
-    float R = 0.f;
-    if (m > 0) {
-        const int ns = (int)((m + mps - 1) / mps);
-        const float* pb = part + (b * H + h) * nsplit * (int64_t)(kP + 2);
-        float M = -INFINITY;
-        for (int s = 0; s < ns; ++s) M = fmaxf(M, pb[s * (kP + 2) + kP]);
-        float D = 0.f, O = 0.f;
-        for (int s = 0; s < ns; ++s) {
-            const float sc = fast_exp2(pb[s * (kP + 2) + kP] - M);
-            D += pb[s * (kP + 2) + kP + 1] * sc;
-            O += pb[s * (kP + 2) + p] * sc;
-        }
-        R = O / D;
+    const int64_t m = pos / S;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ float s_q[N];
+    __shared__ float s_e[kP];
+    __shared__ float s_part[kOneWaves][kP + 2];
+    __shared__ __attribute__((aligned(16))) float s_y[kOneWaves][kP];
+    const T* src = mem + (b * Mcap * H + h) * (int64_t)N * kP;
+    const int64_t step = (int64_t)H * N * kP;
+    Attend<T, N> at;
+    at.po = lane & 7;
+    at.rg = lane >> 3;
+    at.eps = eps;
+    at.normalize = normalize;
+    typename Attend<T, N>::Rows xa;
+    if (wave < m) at.load(src + wave * step, xa);
+    at.load_c(Cm + (b * G + g) * N);
+    norm_q_e<T, N>(q + (b * G + g) * N, e + (b * G + g) * kP, qw, ew, eps, normalize, s_q, s_e);
+    state_update<T, N, kOneWaves>(x, dt, A, Bm, Cm, h_state, chunk_acc, mem, H, G, S, Mcap, pos, m, b, h, g, s_y);
+    lds_barrier();
+    at.init(s_q, s_e);
+    for (int64_t j = wave; j < m; j += kOneWaves) {
+        if (j >= kOneWaves) at.load(src + j * step, xa);
+        at.reduce(xa);
     }
+    at.publish(s_part[wave]);
+    __syncthreads();
+    if (tid >= kP) return;
+    float ys = 0.f, M = -INFINITY, D = 0.f, O = 0.f;
+#pragma unroll
+    for (int w = 0; w < kOneWaves; ++w) {
+        ys += s_y[w][tid];
+        M = fmaxf(M, s_part[w][kP]);
+    }
+#pragma unroll
+    for (int w = 0; w < kOneWaves; ++w) {
+        const float mw = s_part[w][kP];
+        if (mw == -INFINITY) continue;
+        const float sc = fast_exp2(mw - M);
+        D += s_part[w][kP + 1] * sc;
+        O += s_part[w][tid] * sc;
+    }
+    const float R = m > 0 ? O / D : 0.f;
     const float zz = to_f(z_per_head ? z[b * H + h] : z[b]);
-    y[(b * H + h) * kP + p] = from_f<T>(yssd[(b * H + h) * kP + p] + silu(zz) * R);
+    y[(b * H + h) * kP + tid] = from_f<T>(ys + silu(zz) * R);
 }
+
+// One launch where it is the shorter way: at most two memories per wave (more are
+// better spread over the chip) and no more blocks than compute units.
+inline bool decode_in_one(int64_t bh, int64_t m) { return m <= 2 * kOneWaves && bh <= device_cu_count(); }
 
 // Number of splits of a step that attends m memories.
 inline int decode_splits(const Shape& s, int64_t m) {
@@ -381,24 +526,44 @@ hipError_t run_decode(const Shape& s, const SmaArgs& a, int64_t pos, const int64
                       hipStream_t st) {
     // ragged batches size the grid for the largest position (pos = pos_lim)
     const int64_t m = pos / s.S;
+    if (decode_in_one(s.B * s.H, m)) {
+        prof_begin("k_decode_one", st);
+        k_decode_one<T, N><<<dim3((unsigned)s.H, (unsigned)s.B), 64 * kOneWaves, 0, st>>>(
+            (const T*)x, dt, A, (const T*)Bm, h_state, chunk_acc, (T*)mem, (const T*)q, (const T*)e,
+            (const T*)Cm, (const T*)z, (T*)y, a.qw, a.ew, a.eps, a.normalize, s.H, s.G, s.S, s.Mcap, pos,
+            pos_rows, pos, a.z_per_head);
+        prof_end(st);
+        return hipGetLastError();
+    }
     const int mps = decode_mps(s.B * s.H, m);
     const int nsplit_cap =
         nsplit_stride > 0 ? nsplit_stride : (int)((s.Mcap + kMinMPS - 1) / kMinMPS);
     float* part = reinterpret_cast<float*>(ws);
     float* yssd = part + decode_part_floats(s.B, s.H, nsplit_cap);
-    if (m > 0) {
-        const int ns = (int)((m + mps - 1) / mps);
-        prof_begin("k_decode_partial", st);
-        k_decode_partial<T, N><<<dim3((unsigned)ns, (unsigned)s.H, (unsigned)s.B), kThreads, 0, st>>>(
-            (const T*)mem, (const T*)q, (const T*)e, (const T*)Cm, a.qw, a.ew, part, a.eps,
-            a.normalize, s.H, s.G, s.S, s.Mcap, m, pos_rows, pos, nsplit_cap, mps);
-        prof_end(st);
+    const int ns = m > 0 ? (int)((m + mps - 1) / mps) : 0;
+    const int64_t BH = s.B * s.H;
+    // The state updates join the stream's end and save their own pass over the
+    // chip (context 20000, B 8, 24 heads: 51.2 us against 52.7); after a stream of
+    // gigabytes they are faster in a kernel of few registers and many waves
+    // (context 65536, B 64, 32 heads, 8.6 GB: 1274 against 1260; 3.6 GB the same).
+    const bool apart = BH * m * N * kP * (int64_t)sizeof(T) >= (int64_t)4 << 30;
+    const int64_t nb = apart ? BH * ns : BH * (ns + 1), gx = nb < (1 << 23) ? nb : (1 << 23);
+    prof_begin("k_decode_partial", st);
+    k_decode_partial<T, N><<<dim3((unsigned)gx, (unsigned)((nb + gx - 1) / gx)), kThreads, 0, st>>>(
+        (const T*)x, dt, A, (const T*)Bm, h_state, chunk_acc, (T*)mem, yssd, (const T*)q, (const T*)e,
+        (const T*)Cm, a.qw, a.ew, part, a.eps, a.normalize, s.H, s.G, s.S, s.Mcap, pos, pos_rows, pos,
+        nsplit_cap, mps, ns, BH);
+    prof_end(st);
+    if (apart) {
+        prof_begin("k_decode_state_merge", st);
+        k_decode_state_merge<T, N><<<dim3((unsigned)s.H, (unsigned)s.B), kThreads, 0, st>>>(
+            (const T*)x, dt, A, (const T*)Bm, (const T*)Cm, (const T*)z, h_state, chunk_acc, (T*)mem, (T*)y,
+            part, s.H, s.G, s.S, s.Mcap, pos, pos_rows, pos, nsplit_cap, a.z_per_head, mps);
+    } else {
+        prof_begin("k_decode_merge", st);
+        k_decode_merge<T><<<(unsigned)((BH + 3) / 4), kThreads, 0, st>>>(
+            (const T*)z, (T*)y, part, yssd, s.H, s.S, pos, pos_rows, pos, nsplit_cap, a.z_per_head, mps, BH);
     }
-    prof_begin("k_decode_state_merge", st);
-    k_decode_state_merge<T, N><<<dim3((unsigned)s.H, (unsigned)s.B), kThreads, 0, st>>>(
-        (const T*)x, dt, A, (const T*)Bm, (const T*)Cm, (const T*)z, h_state, chunk_acc, (T*)mem,
-        (T*)y, part, yssd, s.H, s.G, s.S, s.Mcap, pos, m, pos_rows, pos, nsplit_cap, a.z_per_head,
-        mps);
     prof_end(st);
     return hipGetLastError();
 }

@@ -204,9 +204,12 @@ def _ptr_rows(t) -> int:
 
 
 def _stream(stream):
+    if stream is not None:
+        return stream.cuda_stream
+    # torch.cuda.current_stream().cuda_stream without building the Stream object
+    # (0.2 instead of 2.8 us per call)
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _workspace(nbytes, device):
