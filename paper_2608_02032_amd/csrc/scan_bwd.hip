@@ -192,7 +192,7 @@ __global__ __launch_bounds__(256) void k_fs_pass(float* dH, float* dR,
     const int h = blockIdx.y;
     const int64_t b = blockIdx.z, bh = b * H + h;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int e0 = (blockIdx.x * 256 + tid) * 4;
+    const int e0 = (blockIdx.x * 256 + tid) * 4;  // NP is a multiple of 1024
     const int nw = gridDim.x * 4, wv = blockIdx.x * 4 + (tid >> 6), nkp = OWN ? 2 * nw : nw;
     const float* ld = lda + bh * pc.nk;
     float* kp = kpart + bh * pc.nk * nkp + wv;
@@ -212,62 +212,78 @@ __global__ __launch_bounds__(256) void k_fs_pass(float* dH, float* dR,
         }
         __syncthreads();
     }
-    const bool in = e0 < NP;
-    // four pieces' values are loaded before the first is replaced: the chains
-    // over the pieces are short, the loads' latency is what bounds them
+    // U pieces' values are loaded while the U before them are used, ahead of
+    // those pieces' stores: the chains over the pieces are short, the loads'
+    // latency is what bounds them (memory operations complete in order)
     constexpr int U = 4;
     float hc[4] = {0.f, 0.f, 0.f, 0.f}, ho[4] = {0.f, 0.f, 0.f, 0.f}, dm[4] = {0.f, 0.f, 0.f, 0.f};
-    if (h0 && in) load4(h0 + bh * (int64_t)NP + e0, hc);
+    if (h0) load4(h0 + bh * (int64_t)NP + e0, hc);
     int i = 0;  // piece of its chunk
-    for (int64_t k0 = 0; k0 < pc.nk; k0 += U) {
-        float d4[U][4], a[U], sf[U];
+    struct Fwd {
+        float d[U][4], a[U], sf[U];
+    };
+    auto fload = [&](int64_t k0, Fwd& f) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t k = k0 + u < pc.nk ? k0 + u : pc.nk - 1;
-            if (in) load4(ph + k * step, d4[u]);
-            a[u] = fast_exp2(ld[k]);
-            if (OWN) sf[u] = suf[bh * pc.nk + k];
+            load4(ph + k * step, f.d[u]);
+            f.a[u] = fast_exp2(ld[k]);
+            f.sf[u] = OWN ? suf[bh * pc.nk + k] : 0.f;
         }
+    };
+    auto fstep = [&](int64_t k0, const Fwd& f) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t k = k0 + u;
-            if (k >= pc.nk) break;
-            if (in) store4(ph + k * step, hc);
+            if (k >= pc.nk) continue;
+            store4(ph + k * step, hc);
             if (OWN) {
                 if (i == 0) {
-                    if (pm && in) load4(pm + k / pc.nq * step, dm);
+                    if (pm) load4(pm + k / pc.nq * step, dm);
                     ho[0] = ho[1] = ho[2] = ho[3] = 0.f;
                 }
                 float s = (ho[0] * dm[0] + ho[1] * dm[1]) + (ho[2] * dm[2] + ho[3] * dm[3]);
-                s = row4_sum(dpp_group_sum<16>(in ? s : 0.f));
-                if (lane == 0) kp[k * nkp + nw] = a[u] * sf[u] * s;
+                s = row4_sum(dpp_group_sum<16>(s));
+                if (lane == 0) kp[k * nkp + nw] = f.a[u] * f.sf[u] * s;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) ho[q] = a[u] * ho[q] + d4[u][q];
+                for (int q = 0; q < 4; ++q) ho[q] = f.a[u] * ho[q] + f.d[u][q];
                 if (++i == pc.nq) i = 0;
             }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) hc[q] = a[u] * hc[q] + d4[u][q];
+            for (int q = 0; q < 4; ++q) hc[q] = f.a[u] * hc[q] + f.d[u][q];
+        }
+    };
+    {
+        Fwd f0, f1;
+        fload(0, f0);
+        for (int64_t k0 = 0; k0 < pc.nk; k0 += 2 * U) {
+            fload(k0 + U, f1);
+            fstep(k0, f0);
+            fload(k0 + 2 * U, f0);
+            fstep(k0 + U, f1);
         }
     }
     float r[4] = {0.f, 0.f, 0.f, 0.f}, dd[4] = {0.f, 0.f, 0.f, 0.f};
-    if (dhl && in) load4(dhl + bh * (int64_t)NP + e0, r);
+    if (dhl) load4(dhl + bh * (int64_t)NP + e0, r);
     const bool nest = pc.S >= kQ;  // a chunk's dmem leaves with its pieces
-    for (int64_t k0 = pc.nk - 1; k0 >= 0; k0 -= U) {
-        float d4[U][4], h4[U][4], a[U];
+    struct Bwd {
+        float d[U][4], h[U][4], a[U];
+    };
+    auto bload = [&](int64_t k0, Bwd& f) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t k = k0 - u > 0 ? k0 - u : 0;
-            if (in) {
-                load4(pr + k * step, d4[u]);
-                load4(ph + k * step, h4[u]);
-            }
-            a[u] = fast_exp2(ld[k]);
+            load4(pr + k * step, f.d[u]);
+            load4(ph + k * step, f.h[u]);
+            f.a[u] = fast_exp2(ld[k]);
         }
+    };
+    auto bstep = [&](int64_t k0, const Bwd& f) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t k = k0 - u;
-            if (k < 0) break;
-            if (nest && pm && in) {
+            if (k < 0) continue;
+            if (nest && pm) {
                 const int64_t c = k / pc.nq;
                 if (k == pc.nk - 1 || (k + 1) / pc.nq != c) load4(pm + c * step, dd);
             }
@@ -275,16 +291,26 @@ __global__ __launch_bounds__(256) void k_fs_pass(float* dH, float* dR,
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 w4[q] = r[q] + dd[q];
-                s += r[q] * h4[u][q];
-                r[q] = a[u] * r[q] + d4[u][q];
-                dd[q] *= a[u];
+                s += r[q] * f.h[u][q];
+                r[q] = f.a[u] * r[q] + f.d[u][q];
+                dd[q] *= f.a[u];
             }
-            if (in) store4(pr + k * step, w4);
-            s = row4_sum(dpp_group_sum<16>(in ? s : 0.f)) * a[u];
+            store4(pr + k * step, w4);
+            s = row4_sum(dpp_group_sum<16>(s)) * f.a[u];
             if (lane == 0) kp[k * nkp] = s;
         }
+    };
+    {
+        Bwd f0, f1;
+        bload(pc.nk - 1, f0);
+        for (int64_t k0 = pc.nk - 1; k0 >= 0; k0 -= 2 * U) {
+            bload(k0 - U, f1);
+            bstep(k0, f0);
+            bload(k0 - 2 * U, f0);
+            bstep(k0 - U, f1);
+        }
     }
-    if (dh0 && in) store4(dh0 + bh * (int64_t)NP + e0, r);
+    if (dh0) store4(dh0 + bh * (int64_t)NP + e0, r);
 }
 
 // ---- per (b, piece, block of heads): the token gradients ----------------------------

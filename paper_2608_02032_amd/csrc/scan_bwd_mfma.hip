@@ -293,54 +293,110 @@ __global__ __launch_bounds__(256) void k_sbwd_pass2(
     const float* __restrict__ h0, const float* __restrict__ dmem, const float* __restrict__ dhl,
     bf16* __restrict__ Hb, bf16* __restrict__ Wb, float* __restrict__ Kp, float* __restrict__ dh0,
     int H, int NP, int64_t M, int64_t Mcap) {
-    __shared__ float red[2][4];
+    // The chains over the chunks are short; the loads' latency bounds this
+    // kernel.  U chunks' values are loaded while the U before them are used, ahead
+    // of those chunks' stores (memory operations complete in order, so a load
+    // issued after a store would wait for it too).  B 2, 47 chunks, 16 heads,
+    // N 64: 53 us with one chunk at a time, 24 here; B 8, 16 chunks, 24 heads,
+    // N 128: 60 and 58 (U = 2: 28 and 58, U = 8: 24 and 62).
+    constexpr int U = 4;
+    __shared__ float red[2][U][4];
     const int h = blockIdx.y;
     const int64_t b = blockIdx.z;
     const int blk = blockIdx.x, nblk = gridDim.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int e0 = (blk * 256 + tid) * 4;
-    const bool ok = e0 < NP;
+    const int e0 = (blk * 256 + tid) * 4;  // NP is a multiple of 1024
     const float* ld = lda + (b * H + h) * M;
+    const int64_t step = (int64_t)H * NP, o0 = (b * M * H + h) * (int64_t)NP + e0;
+    const float* pm = dmem ? dmem + (b * Mcap * H + h) * (int64_t)NP + e0 : nullptr;
     float hc[4] = {0.f, 0.f, 0.f, 0.f};
-    if (ok && h0) load4(h0 + (b * H + h) * (int64_t)NP + e0, hc);
-    for (int64_t c = 0; c < M; ++c) {
-        const int64_t o = ((b * M + c) * H + h) * (int64_t)NP + e0;
-        if (ok) {
-            store4(Hb + o, hc);
-            float d[4];
-            load4(dH + o, d);
-            const float a = __expf(ld[c]);
+    if (h0) load4(h0 + (b * H + h) * (int64_t)NP + e0, hc);
+    struct Fwd {
+        float d[U][4], a[U];
+    };
+    auto fload = [&](int64_t c0, Fwd& f) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) hc[i] = a * hc[i] + d[i];
+        for (int u = 0; u < U; ++u) {
+            const int64_t c = c0 + u < M ? c0 + u : M - 1;
+            load4(dH + o0 + c * step, f.d[u]);
+            f.a[u] = __expf(ld[c]);
+        }
+    };
+    auto fstep = [&](int64_t c0, const Fwd& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (c0 + u < M) {
+                store4(Hb + o0 + (c0 + u) * step, hc);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) hc[i] = f.a[u] * hc[i] + f.d[u][i];
+            }
+        }
+    };
+    {
+        Fwd f0, f1;
+        fload(0, f0);
+        for (int64_t c0 = 0; c0 < M; c0 += 2 * U) {
+            fload(c0 + U, f1);
+            fstep(c0, f0);
+            fload(c0 + 2 * U, f0);
+            fstep(c0 + U, f1);
         }
     }
     float r[4] = {0.f, 0.f, 0.f, 0.f};
-    if (ok && dhl) load4(dhl + (b * H + h) * (int64_t)NP + e0, r);
-    for (int64_t c = M - 1; c >= 0; --c) {
-        const int64_t o = ((b * M + c) * H + h) * (int64_t)NP + e0;
-        const float a = __expf(ld[c]);
-        float kp = 0.f;
-        if (ok) {
-            float m[4] = {0.f, 0.f, 0.f, 0.f}, w[4], hb[4], d[4];
-            if (dmem) load4(dmem + ((b * Mcap + c) * H + h) * (int64_t)NP + e0, m);
+    if (dhl) load4(dhl + (b * H + h) * (int64_t)NP + e0, r);
+    struct Bwd {
+        float d[U][4], hb[U][4], m[U][4], a[U];
+    };
+    auto bload = [&](int64_t c0, Bwd& f) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) w[i] = r[i] + m[i];
-            store4(Wb + o, w);
-            load4(Hb + o, hb);  // this thread's own entry-state values, stored above
+        for (int u = 0; u < U; ++u) {
+            const int64_t c = c0 - u > 0 ? c0 - u : 0;
+            load4(dR + o0 + c * step, f.d[u]);
+            load4(Hb + o0 + c * step, f.hb[u]);  // this thread's own values, stored above
 #pragma unroll
-            for (int i = 0; i < 4; ++i) kp += r[i] * hb[i];
-            load4(dR + o, d);
+            for (int i = 0; i < 4; ++i) f.m[u][i] = 0.f;
+            if (pm) load4(pm + c * step, f.m[u]);
+            f.a[u] = __expf(ld[c]);
+        }
+    };
+    auto bstep = [&](int64_t c0, int par, const Bwd& f) __attribute__((always_inline)) {
+        float kp[U];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) r[i] = a * r[i] + d[i];
+        for (int u = 0; u < U; ++u) {
+            kp[u] = 0.f;
+            if (c0 - u >= 0) {
+                float w[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w[i] = r[i] + f.m[u][i];
+                store4(Wb + o0 + (c0 - u) * step, w);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) kp[u] += r[i] * f.hb[u][i];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) r[i] = f.a[u] * r[i] + f.d[u][i];
+            }
         }
 #pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) kp += __shfl_xor(kp, m, 64);
-        const int u = (int)(c & 1);
-        if (lane == 0) red[u][wave] = kp;
-        __syncthreads();
-        if (tid == 0) Kp[((b * H + h) * M + c) * nblk + blk] = a * ((red[u][0] + red[u][1]) + (red[u][2] + red[u][3]));
+        for (int u = 0; u < U; ++u) {
+            kp[u] = f.a[u] * row4_sum(dpp_group_sum<16>(kp[u]));
+            if (lane == 0) red[par][u][wave] = kp[u];
+        }
+        lds_barrier();  // (the loads stay in flight)
+        if (tid < U && c0 - tid >= 0) {
+            const float* q = red[par][tid];
+            Kp[((b * H + h) * M + c0 - tid) * nblk + blk] = (q[0] + q[1]) + (q[2] + q[3]);
+        }
+    };
+    {
+        Bwd f0, f1;
+        bload(M - 1, f0);
+        for (int64_t c0 = M - 1; c0 >= 0; c0 -= 2 * U) {
+            bload(c0 - U, f1);
+            bstep(c0, 0, f0);
+            bload(c0 - 2 * U, f0);
+            bstep(c0 - U, 1, f1);
+        }
     }
-    if (ok && dh0) store4(dh0 + (b * H + h) * (int64_t)NP + e0, r);
+    if (dh0) store4(dh0 + (b * H + h) * (int64_t)NP + e0, r);
 }
 
 // ---------------------------------------------------------------------------

@@ -159,8 +159,9 @@ __global__ __launch_bounds__(kFT) void k_fs_state(const T* __restrict__ x, const
 }
 
 // In place: a piece's contribution becomes the state entering it.  Four pieces'
-// contributions are loaded before the first is replaced: the chain over the
-// pieces is short, the loads' latency is what bounds it.
+// contributions are loaded while the four before them are used, ahead of their
+// stores: the chain over the pieces is short, the loads' latency is what bounds
+// it (memory operations complete in order).
 template <typename T>
 __global__ __launch_bounds__(256) void k_fs_states(float* dH, const float* __restrict__ lda,
                                                    const float* __restrict__ h0, float* __restrict__ h_last,
@@ -176,30 +177,42 @@ __global__ __launch_bounds__(256) void k_fs_states(float* dH, const float* __res
     float hc[4] = {0.f, 0.f, 0.f, 0.f}, own[4] = {0.f, 0.f, 0.f, 0.f};
     if (h0) load4(h0 + bh * (int64_t)NP + e0, hc);
     int i = 0;  // piece of its chunk
-    for (int64_t k0 = 0; k0 < pc.nk; k0 += 4) {
-        float d4[4][4], a[4];
+    constexpr int U = 4;
+    struct Part {
+        float d[U][4], a[U];
+    };
+    auto load = [&](int64_t k0, Part& f) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (k0 + u < pc.nk) {
-                load4(ph + (k0 + u) * step, d4[u]);
-                a[u] = fast_exp2(ld[k0 + u]);
-            }
+        for (int u = 0; u < U; ++u) {
+            const int64_t k = k0 + u < pc.nk ? k0 + u : pc.nk - 1;
+            load4(ph + k * step, f.d[u]);  // (past the end: read, not used)
+            f.a[u] = fast_exp2(ld[k]);
         }
+    };
+    auto run = [&](int64_t k0, const Part& f) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int64_t k = k0 + u;
-            if (k >= pc.nk) break;
+            if (k >= pc.nk) continue;
             store4(ph + k * step, hc);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                hc[q] = a[u] * hc[q] + d4[u][q];
-                own[q] = (i == 0 ? 0.f : a[u] * own[q]) + d4[u][q];
+                hc[q] = f.a[u] * hc[q] + f.d[u][q];
+                own[q] = (i == 0 ? 0.f : f.a[u] * own[q]) + f.d[u][q];
             }
             if (++i == pc.nq || k == pc.nk - 1) {
                 if (pm) store4(pm + k / pc.nq * step, own);
                 i = 0;
             }
         }
+    };
+    Part f0, f1;
+    load(0, f0);
+    for (int64_t k0 = 0; k0 < pc.nk; k0 += 2 * U) {
+        load(k0 + U, f1);
+        run(k0, f0);
+        load(k0 + 2 * U, f0);
+        run(k0 + U, f1);
     }
     if (h_last) store4(h_last + bh * (int64_t)NP + e0, hc);
 }
