@@ -34,6 +34,8 @@
 //               V = dH^T C from the same reads, l = U . Ebar, the online
 //               softmax of Alg. 1, the gated residual.  Tokens of a wave may
 //               belong to different chunks (each is masked by its own).
+//   k_fsma_split  the same where those blocks are few: 16 tokens a block, the
+//               memories over its four waves.
 //   k_bsma      the forward for bf16 storage and N >= 32, on the bf16
 //               instructions with exact or split operands (comment there).
 //   k_fbwd_prep Qbar and Ebar of every token (float).
@@ -238,6 +240,132 @@ __global__ __launch_bounds__(kFT, 2) void k_fsma(
         store4(y + yi + 4 * r, v);
     }
     if (lse && g == 0) lse[bt * H + h] = jt > 0 ? (mx + log2f(d)) * kLn2 : -INFINITY;
+}
+
+// ... where those blocks leave the chip idle: 16 tokens per block, wave w on the
+// memories w, w + 4, ..., merged at the end.  A block of 64 tokens is a serial
+// chain of memories at one SIMD's MFMA rate per wave (N 32: 2048 cycles a
+// memory), which nothing shortens inside its CU; this takes four times as many
+// CUs and a quarter of the chain.  A wave reads its operands from global memory
+// in MFMA order (four rows of 256 bytes per load, 32 rows ahead of their use),
+// without LDS or barriers before the merge.
+template <typename T, int N>
+__global__ __launch_bounds__(kFT, 2) void k_fsma_split(
+    const T* __restrict__ q, const T* __restrict__ e, const T* __restrict__ Cm,
+    const T* __restrict__ mem, const T* __restrict__ z, const T* y_ssd, T* y, float* __restrict__ lse,
+    const float* __restrict__ qw, const float* __restrict__ ew, float eps, int normalize,
+    int z_per_head, int64_t L, int H, int G, int S, int64_t Mcap, int BH, int nblk) {
+    constexpr int K = N / 16, KC = K < 2 ? K : 2, NC = K / KC;  // 16-row blocks: all, per chunk of loads
+    __shared__ float s_o[4][18][64];
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned blk = (unsigned)flat_block(), bq = blk / (unsigned)BH;
+    if (bq >= (unsigned)nblk) return;
+    const int bh = (int)(blk % (unsigned)BH);
+    const int64_t tw = (int64_t)(nblk - 1 - (int)bq) * 16;
+    const int64_t b = bh / H;
+    const int h = bh % H;
+    const int grp = (int)((int64_t)h * G / H);
+    const int64_t t = tw + m, tc = t < L ? t : L - 1;
+    const int64_t jw = (tw + 15 < L ? tw + 15 : L - 1) / S;
+    const int64_t jt = t < L ? t / S : 0;
+    const int64_t row = (b * L + tc) * G + grp;
+    const int64_t mstep = (int64_t)H * N * kP;
+    const T* mh = mem + (b * Mcap * H + h) * (int64_t)(N * kP) + g * 4 * kP + 4 * m;
+    float nx[KC][4][4];
+    auto load = [&](const T* src) {
+#pragma unroll
+        for (int k = 0; k < KC; ++k)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) load4(src + (16 * k + s) * kP, nx[k][s]);
+    };
+    if (wave < jw) load(mh + wave * mstep);
+    const int64_t bt = b * L + tc;
+    const int64_t yi = (bt * H + h) * kP + 16 * g + 4 * wave;
+    float yv[4];
+    load4(y_ssd + yi, yv);
+    const float zv = jw > 0 ? to_f(z[z_per_head ? bt * H + h : bt]) : 0.f;
+    float qv[K][4], cv[K][4], ev[4][4];
+    load_row<T, K>(q + row * N, g, qv);
+    load_row<T, K>(Cm + row * N, g, cv);
+    load_acc<T>(e + row * kP, g, ev);
+    if (normalize) {
+        norm_pieces<K>(qv, qw, 4 * g, 16, eps);
+        norm_pieces<4>(ev, ew, 16 * g, 4, eps);
+    }
+    const float sc = kLog2e / sqrtf((float)N);
+    // finite, so that a wave without memories (or with logits of -inf) merges as 0
+    float mx = -__FLT_MAX__, d = 0.f;
+    f32x4 O[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) O[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int64_t j = wave; j < jw; j += 4) {
+        f32x4 U[4], V[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) U[i] = V[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            float a[KC][4][4];
+#pragma unroll
+            for (int k = 0; k < KC; ++k)
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) a[k][s][i] = nx[k][s][i];
+            if (c + 1 < NC) load(mh + j * mstep + (c + 1) * KC * 16 * kP);
+            else if (j + 4 < jw) load(mh + (j + 4) * mstep);
+#pragma unroll
+            for (int k = 0; k < KC; ++k)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const float* v = a[k][s];
+                    const float ss = dpp_group_sum<16>(v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3]);
+                    const float r = normalize ? 1.0f / sqrtf(ss * (1.0f / kP) + eps) : 1.0f;
+                    const float bq4 = qv[KC * c + k][s] * r;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        U[i] = mfma4(v[i], bq4, U[i]);
+                        V[i] = mfma4(v[i], cv[KC * c + k][s], V[i]);
+                    }
+                }
+        }
+        const float l = col_dot(U, ev) * sc;
+        if (j < jt) {
+            const float mn = fmaxf(mx, l);
+            const float al = fast_exp2(mx - mn), pw = fast_exp2(l - mn);
+            mx = mn;
+            d = d * al + pw;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) O[i][r] = O[i][r] * al + pw * V[i][r];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s_o[wave][4 * r + i][lane] = O[i][r];
+    s_o[wave][16][lane] = mx;
+    s_o[wave][17][lane] = d;
+    __syncthreads();
+    if (t >= L) return;
+    if (jt > 0) {  // wave r adds up the channels 16 g + 4 r + i
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+        mx = fmaxf(fmaxf(s_o[0][16][lane], s_o[1][16][lane]), fmaxf(s_o[2][16][lane], s_o[3][16][lane]));
+        d = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float al = fast_exp2(s_o[w][16][lane] - mx);
+            d += al * s_o[w][17][lane];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] += al * s_o[w][4 * wave + i][lane];
+        }
+        const float f = silu(zv) / d;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) yv[i] += f * v[i];
+    }
+    store4(y + yi, yv);
+    if (lse && g == 0 && wave == 0) lse[bt * H + h] = jt > 0 ? (mx + log2f(d)) * kLn2 : -INFINITY;
 }
 
 // ---- forward, bf16 storage ------------------------------------------------------------
@@ -794,6 +922,16 @@ hipError_t run_fsma(const Shape& s, const SmaArgs& a, const void* q, const void*
         k_bsma<N><<<grid, 2 * kFT, 0, st>>>(
             (const T*)q, (const T*)e, (const T*)Cm, (const T*)mem, (const T*)z, (const T*)ys, (T*)y, lse,
             a.qw, a.ew, a.eps, a.normalize, a.z_per_head, s.L, s.H, s.G, s.S, s.Mcap, BH, nblk, nblk);
+    } else if ((int64_t)BH * nblk <= device_cu_count()) {
+        // (fp32, blocks of 64 tokens at most one per CU: L 512, 2 heads, N 32, S 64
+        // 19.0 -> 12.5 us; L 1024, 8 heads, N 64, S 16 184 -> 91; L 2048, 8 heads,
+        // N 128, S 64, 256 blocks, 177 -> 132.  At two per CU the waves of k_fsma
+        // fill the SIMDs and its shared staging wins: L 4096, 8 heads, N 128,
+        // S 256 118 against 131; at eight 608 against 896)
+        const int n16 = (int)((s.L + 15) / 16);
+        k_fsma_split<T, N><<<flat_grid((int64_t)BH * n16), kFT, 0, st>>>(
+            (const T*)q, (const T*)e, (const T*)Cm, (const T*)mem, (const T*)z, (const T*)ys, (T*)y, lse,
+            a.qw, a.ew, a.eps, a.normalize, a.z_per_head, s.L, s.H, s.G, s.S, s.Mcap, BH, n16);
     } else {
         k_fsma<T, N><<<grid, kFT, 0, st>>>(
             (const T*)q, (const T*)e, (const T*)Cm, (const T*)mem, (const T*)z, (const T*)ys, (T*)y, lse,

@@ -44,3 +44,29 @@ def test_sma_f32_forward_and_backward(c):
     np.testing.assert_array_equal(to_np(y)[:, :S], y_ssd[:, :S].astype(np.float64))
     got = MB.run_gpu(w, d, mem, y_ssd, dy)
     MB.check(w, got, d, mem, dy)
+
+
+@pytest.mark.parametrize("N,dtype", [(16, "bf16"), (16, "fp32"), (32, "fp32"), (64, "fp32"), (128, "fp32")])
+@pytest.mark.parametrize("S", [9, 30, 100])
+def test_forward_split_and_whole(N, dtype, S):
+    """The forward's two forms on either side of the line between them (one block
+    of 64 tokens per CU): 200 tokens are four blocks per (b, h), the last 16-token
+    one half empty, with none to 22 memories over the four waves; both against
+    the oracle, and against each other on the sequences they share."""
+    import torch
+
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    B, L, H = cus // 4 + 1, 200, 1
+    w = synth.Workload("split_%d_%d" % (N, S), B, L, H, 64, N, S, dtype, ngroups=1, z_per_head=True)
+    print("\n[gpu-case] sma forms %s" % (w,), flush=True)
+    d, mem, y_ssd = sma_case(w, seed=S + N)
+    y, lse = run_sma(w, d, mem, y_ssd)
+    few = synth.Workload("few", B - 1, L, H, 64, N, S, dtype, ngroups=1, z_per_head=True)
+    y1, lse1 = run_sma(few, {k: v[:B - 1] if getattr(v, "ndim", 0) > 1 else v for k, v in d.items()}, mem[:B - 1], y_ssd[:B - 1])
+    y_ref, lse_ref = oracle.sma(d["q"], d["e"], d["Cm"], mem, d["z"], y_ssd, S)
+    tol = TOL[dtype] if dtype == "fp32" else 2.0 ** -8
+    assert_close_slices(to_np(y), y_ref, tol, what="whole")
+    assert_close_slices(to_np(y1), y_ref[:-1], tol, what="split")
+    assert_lse_close(to_np(lse), lse_ref, "fp32")
+    assert_lse_close(to_np(lse1), lse_ref[:-1], "fp32")
+    assert_close_slices(to_np(y1), to_np(y)[:-1], tol, what="split against whole")
