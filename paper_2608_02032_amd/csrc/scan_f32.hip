@@ -367,7 +367,20 @@ hipError_t run_fscan(const Shape& s, const void* x, const float* dt, const float
 
 }  // namespace
 
-size_t fscan_workspace_bytes(const Shape& s) { return fscan_ws(s, nullptr).total; }
+// At least the parts that callers know the workspace by, per chunk and (b, h): a
+// log decay and an entry state in the storage dtype, and at N >= 32 with S in
+// {64, 128, 256} three floats per token and a group's causal Gram tiles, elsewhere
+// two states in float.  The pieces need less at small S, and more where a chunk
+// is several pieces.
+size_t fscan_workspace_bytes(const Shape& s) {
+    const size_t chunks = (size_t)s.B * s.M * s.H, state = (size_t)s.N * s.P, need = fscan_ws(s, nullptr).total;
+    size_t known = align256(4 * chunks) + align256(elem_bytes(s.dtype) * chunks * state);
+    if (s.N >= 32 && (s.S == 64 || s.S == 128 || s.S == 256))
+        known += align256(4 * chunks * 3 * s.S) + align256(4 * (size_t)s.B * s.G * s.M * (s.S / 32) * (s.S / 32 + 1) * 512);
+    else
+        known += 2 * align256(4 * chunks * state);
+    return need > known ? need : known;
+}
 
 hipError_t launch_fscan(const Shape& s, const void* x, const float* dt, const float* A, const void* Bm,
                         const void* Cm, const float* h0, void* y_ssd, void* mem, float* h_last, void* ws,
