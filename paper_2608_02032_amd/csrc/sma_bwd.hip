@@ -229,7 +229,12 @@ __device__ __forceinline__ void load_row_frags(const S* row, int grp, Frag<T> (&
 // W'^T = Kh^T (q (.) w) (this half's part of every logit) and rows n of
 // X^T = diag(1/r) Kh dy^T (its part of dy . V = C . X).  Every memory
 // fragment read from LDS feeds the RT column tiles.  The two partial sums
-// meet in LDS once per step.
+// meet in LDS, a step late: the softmax sums of step k wait for the barrier
+// that step k + 1 has for its tiles, so a step has one barrier and no exposed
+// exchange (B 8, L 4096, 24 heads, N 128, S 256: 391 -> 372 us; 414 with the
+// residual's products behind a runtime flag, its 32 registers held and the
+// fragments' offsets formed per read).  Matrix, LDS and vector work are each
+// about a third of a step and overlap only across the two waves of a SIMD.
 //
 // The logits are formed to about 16 bits although the operands are stored in
 // bf16: the key side streams as hi + lo (the lo tile holds the rounding
@@ -249,13 +254,13 @@ __device__ __forceinline__ void load_row_frags(const S* row, int grp, Frag<T> (&
 // the weights the gradient kernels use are the softmax of the exact logits,
 // whatever rounding the forward's log-sum-exp carries.  Tiles stream through
 // an NS-stage LDS ring by DMA, NS - 1 steps ahead, copied by waves 0-3.
-template <typename T, int N, int RT>
+template <typename T, int N, int RT, bool QL>
 __global__ __launch_bounds__(512) void k_bwd_scores(
     const T* __restrict__ qh, const bf16* __restrict__ ql, const float* __restrict__ qsc,
     const float* __restrict__ eb, const T* __restrict__ Cm, const float* __restrict__ rinv,
     const T* __restrict__ kmem, const T* __restrict__ klo, const float* __restrict__ lse,
     const T* __restrict__ dy, float* __restrict__ lw, float* __restrict__ dwv,
-    float* __restrict__ lsep, float* __restrict__ rdy, int use_ql, int64_t L, int64_t Ls, int H,
+    float* __restrict__ lsep, float* __restrict__ rdy, int64_t L, int64_t Ls, int H,
     int G, int S, int64_t Mp, int hpb, int blk0, int nblk, int64_t BHC) {
     constexpr int NTL = 2;  // tiles per stage: key side and its residual
     constexpr int RB = kP * (int)sizeof(T);
@@ -270,7 +275,7 @@ __global__ __launch_bounds__(512) void k_bwd_scores(
     constexpr int CPS = NTL * Copy::count() + 1;
     __shared__ __attribute__((aligned(16))) char ring[NS][NTL][TILE];
     __shared__ __attribute__((aligned(16))) float rring[NS][N];
-    __shared__ float xch[2][2][kTokWaves][16 * RT];
+    __shared__ float xch[2][2][2][kTokWaves][16 * RT];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
@@ -300,19 +305,14 @@ __global__ __launch_bounds__(512) void k_bwd_scores(
     }
 
     Frag<T> qf[RT][KQ];
-    Frag<bf16> qlf[RT][KQ];
+    Frag<bf16> qlf[QL ? RT : 1][QL ? KQ : 1];
     float qs[RT], ea[RT][2][4];
     typedef T T4 __attribute__((ext_vector_type(4)));
     T4 ca[RT][NTH];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
         load_row_frags<T, T, N>(qh + (bt[rt] * G + g) * N, grp, qf[rt]);
-        if (use_ql) {
-            load_row_frags<bf16, bf16, N>(ql + (bt[rt] * G + g) * N, grp, qlf[rt]);
-        } else {
-#pragma unroll
-            for (int ks = 0; ks < KQ; ++ks) qlf[rt][ks] = bf16x8{};
-        }
+        if constexpr (QL) load_row_frags<bf16, bf16, N>(ql + (bt[rt] * G + g) * N, grp, qlf[rt]);
         qs[rt] = qsc[bt[rt] * G + g];
         const float* erow = eb + (bt[rt] * G + g) * kP;
 #pragma unroll
@@ -352,6 +352,33 @@ __global__ __launch_bounds__(512) void k_bwd_scores(
     float lse2[RT], dsum[RT], dyacc[RT];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) lse2[rt] = dsum[rt] = dyacc[rt] = 0.f;
+    KmOffBf16<RB> kofs[2];
+    uint32_t xofs[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) kofs[q].init(4 * grp, 16 + 4 * grp, 16 * (pt0 + q), lane);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) xofs[ks] = (uint32_t)SwzTile<RB>::off(col, (32 * ks + 8 * grp) * 2);
+    float l2p[RT], dwp[RT];
+    // the step before's sums (its parity's exchange slots), after a barrier
+    auto meet = [&](int par, int h, int j) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            const float lv = (l2p[rt] + xch[par][0][nh ^ 1][tg][16 * rt + col]) * qs[rt];
+            const float dv = dwp[rt] + xch[par][1][nh ^ 1][tg][16 * rt + col];
+            const float p = fast_exp2(lv - lse2[rt]);
+            dsum[rt] += p;
+            dyacc[rt] += p * dv;
+            if (nh == 0 && lane < 16 && valid[rt]) {
+                const int64_t si = ((b * H + h) * Mp + j) * Ls + tc[rt];
+                lw[si] = lv;
+                dwv[si] = dv;
+                if (j == nj - 1) {
+                    lsep[bt[rt] * H + h] = lse2[rt] + __log2f(dsum[rt]);
+                    rdy[bt[rt] * H + h] = dyacc[rt] / dsum[rt];
+                }
+            }
+        }
+    };
     int hh = 0, j = 0;
     for (int k = 0; k < nsteps; ++k) {
         const int h = h0 + hh;
@@ -364,6 +391,7 @@ __global__ __launch_bounds__(512) void k_bwd_scores(
             __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
         }
         lds_barrier();
+        if (k > 0) meet((k - 1) & 1, j == 0 ? h - 1 : h, j == 0 ? nj - 1 : j - 1);
         if (j == 0) {
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
@@ -389,15 +417,14 @@ __global__ __launch_bounds__(512) void k_bwd_scores(
         for (int ks = 0; ks < KQ; ++ks) {
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
-                const int r0 = 32 * ks + 4 * grp, r1 = r0 + 16, cb = 16 * (pt0 + q);
-                const Frag<T> a = frag_km<T, RB>(kt, r0, r1, cb, lane);
+                const Frag<T> a = kofs[q].read(kt, ks * 32 * RB);
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) w[rt][q] = mma16(w[rt][q], a, qf[rt][ks]);
-                const Frag<T> al = frag_km<T, RB>(ring[k % NS][NTL - 1], r0, r1, cb, lane);
+                const Frag<T> al = kofs[q].read(ring[k % NS][NTL - 1], ks * 32 * RB);
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) {
                     w[rt][q] = mma16(w[rt][q], al, qf[rt][ks]);
-                    if (use_ql) w[rt][q] = mma16(w[rt][q], a, qlf[rt][ks]);
+                    if constexpr (QL) w[rt][q] = mma16(w[rt][q], a, qlf[rt][ks]);
                 }
             }
         }
@@ -420,7 +447,7 @@ __global__ __launch_bounds__(512) void k_bwd_scores(
             for (int rt = 0; rt < RT; ++rt) x[rt] = zero4;
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                const Frag<T> a = frag_rowmajor<T, RB>(kt, 16 * nt + col, 32 * ks + 8 * grp);
+                const Frag<T> a = *reinterpret_cast<const bf16x8*>(kt + xofs[ks] + 16 * nt * RB);
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) x[rt] = mma16(x[rt], a, dyf[rt][ks]);
             }
@@ -432,35 +459,21 @@ __global__ __launch_bounds__(512) void k_bwd_scores(
         }
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-            l2[rt] = row4_sum(l2[rt]);
-            dw[rt] = row4_sum(dw[rt]);
+            l2p[rt] = row4_sum(l2[rt]);
+            dwp[rt] = row4_sum(dw[rt]);
             if (lane < 16) {
-                xch[0][nh][tg][16 * rt + col] = l2[rt];
-                xch[1][nh][tg][16 * rt + col] = dw[rt];
-            }
-        }
-        lds_barrier();
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const float lv = (l2[rt] + xch[0][nh ^ 1][tg][16 * rt + col]) * qs[rt];
-            const float dv = dw[rt] + xch[1][nh ^ 1][tg][16 * rt + col];
-            const float p = fast_exp2(lv - lse2[rt]);
-            dsum[rt] += p;
-            dyacc[rt] += p * dv;
-            if (nh == 0 && lane < 16 && valid[rt]) {
-                const int64_t si = ((b * H + h) * Mp + j) * Ls + tc[rt];
-                lw[si] = lv;
-                dwv[si] = dv;
-                if (j == nj - 1) {
-                    lsep[bt[rt] * H + h] = lse2[rt] + __log2f(dsum[rt]);
-                    rdy[bt[rt] * H + h] = dyacc[rt] / dsum[rt];
-                }
+                xch[k & 1][0][nh][tg][16 * rt + col] = l2p[rt];
+                xch[k & 1][1][nh][tg][16 * rt + col] = dwp[rt];
             }
         }
         if (++j == nj) {
             j = 0;
             ++hh;
         }
+    }
+    if (nsteps > 0) {
+        lds_barrier();
+        meet((nsteps - 1) & 1, h0 + hpb - 1, nj - 1);
     }
 }
 
@@ -1178,7 +1191,6 @@ hipError_t run_bwd(const Shape& s, const SmaArgs& a, const void* q, const void* 
         const int64_t BHC = s.B * (s.H / hpb);
         // the query operand needs its residual only when a norm weight makes
         // q (.) w inexact in bf16
-        const int use_ql = a.qw != nullptr;
         // at S >= 128 128 tokens per workgroup (S is a multiple of 128, so a
         // block never straddles chunks)
         constexpr int TB2 = 2 * kTokBlock;
@@ -1186,11 +1198,14 @@ hipError_t run_bwd(const Shape& s, const SmaArgs& a, const void* q, const void* 
         const int tb0 = two ? s.S / TB2 : blk0;
         const int64_t tnblk = two ? (s.L + TB2 - 1) / TB2 - tb0 : nblk;
         const unsigned tgrid = (unsigned)(BHC * tnblk);
-        auto scores = [&](auto rt) {
-            k_bwd_scores<T, N, decltype(rt)::value><<<tgrid, 512, 0, st>>>(
+        auto scores_of = [&](auto rt, auto res) {
+            k_bwd_scores<T, N, decltype(rt)::value, decltype(res)::value><<<tgrid, 512, 0, st>>>(
                 (const T*)w.qh, (const bf16*)w.ql, w.qsc, w.eb, (const T*)Cm, w.rinv,
                 (const T*)w.kmem, (const T*)w.klo, lse, (const T*)dy, w.gp, w.gd, w.lsep, w.rdy,
-                use_ql, s.L, Ls, s.H, s.G, s.S, Mp, hpb, tb0, (int)tnblk, BHC);
+                s.L, Ls, s.H, s.G, s.S, Mp, hpb, tb0, (int)tnblk, BHC);
+        };
+        auto scores = [&](auto rt) {
+            if (a.qw) scores_of(rt, std::true_type()); else scores_of(rt, std::false_type());
         };
         auto tokens = [&](auto rt) {
             k_bwd_tokens<T, N, decltype(rt)::value><<<tgrid, 512, 0, st>>>(
