@@ -33,13 +33,15 @@
  *    calling thread.  Numeric contracts (dt > 0, A < 0) are the caller's.
  *  - Supported shapes: P = 64; N in {16, 32, 64, 128}; 1 <= S <= 4096; any
  *    L >= 1 (a partial last chunk is allowed); any B, H <= 65535 with
- *    H % G == 0.  N in {32, 64, 128} with S in {64, 128, 256} run the tuned
- *    MFMA kernels; every other shape runs generic fp32 kernels (the paper
- *    trains at S = 16, N in {16, 64} and evaluates at S = 32 and 64).
+ *    H % G == 0.  bf16 storage with N in {32, 64, 128} and S in {64, 128, 256}
+ *    runs the bf16 matrix kernels; fp32 storage and every other shape run
+ *    kernels on the fp32 matrix instructions (the SMA forward of bf16 storage
+ *    at N >= 32 on the bf16 ones with exact or split operands).  The paper
+ *    trains at S = 16, N in {16, 64} and evaluates at S = 32 and 64.
  *  - Tuning variables (results do not depend on them beyond floating-point
  *    summation order): DART_SMA_HEADS_PER_BLOCK in {1, 2, 4, 8} forces the
- *    number of heads one SMA workgroup serves (forward and backward; used
- *    when it divides H/G; read at every call, so it must not change between
+ *    number of heads one SMA workgroup of the bf16 matrix kernels serves
+ *    (forward and backward; used when it divides H/G; read at every call, so it must not change between
  *    a workspace query and the call it sizes); DART_DECODE_MPS in
  *    {8, 16, 32, 64, 128} forces the memories per decode split (read once).
  *    Unset, both are chosen per shape.
@@ -122,9 +124,9 @@ dart_status dart_ssd_chunk_scan(const dart_dims* dims, const void* x, const floa
                                 void* y_ssd, void* mem, float* h_last, void* workspace,
                                 size_t workspace_bytes, void* stream);
 
-/* Bytes of workspace dart_ssd_bwd needs for `dims`: a forward scan's own
- * workspace and outputs, plus chunk adjoints, per-token decay pieces and
- * per-head-block dB / dC partials (all float). */
+/* Bytes of workspace dart_ssd_bwd needs for `dims`: state contributions, entry
+ * states and adjoints of every chunk (bf16 matrix kernels) or piece of at most
+ * 64 tokens (float), and partial sums of dB, dC, dA and the decay terms. */
 size_t dart_ssd_bwd_workspace_bytes(const dart_dims* dims);
 
 /*
@@ -132,9 +134,9 @@ size_t dart_ssd_bwd_workspace_bytes(const dart_dims* dims);
  * memories): the gradients of
  *     sum dy . y_ssd + sum_c <dmem_c, dH_[c]> + <dh_last, H_{L-1}>
  * with respect to x, dt, A, Bm, Cm and h0, for the same inputs the forward
- * took.  The forward is recomputed inside (its chunk-entry states seed the
- * token sweeps), so nothing of a previous forward call is needed.  The
- * decay gradient is formed by the exact reverse-cumulative-sum identity
+ * took.  The forward's states are recomputed inside, so nothing of a previous
+ * forward call is needed.  The decay gradient, from parts local to a chunk or
+ * piece, equals the reverse cumulative sum
  *     d loss / d log a_t = sum_{s >= t} (y_s . dy_s - dx_s . x_s)
  *                          + <dh_last, H_{L-1}> + sum_{c' >= c(t)} <dmem_c', dH_[c']>,
  * then ddt_t = dx_t . x_t / dt_t + A_h (that), dA_h = sum_{b,t} dt_t (that).
@@ -158,9 +160,10 @@ dart_status dart_ssd_bwd(const dart_dims* dims, const void* x, const float* dt, 
                          float* dB, float* dC, float* dh0, void* workspace, size_t workspace_bytes,
                          void* stream);
 
-/* Bytes of workspace dart_sma_fwd needs for `dims`: the key side
- * r_j (.) dH_j of memories 0..M-2 in the cache layout (storage dtype); 0 when
- * M = 1 (workspace may then be NULL). */
+/* Bytes of workspace dart_sma_fwd needs for `dims`: at N in {32, 64, 128} with
+ * S in {64, 128, 256} four bytes per element of memories 0..M-2 (bf16: their
+ * key and value sides; the fp32 kernels leave it untouched); 0 at other shapes
+ * and when M = 1 (workspace may then be NULL). */
 size_t dart_sma_workspace_bytes(const dart_dims* dims);
 
 /*
@@ -194,8 +197,8 @@ dart_status dart_sma_fwd(const dart_dims* dims, const dart_sma_opts* opts, const
                          size_t workspace_bytes, void* stream);
 
 /* Bytes of workspace dart_sma_bwd needs for `dims`: the key side of
- * memories 0..M-2 (as dart_sma_workspace_bytes for fp32), the normalised
- * query and E rows, two floats per (b, head, memory 0..M-2, token), the
+ * memories 0..M-2 (bf16 matrix kernels, hi + lo), the normalised query and E
+ * rows, two floats per (b, head, memory 0..M-2, token), the
  * per-head-block partial token gradients and one float per (b, token, head). */
 size_t dart_sma_bwd_workspace_bytes(const dart_dims* dims);
 

@@ -1,9 +1,9 @@
 // dart_common.hpp -- device helpers shared by the DART HIP kernels (gfx950).
 //
 // Storage types: float (fp32 mode) and __bf16 (bf16 mode).  All arithmetic
-// accumulates in float.  Matrix products use the CDNA4 16x16 MFMA tiles:
-//   bf16: v_mfma_f32_16x16x32_bf16 (one instruction per 32-deep k step)
-//   fp32: v_mfma_f32_16x16x4_f32   (eight instructions per 32-deep k step)
+// accumulates in float.  Matrix products of bf16 operands use the CDNA4 16x16
+// MFMA tiles, v_mfma_f32_16x16x32_bf16 (one instruction per 32-deep k step);
+// the pieces for v_mfma_f32_16x16x4_f32 are in f32_tiles.hpp.
 // Operand convention (a "fragment"): lane l of the wave holds 8 consecutive
 // k-elements of row (A) or column (B) index l%16; k-group l/16 selects which
 // 8 of the 32.  Because A and B use the same per-lane k assignment, any
@@ -21,23 +21,16 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x8 __attribute__((ext_vector_type(8)));
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
 template <typename T> struct FragT;
 template <> struct FragT<bf16> { using type = bf16x8; };
-template <> struct FragT<float> { using type = f32x8; };
 template <typename T> using Frag = typename FragT<T>::type;
 
 __device__ __forceinline__ f32x4 mma16(f32x4 acc, bf16x8 a, bf16x8 b) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
-}
-__device__ __forceinline__ f32x4 mma16(f32x4 acc, f32x8 a, f32x8 b) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[i], acc, 0, 0, 0);
-    return acc;
 }
 
 // ---- conversions --------------------------------------------------------
@@ -52,12 +45,6 @@ template <> __device__ __forceinline__ bf16x8 make_frag<bf16>(const float (&v)[8
     bf16x8 r;
 #pragma unroll
     for (int i = 0; i < 8; ++i) r[i] = (bf16)v[i];
-    return r;
-}
-template <> __device__ __forceinline__ f32x8 make_frag<float>(const float (&v)[8]) {
-    f32x8 r;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) r[i] = v[i];
     return r;
 }
 
@@ -139,17 +126,6 @@ __device__ __forceinline__ void store8_nt(float* p, const float (&v)[8]) {
 }
 // Raw fragment load (no conversion) from 8 consecutive elements.
 __device__ __forceinline__ bf16x8 load_frag(const bf16* p) { return *reinterpret_cast<const bf16x8*>(p); }
-__device__ __forceinline__ f32x8 load_frag(const float* p) {
-    const f32x4 a = *reinterpret_cast<const f32x4*>(p);
-    const f32x4 b = *reinterpret_cast<const f32x4*>(p + 4);
-    f32x8 r;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        r[i] = a[i];
-        r[4 + i] = b[i];
-    }
-    return r;
-}
 // 4-element loads/stores (8 B bf16, 16 B float).
 __device__ __forceinline__ void load4(const bf16* p, float (&v)[4]) {
     const bf16x4 r = *reinterpret_cast<const bf16x4*>(p);
@@ -532,7 +508,7 @@ struct LinearPlan {
 // cbase + j, the 8 values of rows krow0(g) + 0..3 and krow1(g) + 0..3.
 // bf16 uses two ds_read_b64_tr_b16 (within each 16-lane group, lane j points at
 // row r0 + j/4, columns c0 + 4 (j%4); lane i then holds column c0 + i of rows
-// r0..r0+3); fp32 falls back to eight scalar reads.
+// r0..r0+3).
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 template <int RB, class Tl = SwzTile<RB>>
 __device__ __forceinline__ bf16x8 frag_kmajor_bf16(const char* tile, int krow0, int krow1,
@@ -549,26 +525,10 @@ __device__ __forceinline__ bf16x8 frag_kmajor_bf16(const char* tile, int krow0, 
     const bf16x4 b1 = __builtin_bit_cast(bf16x4, v1);
     return bf16x8{b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]};
 }
-template <int RB, class Tl = SwzTile<RB>>
-__device__ __forceinline__ f32x8 frag_kmajor_f32(const char* tile, int krow0, int krow1,
-                                                 int cbase, int lane) {
-    const int col_b = (cbase + (lane & 15)) * 4;
-    f32x8 r;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        r[i] = *reinterpret_cast<const float*>(tile + Tl::off(krow0 + i, col_b));
-        r[4 + i] = *reinterpret_cast<const float*>(tile + Tl::off(krow1 + i, col_b));
-    }
-    return r;
-}
 template <typename T, int RB, class Tl = SwzTile<RB>>
 __device__ __forceinline__ Frag<T> frag_km(const char* tile, int krow0, int krow1, int cbase,
                                            int lane) {
-    if constexpr (sizeof(T) == 2) {
-        return frag_kmajor_bf16<RB, Tl>(tile, krow0, krow1, cbase, lane);
-    } else {
-        return frag_kmajor_f32<RB, Tl>(tile, krow0, krow1, cbase, lane);
-    }
+    return frag_kmajor_bf16<RB, Tl>(tile, krow0, krow1, cbase, lane);
 }
 
 // The two transposing reads of frag_kmajor_bf16 with their per-lane byte
@@ -599,17 +559,10 @@ struct KmOffBf16 {
 };
 
 // Fragment from a row-major swizzled tile (rows = the operand's m or n index,
-// 8 consecutive k per lane): one 16-byte read (two for fp32).
+// 8 consecutive k per lane): one 16-byte read.
 template <typename T, int RB>
 __device__ __forceinline__ Frag<T> frag_rowmajor(const char* tile, int row, int kcol) {
-    using Tl = SwzTile<RB>;
-    if constexpr (sizeof(T) == 2) {
-        return *reinterpret_cast<const bf16x8*>(tile + Tl::off(row, kcol * 2));
-    } else {
-        const f32x4 a = *reinterpret_cast<const f32x4*>(tile + Tl::off(row, kcol * 4));
-        const f32x4 b = *reinterpret_cast<const f32x4*>(tile + Tl::off(row, kcol * 4 + 16));
-        return f32x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-    }
+    return *reinterpret_cast<const Frag<T>*>(tile + SwzTile<RB>::off(row, kcol * 2));
 }
 
 }  // namespace dart
