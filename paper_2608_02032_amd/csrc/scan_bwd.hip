@@ -316,7 +316,10 @@ __global__ __launch_bounds__(256) void k_fs_pass(float* dH, float* dR,
 // ---- per (b, piece, block of heads): the token gradients ----------------------------
 // A wave owns 16 tokens, as columns t of the tiles with s >= t and as rows of
 // dB, dC and dx.
-// 36 + N / 4 KB of LDS, 256 registers: two blocks per CU.  SMALL: S < 64.
+// 256 registers and at most 68 KB of LDS: two blocks per CU.  W and H stand in
+// LDS together up to N = 64, so that one wait covers both (the whole backward at
+// B 64, L 512, H 4, N 64, S 16: 266 us with H staged over W, 259 so); at N = 128
+// the second tile would leave one block per CU.  SMALL: S < 64.
 template <typename T, int N, bool SMALL>
 __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
     const T* __restrict__ x, const float* __restrict__ dt, const float* __restrict__ A,
@@ -327,7 +330,9 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
     int64_t Mcap, int hpb, int nkp, int64_t blocks) {
     constexpr int K = N / 16, NV = K < 4 ? K : 4, NQ = K / NV;
     constexpr int MP = kQ + 4;  // row pitch of the summed M2, in floats
-    __shared__ __attribute__((aligned(16))) char s_xy[2 * kQ * 256], s_w[N * 256];
+    constexpr bool BOTH = N <= 64;  // W and H at once
+    __shared__ __attribute__((aligned(16))) char s_xy[2 * kQ * 256], s_w[(BOTH ? 2 : 1) * N * 256];
+    char* const s_h = s_w + (BOTH ? N * 256 : 0);
     __shared__ __attribute__((aligned(16))) float s_cl[kQ], s_dt[kQ];
     __shared__ f32x4 s_T;
     __shared__ float s_r[4][kQ], s_c[kQ], s_v[kQ], s_d[kQ], s_u[kQ], s_bx[kQ];
@@ -392,6 +397,7 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
         const int64_t st = ((b * pc.nk + k) * H + h) * (int64_t)(N * kP);
         __syncthreads();  // the last head's reads are done
         PieceOff<N>::stage(Ws + st, s_w, tid);
+        if constexpr (BOTH) PieceOff<N>::stage(Hs + st, s_h, tid);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int s = (tid >> 4) + 16 * q, c = tid & 15;
@@ -538,9 +544,11 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
                 }
             }
         }
-        __syncthreads();  // W is read
-        PieceOff<N>::stage(Hs + st, s_w, tid);
-        __syncthreads();
+        if constexpr (!BOTH) {
+            __syncthreads();  // W is read
+            PieceOff<N>::stage(Hs + st, s_h, tid);
+            __syncthreads();
+        }
         if (used) {
             // dC += e^{cs_s} H dy_s, and its dot with C_s
             f32x4 ys[4];
@@ -557,7 +565,7 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
                 for (int q = 0; q < 4; ++q)
 #pragma unroll
                     for (int i = 0; i < NV; ++i) {
-                        const f32x4 a = off.state_n(s_w, qn * NV + i, q);
+                        const f32x4 a = off.state_n(s_h, qn * NV + i, q);
 #pragma unroll
                         for (int s = 0; s < 4; ++s) acc[i] = mfma4(a[s], ys[q][s], acc[i]);
                     }
