@@ -502,8 +502,9 @@ __global__ __launch_bounds__(256) void k_gated_rmsnorm_bwd(
     __shared__ float s_w[3][KEEP * 256];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ngr = D / group;
-    const int64_t rb = blockIdx.x / ngr;
-    const int g0 = (int)(blockIdx.x - rb * ngr) * group;
+    const int64_t blk = flat_block(), rb = blk / ngr;
+    const int g0 = (int)(blk - rb * ngr) * group;
+    if (rb * kNormRows >= rows) return;
     float wacc[KEEP][4], wv[KEEP][4];
 #pragma unroll
     for (int q = 0; q < KEEP; ++q) {
@@ -591,7 +592,7 @@ void run_gated_rmsnorm_bwd(int64_t blocks, const T* y, const T* z, int64_t zstri
                            float eps, const float* dout, float* dy, float* dz, int64_t dzstride,
                            float* part, int64_t rows, int D, int group, hipStream_t st) {
 #define DART_NB(K) \
-    k_gated_rmsnorm_bwd<T, K><<<(unsigned)blocks, 256, 0, st>>>(y, z, zstride, w, eps, dout, dy, dz, dzstride, part, rows, D, group)
+    k_gated_rmsnorm_bwd<T, K><<<flat_grid(blocks), 256, 0, st>>>(y, z, zstride, w, eps, dout, dy, dz, dzstride, part, rows, D, group)
     if (group <= 512) DART_NB(2);
     else if (group <= 1024) DART_NB(4);
     else if (group <= 1536) DART_NB(6);

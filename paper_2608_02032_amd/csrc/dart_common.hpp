@@ -33,6 +33,14 @@ __device__ __forceinline__ f32x4 mma16(f32x4 acc, bf16x8 a, bf16x8 b) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
 }
 
+// A grid of any length along x and y (a launch takes at most 2^32 threads
+// along x), and the block's place in it.
+inline dim3 flat_grid(int64_t blocks) {
+    const int64_t x = blocks < (1 << 23) ? blocks : (1 << 23);
+    return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
+}
+__device__ __forceinline__ int64_t flat_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 // ---- conversions --------------------------------------------------------
 __device__ __forceinline__ float to_f(float v) { return v; }
 __device__ __forceinline__ float to_f(bf16 v) { return (float)v; }

@@ -12,14 +12,6 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
 }
 __device__ __forceinline__ f32x4 lds4(const char* p) { return *reinterpret_cast<const f32x4*>(p); }
 
-// A grid of any length along x and y (a launch takes at most 2^32 threads
-// along x), and the block's place in it.
-inline dim3 flat_grid(int64_t blocks) {
-    const int64_t x = blocks < (1 << 23) ? blocks : (1 << 23);
-    return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
-}
-__device__ __forceinline__ int64_t flat_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
-
 // The scan's pieces of a sequence: at most kQ tokens, nested with the memory
 // chunks (a chunk of S >= kQ tokens is nq pieces, the last one shorter; for
 // S < kQ a piece is Q / S whole chunks).
