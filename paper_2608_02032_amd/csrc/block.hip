@@ -13,7 +13,10 @@ namespace dart {
 namespace {
 
 constexpr int kConvTok = 64;  // tokens per thread of the scalar convolution
-constexpr int kConvTok8 = 32; // tokens per thread of the 8-channel convolution
+constexpr int kConvTok4 = 32; // tokens per thread of the 4-channel convolution
+constexpr int kConvU = 4;     // rows of a batch of its loads and of its backward's
+
+template <typename T> using Vec4 = T __attribute__((ext_vector_type(4)));
 
 // SiLU through the hardware reciprocal (about 1 ulp) instead of an IEEE
 // division: these kernels evaluate it once per element they stream.
@@ -62,61 +65,96 @@ __global__ __launch_bounds__(256) void k_conv1d_silu(const T* __restrict__ in, i
     }
 }
 
-// The same convolution with 8 consecutive channels per thread (16-byte rows
-// of bf16, 32 of fp32): used when C, the row stride and the pointers are
-// multiples of 8 elements.
+// The same convolution with 4 consecutive channels per thread (8-byte rows
+// of bf16, 16 of fp32): used when C, the row stride and the pointers are
+// multiples of 4 elements.  HBM-bound.  A wave's memory operations complete in
+// order, so a load issued behind a store waits for it: the next kConvU rows are
+// requested ahead of the current ones' stores, the rows before the run and the
+// first batch together (32768 tokens of 1792 bf16 channels, 235 MB, before the
+// backward: 57 us with 8 channels per thread, its loads behind the stores and up to three
+// exposed latencies before the first token; 48 us, 4.9 TB/s.  8 channels per
+// thread in this form spill).
 template <typename T>
-__global__ __launch_bounds__(64) void k_conv1d_silu_v8(const T* __restrict__ in, int64_t stride,
+__global__ __launch_bounds__(64) void k_conv1d_silu_v4(const T* __restrict__ in, int64_t stride,
                                                         const float* __restrict__ w,
                                                         const float* __restrict__ bias,
                                                         const float* __restrict__ st_in,
                                                         float* __restrict__ st_out,
                                                         T* __restrict__ out, int64_t L, int C) {
-    const int c0 = (blockIdx.x * 64 + threadIdx.x) * 8;
-    const int64_t t0 = (int64_t)blockIdx.y * kConvTok8;
+    const unsigned c0 = (blockIdx.x * 64 + threadIdx.x) * 4;
+    const int64_t t0 = (int64_t)blockIdx.y * kConvTok4;
     const int64_t b = blockIdx.z;
-    if (c0 >= C) return;
-    float wk[8][4], bc[8];
+    if (c0 >= (unsigned)C) return;
+    const T* src = in + (b * L) * stride;  // (uniform; c0 is the lane's offset)
+    const int64_t t1 = t0 + kConvTok4 < L ? t0 + kConvTok4 : L;
+    T* dst = out + (b * L) * C;
+    // kConvU rows ahead of the stores of the rows before them; past the end the
+    // last row is read and not used
+    auto load = [&](int64_t t, Vec4<T>(&f)[kConvU]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const f32x4 wv = *reinterpret_cast<const f32x4*>(w + (c0 + i) * 4);
+        for (int u = 0; u < kConvU; ++u)
+            f[u] = *reinterpret_cast<const Vec4<T>*>(src + (t + u < t1 ? t + u : t1 - 1) * stride + c0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    Vec4<T> hr[3], f0[kConvU], f1[kConvU];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) wk[i][k] = wv[k];
-        bc[i] = bias ? bias[c0 + i] : 0.f;
+    for (int k = 0; k < 3; ++k)
+        hr[k] = *reinterpret_cast<const Vec4<T>*>(src + (t0 > 0 ? t0 - 3 + k : 0) * stride + c0);
+    int64_t t = t0;
+    load(t, f0);
+    float wk[4][4], bc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load4(w + (c0 + i) * 4, wk[i]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bc[i] = 0.f;
+    if (bias) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bc[i] = bias[c0 + i];
     }
-    const T* src = in + (b * L) * stride + c0;
-    float win[3][8];
+    // the three tokens before the run (the carried state before token 0)
+    float win[3][4];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const int64_t s = t0 - 3 + k;
-        if (s >= 0) {
-            load8(src + s * stride, win[k]);
-        } else {
+    for (int k = 0; k < 3; ++k)
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                win[k][i] = st_in ? st_in[(b * C + c0 + i) * 3 + (3 + s)] : 0.f;
-        }
+        for (int i = 0; i < 4; ++i) win[k][i] = t0 > 0 ? (float)hr[k][i] : 0.f;
+    if (t0 == 0 && st_in) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) win[k][i] = st_in[(b * C + c0 + i) * 3 + k];
     }
-    const int64_t t1 = t0 + kConvTok8 < L ? t0 + kConvTok8 : L;
-    T* dst = out + (b * L) * C + c0;
-#pragma unroll 4
-    for (int64_t t = t0; t < t1; ++t) {
-        float v[8], o[8];
-        load8(src + t * stride, v);
+    auto run = [&](int64_t t, const Vec4<T>(&f)[kConvU], bool all) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float a = bc[i] + wk[i][0] * win[0][i] + wk[i][1] * win[1][i] +
-                            wk[i][2] * win[2][i] + wk[i][3] * v[i];
-            o[i] = silu_rcp(a);
-            win[0][i] = win[1][i];
-            win[1][i] = win[2][i];
-            win[2][i] = v[i];
+        for (int u = 0; u < kConvU; ++u) {
+            if (!all && t + u >= t1) break;
+            float o[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float v = (float)f[u][i];
+                const float a = bc[i] + wk[i][0] * win[0][i] + wk[i][1] * win[1][i] +
+                                wk[i][2] * win[2][i] + wk[i][3] * v;
+                o[i] = silu_rcp(a);
+                win[0][i] = win[1][i];
+                win[1][i] = win[2][i];
+                win[2][i] = v;
+            }
+            store4(dst + (t + u) * C + c0, o);
         }
-        store8(dst + t * C, o);
+    };
+    for (; t + 2 * kConvU <= t1; t += 2 * kConvU) {
+        load(t + kConvU, f1);
+        run(t, f0, true);
+        load(t + 2 * kConvU, f0);
+        run(t + kConvU, f1, true);
+    }
+    if (t < t1) {
+        if (t + kConvU < t1) load(t + kConvU, f1);
+        run(t, f0, false);
+        if (t + kConvU < t1) run(t + kConvU, f1, false);
     }
     if (st_out && t1 == L) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int k = 0; k < 3; ++k) st_out[(b * C + c0 + i) * 3 + k] = win[k][i];
     }
@@ -308,42 +346,28 @@ __global__ __launch_bounds__(256) void k_conv1d_silu_bwd(
 // The same for four consecutive channels per thread (8-byte rows of bf16, 16
 // of fp32, 16-byte gradients): used when the channel count, the row strides
 // and the pointers are multiples of 4 elements.  HBM-bound, every input read
-// once plus three tokens of overlap per run: 587 MB at 32768 tokens of 1792
-// bf16 channels take about 140 us (4.2 TB/s; 154 with one channel per thread and
-// 2-byte loads; runs of 16 tokens 162, of 64 the same).
+// once plus three tokens of overlap per run; loads ahead of the stores as in the
+// forward.  587 MB at 32768 tokens of 1792 bf16 channels: 167 us with the loads
+// behind the stores, 152 so (kernel trace of a layer's calls; one channel per
+// thread and 2-byte loads took a tenth longer than the former, runs of 16 tokens
+// 5 % longer, of 64 the same).  The block of a 130M-parameter model's layer, with
+// the forward above: 465 -> 442 us; 453 with this kernel held to 168
+// registers, 445 with batches of two tokens.
 template <typename T>
 __global__ __launch_bounds__(64) void k_conv1d_silu_bwd_v4(
     const T* __restrict__ in, int64_t stride, const float* __restrict__ w,
     const float* __restrict__ bias, const float* __restrict__ st_in,
     const float* __restrict__ dout, float* __restrict__ din, int64_t dstride,
     float* __restrict__ dst_in, float* __restrict__ part, int64_t L, int C, int nruns) {
-    const int c0 = (blockIdx.x * 64 + threadIdx.x) * 4;
+    const unsigned c0 = (blockIdx.x * 64 + threadIdx.x) * 4;
     const int run = blockIdx.y;
     const int64_t b = blockIdx.z;
-    if (c0 >= C) return;
+    if (c0 >= (unsigned)C) return;
     const int64_t t0 = (int64_t)run * kConvBwdTok;
     const int64_t t1 = t0 + kConvBwdTok < L ? t0 + kConvBwdTok : L;
-    float wk[4][4], bc[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        load4(w + (c0 + i) * 4, wk[i]);
-        bc[i] = bias ? bias[c0 + i] : 0.f;
-    }
-    const T* src = in + (b * L) * stride + c0;
-    const float* dsrc = dout + (b * L) * C + c0;
-    float* dd = din + (b * L) * dstride + c0;
-    float win[3][4];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const int64_t s = t0 - 3 + k;
-        if (s >= 0) {
-            load4(src + s * stride, win[k]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                win[k][i] = st_in ? st_in[(b * C + c0 + i) * 3 + (3 + s)] : 0.f;
-        }
-    }
+    const T* src = in + (b * L) * stride;  // (uniform; c0 is the lane's offset)
+    const float* dsrc = dout + (b * L) * C;
+    float* dd = din + (b * L) * dstride;
     float q[3][4];  // du at t-3, t-2, t-1 (zero before t0)
     float acc[4][5];
 #pragma unroll
@@ -352,48 +376,112 @@ __global__ __launch_bounds__(64) void k_conv1d_silu_bwd_v4(
 #pragma unroll
         for (int k = 0; k < 5; ++k) acc[i][k] = 0.f;
     }
-    // token t (own: t < t1; the three after it complete din of the last own
-    // tokens; beyond L du is zero): du, the weight sums and din of token t - 3
-    auto step = [&](int64_t t, bool own, bool inside) {
-        float v[4] = {0.f, 0.f, 0.f, 0.f}, dv[4] = {0.f, 0.f, 0.f, 0.f}, o[4];
-        if (inside) {
-            load4(src + t * stride, v);
-            load4(dsrc + t * C, dv);
-        }
+    const int64_t n = t1 - t0;
+    struct Rows {
+        Vec4<T> v[kConvU];
+        f32x4 d[kConvU];
+    };
+    // tokens t0 + k .. of `in` and `dout`, ahead of the stores of the tokens
+    // before them; past the sequence's end the last row is read and not used
+    auto load = [&](int64_t k, Rows& f) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float u = bc[i] + wk[i][0] * win[0][i] + wk[i][1] * win[1][i] + wk[i][2] * win[2][i] + wk[i][3] * v[i];
-            const float du = dv[i] * silu_grad_f(u);
-            if (own) {
-                acc[i][0] += du * win[0][i];
-                acc[i][1] += du * win[1][i];
-                acc[i][2] += du * win[2][i];
-                acc[i][3] += du * v[i];
-                acc[i][4] += du;
-            }
-            o[i] = wk[i][3] * q[0][i] + wk[i][2] * q[1][i] + wk[i][1] * q[2][i] + wk[i][0] * du;
-            q[0][i] = q[1][i];
-            q[1][i] = q[2][i];
-            q[2][i] = du;
-            win[0][i] = win[1][i];
-            win[1][i] = win[2][i];
-            win[2][i] = v[i];
+        for (int u = 0; u < kConvU; ++u) {
+            const int64_t t = t0 + k + u < L ? t0 + k + u : L - 1;
+            f.v[u] = *reinterpret_cast<const Vec4<T>*>(src + t * stride + c0);
+            f.d[u] = *reinterpret_cast<const f32x4*>(dsrc + t * C + c0);
         }
-        if (t - 3 >= t0 && t - 3 < t1) store4(dd + (t - 3) * dstride, o);
-        if (dst_in && t0 == 0 && t == 2) {
-            // du of tokens 0, 1 and 2 stand in q
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    Vec4<T> hr[3];
+    Rows f0, f1;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        hr[k] = *reinterpret_cast<const Vec4<T>*>(src + (t0 > 0 ? t0 - 3 + k : 0) * stride + c0);
+    load(0, f0);
+    load(kConvU, f1);
+    float wk[4][4], bc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        load4(w + (c0 + i) * 4, wk[i]);
+        bc[i] = 0.f;
+    }
+    if (bias) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bc[i] = bias[c0 + i];
+    }
+    // the three tokens before the run (the carried state before token 0)
+    float win[3][4];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) win[k][i] = t0 > 0 ? (float)hr[k][i] : 0.f;
+    if (t0 == 0 && st_in) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) win[k][i] = st_in[(b * C + c0 + i) * 3 + k];
+    }
+    // token t (own: t < t1; the three after it complete din of the last own
+    // tokens; beyond L du is zero): du, the weight sums and din of token t - 3.
+    // `all`: tokens of the run that follow its first three.
+    auto step = [&](int64_t k, const Rows& f, bool all) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kConvU; ++u) {
+            const int64_t t = t0 + k + u;
+            const bool own = all || k + u < n, inside = all || t < L;
+            float v[4], dv[4], o[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                float* ds = dst_in + (b * C + c0 + i) * 3;
-                ds[0] = q[0][i] * wk[i][0];
-                ds[1] = q[0][i] * wk[i][1] + q[1][i] * wk[i][0];
-                ds[2] = q[0][i] * wk[i][2] + q[1][i] * wk[i][1] + q[2][i] * wk[i][0];
+                v[i] = inside ? (float)f.v[u][i] : 0.f;
+                dv[i] = inside ? f.d[u][i] : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float uu = bc[i] + wk[i][0] * win[0][i] + wk[i][1] * win[1][i] + wk[i][2] * win[2][i] + wk[i][3] * v[i];
+                const float du = dv[i] * silu_grad_f(uu);
+                if (own) {
+                    acc[i][0] += du * win[0][i];
+                    acc[i][1] += du * win[1][i];
+                    acc[i][2] += du * win[2][i];
+                    acc[i][3] += du * v[i];
+                    acc[i][4] += du;
+                }
+                o[i] = wk[i][3] * q[0][i] + wk[i][2] * q[1][i] + wk[i][1] * q[2][i] + wk[i][0] * du;
+                q[0][i] = q[1][i];
+                q[1][i] = q[2][i];
+                q[2][i] = du;
+                win[0][i] = win[1][i];
+                win[1][i] = win[2][i];
+                win[2][i] = v[i];
+            }
+            if (all || (k + u >= 3 && k + u < n + 3)) store4(dd + (t - 3) * dstride + c0, o);
+            if (!all && dst_in && t == 2) {
+                // du of tokens 0, 1 and 2 stand in q
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float* ds = dst_in + (b * C + c0 + i) * 3;
+                    ds[0] = q[0][i] * wk[i][0];
+                    ds[1] = q[0][i] * wk[i][1] + q[1][i] * wk[i][0];
+                    ds[2] = q[0][i] * wk[i][2] + q[1][i] * wk[i][1] + q[2][i] * wk[i][0];
+                }
             }
         }
     };
-#pragma unroll 4
-    for (int64_t t = t0; t < t1; ++t) step(t, true, true);
-    for (int64_t t = t1; t < t1 + 3; ++t) step(t, false, t < L);
+    step(0, f0, false);
+    int64_t k = kConvU;
+    for (; k + 2 * kConvU <= n; k += 2 * kConvU) {
+        load(k + kConvU, f0);
+        step(k, f1, true);
+        load(k + 2 * kConvU, f1);
+        step(k + kConvU, f0, true);
+    }
+    for (; k < n + 3; k += 2 * kConvU) {
+        load(k + kConvU, f0);
+        step(k, f1, false);
+        if (k + kConvU >= n + 3) break;
+        load(k + 2 * kConvU, f1);
+        step(k + kConvU, f0, false);
+    }
     float* pr = part + ((b * nruns + run) * (int64_t)C + c0) * 5;
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
@@ -608,16 +696,16 @@ hipError_t launch_conv1d_silu(int dtype, int64_t B, int64_t L, int C, int64_t st
     const dim3 grid((unsigned)((C + 255) / 256), (unsigned)((L + kConvTok - 1) / kConvTok),
                     (unsigned)B);
     const size_t es = dtype == 1 ? 2 : 4;
-    if (C % 8 == 0 && stride % 8 == 0 && (uintptr_t)in % (8 * es) == 0 &&
-        (uintptr_t)out % (8 * es) == 0 && (uintptr_t)w % 16 == 0) {
-        const dim3 g8((unsigned)((C / 8 + 63) / 64), (unsigned)((L + kConvTok8 - 1) / kConvTok8),
+    if (C % 4 == 0 && stride % 4 == 0 && (uintptr_t)in % (4 * es) == 0 &&
+        (uintptr_t)out % (4 * es) == 0 && (uintptr_t)w % 16 == 0) {
+        const dim3 g4((unsigned)((C / 4 + 63) / 64), (unsigned)((L + kConvTok4 - 1) / kConvTok4),
                       (unsigned)B);
         prof_begin("k_conv1d_silu", st);
         if (dtype == 1) {
-            k_conv1d_silu_v8<bf16><<<g8, 64, 0, st>>>((const bf16*)in, stride, w, bias, st_in,
+            k_conv1d_silu_v4<bf16><<<g4, 64, 0, st>>>((const bf16*)in, stride, w, bias, st_in,
                                                       st_out, (bf16*)out, L, C);
         } else {
-            k_conv1d_silu_v8<float><<<g8, 64, 0, st>>>((const float*)in, stride, w, bias, st_in,
+            k_conv1d_silu_v4<float><<<g4, 64, 0, st>>>((const float*)in, stride, w, bias, st_in,
                                                        st_out, (float*)out, L, C);
         }
         prof_end(st);

@@ -18,7 +18,7 @@ def announce(msg):
     print("\n[gpu-case] " + msg, flush=True)
 
 
-# C, the row stride and the pointers multiples of 8 take the 8-channel kernel
+# C, the row stride and the pointers multiples of 4 take the 4-channel kernel
 @pytest.mark.parametrize("dtype,B,L,R,C", [("fp32", 2, 150, 40, 33), ("bf16", 3, 64, 300, 290),
                                            ("bf16", 1, 1000, 2304, 2304), ("fp32", 2, 5, 8, 8),
                                            ("bf16", 2, 200, 2400, 2304), ("fp32", 2, 130, 72, 64)])
@@ -37,6 +37,26 @@ def test_conv1d_silu_matches_definition(dtype, B, L, R, C):
     ref, st_ref = oracle.conv1d_silu(x, w, bias, state=st0, channels=C)
     tol = TOL[dtype]
     assert_close_slices(to_np(out), ref, tol, axes_keep=(0, 2), what="conv out")
+    np.testing.assert_array_equal(to_np(st), st_ref)
+
+
+# batches of four tokens in runs of 32 and their remainders, channels in multiples
+# of 4 that are not multiples of 8, strided rows; the sums are of four products
+@pytest.mark.parametrize("dtype,C,pad", [("fp32", 4, 0), ("bf16", 12, 4), ("fp32", 260, 8), ("bf16", 260, 0)])
+@pytest.mark.parametrize("L", [1, 3, 4, 7, 8, 29, 32, 36, 45, 67])
+@pytest.mark.parametrize("with_state", [False, True])
+def test_conv1d_silu_batches_of_tokens(dtype, C, pad, L, with_state):
+    import torch
+    announce("conv1d batches %s L=%d C=%d pad=%d state=%s" % (dtype, L, C, pad, with_state))
+    rng = np.random.default_rng(L * C)
+    x = synth.to_storage(rng.standard_normal((2, L, C + pad)).astype(np.float32), dtype)
+    w = (rng.standard_normal((C, 4)) * 0.5).astype(np.float32)
+    st0 = rng.standard_normal((2, C, 3)).astype(np.float32) if with_state else None
+    out, st = dart.conv1d_silu(to_dev(x, dtype), f32_dev(w), None, state_in=f32_dev(st0) if with_state else None,
+                               state_out=True, channels=C)
+    torch.cuda.synchronize()
+    ref, st_ref = oracle.conv1d_silu(x, w, None, state=st0, channels=C)
+    assert_close_slices(to_np(out), ref, TOL[dtype], axes_keep=(0, 2), what="conv out")
     np.testing.assert_array_equal(to_np(st), st_ref)
 
 
