@@ -698,6 +698,13 @@ __global__ __launch_bounds__(kFT, 2) void k_fbwd_tok(
             }
             const char* tile = s_h[buf];
             const float* r = s_r[buf];
+            // A memory's sums are formed apart and added to the earlier ones' as a
+            // whole: one chain over all memories rounds at every 4 products (B 2,
+            // L 1000, 4 heads, N 16, S 16: dq 1.24e-6 and dC 8.6e-7 from 64 bits,
+            // 1.11e-6 and 7.6e-7 so; a layer's training step takes 0.5 % longer).
+            f32x4 e1[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) e1[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 const f32x4 rk = *reinterpret_cast<const f32x4*>(r + 16 * k + 4 * g);
@@ -706,9 +713,11 @@ __global__ __launch_bounds__(kFT, 2) void k_fbwd_tok(
                     const f32x4 a = lds4(tile + off.p[s] + 4096 * k);
                     const float bq = qv[k][s] * rk[s] * dlv;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) aE[i] = mfma4(a[i], bq, aE[i]);
+                    for (int i = 0; i < 4; ++i) e1[i] = mfma4(a[i], bq, e1[i]);
                 }
             }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) aE[i] += e1[i];
             float eg[4][4], dg[4][4];
 #pragma unroll
             for (int k = 0; k < 4; ++k)
@@ -720,15 +729,18 @@ __global__ __launch_bounds__(kFT, 2) void k_fbwd_tok(
 #pragma unroll
             for (int nt = 0; nt < K; ++nt) {
                 const float rn = r[16 * nt + m];
+                f32x4 c1 = f32x4{0.f, 0.f, 0.f, 0.f}, q1 = c1;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const f32x4 a = lds4(tile + off.n[k] + 4096 * nt);
 #pragma unroll
                     for (int s = 0; s < 4; ++s) {
-                        aC[nt] = mfma4(a[s], dg[k][s], aC[nt]);
-                        aQ[nt] = mfma4(a[s] * rn, eg[k][s], aQ[nt]);
+                        c1 = mfma4(a[s], dg[k][s], c1);
+                        q1 = mfma4(a[s] * rn, eg[k][s], q1);
                     }
                 }
+                aC[nt] += c1;
+                aQ[nt] += q1;
             }
         }
         if (j + 1 < jb) st.store(s_h[buf ^ 1], s_r[buf ^ 1], eps, normalize, tid);
