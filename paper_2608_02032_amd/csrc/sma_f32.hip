@@ -370,17 +370,20 @@ __global__ __launch_bounds__(kFT, 2) void k_fsma_split(
 
 // ---- forward, bf16 storage ------------------------------------------------------------
 // The same with the products on the bf16 matrix instructions, eight times the
-// fp32 ones' rate, at the precision of the kernel above: a stored memory and C
-// are bf16 as they stand, so V = dH^T C^T is exact in its operands, and the
-// logit contracts over p first, W = dH Ebar^T with Ebar as hi + lo bf16 (16
-// bits), then l = sum_n Qbar_n r_n W_n in float.  (The other order would round
-// r . dH or Qbar.)  Rows of 128 bytes in LDS, 16-byte chunks swizzled by row.
-// Eight waves: four take the even memories of the block's 64 tokens, four the
-// odd ones, and their softmax states merge at the end, so that the heaviest
-// blocks of a small problem are half as long (B 2, L 2048, 8 heads, N 128,
-// S 32: 466 us with the fp32 instructions, 141 with four waves, 84 here; at 32
-// heads 332).  Bound by the vector work beside the 48 MFMAs per 16 tokens and
-// memory (two operations per W element, and the staging).
+// fp32 ones' rate, and nothing rounded on the way: a stored memory and C are
+// bf16 as they stand, so V = dH^T C^T is exact in its operands, and the logit
+// contracts over p first, W = dH Ebar^T with Ebar as three bf16 (8 bits each,
+// all 24 of the float), then l = sum_n Qbar_n r_n W_n in float.  (The other order
+// would need that split of r . dH or Qbar.)  Rows of 128 bytes in LDS, 16-byte
+// chunks swizzled by row.  Eight waves: four take the even memories of the
+// block's 64 tokens, four the odd ones, and their softmax states merge at the
+// end, so that the heaviest blocks of a small problem are half as long.
+// Bound by the 64 MFMAs per 16 tokens and memory and the vector work beside them
+// (two operations per W element, and the staging), two waves a SIMD at N = 128.
+// B 2, L 2048, 8 heads, N 128, S 32: 85 us (the VALU kernel before the matrix
+// ones 5394, the fp32 instructions 466); 72 with Ebar cut to two bf16 and the
+// hardware's approximate 1/sqrt, which put the logits 1.9e-5 from 64 bits instead
+// of 1.0e-6 (the VALU kernel 1.4e-6).
 template <int N>
 struct MemStage16 {
     static constexpr int K = N / 32;  // 16-byte pieces per thread
@@ -391,6 +394,7 @@ struct MemStage16 {
     }
     __device__ __forceinline__ void store(char* tile, float* r, float eps, int normalize, int tid) const {
         const int row = tid >> 3, c = tid & 7;
+        float mine = 0.f;  // lane c of a row's eight finishes the row of piece c
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             *reinterpret_cast<uint4*>(tile + SwzTile<128>::off(row, c * 16) + k * 4096) = v[k];
@@ -402,8 +406,9 @@ struct MemStage16 {
                 ss = __builtin_amdgcn_fdot2_f32_bf16(h, h, ss, false);
             }
             ss = dpp_group_sum<8>(ss);
-            if (c == 0) r[row + 32 * k] = normalize ? __builtin_amdgcn_rsqf(ss * (1.0f / kP) + eps) : 1.0f;
+            mine = c == k ? ss : mine;
         }
+        if (c < K) r[row + 32 * c] = normalize ? 1.0f / sqrtf(mine * (1.0f / kP) + eps) : 1.0f;
     }
 };
 
@@ -441,7 +446,7 @@ __global__ __launch_bounds__(2 * kFT, N < 128 ? 4 : 2) void k_bsma(
     float qv[NT][4];
     load_row<bf16, NT>(q + row * N, g, qv);
     if (normalize) norm_pieces<NT>(qv, qw, 4 * g, 16, eps);
-    bf16x8 eh[2], el[2], cf[KS];
+    bf16x8 eh[2], em[2], el[2], cf[KS];
     {
         // Ebar in operand order: elements 32 ks + 8 g + 0 .. 7
         float ev[4][4];
@@ -459,9 +464,10 @@ __global__ __launch_bounds__(2 * kFT, N < 128 ? 4 : 2) void k_bsma(
             for (int i = 0; i < 4; ++i) {
                 const int p = 32 * (k >> 1) + 8 * g + 4 * (k & 1) + i;
                 const float v = ev[k][i] * (inv * (normalize && ew ? ew[p] : 1.0f));
-                const bf16 hi = (bf16)v;
+                const bf16 hi = (bf16)v, mid = (bf16)(v - (float)hi);
                 eh[k >> 1][4 * (k & 1) + i] = hi;
-                el[k >> 1][4 * (k & 1) + i] = (bf16)(v - (float)hi);
+                em[k >> 1][4 * (k & 1) + i] = mid;
+                el[k >> 1][4 * (k & 1) + i] = (bf16)((v - (float)hi) - (float)mid);
             }
     }
 #pragma unroll
@@ -493,23 +499,16 @@ __global__ __launch_bounds__(2 * kFT, N < 128 ? 4 : 2) void k_bsma(
             float l4[2] = {0.f, 0.f};
 #pragma unroll
             for (int n = 0; n < NT; ++n) {
-                f32x4 w = f32x4{0.f, 0.f, 0.f, 0.f};
+                bf16x8 a[2];
 #pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    const bf16x8 a = *reinterpret_cast<const bf16x8*>(tile + on[k] + 2048 * n);
-                    w = mma16(w, a, eh[k]);
-                    w = mma16(w, a, el[k]);
-                }
+                for (int k = 0; k < 2; ++k) a[k] = *reinterpret_cast<const bf16x8*>(tile + on[k] + 2048 * n);
+                // the small parts first
+                f32x4 w = mma16(mma16(f32x4{0.f, 0.f, 0.f, 0.f}, a[0], el[0]), a[1], el[1]);
+                w = mma16(mma16(w, a[0], em[0]), a[1], em[1]);
+                w = mma16(mma16(w, a[0], eh[0]), a[1], eh[1]);
                 const f32x4 rn = *reinterpret_cast<const f32x4*>(&s_r[buf][odd][16 * n + 4 * g]);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) l4[n & 1] += qv[n][i] * rn[i] * w[i];
-            }
-            f32x4 V[4];
-#pragma unroll
-            for (int pt = 0; pt < 4; ++pt) {
-                V[pt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int k = 0; k < KS; ++k) V[pt] = mma16(V[pt], ot[pt].read(tile, 4096 * k), cf[k]);
             }
             const float l = row4_sum(l4[0] + l4[1]) * sc;
             const bool at = j < jt, grow = at && l > mx;
@@ -523,7 +522,12 @@ __global__ __launch_bounds__(2 * kFT, N < 128 ? 4 : 2) void k_bsma(
             const float pw = at ? fast_exp2(l - mx) : 0.f;
             d += pw;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) O[i] += V[i] * pw;
+            for (int pt = 0; pt < 4; ++pt) {
+                f32x4 V = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int k = 0; k < KS; ++k) V = mma16(V, ot[pt].read(tile, 4096 * k), cf[k]);
+                O[pt] += V * pw;
+            }
         }
         if (j + 2 < jb) st.store(s_h[buf ^ 1][odd], s_r[buf ^ 1][odd], eps, normalize, tid);
     }

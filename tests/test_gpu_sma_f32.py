@@ -9,7 +9,7 @@ import pytest
 
 import oracle
 from paper_2608_02032_amd import synth
-from tests.helpers import TOL, assert_close_slices, assert_lse_close, to_np
+from tests.helpers import TOL, assert_close_slices, assert_lse_close, f32_dev, to_np
 from tests import test_gpu_sma_bwd as MB
 from tests.test_gpu_parity import run_sma, sma_case
 
@@ -70,3 +70,24 @@ def test_forward_split_and_whole(N, dtype, S):
     assert_lse_close(to_np(lse), lse_ref, "fp32")
     assert_lse_close(to_np(lse1), lse_ref[:-1], "fp32")
     assert_close_slices(to_np(y1), to_np(y)[:-1], tol, what="split against whole")
+
+
+@pytest.mark.parametrize("N,S", [(32, 17), (64, 100), (128, 32)])
+def test_bf16_forward_rounds_no_operand(N, S):
+    """bf16 storage outside the bf16 kernels' shapes: the logits carry fp32 roundings only.
+    With one memory attended the log-sum-exp is the logit, whose terms have a
+    root mean square of sqrt(P) = 8 in all; 16 independent roundings of 2^-24 of it
+    are 8 x 4 x 2^-24 = 1.9e-6, and twice that is the bound.  (An Ebar of 16 bits
+    alone gives 8 x 2^-17 / sqrt(6) = 2.5e-5.)"""
+    L = 2 * S
+    w = synth.Workload("round_%d" % N, 3, L, 4, 64, N, S, "bf16", ngroups=2)
+    print("\n[gpu-case] sma logits %s" % (w,), flush=True)
+    d, mem, y_ssd = sma_case(w, seed=N)
+    rng = np.random.default_rng(N)
+    qw, ew = (rng.uniform(0.5, 1.5, n).astype(np.float32) for n in (N, 64))
+    for kw in ({}, dict(q_norm_w=qw, e_norm_w=ew)):
+        _, lse = run_sma(w, d, mem, y_ssd, **{k: f32_dev(v) for k, v in kw.items()})
+        _, ref = oracle.sma(d["q"], d["e"], d["Cm"], mem, d["z"], y_ssd, S, **kw)
+        rms = float(np.sqrt(np.mean((to_np(lse)[:, S:] - ref[:, S:]) ** 2)))
+        print("  rms of the logits' error %.3e" % rms, flush=True)
+        assert rms <= 2 * 8 * 4 * 2.0 ** -24
