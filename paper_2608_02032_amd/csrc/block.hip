@@ -504,7 +504,7 @@ __global__ __launch_bounds__(64 * kSumLanes) void k_sum_parts(const float* __res
                                                               float* __restrict__ out2) {
     __shared__ float s_sum[kSumLanes][64];
     const int col = threadIdx.x & 63, pl = threadIdx.x >> 6;
-    const int64_t i = (int64_t)blockIdx.x * 64 + col;
+    const int64_t i = flat_block() * 64 + col;
     float s = 0.f;
     if (i < width) {
 #pragma unroll 8
@@ -525,7 +525,7 @@ __global__ __launch_bounds__(64 * kSumLanes) void k_sum_parts(const float* __res
         out2[item] = s;
     }
 }
-inline unsigned sum_blocks(int64_t width) { return (unsigned)((width + 63) / 64); }
+inline dim3 sum_grid(int64_t width) { return flat_grid((width + 63) / 64, 64 * kSumLanes); }
 
 // dt = softplus(raw + bias): draw = ddt sigmoid(raw + bias), dbias = sum over
 // rows.  A block serves kDtRows rows of up to 256 heads: its threads tile
@@ -543,7 +543,9 @@ __global__ __launch_bounds__(kDtThreads) void k_dt_softplus_bwd(const T* __restr
                                                          int64_t dstride, float* __restrict__ part,
                                                          int64_t rows, int H) {
     __shared__ float s_acc[kDtThreads];
-    const int h0 = blockIdx.x * 256;
+    const int64_t first = ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * 256;
+    if (first >= H) return;
+    const int h0 = (int)first;
     const int hc = H - h0 < 256 ? H - h0 : 256;  // heads of this block
     const int nrl = kDtThreads / hc;             // rows at a time
     const int rl = threadIdx.x / hc, h = h0 + threadIdx.x % hc;
@@ -680,7 +682,7 @@ void run_gated_rmsnorm_bwd(int64_t blocks, const T* y, const T* z, int64_t zstri
                            float eps, const float* dout, float* dy, float* dz, int64_t dzstride,
                            float* part, int64_t rows, int D, int group, hipStream_t st) {
 #define DART_NB(K) \
-    k_gated_rmsnorm_bwd<T, K><<<flat_grid(blocks), 256, 0, st>>>(y, z, zstride, w, eps, dout, dy, dz, dzstride, part, rows, D, group)
+    k_gated_rmsnorm_bwd<T, K><<<flat_grid(blocks, 256), 256, 0, st>>>(y, z, zstride, w, eps, dout, dy, dz, dzstride, part, rows, D, group)
     if (group <= 512) DART_NB(2);
     else if (group <= 1024) DART_NB(4);
     else if (group <= 1536) DART_NB(6);
@@ -786,7 +788,7 @@ hipError_t launch_conv1d_silu_bwd(int dtype, int64_t B, int64_t L, int C, int64_
     prof_end(st);
     const int64_t width = (int64_t)C * 5;
     prof_begin("k_sum_parts", st);
-    k_sum_parts<<<sum_blocks(width), 64 * kSumLanes, 0, st>>>(part, B * nruns, width, dw, 5, 4, db);
+    k_sum_parts<<<sum_grid(width), 64 * kSumLanes, 0, st>>>(part, B * nruns, width, dw, 5, 4, db);
     prof_end(st);
     return hipGetLastError();
 }
@@ -800,7 +802,7 @@ hipError_t launch_dt_softplus_bwd(int dtype, int64_t rows, int H, const void* ra
                                   int64_t dstride, float* dbias, void* ws, hipStream_t st) {
     const int64_t nrb = (rows + kDtRows - 1) / kDtRows;
     float* part = reinterpret_cast<float*>(ws);
-    const dim3 grid((unsigned)((H + 255) / 256), (unsigned)nrb);
+    const dim3 hg = flat_grid(((int64_t)H + 255) / 256, kDtThreads), grid(hg.x, (unsigned)nrb, hg.y);
     prof_begin("k_dt_softplus_bwd", st);
     if (dtype == 1) {
         k_dt_softplus_bwd<bf16><<<grid, kDtThreads, 0, st>>>((const bf16*)raw, stride, bias, ddt, draw,
@@ -812,7 +814,7 @@ hipError_t launch_dt_softplus_bwd(int dtype, int64_t rows, int H, const void* ra
     prof_end(st);
     if (dbias) {
         prof_begin("k_sum_parts", st);
-        k_sum_parts<<<sum_blocks(H), 64 * kSumLanes, 0, st>>>(part, nrb, H, dbias, 1, 1, nullptr);
+        k_sum_parts<<<sum_grid(H), 64 * kSumLanes, 0, st>>>(part, nrb, H, dbias, 1, 1, nullptr);
         prof_end(st);
     }
     return hipGetLastError();
@@ -840,7 +842,7 @@ hipError_t launch_gated_rmsnorm_bwd(int dtype, int64_t rows, int D, int group, c
     prof_end(st);
     if (dw) {
         prof_begin("k_sum_parts", st);
-        k_sum_parts<<<sum_blocks(D), 64 * kSumLanes, 0, st>>>(part, nrb, D, dw, 1, 1, nullptr);
+        k_sum_parts<<<sum_grid(D), 64 * kSumLanes, 0, st>>>(part, nrb, D, dw, 1, 1, nullptr);
         prof_end(st);
     }
     return hipGetLastError();

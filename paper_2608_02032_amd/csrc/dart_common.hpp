@@ -33,11 +33,11 @@ __device__ __forceinline__ f32x4 mma16(f32x4 acc, bf16x8 a, bf16x8 b) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
 }
 
-// A grid of any length along x and y (a launch takes at most 2^32 threads
-// along x), and the block's place in it.
-inline dim3 flat_grid(int64_t blocks) {
-    const int64_t x = blocks < (1 << 23) ? blocks : (1 << 23);
-    return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
+// A grid of any length along x and y (a launch takes fewer than 2^32 threads
+// along x), and the block's place in it.  Blocks past `blocks` must return.
+inline dim3 flat_grid(int64_t blocks, int threads) {
+    const int64_t cap = 0xFFFFFFFFll / threads, y = (blocks + cap - 1) / cap;
+    return dim3((unsigned)((blocks + y - 1) / y), (unsigned)y);
 }
 __device__ __forceinline__ int64_t flat_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
 

@@ -763,7 +763,7 @@ hipError_t run_sbwd(const Shape& s, const void* x, const float* dt, const float*
     constexpr int NP = N * kP;
     const int64_t units = s.B * pc.nk * s.H;
     prof_begin("k_sbwd_contract", st);
-    k_fs_contract<T, N><<<flat_grid(units), kBT, 0, st>>>((const T*)x, dt, A, (const T*)Bm, (const T*)Cm,
+    k_fs_contract<T, N><<<flat_grid(units, kBT), kBT, 0, st>>>((const T*)x, dt, A, (const T*)Bm, (const T*)Cm,
                                                           (const T*)dy, w.dH, w.dR, w.lda, pc, s.H, s.G, units);
     prof_end(st);
     const dim3 pg((unsigned)((NP + 1023) / 1024), (unsigned)s.H, (unsigned)s.B);
@@ -778,7 +778,7 @@ hipError_t run_sbwd(const Shape& s, const void* x, const float* dt, const float*
     const int64_t blocks = s.B * pc.nk * (s.H / hpb);
     prof_begin("k_sbwd_tokens", st);
     auto tokens = [&](auto small) {
-        k_fs_tokens<T, N, decltype(small)::value><<<flat_grid(blocks), kBT, 0, st>>>(
+        k_fs_tokens<T, N, decltype(small)::value><<<flat_grid(blocks, kBT), kBT, 0, st>>>(
             (const T*)x, dt, A, (const T*)Bm, (const T*)Cm, (const T*)dy, w.dH, w.dR, dmem, w.kpart, dx, ddt,
             w.dBp, w.dCp, w.dAp, pc, s.H, s.G, s.Mcap, hpb, (int)pg.x * (pc.nq > 1 ? 8 : 4), blocks);
     };

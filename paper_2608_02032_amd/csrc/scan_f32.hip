@@ -349,7 +349,7 @@ hipError_t run_fscan(const Shape& s, const void* x, const float* dt, const float
     constexpr int NP = N * kP;
     const int64_t units = s.B * pc.nk * s.H;
     prof_begin("k_chunk_state", st);
-    k_fs_state<T, N><<<flat_grid(units), kFT, 0, st>>>((const T*)x, dt, A, (const T*)Bm, (T*)mem, w.dH,
+    k_fs_state<T, N><<<flat_grid(units, kFT), kFT, 0, st>>>((const T*)x, dt, A, (const T*)Bm, (T*)mem, w.dH,
                                                        w.lda, pc, s.H, s.G, s.Mcap, units);
     prof_end(st);
     prof_begin("k_state_pass", st);
@@ -359,7 +359,7 @@ hipError_t run_fscan(const Shape& s, const void* x, const float* dt, const float
     const int hpb = piece_heads_per_block(s, pc.nk);
     const int64_t blocks = s.B * pc.nk * (s.H / hpb);
     prof_begin("k_chunk_out", st);
-    k_fs_out<T, N><<<flat_grid(blocks), kFT, 0, st>>>((const T*)x, dt, A, (const T*)Bm, (const T*)Cm, w.dH,
+    k_fs_out<T, N><<<flat_grid(blocks, kFT), kFT, 0, st>>>((const T*)x, dt, A, (const T*)Bm, (const T*)Cm, w.dH,
                                                       (T*)y, pc, s.H, s.G, hpb, blocks);
     prof_end(st);
     return hipGetLastError();

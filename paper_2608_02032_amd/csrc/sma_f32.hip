@@ -931,11 +931,10 @@ hipError_t run_fsma(const Shape& s, const SmaArgs& a, const void* q, const void*
                     const void* mem, const void* z, const void* ys, void* y, float* lse, hipStream_t st) {
     const int BH = (int)(s.B * s.H);
     const int nblk = (int)((s.L + kFTok - 1) / kFTok);
-    const dim3 grid = flat_grid((int64_t)BH * nblk);
     prof_begin("k_sma", st);
     // (at N = 16 a bf16 k step of 32 would be half empty)
     if constexpr (sizeof(T) == 2 && N >= 32) {
-        k_bsma<N><<<grid, 2 * kFT, 0, st>>>(
+        k_bsma<N><<<flat_grid((int64_t)BH * nblk, 2 * kFT), 2 * kFT, 0, st>>>(
             (const T*)q, (const T*)e, (const T*)Cm, (const T*)mem, (const T*)z, (const T*)ys, (T*)y, lse,
             a.qw, a.ew, a.eps, a.normalize, a.z_per_head, s.L, s.H, s.G, s.S, s.Mcap, BH, nblk, nblk);
     } else if ((int64_t)BH * nblk <= device_cu_count()) {
@@ -945,11 +944,11 @@ hipError_t run_fsma(const Shape& s, const SmaArgs& a, const void* q, const void*
         // fill the SIMDs and its shared staging wins: L 4096, 8 heads, N 128,
         // S 256 118 against 131; at eight 608 against 896)
         const int n16 = (int)((s.L + 15) / 16);
-        k_fsma_split<T, N><<<flat_grid((int64_t)BH * n16), kFT, 0, st>>>(
+        k_fsma_split<T, N><<<flat_grid((int64_t)BH * n16, kFT), kFT, 0, st>>>(
             (const T*)q, (const T*)e, (const T*)Cm, (const T*)mem, (const T*)z, (const T*)ys, (T*)y, lse,
             a.qw, a.ew, a.eps, a.normalize, a.z_per_head, s.L, s.H, s.G, s.S, s.Mcap, BH, n16);
     } else {
-        k_fsma<T, N><<<grid, kFT, 0, st>>>(
+        k_fsma<T, N><<<flat_grid((int64_t)BH * nblk, kFT), kFT, 0, st>>>(
             (const T*)q, (const T*)e, (const T*)Cm, (const T*)mem, (const T*)z, (const T*)ys, (T*)y, lse,
             a.qw, a.ew, a.eps, a.normalize, a.z_per_head, s.L, s.H, s.G, s.S, s.Mcap, BH, nblk, nblk);
     }
@@ -971,7 +970,7 @@ hipError_t run_fsma_bwd(const Shape& s, const SmaArgs& a, const void* q, const v
         prof_end(st);
         const int64_t nblk = (s.L + kFTok - 1) / kFTok, used = nblk - s.S / kFTok;
         prof_begin("k_bwd_tokens", st);
-        k_fbwd_tok<T, N><<<flat_grid(BH * used), kFT, 0, st>>>(
+        k_fbwd_tok<T, N><<<flat_grid(BH * used, kFT), kFT, 0, st>>>(
             w.qb, w.eb, (const T*)Cm, (const T*)mem, (const T*)z, (const T*)dy, a.eps, a.normalize,
             a.z_per_head, w.gp, w.dl, w.rdy, w.part, s.L, w.Ls, s.H, s.G, s.S, s.Mcap, Mp, BH, (int)nblk, (int)used);
         prof_end(st);
@@ -984,7 +983,7 @@ hipError_t run_fsma_bwd(const Shape& s, const SmaArgs& a, const void* q, const v
     constexpr int JJ = MemSplit<N>::JWMAX * MemSplit<N>::WJ;
     const int64_t full = BH * ((s.Mcap + JJ - 1) / JJ);
     auto mem_side = [&](auto nr, auto jw, int64_t blocks) {
-        k_fbwd_mem<T, N, decltype(nr)::value, decltype(jw)::value><<<flat_grid(blocks), kFT, 0, st>>>(
+        k_fbwd_mem<T, N, decltype(nr)::value, decltype(jw)::value><<<flat_grid(blocks, kFT), kFT, 0, st>>>(
             w.qb, w.eb, (const T*)Cm, (const T*)dy, (const T*)mem, w.gp, w.dl, dmem, a.eps, a.normalize,
             s.L, w.Ls, s.H, s.G, s.S, s.Mcap, Mp, BH);
     };
