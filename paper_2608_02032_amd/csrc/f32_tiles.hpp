@@ -58,7 +58,10 @@ struct PieceDecay {
     __device__ __forceinline__ void load(const float* __restrict__ dt, float Ah, int64_t b, int64_t L, int H,
                                          int h, int64_t t0, int64_t t1, int lane) {
         d = t0 + lane < t1 ? dt[(b * L + t0 + lane) * H + h] : 0.f;
-        cl = d * Ah * kLog2e;
+        // a decay below the float range is zero however far below, and without the
+        // bound an infinite one would make a NaN of every difference over it
+        cl = t0 + lane < t1 ? d * Ah * kLog2e : 0.f;
+        cl = cl < -160.f ? -160.f : cl;
 #pragma unroll
         for (int o = 1; o < 16; o <<= 1) {
             const float u = __shfl_up(cl, o, 64);
@@ -85,6 +88,22 @@ __device__ __forceinline__ float log_to_end(const f32x4& T, int jt, float ct) {
 }
 __device__ __forceinline__ float log_from_start(const f32x4& T, int js, float cs) {
     return tiles_between(T, -1, js) + cs;
+}
+
+// Whether any lane of the wave holds a non-finite value in its accumulators.
+template <int NT>
+__device__ __forceinline__ bool any_nonfinite(const f32x4 (&v)[NT]) {
+    f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[r] = __builtin_fmaf(v[i][r], 0.f, s[r]);
+    const bool bad = (s[0] + s[1]) + (s[2] + s[3]) != 0.f;  // (NaN)
+    return __builtin_expect(__builtin_amdgcn_ballot_w64(bad) != 0, 0);
+}
+__device__ __forceinline__ bool any_nonfinite(const f32x4& v) {
+    const f32x4 a[1] = {v};
+    return any_nonfinite(a);
 }
 
 // Heads per block of the per-piece output kernels: the more, the fewer repeats

@@ -110,12 +110,14 @@ __global__ __launch_bounds__(kFT) void k_fs_state(const T* __restrict__ x, const
 #pragma unroll
             for (int ks = 0; ks < 16; ks += 4) {
                 if (k16 + ks >= hi || k16 + ks + 4 <= lo) continue;
+                // tokens of another memory leave no operand, whatever they hold
                 const int t = k16 + ks + g;
-                const float f = t >= lo && t < hi ? s_f[t] : 0.f;
+                const bool in = t >= lo && t < hi;
+                const float f = s_f[t];
                 float ab[NTW];
 #pragma unroll
-                for (int n = 0; n < NTW; ++n) ab[n] = s_b[t][wn * 16 * NTW + NTW * m + n] * f;
-                const f32x4 vx = *reinterpret_cast<const f32x4*>(&s_x[t][4 * m]);
+                for (int n = 0; n < NTW; ++n) ab[n] = in ? s_b[t][wn * 16 * NTW + NTW * m + n] * f : 0.f;
+                const f32x4 vx = in ? *reinterpret_cast<const f32x4*>(&s_x[t][4 * m]) : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int n = 0; n < NTW; ++n)
 #pragma unroll
@@ -217,7 +219,9 @@ __global__ __launch_bounds__(256) void k_fs_states(float* dH, const float* __res
     if (h_last) store4(h_last + bh * (int64_t)NP + e0, hc);
 }
 
-// A wave owns 16 tokens s, as columns of the tiles with t <= s and of y.
+// A wave owns 16 tokens s, as columns of the tiles with t <= s and of y.  In its
+// own tile a zero factor does not keep the infinity or NaN of a token t > s out
+// of y_s; such a tile is summed token by token instead.
 template <typename T, int N>
 __global__ __launch_bounds__(kFT, 2) void k_fs_out(const T* __restrict__ x, const float* __restrict__ dt,
                                                    const float* __restrict__ A, const T* __restrict__ Bm,
@@ -302,15 +306,38 @@ __global__ __launch_bounds__(kFT, 2) void k_fs_out(const T* __restrict__ x, cons
             if (j <= w && 16 * j < nt) {
                 const f32x4 ct = *reinterpret_cast<const f32x4*>(s_cl + 16 * j + 4 * g);
                 const f32x4 dtt = *reinterpret_cast<const f32x4*>(s_dt + 16 * j + 4 * g);
+                float bq[4];
+                f32x4 yj[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) yj[i] = yi[i];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    float e = fast_exp2(fminf(log_decay(tt, w, cs, j, ct[r]), 0.f)) * dtt[r];
-                    if (j == w && 4 * g + r > m) e = 0.f;
-                    const float bq = e * g1[j][r];
+                    const float e = fast_exp2(fminf(log_decay(tt, w, cs, j, ct[r]), 0.f)) * dtt[r];
+                    bq[r] = j == w && 4 * g + r > m ? 0.f : e * g1[j][r];
                     const f32x4 a = lds4(s_x + j * 4096 + off.op[r]);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) yi[i] = mfma4(a[i], bq, yi[i]);
+                    for (int i = 0; i < 4; ++i) yj[i] = mfma4(a[i], bq[r], yj[i]);
                 }
+                if (j == w && any_nonfinite(yj)) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) yj[i] = yi[i];
+#pragma unroll 1
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int t = 4 * q + r;
+                            const float f = __shfl(bq[r], 16 * q + m, 64);
+#pragma unroll
+                            for (int r2 = 0; r2 < 4; ++r2) {
+                                const f32x4 xv = lds4(s_x + j * 4096 + t * 256 + (((4 * g + r2) ^ t) << 4));
+#pragma unroll
+                                for (int i = 0; i < 4; ++i)
+                                    if (t <= m) yj[i][r2] += f * xv[i];
+                            }
+                        }
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) yi[i] = yj[i];
             }
         }
         if (tl < nt) {
