@@ -441,18 +441,36 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
                     f32x4 m1, ps;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        float e = fast_exp2(fminf(log_decay(tt, j, cs[r], w, ct), 0.f));
-                        if (j == w && 4 * g + r < m) e = 0.f;
-                        m1[r] = e * g1[j][r];
-                        mb[j][r] += dtt * (e * g2[r]);
-                        ps[r] = dpp_group_sum<16>(m1[r] * (g2[r] * dtt));
+                        const float e = fast_exp2(fminf(log_decay(tt, j, cs[r], w, ct), 0.f));
+                        const bool on = j != w || 4 * g + r >= m;  // (selected: 0 times an infinity is not 0)
+                        m1[r] = on ? e * g1[j][r] : 0.f;
+                        mb[j][r] += on ? dtt * (e * g2[r]) : 0.f;
+                        ps[r] = dpp_group_sum<16>(on ? m1[r] * (g2[r] * dtt) : 0.f);
                     }
                     if (m == 0) *reinterpret_cast<f32x4*>(&s_r[w][16 * j + 4 * g]) = ps;
+                    if (j == w && any_nonfinite(g2)) {
+                        // dy_s of the tokens s >= t alone
+#pragma unroll 1
+                        for (int q = 0; q < 4; ++q)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const f32x4 a = lds4(s_y + j * 4096 + off.op[r]);
+                            for (int r = 0; r < 4; ++r) {
+                                const int s = 4 * q + r;
+                                const float f = __shfl(m1[r], 16 * q + m, 64);
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) di[i] = mfma4(a[i], m1[r], di[i]);
+                                for (int r2 = 0; r2 < 4; ++r2) {
+                                    const f32x4 yv = lds4(yr + s * 256 + (((4 * g + r2) ^ s) << 4));
+#pragma unroll
+                                    for (int i = 0; i < 4; ++i)
+                                        if (s >= m) di[i][r2] += f * yv[i];
+                                }
+                            }
+                    } else {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const f32x4 a = lds4(s_y + j * 4096 + off.op[r]);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) di[i] = mfma4(a[i], m1[r], di[i]);
+                        }
                     }
                 }
             }
@@ -469,15 +487,22 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
             // the chunks of the wave's tokens, each dmem_c for its own tokens only
             const int64_t c0 = (t0 + 16 * w) / pc.S;
             const int nc = SMALL && dmem ? (int)((t0 + (16 * w + 15 < nt ? 16 * w + 15 : nt - 1)) / pc.S - c0) + 1 : 0;
-            auto own = [&](int c) {  // e^{cs_ce - cs_t}, zero for the others
+            // whether a token is the chunk's, and then f = e^{cs_ce - cs_t}
+            auto own = [&](int c, float& f) {
                 const int lo = (int)((c0 + c) * pc.S - t0), hi = lo + pc.S < nt ? lo + pc.S : nt;
-                return tl >= lo && tl < hi ? fast_exp2(log_decay(tt, (hi - 1) >> 4, s_cl[hi - 1], w, ct)) : 0.f;
+                const bool in = tl >= lo && tl < hi;
+                f = in ? fast_exp2(log_decay(tt, (hi - 1) >> 4, s_cl[hi - 1], w, ct)) : 0.f;
+                return in;
             };
             auto dmem_of = [&](int c) { return dmem + ((b * Mcap + c0 + c) * H + h) * (int64_t)(N * kP); };
             if constexpr (SMALL) {
                 for (int c = 0; c < nc; ++c) {
-                    const float fd = own(c);
+                    float fd;
+                    const bool in = own(c, fd);
                     const float* dm = dmem_of(c) + 4 * g * kP + 4 * m;
+                    f32x4 b1[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) b1[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int q = 0; q < K; ++q)
 #pragma unroll
@@ -485,8 +510,10 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
                             const f32x4 a = *reinterpret_cast<const f32x4*>(dm + (16 * q + s) * kP);
                             const float bq = bv[q][s] * fd;
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) bd[i] = mfma4(a[i], bq, bd[i]);
+                            for (int i = 0; i < 4; ++i) b1[i] = mfma4(a[i], bq, b1[i]);
                         }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) bd[i] = in ? b1[i] : bd[i];
                 }
             }
             // dx, and x_t . of its three parts
@@ -528,19 +555,23 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
                 }
             if constexpr (SMALL) {
                 for (int c = 0; c < nc; ++c) {
-                    const float fx = dtt * own(c);
+                    float fx;
+                    const bool in = own(c, fx);
                     const float* dm = dmem_of(c) + NV * m * kP + 4 * g;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) xs[q] = xt[q] * fx;
+                    for (int q = 0; q < 4; ++q) xs[q] = xt[q] * (dtt * fx);
 #pragma unroll
-                    for (int tile = 0; tile < K; ++tile)
+                    for (int tile = 0; tile < K; ++tile) {
+                        f32x4 b1 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
                             const f32x4 a = *reinterpret_cast<const f32x4*>(
                                 dm + (16 * NV * (tile / NV) + tile % NV) * kP + 16 * q);
 #pragma unroll
-                            for (int s = 0; s < 4; ++s) aB[tile] = mfma4(a[s], xs[q][s], aB[tile]);
+                            for (int s = 0; s < 4; ++s) b1 = mfma4(a[s], xs[q][s], b1);
                         }
+                        if (in) aB[tile] += b1;
+                    }
                 }
             }
         }
@@ -626,8 +657,35 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
         if (j >= w) *reinterpret_cast<f32x4*>(s_m + tl * MP + 16 * j + 4 * g) = mb[j];
     __syncthreads();
     if (!used) return;
+    // C and B rows of the wave's own tile with an infinity or NaN: each token
+    // takes the rows s >= t (of C) and t <= s (of B) alone
+    bool bad = false;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if (j == w) bad = any_nonfinite(g1[j]);
+    if (bad) {
+#pragma unroll 1
+        for (int s = 0; s < 16 && 16 * w + s < nt; ++s) {
+            const float mc = s_m[tl * MP + 16 * w + s], mt = s_m[(16 * w + s) * MP + tl];
+#pragma unroll
+            for (int qn = 0; qn < NQ; ++qn)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float c4[NV], b4[NV];
+                    const int64_t o = (row(16 * w + s) * G + grp) * N + 16 * NV * qn + NV * (4 * g + r);
+                    vec(Cm + o, c4);
+                    vec(Bm + o, b4);
+#pragma unroll
+                    for (int i = 0; i < NV; ++i) {
+                        if (s >= m) aB[qn * NV + i][r] += mc * c4[i];
+                        if (s <= m) aC[qn * NV + i][r] += mt * b4[i];
+                    }
+                }
+        }
+    }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
+        if (bad && j == w) continue;
         if (j >= w && 16 * j < nt) {
 #pragma unroll
             for (int r = 0; r < 4; ++r)

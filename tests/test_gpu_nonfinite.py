@@ -64,3 +64,52 @@ def test_scan_of_an_infinite_decay():
     assert_close_slices(to_np(y), y_ref, 1e-5, what="y")
     assert_close_slices(to_np(mem), oracle.chunk_memories(d["x"], d["dt"], A, d["Bm"], 16), 1e-5, axes_keep=(0, 1, 2), what="mem")
     assert_close_slices(to_np(hl), hl_ref, 1e-5, axes_keep=(0, 1), what="h_last")
+
+
+def ssd_bwd(d, S, dtype, dy, dmem):
+    import torch
+    x, Bm, Cm, g = (to_dev(v, dtype) for v in (d["x"], d["Bm"], d["Cm"], dy))
+    out = dart.ssd_bwd(x, f32_dev(d["dt"]), f32_dev(d["A"]), Bm, Cm, S, g, dmem=f32_dev(dmem))
+    torch.cuda.synchronize()
+    return {k: to_np(v) for k, v in out.items()}
+
+
+@pytest.mark.parametrize("N,S,dtype", [(16, 16, "fp32"), (64, 6, "fp32"), (32, 17, "bf16"), (128, 32, "fp32"),
+                                       (16, 100, "bf16"), (64, 64, "fp32")])
+@pytest.mark.parametrize("bad", BAD)
+def test_scan_backward_keeps_a_token_to_what_depends_on_it(N, S, dtype, bad):
+    """One entry of batch row 0 is not finite: the gradients that do not depend on it are those
+    without it (dx does not depend on x, dB not on B, dC not on C; through the
+    state, dx and dB of a token depend on dy and C of the tokens from it on, dC on
+    x and B of the tokens up to it; a memory's gradient reaches its own chunk)."""
+    B, L, H, t0 = 2, 90, 4, 37
+    w = synth.Workload("nonfinite_%d_%d" % (N, S), B, L, H, 64, N, S, dtype, ngroups=2)
+    print("\n[gpu-case] scan bwd %s %s" % (bad, w), flush=True)
+    d = synth.forward_inputs(w, seed=N + S)
+    rng = np.random.default_rng(N)
+    dy = synth.to_storage(rng.standard_normal((B, L, H, 64)).astype(np.float32), dtype)
+    dmem = rng.standard_normal((B, -(-L // S), H, N, 64)).astype(np.float32)
+    ref = ssd_bwd(d, S, dtype, dy, dmem)
+    t = np.arange(L)
+    c0, c1 = t0 // S * S, t0 // S * S + S
+    own = (t >= c0) & (t < c1)
+    always, never = t >= 0, t < 0
+    # input, entry, and the tokens whose dx, dB, dC may change
+    for name, at, may in (("x", (0, t0, 1, 7), (never, t == t0, t >= t0)),
+                          ("Bm", (0, t0, 0, 3), (t == t0, never, t >= t0)),
+                          ("Cm", (0, t0, 0, 2), (t <= t0, t <= t0, never)),
+                          ("dy", (0, t0, 1, 7), (t <= t0, t <= t0, t == t0)),
+                          ("dmem", (0, t0 // S, 1, 3, 9), (own, own, never)),
+                          ("x", (0, L - 1, 0, 0), (never, t == L - 1, t == L - 1)),
+                          ("Cm", (0, 70, 0, 1), (t <= 70, t <= 70, never))):
+        e = dict(d, dy=dy, dmem=dmem)
+        e[name] = e[name].copy()
+        e[name][at] = bad
+        got = ssd_bwd(e, S, dtype, e["dy"], e["dmem"])
+        for k, m in zip(("dx", "dB", "dC"), may):
+            np.testing.assert_allclose(got[k][1], ref[k][1], rtol=0, atol=1e-5 * np.abs(ref[k]).max())
+            clean = got[k][0][~m]
+            assert np.isfinite(clean).all(), "%s of other tokens (%s)" % (k, name)
+            # the same sums in another order where the tile is summed token by token
+            np.testing.assert_allclose(clean, ref[k][0][~m], rtol=0, atol=1e-5 * np.abs(ref[k]).max())
+            assert not m.any() or not np.isfinite(got[k][0][m]).all(), "%s (%s)" % (k, name)
