@@ -526,7 +526,7 @@ __global__ __launch_bounds__(2 * kFT, N < 128 ? 4 : 2) void k_bsma(
                 f32x4 V = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int k = 0; k < KS; ++k) V = mma16(V, ot[pt].read(tile, 4096 * k), cf[k]);
-                O[pt] += V * pw;
+                if (at) O[pt] += V * pw;  // (0 times an infinity or NaN of a memory past the token's is not 0)
             }
         }
         if (j + 2 < jb) st.store(s_h[buf ^ 1][odd], s_r[buf ^ 1][odd], eps, normalize, tid);
@@ -720,8 +720,11 @@ __global__ __launch_bounds__(kFT, 2) void k_fbwd_tok(
                     for (int i = 0; i < 4; ++i) e1[i] = mfma4(a[i], bq, e1[i]);
                 }
             }
+            // (a branch: 0 times an infinity or NaN of a memory past the token's is not 0)
+            if (j < jt) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) aE[i] += e1[i];
+                for (int i = 0; i < 4; ++i) aE[i] += e1[i];
+            }
             float eg[4][4], dg[4][4];
 #pragma unroll
             for (int k = 0; k < 4; ++k)
@@ -743,8 +746,10 @@ __global__ __launch_bounds__(kFT, 2) void k_fbwd_tok(
                         q1 = mfma4(a[s] * rn, eg[k][s], q1);
                     }
                 }
-                aC[nt] += c1;
-                aQ[nt] += q1;
+                if (j < jt) {
+                    aC[nt] += c1;
+                    aQ[nt] += q1;
+                }
             }
         }
         if (j + 1 < jb) st.store(s_h[buf ^ 1], s_r[buf ^ 1], eps, normalize, tid);
@@ -859,8 +864,12 @@ __global__ __launch_bounds__(kFT, 2) void k_fbwd_mem(
         load(tbeg);
         store(0);
     }
-    if (j0 < Mp) {
-        for (int64_t t0 = tbeg; t0 < L; t0 += TT, buf ^= 1) {
+    int64_t t0 = tbeg;
+    // Until the last of the block's memories is attended (RAMP), a token's operands
+    // are taken for the memories before its chunk only: a factor of 0 would let
+    // its infinities and NaN through to the others.
+    auto sweep = [&](int64_t end, auto ramp) __attribute__((always_inline)) {
+        for (; t0 < end; t0 += TT, buf ^= 1) {
             __syncthreads();
             const bool more = t0 + TT < L;
             if (more) load(t0 + TT);
@@ -878,17 +887,24 @@ __global__ __launch_bounds__(kFT, 2) void k_fbwd_mem(
 #pragma unroll
                 for (int a = 0; a < JW; ++a) {
                     const float fg = s_f[buf][0][wj * JW + a][t], fd = s_f[buf][1][wj * JW + a][t];
+                    const bool in = !decltype(ramp)::value || t0 + t >= (j0 + wj * JW + a + 1) * S;
 #pragma unroll
-                    for (int n = 0; n < NTW; ++n)
+                    for (int n = 0; n < NTW; ++n) {
+                        const float c1 = in ? ac[n] * fg : 0.f, q1 = in ? aq[n] * fd : 0.f;
 #pragma unroll
                         for (int p = 0; p < 4; ++p) {
-                            m1[a][n][p] = mfma4(ac[n] * fg, vy[p], m1[a][n][p]);
-                            m2[a][n][p] = mfma4(aq[n] * fd, ve[p], m2[a][n][p]);
+                            m1[a][n][p] = mfma4(c1, in ? vy[p] : 0.f, m1[a][n][p]);
+                            m2[a][n][p] = mfma4(q1, in ? ve[p] : 0.f, m2[a][n][p]);
                         }
+                    }
                 }
             }
             if (more) store(buf ^ 1);
         }
+    };
+    if (j0 < Mp) {
+        if constexpr (JJ > 1) sweep((j0 + JJ) * S < L ? (j0 + JJ) * S : L, std::true_type());
+        sweep(L, std::false_type());
     }
     // through r_j: ddH = M1 + r M2 - (r^3 / P) rowsum(dH M2) dH; lane: row
     // NTW (4 g + r) + n of the wave's rows, columns 4 m .. 4 m + 3

@@ -113,3 +113,48 @@ def test_scan_backward_keeps_a_token_to_what_depends_on_it(N, S, dtype, bad):
             # the same sums in another order where the tile is summed token by token
             np.testing.assert_allclose(clean, ref[k][0][~m], rtol=0, atol=1e-5 * np.abs(ref[k]).max())
             assert not m.any() or not np.isfinite(got[k][0][m]).all(), "%s (%s)" % (k, name)
+
+
+@pytest.mark.parametrize("N,S,dtype,B", [(16, 5, "fp32", 1), (64, 17, "fp32", 1), (32, 20, "bf16", 1), (128, 40, "bf16", 1),
+                                         (16, 5, "bf16", 300), (64, 12, "fp32", 90), (128, 12, "fp32", 90)])
+@pytest.mark.parametrize("bad", BAD)
+def test_attention_keeps_a_memory_to_the_tokens_after_it(N, S, dtype, B, bad):
+    """A memory that is not finite reaches the tokens of later chunks only, and a
+    token the gradients of the memories before its chunk only (both forms of the
+    forward and of the memory side: few and many sequences)."""
+    import torch
+    from tests import test_gpu_sma_bwd as MB
+    L, H = 90, 2
+    w = synth.Workload("nonfinite_%d_%d" % (N, S), B, L, H, 64, N, S, dtype)
+    print("\n[gpu-case] attention %s %s" % (bad, w), flush=True)
+    d, mem, y_ssd, dy = MB.bwd_case(w, seed=N)
+    q, e, Cm, z, ys, g = (to_dev(v, dtype) for v in (d["q"], d["e"], d["Cm"], d["z"], y_ssd, dy))
+    t, j0 = np.arange(L), 1
+    chunk = t // S
+
+    def run(mem, g):
+        y, lse = dart.sma_fwd(q, e, Cm, mem, z, ys, S)
+        out = dart.sma_bwd(q, e, Cm, mem, z, lse, g, S)
+        torch.cuda.synchronize()
+        return dict({k: to_np(v) for k, v in out.items()}, y=to_np(y), lse=to_np(lse))
+
+    m0 = to_dev(mem, dtype)
+    ref = run(m0, g)
+    bm = m0.clone()
+    bm[0, j0, 1, 3, 9] = bad
+    got = run(bm, g)
+    for k in ("y", "lse", "dq", "de", "dC", "dz"):
+        np.testing.assert_array_equal(got[k][0][chunk <= j0], ref[k][0][chunk <= j0], err_msg=k)
+        np.testing.assert_array_equal(got[k][1:], ref[k][1:], err_msg=k)
+        assert not np.isfinite(got[k][0][chunk > j0]).all(), k
+    # dy of one token: the memories of its chunk and after do not see it
+    t0 = 2 * S + 1
+    bg = g.clone()
+    bg[0, t0, 1, 5] = bad
+    got = run(m0, bg)
+    np.testing.assert_array_equal(got["dmem"][0, t0 // S:], ref["dmem"][0, t0 // S:])
+    np.testing.assert_array_equal(got["dmem"][1:], ref["dmem"][1:])
+    assert not np.isfinite(got["dmem"][0, :t0 // S]).all()
+    others = t != t0
+    for k in ("dq", "de", "dC", "dz"):
+        np.testing.assert_array_equal(got[k][0][others], ref[k][0][others], err_msg=k)
