@@ -36,6 +36,7 @@
 
 #include <cstdlib>
 #include <mutex>
+#include <type_traits>
 
 #include "dart.h"
 
@@ -280,7 +281,8 @@ __device__ __forceinline__ void norm_q_e(const T* __restrict__ qrow, const T* __
     }
 }
 
-template <typename T, int N>
+// STATE: the blocks past the stream's make the state updates.
+template <typename T, int N, bool STATE>
 __global__ __launch_bounds__(kThreads) void k_decode_partial(
     const T* __restrict__ x, const float* __restrict__ dt, const float* __restrict__ A,
     const T* __restrict__ Bm, float* __restrict__ h_state, float* __restrict__ chunk_acc,
@@ -289,14 +291,14 @@ __global__ __launch_bounds__(kThreads) void k_decode_partial(
     float* __restrict__ part, float eps, int normalize, int H, int G, int S, int64_t Mcap,
     int64_t pos, const int64_t* __restrict__ pos_rows, int64_t pos_lim, int nsplit, int mps, int ns,
     int64_t BH) {
-    const int64_t id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, nstream = BH * ns;
-    if (id >= nstream + BH) return;  // (the grid may end with the stream)
+    const int64_t id = flat_block(), nstream = BH * ns;
+    if (id >= (STATE ? nstream + BH : nstream)) return;  // (past the last block of the grid's last row)
     // A (b, h)'s splits one after the other (1253 us against 1265 with (b, h)
     // fastest at B 64, context 65536), except in a ragged batch: its short rows
     // leave the later splits empty, and with the split index fastest (8 splits, 8
     // XCDs, workgroups dealt in turn) some XCDs would get the empty ones.  The
     // state blocks come last and overlap the stream's end.
-    const bool state = id >= nstream;
+    const bool state = STATE && id >= nstream;
     const int64_t bh = state ? id - nstream : pos_rows ? id % BH : id / ns;
     const int s = (int)(state ? 0 : pos_rows ? id / BH : id % ns);
     const int64_t b = bh / H;
@@ -313,7 +315,7 @@ __global__ __launch_bounds__(kThreads) void k_decode_partial(
     __shared__ float s_q[N];
     __shared__ float s_e[kP];
     __shared__ __attribute__((aligned(16))) float s_part[4][kP + 4];
-    if (state) {
+    if constexpr (STATE) if (state) {
         float(*s_y)[kP] = reinterpret_cast<float(*)[kP]>(&s_part[0][0]);
         state_update<T, N, 4>(x, dt, A, Bm, Cm, h_state, chunk_acc, mem, H, G, S, Mcap, pos, m, b, h, g, s_y);
         __syncthreads();
@@ -547,13 +549,16 @@ hipError_t run_decode(const Shape& s, const SmaArgs& a, int64_t pos, const int64
     // gigabytes they are faster in a kernel of few registers and many waves
     // (context 65536, B 64, 32 heads, 8.6 GB: 1274 against 1260; 3.6 GB the same).
     const bool apart = BH * m * N * kP * (int64_t)sizeof(T) >= (int64_t)4 << 30;
-    const int64_t nb = apart ? BH * ns : BH * (ns + 1), gx = nb < (1 << 23) ? nb : (1 << 23);
-    prof_begin("k_decode_partial", st);
-    k_decode_partial<T, N><<<dim3((unsigned)gx, (unsigned)((nb + gx - 1) / gx)), kThreads, 0, st>>>(
-        (const T*)x, dt, A, (const T*)Bm, h_state, chunk_acc, (T*)mem, yssd, (const T*)q, (const T*)e,
-        (const T*)Cm, a.qw, a.ew, part, a.eps, a.normalize, s.H, s.G, s.S, s.Mcap, pos, pos_rows, pos,
-        nsplit_cap, mps, ns, BH);
-    prof_end(st);
+    auto stream = [&](auto state) {
+        constexpr bool STATE = decltype(state)::value;
+        prof_begin("k_decode_partial", st);
+        k_decode_partial<T, N, STATE><<<flat_grid(BH * (STATE ? ns + 1 : ns), kThreads), kThreads, 0, st>>>(
+            (const T*)x, dt, A, (const T*)Bm, h_state, chunk_acc, (T*)mem, yssd, (const T*)q, (const T*)e,
+            (const T*)Cm, a.qw, a.ew, part, a.eps, a.normalize, s.H, s.G, s.S, s.Mcap, pos, pos_rows, pos,
+            nsplit_cap, mps, ns, BH);
+        prof_end(st);
+    };
+    if (apart) stream(std::false_type()); else stream(std::true_type());
     if (apart) {
         prof_begin("k_decode_state_merge", st);
         k_decode_state_merge<T, N><<<dim3((unsigned)s.H, (unsigned)s.B), kThreads, 0, st>>>(
