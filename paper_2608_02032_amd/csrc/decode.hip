@@ -49,15 +49,18 @@ constexpr int kThreads = 256;
 // at 64 x 32 heads and 256 memories, 128-memory splits beat 32-memory ones by
 // 4 % on a uniform batch and 18 % on a ragged one); the split size is halved
 // (down to 8) while that leaves fewer than 4096 blocks (16 per CU).
-// DART_DECODE_MPS in {8, 16, 32, 64, 128} forces a size (tuning); the workspace is
-// sized for the smallest.
-int decode_mps(int64_t bh, int64_t m) {
+// DART_DECODE_MPS in {8, 16, 32, 64, 128} forces a size, and with it the step in
+// splits (tuning); the workspace is sized for the smallest.
+int forced_mps() {
     static const int forced = [] {
         const char* e = getenv("DART_DECODE_MPS");
         const int x = e ? atoi(e) : 0;
         return (x == 8 || x == 16 || x == 32 || x == 64 || x == 128) ? x : 0;
     }();
-    if (forced) return forced;
+    return forced;
+}
+int decode_mps(int64_t bh, int64_t m) {
+    if (forced_mps()) return forced_mps();
     int mps = 128;
     while (mps > 8 && bh * ((m + mps - 1) / mps) < 4096) mps >>= 1;
     return mps;
@@ -509,7 +512,9 @@ __global__ __launch_bounds__(64 * kOneWaves, 2) void k_decode_one(
 
 // One launch where it is the shorter way: at most two memories per wave (more are
 // better spread over the chip) and no more blocks than compute units.
-inline bool decode_in_one(int64_t bh, int64_t m) { return m <= 2 * kOneWaves && bh <= device_cu_count(); }
+inline bool decode_in_one(int64_t bh, int64_t m) {
+    return !forced_mps() && m <= 2 * kOneWaves && bh <= device_cu_count();
+}
 
 // Number of splits of a step that attends m memories.
 inline int decode_splits(const Shape& s, int64_t m) {

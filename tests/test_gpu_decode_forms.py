@@ -60,3 +60,26 @@ def test_decode_step_forms(c):
         assert_close_slices(to_np(h_t)[s], hr, 1e-5, axes_keep=(0, 1), what="h_state")
         assert_close_slices(to_np(a_t)[s], cr, 1e-5, axes_keep=(0, 1), what="chunk_acc")
         assert_close_slices(to_np(m_t)[s], mr, 2.0 ** -8 if dtype == "bf16" else 1e-5, axes_keep=(0, 1, 2), what="cache")
+
+
+def test_forced_split_size_takes_the_step_in_splits():
+    """DART_DECODE_MPS forces the memories per split also where one launch would do
+    (it is read once, so in a process of its own)."""
+    import os
+    import subprocess
+    import sys
+    code = ("import torch\nfrom paper_2608_02032_amd import dart\n"
+            "f = lambda *s: torch.zeros(*s, device='cuda')\n"
+            "dart.profile_enable(True)\n"
+            "dart.decode_step(100, f(1, 2, 64), f(1, 2) + 0.1, f(2) - 1, f(1, 1, 16), f(1, 1, 16), f(1, 1, 16), f(1, 1, 64),\n"
+            "                 f(1, 2), f(1, 2, 16, 64), f(1, 2, 16, 64), f(1, 9, 2, 16, 64), 12)\n"
+            "torch.cuda.synchronize()\nprint(sorted(dart.profile_read()))\n")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = {}
+    for mps in ("", "8"):
+        r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100, cwd=root,
+                           env=dict(os.environ, DART_DECODE_MPS=mps))
+        assert r.returncode == 0, r.stderr
+        out[mps] = r.stdout
+    assert "k_decode_one" in out[""] and "k_decode_partial" not in out[""]
+    assert "k_decode_partial" in out["8"] and "k_decode_one" not in out["8"]
