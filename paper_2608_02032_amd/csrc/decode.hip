@@ -14,23 +14,25 @@
 //                         reduces the current one (r, the logit and C dH on
 //                         the fly; online softmax (m, d, O[P])).  Waves merge
 //                         in LDS; one partial per split goes to the workspace.
-//                         After these (or, for a long stream, in
-//                         k_decode_state_merge), a block per (head, batch) makes
-//                         the recurrent update of h_state and of the running chunk
-//                         contribution, y_ssd = C h_state, and the append of
-//                         the running contribution when the token closes its
-//                         chunk (slot m, never read by this step).
+//                         After these (or in k_decode_state_merge, state_apart()),
+//                         a block per (head, batch) makes the recurrent update of
+//                         h_state and of the running chunk contribution,
+//                         y_ssd = C h_state, and the append of the running
+//                         contribution when the token closes its chunk (slot m,
+//                         never read by this step).
 //   k_decode_merge        a wave per (head, batch): the deterministic LSE merge
 //                         of the split partials and y = y_ssd + SiLU(z) R.
 //   k_decode_one          both in one launch, a block of eight waves per (head,
-//                         batch), where the context is short and the blocks few.
-// A block's first memory rows are requested before anything else, so that their
-// latency covers the set-up (row norms of q and e, C).  Measured, N 128, S 256,
-// bf16, against the state update in the merging kernel, the first loads after
-// the set-up and the split index fastest: B 16, 24 heads, ragged contexts up to 16384: 72 -> 57 us (state blocks
-// among the streaming ones 59 there, but 1500 against 1270 at B 64, 32 heads,
-// context 65536); B 64, 32 heads, ragged up to 32768: 436 -> 374; B 1, context
-// 4095: 12.1 -> 10.5 (and one launch instead of two).
+//                         batch), where decode_in_one() says so.
+// A block requests q, e and C, then its first memory rows, and forms the row
+// norms while those are on their way (loads return in order: with the rows
+// first, or after the norms, 384 (b, h) of bf16, N 128, one memory take 8.0 us in
+// the streaming kernel, 7.9 so; 2048 (b, h) of fp32, N 16, 64 memories 109 and 107
+// us a step).
+// Measured, N 128, S 256, bf16, ragged contexts, against the state update in the
+// merging kernel, the first loads after the set-up and the split index fastest:
+// B 16, 24 heads, up to 16384: 72 -> 57 us; B 64, 32 heads, up to 32768: 436 ->
+// 374.  B 1, context 4095: 12.1 -> 10.5 (and one launch instead of two).
 #include "dart_common.hpp"
 #include "dart_internal.hpp"
 
@@ -98,21 +100,32 @@ inline size_t decode_part_floats(int64_t B, int H, int nsplit) {
     return (size_t)B * H * nsplit * (kP + 2);
 }
 
-// By a block of 64 WAVES threads; s_y holds a row per wave.
+// By a block of 64 WAVES threads; s_y holds a row per wave.  At N = 128 the rows of B
+// and C come through LDS (s_bc): as elements of each thread's own rows they are
+// 16 loads more in flight per thread, 0.2 us of a 5.5 us step without memories.
+// (With fewer rows the barrier costs as much: 2048 (b, h), N 64, one memory 33.2 us
+// without and 34.5 with it.)
+template <int N> constexpr bool stage_bc() { return N == 128; }
 template <typename T, int N, int WAVES>
 __device__ __forceinline__ void state_update(const T* __restrict__ x, const float* __restrict__ dt,
                                              const float* __restrict__ A, const T* __restrict__ Bm,
                                              const T* __restrict__ Cm, float* __restrict__ h_state,
                                              float* __restrict__ chunk_acc, T* __restrict__ mem,
                                              int H, int G, int S, int64_t Mcap, int64_t pos,
-                                             int64_t m, int64_t b, int h, int g, float (*s_y)[kP]) {
+                                             int64_t m, int64_t b, int h, int g, float (*s_y)[kP],
+                                             float (*s_bc)[stage_bc<N>() ? N : 1]) {
     constexpr int RG = 4 * WAVES, K = (N + RG - 1) / RG;  // row groups, rows per thread
     const int tid = threadIdx.x;
     const int pq = tid & 15, rg = tid >> 4;  // p quad, row group
     const bool reset = (pos % S) == 0;
     const bool append = (pos % S) == S - 1;
     const int64_t sbase = (b * H + h) * (int64_t)N * kP;
-    float hs[K][4], ca[K][4], xv[4], yp[4] = {0.f, 0.f, 0.f, 0.f};
+    float hs[K][4], ca[K][4], xv[4], yp[4] = {0.f, 0.f, 0.f, 0.f}, bt = 0.f, ct = 0.f;
+    if (stage_bc<N>() && tid < N) {
+        bt = to_f(Bm[(b * G + g) * N + tid]);
+        ct = to_f(Cm[(b * G + g) * N + tid]);
+    }
+    if constexpr (stage_bc<N>()) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int n = rg + RG * k;
@@ -126,11 +139,20 @@ __device__ __forceinline__ void state_update(const T* __restrict__ x, const floa
     const float dtv = dt[b * H + h];
     const float a = __expf(dtv * A[h]);
     T* mdst = mem + ((b * Mcap + m) * H + h) * (int64_t)N * kP;
+    if constexpr (stage_bc<N>()) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (tid < N) {
+            s_bc[0][tid] = bt;
+            s_bc[1][tid] = ct;
+        }
+        lds_barrier();  // (the state stays in flight)
+    }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int n = rg + RG * k;
         if (n >= N) continue;
-        const float bn = dtv * to_f(Bm[(b * G + g) * N + n]), cn = to_f(Cm[(b * G + g) * N + n]);
+        const float bn = dtv * (stage_bc<N>() ? s_bc[0][n] : to_f(Bm[(b * G + g) * N + n]));
+        const float cn = stage_bc<N>() ? s_bc[1][n] : to_f(Cm[(b * G + g) * N + n]);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const float u = bn * xv[i];
@@ -258,35 +280,73 @@ struct Attend {
     }
 };
 
-// Qbar log2(e)/sqrt(N) by wave 0, Ebar by wave 1, into LDS.
+// n / d and n % d, in 32 bits where n fits (a division in 64 is some hundred
+// instructions ahead of the block's first load).
+__device__ __forceinline__ void div_mod(int64_t n, int d, int64_t& quot, int& rem) {
+    if (n <= 0xFFFFFFFFll) {
+        const unsigned u = (unsigned)n, k = u / (unsigned)d;
+        quot = k;
+        rem = (int)(u - k * (unsigned)d);
+    } else {
+        quot = n / d;
+        rem = (int)(n - quot * d);
+    }
+}
+// Block id's (b, h) and split, with (b, h) fastest of BH = d, or the split of
+// ns = d.
+__device__ __forceinline__ void split_block(int64_t id, int64_t d, bool bh_fastest, int64_t& bh, int& s) {
+    int64_t k, r;
+    if (id <= 0xFFFFFFFFll) {
+        const unsigned u = (unsigned)id, v = u / (unsigned)d;
+        k = v;
+        r = u - v * (unsigned)d;
+    } else {
+        k = id / d;
+        r = id - k * d;
+    }
+    bh = bh_fastest ? r : k;
+    s = (int)(bh_fastest ? k : r);
+}
+
+// Qbar log2(e)/sqrt(N) by wave 0, Ebar by wave 1, into LDS.  Requested ahead of the
+// memories (loads return in order), so that the norms are formed while those
+// are on their way.
 template <typename T, int N>
-__device__ __forceinline__ void norm_q_e(const T* __restrict__ qrow, const T* __restrict__ erow,
-                                         const float* __restrict__ qw, const float* __restrict__ ew,
-                                         float eps, int normalize, float* s_q, float* s_e) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (wave == 0) {
-        const float v0 = lane < N ? to_f(qrow[lane]) : 0.f;
-        const float v1 = lane + 64 < N ? to_f(qrow[lane + 64]) : 0.f;
+struct NormQE {
+    float v0, v1;
+    __device__ __forceinline__ void request(const T* __restrict__ qrow, const T* __restrict__ erow) {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        v0 = v1 = 0.f;
+        if (wave == 0) {
+            if (lane < N) v0 = to_f(qrow[lane]);
+            if (lane + 64 < N) v1 = to_f(qrow[lane + 64]);
+        } else if (wave == 1) {
+            v0 = to_f(erow[lane]);
+        }
+    }
+    __device__ __forceinline__ void finish(const float* __restrict__ qw, const float* __restrict__ ew, float eps,
+                                           int normalize, float* s_q, float* s_e) const {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        if (wave > 1) return;
         float ss = v0 * v0 + v1 * v1;
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) ss += shfl_xor(ss, o);
-        const float inv = (normalize ? 1.0f / sqrtf(ss * (1.0f / N) + eps) : 1.0f) *
-                          (kLog2e / sqrtf((float)N));
-        if (lane < N) s_q[lane] = v0 * inv * (qw ? qw[lane] : 1.0f);
-        if (lane + 64 < N) s_q[lane + 64] = v1 * inv * (qw ? qw[lane + 64] : 1.0f);
-    } else if (wave == 1) {
-        const float v = to_f(erow[lane]);
-        float ss = v * v;
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) ss += shfl_xor(ss, o);
-        const float inv = normalize ? 1.0f / sqrtf(ss * (1.0f / kP) + eps) : 1.0f;
-        s_e[lane] = v * inv * (ew ? ew[lane] : 1.0f);
+        if (wave == 0) {
+            const float inv = (normalize ? 1.0f / sqrtf(ss * (1.0f / N) + eps) : 1.0f) *
+                              (kLog2e / sqrtf((float)N));
+            if (lane < N) s_q[lane] = v0 * inv * (qw ? qw[lane] : 1.0f);
+            if (lane + 64 < N) s_q[lane + 64] = v1 * inv * (qw ? qw[lane + 64] : 1.0f);
+        } else {
+            const float inv = normalize ? 1.0f / sqrtf(ss * (1.0f / kP) + eps) : 1.0f;
+            s_e[lane] = v0 * inv * (ew ? ew[lane] : 1.0f);
+        }
     }
-}
+};
 
 // STATE: the blocks past the stream's make the state updates.
+// (bf16, N = 64: held to the 128 registers of four waves a SIMD.)
 template <typename T, int N, bool STATE>
-__global__ __launch_bounds__(kThreads) void k_decode_partial(
+__global__ __launch_bounds__(kThreads, (sizeof(T) == 2 && N == 64 ? 4 : 1)) void k_decode_partial(
     const T* __restrict__ x, const float* __restrict__ dt, const float* __restrict__ A,
     const T* __restrict__ Bm, float* __restrict__ h_state, float* __restrict__ chunk_acc,
     T* mem, float* __restrict__ yssd, const T* __restrict__ q, const T* __restrict__ e,
@@ -297,15 +357,18 @@ __global__ __launch_bounds__(kThreads) void k_decode_partial(
     const int64_t id = flat_block(), nstream = BH * ns;
     if (id >= (STATE ? nstream + BH : nstream)) return;  // (past the last block of the grid's last row)
     // A (b, h)'s splits one after the other (1253 us against 1265 with (b, h)
-    // fastest at B 64, context 65536), except in a ragged batch: its short rows
-    // leave the later splits empty, and with the split index fastest (8 splits, 8
-    // XCDs, workgroups dealt in turn) some XCDs would get the empty ones.  The
+    // fastest at B 64, context 65536), except in a ragged batch of a multiple of four
+    // splits: its short rows leave the later splits empty, and with the split index
+    // fastest (8 XCDs, workgroups dealt in turn) some XCDs would get the empty
+    // ones.  (Other counts deal every split over four or eight XCDs either way: 13
+    // splits, 384 (b, h) of fp32, N 64: 127 us, 137 with (b, h) fastest.)  The
     // state blocks come last and overlap the stream's end.
     const bool state = STATE && id >= nstream;
-    const int64_t bh = state ? id - nstream : pos_rows ? id % BH : id / ns;
-    const int s = (int)(state ? 0 : pos_rows ? id / BH : id % ns);
-    const int64_t b = bh / H;
-    const int h = (int)(bh - b * H);
+    int64_t bh = id - nstream, b;
+    int s = 0, h;
+    const bool bh_fastest = pos_rows && ns % 4 == 0;
+    if (!state) split_block(id, bh_fastest ? BH : ns, bh_fastest, bh, s);
+    div_mod(bh, H, b, h);
     const int g = (int)((int64_t)h * G / H);
     if (pos_rows) {
         // ragged batch: this row's own position; rows outside [0, pos_lim]
@@ -320,7 +383,8 @@ __global__ __launch_bounds__(kThreads) void k_decode_partial(
     __shared__ __attribute__((aligned(16))) float s_part[4][kP + 4];
     if constexpr (STATE) if (state) {
         float(*s_y)[kP] = reinterpret_cast<float(*)[kP]>(&s_part[0][0]);
-        state_update<T, N, 4>(x, dt, A, Bm, Cm, h_state, chunk_acc, mem, H, G, S, Mcap, pos, m, b, h, g, s_y);
+        __shared__ float s_bc[2][stage_bc<N>() ? N : 1];
+        state_update<T, N, 4>(x, dt, A, Bm, Cm, h_state, chunk_acc, mem, H, G, S, Mcap, pos, m, b, h, g, s_y, s_bc);
         __syncthreads();
         if (tid < kP) yssd[(b * H + h) * kP + tid] = (s_y[0][tid] + s_y[1][tid]) + (s_y[2][tid] + s_y[3][tid]);
         return;
@@ -339,10 +403,14 @@ __global__ __launch_bounds__(kThreads) void k_decode_partial(
     at.eps = eps;
     at.normalize = normalize;
     typename Attend<T, N>::Rows xa, xb;
+    NormQE<T, N> nq;
+    nq.request(q + (b * G + g) * N, e + (b * G + g) * kP);
+    at.load_c(Cm + (b * G + g) * N);
+    __builtin_amdgcn_sched_barrier(0);
     int64_t j = j0 + wave;
     if (j < j1) at.load(src + j * step, xa);
-    at.load_c(Cm + (b * G + g) * N);
-    norm_q_e<T, N>(q + (b * G + g) * N, e + (b * G + g) * kP, qw, ew, eps, normalize, s_q, s_e);
+    __builtin_amdgcn_sched_barrier(0);
+    nq.finish(qw, ew, eps, normalize, s_q, s_e);
     lds_barrier();  // (the first rows stay in flight)
     at.init(s_q, s_e);
     while (j < j1) {
@@ -378,32 +446,48 @@ __global__ __launch_bounds__(kThreads) void k_decode_partial(
     }
 }
 
-// The LSE merge of a (b, h)'s split partials, the gate and y, by one wave
-// (lane = p); ys: y_ssd of the lane's column.
+// The LSE merge of a (b, h)'s split partials and the gate, by one wave (lane = p),
+// in two steps: `request` loads what the merge begins with (the gate, and the
+// statistics of the split of the lane's number), so that the latency passes
+// behind other work, `finish` merges and writes y (ys: y_ssd of the lane's column).
 template <typename T>
-__device__ __forceinline__ void merge_splits(const T* __restrict__ z, T* __restrict__ y,
-                                             const float* __restrict__ part, float ys, int64_t bh,
-                                             int64_t b, int64_t m, int nsplit, int z_per_head, int mps) {
-    const int p = threadIdx.x & 63;
-    float R = 0.f;
-    if (m > 0) {
-        const int ns = (int)((m + mps - 1) / mps);
-        const float* pb = part + bh * nsplit * (int64_t)(kP + 2);
-        // maximum and sum with a split per lane, O with a column per lane
-        float M = -INFINITY, D = 0.f, O = 0.f;
-        for (int s = p; s < ns; s += 64) M = fmaxf(M, pb[s * (kP + 2) + kP]);
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) M = fmaxf(M, shfl_xor(M, o));
-        for (int s = p; s < ns; s += 64) D += pb[s * (kP + 2) + kP + 1] * fast_exp2(pb[s * (kP + 2) + kP] - M);
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) D += shfl_xor(D, o);
-#pragma unroll 8
-        for (int s = 0; s < ns; ++s) O += pb[s * (kP + 2) + p] * fast_exp2(pb[s * (kP + 2) + kP] - M);
-        R = O / D;
+struct Merge {
+    const float* pb;
+    float zz, m0, d0;
+    int ns;
+    __device__ __forceinline__ void request(const T* __restrict__ z, const float* __restrict__ part, int64_t bh,
+                                            int64_t b, int64_t m, int nsplit, int z_per_head, int mps) {
+        const int p = threadIdx.x & 63;
+        zz = to_f(z_per_head ? z[bh] : z[b]);
+        ns = (int)((m + mps - 1) / mps);
+        pb = part + bh * nsplit * (int64_t)(kP + 2);
+        m0 = -INFINITY;
+        d0 = 0.f;
+        if (p < ns) {
+            m0 = pb[p * (kP + 2) + kP];
+            d0 = pb[p * (kP + 2) + kP + 1];
+        }
     }
-    const float zz = to_f(z_per_head ? z[bh] : z[b]);
-    y[bh * kP + p] = from_f<T>(ys + silu(zz) * R);
-}
+    __device__ __forceinline__ void finish(T* __restrict__ y, float ys, int64_t bh) const {
+        const int p = threadIdx.x & 63;
+        float R = 0.f;
+        if (ns > 0) {
+            // maximum and sum with a split per lane, O with a column per lane
+            float M = m0, D, O = 0.f;
+            for (int s = p + 64; s < ns; s += 64) M = fmaxf(M, pb[s * (kP + 2) + kP]);
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) M = fmaxf(M, shfl_xor(M, o));
+            D = p < ns ? d0 * fast_exp2(m0 - M) : 0.f;
+            for (int s = p + 64; s < ns; s += 64) D += pb[s * (kP + 2) + kP + 1] * fast_exp2(pb[s * (kP + 2) + kP] - M);
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) D += shfl_xor(D, o);
+#pragma unroll 8
+            for (int s = 0; s < ns; ++s) O += pb[s * (kP + 2) + p] * fast_exp2(pb[s * (kP + 2) + kP] - M);
+            R = O / D;
+        }
+        y[bh * kP + p] = from_f<T>(ys + silu(zz) * R);
+    }
+};
 
 // After a stream that made the state updates: one wave per (b, h).
 template <typename T>
@@ -413,16 +497,20 @@ __global__ __launch_bounds__(kThreads) void k_decode_merge(
     int64_t pos_lim, int nsplit, int z_per_head, int mps, int64_t BH) {
     const int64_t bh = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (bh >= BH) return;
-    const int64_t b = bh / H;
+    int64_t b;
+    int h;
+    div_mod(bh, H, b, h);
     if (pos_rows) {
         pos = pos_rows[b];
         if (pos < 0 || pos > pos_lim) return;  // the row takes no part in the step
     }
-    merge_splits(z, y, part, yssd[bh * kP + (threadIdx.x & 63)], bh, b, pos / S, nsplit, z_per_head, mps);
+    Merge<T> mg;
+    mg.request(z, part, bh, b, pos / S, nsplit, z_per_head, mps);
+    mg.finish(y, yssd[bh * kP + (threadIdx.x & 63)], bh);
 }
 
-// After a stream that did not: a block per (b, h) makes the state update, then
-// its first wave merges.
+// After a stream that did not, or without one: a block per (b, h) makes the state
+// update, then its first wave merges.
 template <typename T, int N>
 __global__ __launch_bounds__(kThreads) void k_decode_state_merge(
     const T* __restrict__ x, const float* __restrict__ dt, const float* __restrict__ A,
@@ -437,13 +525,15 @@ __global__ __launch_bounds__(kThreads) void k_decode_state_merge(
         if (pos < 0 || pos > pos_lim) return;
     }
     __shared__ __attribute__((aligned(16))) float s_y[4][kP];
+    __shared__ float s_bc[2][stage_bc<N>() ? N : 1];
     const int tid = threadIdx.x;
+    Merge<T> mg;
+    if (tid < kP) mg.request(z, part, b * H + h, b, pos / S, nsplit, z_per_head, mps);
     state_update<T, N, 4>(x, dt, A, Bm, Cm, h_state, chunk_acc, mem, H, G, S, Mcap, pos, pos / S, b, h,
-                          (int)((int64_t)h * G / H), s_y);
-    __syncthreads();
+                          (int)((int64_t)h * G / H), s_y, s_bc);
+    lds_barrier();
     if (tid >= kP) return;
-    const float ys = (s_y[0][tid] + s_y[1][tid]) + (s_y[2][tid] + s_y[3][tid]);
-    merge_splits(z, y, part, ys, b * H + h, b, pos / S, nsplit, z_per_head, mps);
+    mg.finish(y, (s_y[0][tid] + s_y[1][tid]) + (s_y[2][tid] + s_y[3][tid]), b * H + h);
 }
 
 // The whole step of one (b, h) in one block of eight waves: wave w takes
@@ -470,6 +560,7 @@ __global__ __launch_bounds__(64 * kOneWaves, 2) void k_decode_one(
     __shared__ float s_e[kP];
     __shared__ float s_part[kOneWaves][kP + 2];
     __shared__ __attribute__((aligned(16))) float s_y[kOneWaves][kP];
+    __shared__ float s_bc[2][stage_bc<N>() ? N : 1];
     const T* src = mem + (b * Mcap * H + h) * (int64_t)N * kP;
     const int64_t step = (int64_t)H * N * kP;
     Attend<T, N> at;
@@ -478,10 +569,14 @@ __global__ __launch_bounds__(64 * kOneWaves, 2) void k_decode_one(
     at.eps = eps;
     at.normalize = normalize;
     typename Attend<T, N>::Rows xa;
-    if (wave < m) at.load(src + wave * step, xa);
+    NormQE<T, N> nq;
+    nq.request(q + (b * G + g) * N, e + (b * G + g) * kP);
     at.load_c(Cm + (b * G + g) * N);
-    norm_q_e<T, N>(q + (b * G + g) * N, e + (b * G + g) * kP, qw, ew, eps, normalize, s_q, s_e);
-    state_update<T, N, kOneWaves>(x, dt, A, Bm, Cm, h_state, chunk_acc, mem, H, G, S, Mcap, pos, m, b, h, g, s_y);
+    __builtin_amdgcn_sched_barrier(0);
+    if (wave < m) at.load(src + wave * step, xa);
+    __builtin_amdgcn_sched_barrier(0);
+    nq.finish(qw, ew, eps, normalize, s_q, s_e);
+    state_update<T, N, kOneWaves>(x, dt, A, Bm, Cm, h_state, chunk_acc, mem, H, G, S, Mcap, pos, m, b, h, g, s_y, s_bc);
     lds_barrier();
     at.init(s_q, s_e);
     for (int64_t j = wave; j < m; j += kOneWaves) {
@@ -510,10 +605,34 @@ __global__ __launch_bounds__(64 * kOneWaves, 2) void k_decode_one(
     y[(b * H + h) * kP + tid] = from_f<T>(ys + silu(zz) * R);
 }
 
-// One launch where it is the shorter way: at most two memories per wave (more are
-// better spread over the chip) and no more blocks than compute units.
+// One launch where it is the shorter way: at most two memories per wave (one of
+// fp32 at N = 128, unless the blocks fill the chip) and the blocks resident at
+// once, one per CU at N = 128, two at 64, four at 32, or soon (eight at 16).  bf16,
+// N 128, 16 memories: 256 (b, h) 20.8 us against 23.3 in two launches, 384 33.3
+// against 31.5.  fp32, N 128, 16 memories: 4 (b, h) 21.1 against 13.8.  At fp32,
+// N = 128, the streaming kernel has one wave a SIMD and the one launch is the
+// shorter way for any number of blocks (2048 (b, h): 1 memory 76 us against 84,
+// 16 272 against 297).
+template <typename T, int N>
 inline bool decode_in_one(int64_t bh, int64_t m) {
-    return !forced_mps() && m <= 2 * kOneWaves && bh <= device_cu_count();
+    const int64_t cus = device_cu_count();
+    const bool fills = bh >= cus, wide = sizeof(T) == 4 && N == 128;
+    if (forced_mps() || m < 1 || m > (wide && !fills ? 1 : 2) * kOneWaves) return false;
+    return (wide && fills) || bh <= cus * (N == 128 ? 1 : 128 / N);
+}
+// Otherwise, or without memories: whether the state updates have their own
+// kernel.  In the stream they save a pass over the chip (context 20000, B 8, 24
+// heads: 51.2 us against 52.7), but there they run in blocks of many registers:
+// after a stream of gigabytes (context 65536, B 64, 32 heads, 8.6 GB: 1274 us in
+// the stream, 1260 apart; 3.6 GB the same), where the stream is no longer than
+// the states' own traffic (2048 (b, h), N 128, 1 memory: 63.4 and 60.6; 3: 68.2 and
+// 70.2), and for fp32 at N = 128 with a block per CU or more (768 (b, h), 3
+// memories: 49.7 and 43.5) the kernel of few registers is faster.
+template <typename T, int N>
+inline bool state_apart(int64_t bh, int64_t m) {
+    const int64_t cus = device_cu_count();
+    return m == 0 || bh * m * N * kP * (int64_t)sizeof(T) >= (int64_t)4 << 30 ||
+           (bh > cus && m * (int64_t)sizeof(T) <= 4) || (sizeof(T) == 4 && N == 128 && bh >= cus);
 }
 
 // Number of splits of a step that attends m memories.
@@ -533,7 +652,7 @@ hipError_t run_decode(const Shape& s, const SmaArgs& a, int64_t pos, const int64
                       hipStream_t st) {
     // ragged batches size the grid for the largest position (pos = pos_lim)
     const int64_t m = pos / s.S;
-    if (decode_in_one(s.B * s.H, m)) {
+    if (decode_in_one<T, N>(s.B * s.H, m)) {
         prof_begin("k_decode_one", st);
         k_decode_one<T, N><<<dim3((unsigned)s.H, (unsigned)s.B), 64 * kOneWaves, 0, st>>>(
             (const T*)x, dt, A, (const T*)Bm, h_state, chunk_acc, (T*)mem, (const T*)q, (const T*)e,
@@ -549,11 +668,7 @@ hipError_t run_decode(const Shape& s, const SmaArgs& a, int64_t pos, const int64
     float* yssd = part + decode_part_floats(s.B, s.H, nsplit_cap);
     const int ns = m > 0 ? (int)((m + mps - 1) / mps) : 0;
     const int64_t BH = s.B * s.H;
-    // The state updates join the stream's end and save their own pass over the
-    // chip (context 20000, B 8, 24 heads: 51.2 us against 52.7); after a stream of
-    // gigabytes they are faster in a kernel of few registers and many waves
-    // (context 65536, B 64, 32 heads, 8.6 GB: 1274 against 1260; 3.6 GB the same).
-    const bool apart = BH * m * N * kP * (int64_t)sizeof(T) >= (int64_t)4 << 30;
+    const bool apart = state_apart<T, N>(BH, m);
     auto stream = [&](auto state) {
         constexpr bool STATE = decltype(state)::value;
         prof_begin("k_decode_partial", st);
@@ -563,7 +678,7 @@ hipError_t run_decode(const Shape& s, const SmaArgs& a, int64_t pos, const int64
             nsplit_cap, mps, ns, BH);
         prof_end(st);
     };
-    if (apart) stream(std::false_type()); else stream(std::true_type());
+    if (!apart) stream(std::true_type()); else if (m > 0) stream(std::false_type());
     if (apart) {
         prof_begin("k_decode_state_merge", st);
         k_decode_state_merge<T, N><<<dim3((unsigned)s.H, (unsigned)s.B), kThreads, 0, st>>>(

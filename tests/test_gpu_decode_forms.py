@@ -83,3 +83,61 @@ def test_forced_split_size_takes_the_step_in_splits():
         out[mps] = r.stdout
     assert "k_decode_one" in out[""] and "k_decode_partial" not in out[""]
     assert "k_decode_partial" in out["8"] and "k_decode_one" not in out["8"]
+
+
+@pytest.mark.parametrize("c", [
+    # (b, h) pairs in CUs, N, dtype, memories: either side of each line between the forms
+    (1.0, 128, "bf16", 1), (1.5, 128, "bf16", 1), (1.5, 128, "bf16", 2), (1.5, 128, "bf16", 3), (0.1, 128, "fp32", 8),
+    (0.1, 128, "fp32", 9), (1.0, 128, "fp32", 16), (1.5, 128, "fp32", 17), (2.0, 64, "fp32", 1), (2.1, 64, "fp32", 1),
+    (2.1, 64, "bf16", 3), (4.1, 32, "fp32", 2), (4.0, 32, "bf16", 16), (8.0, 16, "fp32", 16), (8.1, 16, "bf16", 1),
+    (1.5, 64, "bf16", 0)], ids=lambda c: "cus%s_N%d_%s_m%d" % c)
+@pytest.mark.parametrize("ragged", [False, True])
+def test_decode_step_forms_by_blocks(c, ragged):
+    """Every form of the step (one launch; state updates in the stream; in their own kernel),
+    uniform and ragged with rows without memories, closing a chunk and outside the
+    step, against the definition in 64 bits on the device."""
+    import torch
+    import torch.nn.functional as F
+    k, N, dtype, m = c
+    S, H = 4, 8
+    B = int(k * torch.cuda.get_device_properties(0).multi_processor_count) // H
+    print("\n[gpu-case] decode forms %s B %d ragged %s" % (c, B, ragged), flush=True)
+    g = torch.Generator(device="cuda").manual_seed(N + m)
+    st = torch.bfloat16 if dtype == "bf16" else torch.float32
+
+    def r(*s, std=1.0, dt=st):
+        return (torch.randn(s, generator=g, device="cuda") * std).to(dt)
+    x, Bm, Cm, q, e, z = r(B, H, 64), r(B, 2, N, std=N ** -0.5), r(B, 2, N, std=N ** -0.5), r(B, 2, N), r(B, 2, 64), r(B, H)
+    dt, A = torch.rand((B, H), generator=g, device="cuda") * 0.1 + 1e-3, -torch.rand((H,), generator=g, device="cuda") * 8 - 0.5
+    h0, a0 = r(B, H, N, 64, std=0.02, dt=torch.float32), r(B, H, N, 64, std=0.01, dt=torch.float32)
+    mem = r(B, m + 1, H, N, 64, std=0.01)
+    top = m * S + S - 1
+    pos = torch.full((B,), top, device="cuda")
+    if ragged:
+        pos = torch.randint(0, top + 1, (B,), generator=g, device="cuda")
+        pos[0], pos[1], pos[-1] = top, -1, 0
+    h, a, mm = h0.clone(), a0.clone(), mem.clone()
+    y0 = torch.full_like(x, 3.0)
+    args = (x, dt, A, Bm, Cm, q, e, z, h, a, mm, S)
+    y = dart.decode_step_ragged(pos, top, *args, y=y0) if ragged else dart.decode_step(top, *args, y=y0)
+    torch.cuda.synchronize()
+    X, BM, CM, Q, E, Z, DT, AA, H0, A0, MM = (t.double() for t in (x, Bm, Cm, q, e, z, dt, A, h0, a0, mem))
+    hd = lambda t: t.repeat_interleave(H // 2, 1)
+    rms = lambda t: t / torch.sqrt(t.square().mean(-1, keepdim=True) + 1e-6)
+    dec, push = torch.exp(DT * AA)[..., None, None], (DT[..., None] * hd(BM))[..., None] * X[:, :, None]
+    hr = dec * H0 + push
+    ar = torch.where((pos % S == 0)[:, None, None, None], push, dec * A0 + push)
+    yr = (hd(CM)[..., None] * hr).sum(2)
+    lg = ((rms(MM[:, :m]) @ hd(rms(E))[:, None, :, :, None])[..., 0] * hd(rms(Q))[:, None]).sum(-1) / N ** 0.5
+    seen = torch.arange(m, device="cuda")[None] < (pos // S)[:, None]
+    w = torch.softmax(lg.masked_fill(~seen[..., None], -1e30), 1) * seen[..., None] if m else lg
+    yr = yr + F.silu(Z)[..., None] * (w[..., None] * (hd(CM)[:, None, :, :, None] * MM[:, :m]).sum(3)).sum(1)
+    mr, on, b = MM.clone(), pos >= 0, torch.arange(B, device="cuda")
+    close = on & (pos % S == S - 1)
+    mr[b[close], (pos // S)[close]] = ar[close]
+    for got, ref, old, tol in ((h, hr, H0, 1e-5), (a, ar, A0, 1e-5), (y, yr, y0.double(), TOL[dtype]),
+                               (mm, mr, MM, 2.0 ** -8 if dtype == "bf16" else 1e-5)):
+        ref = torch.where(on.view(-1, *([1] * (ref.dim() - 1))), ref, old)
+        err = float((got.double() - ref).abs().max() / ref.abs().max())
+        print("  err %.2e (tol %.0e)" % (err, tol), flush=True)
+        assert err <= tol
