@@ -493,28 +493,34 @@ __global__ __launch_bounds__(64) void k_conv1d_silu_bwd_v4(
 }
 
 // Sum of nparts partial rows of K floats per item: out[i][k] = sum_p part[p][i][k].
-// A block serves 64 columns with 16 waves, each adding every 16th row, and
-// adds the waves' sums in a fixed order.  The kernel is bound by the latency of
-// its loads: one thread per column walking all rows serially took 274 us per
-// call at 1024 rows of 8960 columns (35 blocks), this split 9 us.
-constexpr int kSumLanes = 16;
-__global__ __launch_bounds__(64 * kSumLanes) void k_sum_parts(const float* __restrict__ part,
-                                                              int64_t nparts, int64_t width,
-                                                              float* __restrict__ out, int K, int keep,
-                                                              float* __restrict__ out2) {
-    __shared__ float s_sum[kSumLanes][64];
-    const int col = threadIdx.x & 63, pl = threadIdx.x >> 6;
-    const int64_t i = flat_block() * 64 + col;
+// A block serves COLS columns with LANES waves' worth of threads each, which add
+// every LANES-th row, and adds their sums in a fixed order.  The kernel is bound
+// by the latency of its loads: one thread per column walking all rows serially
+// took 274 us per call at 1024 rows of 8960 columns (35 blocks), 16 lanes 9 us.  One
+// or two rows are added as they are, without the exchange (a norm backward of 8
+// rows of 256 channels 6.4 -> 5.9 us; of four rows, 16 lanes are faster again).
+constexpr int kSumLanes = 16, kSumFew = 2;  // lanes; rows that one lane takes
+template <int LANES, int COLS>
+__global__ __launch_bounds__(LANES * COLS) void k_sum_parts(const float* __restrict__ part,
+                                                            int64_t nparts, int64_t width,
+                                                            float* __restrict__ out, int K, int keep,
+                                                            float* __restrict__ out2) {
+    const int col = threadIdx.x % COLS, pl = threadIdx.x / COLS;
+    const int64_t i = flat_block() * COLS + col;
     float s = 0.f;
     if (i < width) {
 #pragma unroll 8
-        for (int64_t p = pl; p < nparts; p += kSumLanes) s += part[p * width + i];
+        for (int64_t p = pl; p < nparts; p += LANES) s += part[p * width + i];
     }
-    s_sum[pl][col] = s;
-    __syncthreads();
-    if (pl != 0 || i >= width) return;
+    if constexpr (LANES > 1) {
+        __shared__ float s_sum[LANES][COLS];
+        s_sum[pl][col] = s;
+        __syncthreads();
+        if (pl != 0) return;
 #pragma unroll
-    for (int k = 1; k < kSumLanes; ++k) s += s_sum[k][col];
+        for (int k = 1; k < LANES; ++k) s += s_sum[k][col];
+    }
+    if (i >= width) return;
     // items of K values: the first `keep` go to out ([item][keep]), the rest
     // (at most one) to out2 ([item])
     const int64_t item = i / K;
@@ -525,14 +531,24 @@ __global__ __launch_bounds__(64 * kSumLanes) void k_sum_parts(const float* __res
         out2[item] = s;
     }
 }
-inline dim3 sum_grid(int64_t width) { return flat_grid((width + 63) / 64, 64 * kSumLanes); }
+void sum_parts(const float* part, int64_t nparts, int64_t width, float* out, int K, int keep, float* out2,
+               hipStream_t st) {
+    prof_begin("k_sum_parts", st);
+    if (nparts <= kSumFew)
+        k_sum_parts<1, 256><<<flat_grid((width + 255) / 256, 256), 256, 0, st>>>(part, nparts, width, out, K, keep, out2);
+    else
+        k_sum_parts<kSumLanes, 64><<<flat_grid((width + 63) / 64, 64 * kSumLanes), 64 * kSumLanes, 0, st>>>(
+            part, nparts, width, out, K, keep, out2);
+    prof_end(st);
+}
 
 // dt = softplus(raw + bias): draw = ddt sigmoid(raw + bias), dbias = sum over
 // rows.  A block serves kDtRows rows of up to 256 heads: its threads tile
 // (rows at a time) x heads, so that few heads still fill the block, and each
-// head's row sums meet in LDS in a fixed order.  Latency-bound: with one thread
-// per head walking the 256 rows serially, 24 heads and 32768 rows took 118 us
-// (24 of 256 threads active), this tiling 9 us.
+// head's row sums meet in LDS in a fixed order, by halves.  Latency-bound: with one
+// thread per head walking the 256 rows serially, 24 heads and 32768 rows took 118 us
+// (24 of 256 threads active), this tiling 7 us; 4 heads and 4096 rows 46 and
+// 5.2 (7.7 with the sums of the up to 256 row lanes added one by one).
 constexpr int kDtRows = 256;
 constexpr int kDtThreads = 1024;
 template <typename T>
@@ -547,7 +563,7 @@ __global__ __launch_bounds__(kDtThreads) void k_dt_softplus_bwd(const T* __restr
     if (first >= H) return;
     const int h0 = (int)first;
     const int hc = H - h0 < 256 ? H - h0 : 256;  // heads of this block
-    const int nrl = kDtThreads / hc;             // rows at a time
+    const int nrl = (int)blockDim.x / hc;        // rows at a time
     const int rl = threadIdx.x / hc, h = h0 + threadIdx.x % hc;
     const int64_t rb = blockIdx.y;
     const int64_t r0 = rb * kDtRows;
@@ -564,10 +580,13 @@ __global__ __launch_bounds__(kDtThreads) void k_dt_softplus_bwd(const T* __restr
         }
     }
     s_acc[threadIdx.x] = acc;
-    __syncthreads();
-    if ((int)threadIdx.x >= hc) return;
-    for (int k = 1; k < nrl; ++k) acc += s_acc[k * hc + threadIdx.x];
-    part[rb * H + h] = acc;
+    for (int n = r1 - r0 < nrl ? (int)(r1 - r0) : nrl; n > 1;) {
+        const int half = (n + 1) / 2;
+        __syncthreads();
+        if (rl < n - half) s_acc[threadIdx.x] = acc += s_acc[threadIdx.x + half * hc];
+        n = half;
+    }
+    if ((int)threadIdx.x < hc) part[rb * H + h] = acc;
 }
 
 // Gated RMSNorm backward, one block per (kNormRows rows, group), its four
@@ -654,12 +673,15 @@ __global__ __launch_bounds__(256) void k_gated_rmsnorm_bwd(
             }
         }
     }
-    // the waves' weight sums, added in wave order
+    // the waves' weight sums, added in wave order (the first wave's alone of one row)
+    const bool alone = r1 - rb * kNormRows == 1;
+    if (!alone) {
 #pragma unroll
-    for (int q = 0; q < KEEP; ++q) {
-        if (wave > 0) store4(&s_w[wave - 1][lane * 4 + q * 256], wacc[q]);
+        for (int q = 0; q < KEEP; ++q) {
+            if (wave > 0) store4(&s_w[wave - 1][lane * 4 + q * 256], wacc[q]);
+        }
+        __syncthreads();
     }
-    __syncthreads();
     if (wave > 0) return;
 #pragma unroll
     for (int q = 0; q < KEEP; ++q) {
@@ -667,6 +689,7 @@ __global__ __launch_bounds__(256) void k_gated_rmsnorm_bwd(
         if (k < group) {
 #pragma unroll
             for (int v = 0; v < 3; ++v) {
+                if (alone) break;
                 float o[4];
                 load4(&s_w[v][k], o);
 #pragma unroll
@@ -768,9 +791,13 @@ hipError_t launch_conv1d_silu_bwd(int dtype, int64_t B, int64_t L, int C, int64_
     const int nruns = (int)((L + kConvBwdTok - 1) / kConvBwdTok);
     float* part = reinterpret_cast<float*>(ws);
     const size_t es = dtype == 1 ? 2 : 4;
-    const bool v4 = C % 4 == 0 && stride % 4 == 0 && dstride % 4 == 0 && (uintptr_t)in % (4 * es) == 0 &&
+    const bool aligned4 = C % 4 == 0 && stride % 4 == 0 && dstride % 4 == 0 && (uintptr_t)in % (4 * es) == 0 &&
                     ((uintptr_t)w | (uintptr_t)dout | (uintptr_t)din | (uintptr_t)ws) % 16 == 0;
     const dim3 grid((unsigned)((C + 255) / 256), (unsigned)nruns, (unsigned)B);
+    // below a wave of the four-channel form per CU, its fourfold work per thread is the
+    // longer chain (1792 bf16 channels: 256 tokens, 56 waves, 16.6 us against 14.5 with
+    // a channel per thread; 1024 tokens 18.3 and 16.4; 2048, 448 waves, 20.5 and 23.0)
+    const bool v4 = aligned4 && (int64_t)grid.x * nruns * B > device_cu_count();
     prof_begin("k_conv1d_silu_bwd", st);
     if (dtype == 1 && v4) {
         k_conv1d_silu_bwd_v4<bf16><<<grid, 64, 0, st>>>((const bf16*)in, stride, w, bias, st_in, dout,
@@ -787,9 +814,7 @@ hipError_t launch_conv1d_silu_bwd(int dtype, int64_t B, int64_t L, int C, int64_
     }
     prof_end(st);
     const int64_t width = (int64_t)C * 5;
-    prof_begin("k_sum_parts", st);
-    k_sum_parts<<<sum_grid(width), 64 * kSumLanes, 0, st>>>(part, B * nruns, width, dw, 5, 4, db);
-    prof_end(st);
+    sum_parts(part, B * nruns, width, dw, 5, 4, db, st);
     return hipGetLastError();
 }
 
@@ -803,20 +828,19 @@ hipError_t launch_dt_softplus_bwd(int dtype, int64_t rows, int H, const void* ra
     const int64_t nrb = (rows + kDtRows - 1) / kDtRows;
     float* part = reinterpret_cast<float*>(ws);
     const dim3 hg = flat_grid(((int64_t)H + 255) / 256, kDtThreads), grid(hg.x, (unsigned)nrb, hg.y);
+    // no more threads than a block has (row, head) pairs, and at least a row of them
+    const int64_t pairs = (rows < kDtRows ? rows : kDtRows) * (H < 256 ? H : 256);
+    const unsigned threads = pairs < kDtThreads ? (unsigned)(pairs + 63) / 64 * 64 : kDtThreads;
     prof_begin("k_dt_softplus_bwd", st);
     if (dtype == 1) {
-        k_dt_softplus_bwd<bf16><<<grid, kDtThreads, 0, st>>>((const bf16*)raw, stride, bias, ddt, draw,
+        k_dt_softplus_bwd<bf16><<<grid, threads, 0, st>>>((const bf16*)raw, stride, bias, ddt, draw,
                                                       dstride, part, rows, H);
     } else {
-        k_dt_softplus_bwd<float><<<grid, kDtThreads, 0, st>>>((const float*)raw, stride, bias, ddt, draw,
+        k_dt_softplus_bwd<float><<<grid, threads, 0, st>>>((const float*)raw, stride, bias, ddt, draw,
                                                        dstride, part, rows, H);
     }
     prof_end(st);
-    if (dbias) {
-        prof_begin("k_sum_parts", st);
-        k_sum_parts<<<sum_grid(H), 64 * kSumLanes, 0, st>>>(part, nrb, H, dbias, 1, 1, nullptr);
-        prof_end(st);
-    }
+    if (dbias) sum_parts(part, nrb, H, dbias, 1, 1, nullptr, st);
     return hipGetLastError();
 }
 
@@ -840,11 +864,7 @@ hipError_t launch_gated_rmsnorm_bwd(int dtype, int64_t rows, int D, int group, c
                               dy, dz, dzstride, part, rows, D, group, st);
     }
     prof_end(st);
-    if (dw) {
-        prof_begin("k_sum_parts", st);
-        k_sum_parts<<<sum_grid(D), 64 * kSumLanes, 0, st>>>(part, nrb, D, dw, 1, 1, nullptr);
-        prof_end(st);
-    }
+    if (dw) sum_parts(part, nrb, D, dw, 1, 1, nullptr, st);
     return hipGetLastError();
 }
 

@@ -74,3 +74,25 @@ def test_gated_rmsnorm_bwd_register_pieces(dtype, rows, D, group):
     for k in ("dy", "dz"):
         assert_close_slices(to_np(g[k]), ref[k], TOL, axes_keep=(0,), what=k)
     assert_close_slices(to_np(g["dweight"]), ref["dw"], TOL, axes_keep=(), what="dweight")
+
+
+@pytest.mark.parametrize("dtype,B,L,C,pad", [("bf16", 300, 1, 4, 0), ("fp32", 260, 2, 8, 4), ("bf16", 130, 3, 260, 8),
+                                             ("fp32", 260, 32, 64, 0), ("bf16", 130, 33, 252, 4), ("bf16", 27, 130, 512, 12)])
+@pytest.mark.parametrize("with_state", [False, True])
+def test_conv1d_silu_bwd_four_channels_and_many_blocks(dtype, B, L, C, pad, with_state):
+    """The form of four channels per thread runs where its blocks of 64 threads outnumber the compute
+    units (256); with fewer a thread takes one channel."""
+    assert B * -(-L // 32) * -(-C // 256) > 256
+    test_conv1d_silu_bwd_four_channels_per_thread(dtype, B, L, C, pad, with_state)
+
+
+@pytest.mark.parametrize("rows,H", [(1, 4), (3, 4), (65, 4), (256, 1), (1000, 3), (2, 300)])
+def test_dt_softplus_bwd_few_heads_and_rows(rows, H):
+    """Blocks of fewer threads than the most, and halves of odd numbers of row sums."""
+    test_dt_softplus_bwd_row_tiles(rows, H)
+
+
+@pytest.mark.parametrize("rows", [1, 2, 17, 32, 33, 49])
+def test_weight_sums_of_few_and_more_partial_rows(rows):
+    """One block of 16 rows, one row in the last, and one, two, three and four partial rows to add."""
+    test_gated_rmsnorm_bwd_register_pieces("bf16", rows, 264, 264)
