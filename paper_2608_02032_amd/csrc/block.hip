@@ -438,7 +438,9 @@ __global__ __launch_bounds__(64) void k_conv1d_silu_bwd_v4(
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float uu = bc[i] + wk[i][0] * win[0][i] + wk[i][1] * win[1][i] + wk[i][2] * win[2][i] + wk[i][3] * v[i];
-                const float du = dv[i] * silu_grad_f(uu);
+                // (past the end uu may overflow where no token's did, and 0 times the
+                // NaN that makes of it is not 0)
+                const float du = inside ? dv[i] * silu_grad_f(uu) : 0.f;
                 if (own) {
                     acc[i][0] += du * win[0][i];
                     acc[i][1] += du * win[1][i];

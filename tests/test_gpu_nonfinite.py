@@ -158,3 +158,21 @@ def test_attention_keeps_a_memory_to_the_tokens_after_it(N, S, dtype, B, bad):
     others = t != t0
     for k in ("dq", "de", "dC", "dz"):
         np.testing.assert_array_equal(got[k][0][others], ref[k][0][others], err_msg=k)
+
+
+@pytest.mark.parametrize("C", [4, 5])
+def test_convolution_backward_ends_with_the_sequence(C):
+    """Inputs whose products overflow only past the last token, in the forms of four channels per
+    thread (260 blocks) and of one."""
+    import torch
+    B, L = 260, 6
+    print("\n[gpu-case] conv bwd end C %d" % C, flush=True)
+    x = torch.zeros(B, L, C, device="cuda")
+    x[:, -1] = 3e38
+    w = torch.tensor([1.0, 1.0, 4.0, 0.1], device="cuda").repeat(C, 1)
+    g = dart.conv1d_silu_bwd(x, w, torch.ones(B, L, C, device="cuda"), bias=torch.zeros(C, device="cuda"))
+    torch.cuda.synchronize()
+    # SiLU'(0) = 1/2 for the tokens before the last, SiLU'(3e37) = 1 for it
+    du = torch.tensor([0.5] * 5 + [1.0, 0, 0, 0], device="cuda")
+    ref = w[0, 3] * du[:6] + w[0, 2] * du[1:7] + w[0, 1] * du[2:8] + w[0, 0] * du[3:]
+    torch.testing.assert_close(g["din"], ref[None, :, None].expand(B, L, C), rtol=1e-6, atol=0)
