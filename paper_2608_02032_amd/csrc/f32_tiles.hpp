@@ -46,29 +46,49 @@ __device__ __forceinline__ void piece_range(const Pieces& p, int64_t k, int64_t&
     }
 }
 
+// v of the lane N to the left in the row of 16 lanes, zero in its first N lanes.
+template <int N>
+__device__ __forceinline__ double row_shr(double v) {
+    const int2 u = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_update_dpp(0, u.x, 0x110 + N, 0xF, 0xF, true),
+                                                __builtin_amdgcn_update_dpp(0, u.y, 0x110 + N, 0xF, 0xF, true)));
+}
+__device__ __forceinline__ double read_lane(double v, int lane) {
+    const int2 u = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(u.x, lane), __builtin_amdgcn_readlane(u.y, lane)));
+}
+
 // The decays of one piece, lane = token: dt (0 past the piece's end), the
-// inclusive cumulative log decay cl inside its 16-token tile (log2 units) and
-// the four tiles' totals T.  The decay between two tokens is then the
-// difference of two small numbers inside a tile, and a sum of non-positive
-// terms across tiles: cumulative sums over longer ranges would lose their last
-// bits in the difference.
+// inclusive cumulative log decay cl + lo inside its 16-token tile (log2 units), te
+// the log decay from the token to its tile's end, and the four tiles' totals T.
+// Formed in 64 bits: the decay between two tokens of a tile is the difference of
+// two sums that may be far larger, and in 32 bits it keeps the rounding of those
+// (dt A = -1.6 a token: 1e-6 of a decay that its own rounding puts at 1e-7);
+// across tiles it is a sum of non-positive terms.
 struct PieceDecay {
-    float d, cl;
+    float d, cl, lo, te;
     f32x4 T;
     __device__ __forceinline__ void load(const float* __restrict__ dt, float Ah, int64_t b, int64_t L, int H,
                                          int h, int64_t t0, int64_t t1, int lane) {
         d = t0 + lane < t1 ? dt[(b * L + t0 + lane) * H + h] : 0.f;
         // a decay below the float range is zero however far below, and without the
         // bound an infinite one would make a NaN of every difference over it
-        cl = t0 + lane < t1 ? d * Ah * kLog2e : 0.f;
-        cl = cl < -160.f ? -160.f : cl;
+        double c = t0 + lane < t1 ? (double)d * (double)Ah * 1.4426950408889634 : 0.0;
+        c = c < -160.0 ? -160.0 : c;
+        c += row_shr<1>(c);
+        c += row_shr<2>(c);
+        c += row_shr<4>(c);
+        c += row_shr<8>(c);
+        cl = (float)c;
+        lo = (float)(c - (double)cl);
+        double own = 0.0;
 #pragma unroll
-        for (int o = 1; o < 16; o <<= 1) {
-            const float u = __shfl_up(cl, o, 64);
-            if ((lane & 15) >= o) cl += u;
+        for (int i = 0; i < 4; ++i) {
+            const double t = read_lane(c, 16 * i + 15);
+            T[i] = (float)t;
+            own = lane >> 4 == i ? t : own;
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) T[i] = __shfl(cl, 16 * i + 15, 64);
+        te = (float)(own - c);
     }
 };
 // Sum of the tile totals between tiles a and b (exclusive).
@@ -78,14 +98,13 @@ __device__ __forceinline__ float tiles_between(const f32x4& T, int a, int b) {
     for (int i = 0; i < 4; ++i) s += i > a && i < b ? T[i] : 0.f;
     return s;
 }
-// Log decay from token t (tile jt, cl ct) to token s >= t (tile js, cl cs).
-__device__ __forceinline__ float log_decay(const f32x4& T, int js, float cs, int jt, float ct) {
-    return js == jt ? cs - ct : (T[jt & 3] - ct) + tiles_between(T, jt, js) + cs;
+// Log decay from token t to token s >= t of its tile, and of a later tile js.
+__device__ __forceinline__ float log_decay_in(float cs, float slo, float ct, float tlo) { return (cs - ct) + (slo - tlo); }
+__device__ __forceinline__ float log_decay_over(const f32x4& T, int js, float cs, int jt, float te) {
+    return te + tiles_between(T, jt, js) + cs;
 }
 // ... from token t to the piece's end, and from its start to token s.
-__device__ __forceinline__ float log_to_end(const f32x4& T, int jt, float ct) {
-    return (T[jt & 3] - ct) + tiles_between(T, jt, 4);
-}
+__device__ __forceinline__ float log_to_end(const f32x4& T, int jt, float te) { return te + tiles_between(T, jt, 4); }
 __device__ __forceinline__ float log_from_start(const f32x4& T, int js, float cs) {
     return tiles_between(T, -1, js) + cs;
 }

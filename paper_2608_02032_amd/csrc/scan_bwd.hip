@@ -88,7 +88,7 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_contract(
         PieceDecay pd;
         pd.load(dt, A[h], b, pc.L, H, h, t0, t1, lane);
         const bool in = t0 + lane < t1;
-        s_f[0][lane] = in ? fast_exp2(log_to_end(pd.T, lane >> 4, pd.cl)) * pd.d : 0.f;
+        s_f[0][lane] = in ? fast_exp2(log_to_end(pd.T, lane >> 4, pd.te)) * pd.d : 0.f;
         s_f[1][lane] = in ? fast_exp2(log_from_start(pd.T, lane >> 4, pd.cl)) : 0.f;
         if (lane == 0) lda[(b * H + h) * pc.nk + k] = tiles_between(pd.T, -1, 4);
     }
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
     constexpr bool BOTH = N <= 64;  // W and H at once
     __shared__ __attribute__((aligned(16))) char s_xy[2 * kQ * 256], s_w[(BOTH ? 2 : 1) * N * 256];
     char* const s_h = s_w + (BOTH ? N * 256 : 0);
-    __shared__ __attribute__((aligned(16))) float s_cl[kQ], s_dt[kQ];
+    __shared__ __attribute__((aligned(16))) float s_cl[kQ], s_lo[kQ], s_te[kQ], s_dt[kQ];
     __shared__ f32x4 s_T;
     __shared__ float s_r[4][kQ], s_c[kQ], s_v[kQ], s_d[kQ], s_u[kQ], s_bx[kQ];
     static_assert(kQ * MP * 4 <= 2 * kQ * 256, "the summed M2 takes the place of x and dy");
@@ -414,12 +414,14 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
             PieceDecay pd;
             pd.load(dt, Ah, b, pc.L, H, h, t0, t1, lane);
             s_cl[lane] = pd.cl;
+            s_lo[lane] = pd.lo;
+            s_te[lane] = pd.te;
             s_dt[lane] = pd.d;
             if (lane == 0) s_T = pd.T;
         }
         __syncthreads();
         const f32x4 tt = s_T;
-        const float ct = s_cl[tl], dtt = s_dt[tl];
+        const float ct = s_cl[tl], tlo = s_lo[tl], te = s_te[tl], dtt = s_dt[tl];
         if (used) {
             f32x4 xt[4], di[4], bw[4], bd[4];
 #pragma unroll
@@ -438,10 +440,12 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
                         for (int s = 0; s < 4; ++s) g2 = mfma4(a[s], xt[q][s], g2);
                     }
                     const f32x4 cs = *reinterpret_cast<const f32x4*>(s_cl + 16 * j + 4 * g);
+                    const f32x4 slo = *reinterpret_cast<const f32x4*>(s_lo + 16 * j + 4 * g);
                     f32x4 m1, ps;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const float e = fast_exp2(fminf(log_decay(tt, j, cs[r], w, ct), 0.f));
+                        const float l = j == w ? log_decay_in(cs[r], slo[r], ct, tlo) : log_decay_over(tt, j, cs[r], w, te);
+                        const float e = fast_exp2(fminf(l, 0.f));
                         const bool on = j != w || 4 * g + r >= m;  // (selected: 0 times an infinity is not 0)
                         m1[r] = on ? e * g1[j][r] : 0.f;
                         mb[j][r] += on ? dtt * (e * g2[r]) : 0.f;
@@ -483,7 +487,7 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
 #pragma unroll
                     for (int i = 0; i < 4; ++i) bw[i] = mfma4(a[i], bv[q][s], bw[i]);
                 }
-            const float fw = fast_exp2(log_to_end(tt, w, ct));
+            const float fw = fast_exp2(log_to_end(tt, w, te));
             // the chunks of the wave's tokens, each dmem_c for its own tokens only
             const int64_t c0 = (t0 + 16 * w) / pc.S;
             const int nc = SMALL && dmem ? (int)((t0 + (16 * w + 15 < nt ? 16 * w + 15 : nt - 1)) / pc.S - c0) + 1 : 0;
@@ -491,7 +495,9 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
             auto own = [&](int c, float& f) {
                 const int lo = (int)((c0 + c) * pc.S - t0), hi = lo + pc.S < nt ? lo + pc.S : nt;
                 const bool in = tl >= lo && tl < hi;
-                f = in ? fast_exp2(log_decay(tt, (hi - 1) >> 4, s_cl[hi - 1], w, ct)) : 0.f;
+                const float ce = s_cl[hi - 1];
+                f = in ? fast_exp2((hi - 1) >> 4 == w ? log_decay_in(ce, s_lo[hi - 1], ct, tlo)
+                                                      : log_decay_over(tt, (hi - 1) >> 4, ce, w, te)) : 0.f;
                 return in;
             };
             auto dmem_of = [&](int c) { return dmem + ((b * Mcap + c0 + c) * H + h) * (int64_t)(N * kP); };

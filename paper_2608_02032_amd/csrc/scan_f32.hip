@@ -41,7 +41,7 @@ __global__ __launch_bounds__(kFT) void k_fs_state(const T* __restrict__ x, const
                                                   int64_t Mcap, int64_t blocks) {
     constexpr int WN = N / 16 < 4 ? N / 16 : 4, NTW = N / 16 / WN, PT = WN;
     __shared__ __attribute__((aligned(16))) float s_b[kQ][N + 16], s_x[kQ][kP + 16];
-    __shared__ float s_f[kQ], s_cl[kQ];
+    __shared__ float s_f[kQ], s_cl[kQ], s_lo[kQ], s_te[kQ];
     __shared__ f32x4 s_T;
     const int64_t blk = flat_block();
     if (blk >= blocks) return;
@@ -71,15 +71,18 @@ __global__ __launch_bounds__(kFT) void k_fs_state(const T* __restrict__ x, const
         PieceDecay pd;
         pd.load(dt, A[h], b, pc.L, H, h, t0, t1, lane);
         // to the last token of this token's chunk inside the piece
-        float to = log_to_end(pd.T, lane >> 4, pd.cl);
+        float to = log_to_end(pd.T, lane >> 4, pd.te);
         if (pc.S < kQ) {
             int e = lane - (int)((t0 + lane) % pc.S) + pc.S - 1;
             e = e < nt ? e : nt - 1;
-            const float ce = __shfl(pd.cl, e, 64);
-            to = log_decay(pd.T, e >> 4, ce, lane >> 4, pd.cl);
+            const float ce = __shfl(pd.cl, e, 64), le = __shfl(pd.lo, e, 64);
+            to = e >> 4 == lane >> 4 ? log_decay_in(ce, le, pd.cl, pd.lo)
+                                     : log_decay_over(pd.T, e >> 4, ce, lane >> 4, pd.te);
         }
         s_f[lane] = lane < nt ? fast_exp2(to) * pd.d : 0.f;
         s_cl[lane] = pd.cl;
+        s_lo[lane] = pd.lo;
+        s_te[lane] = pd.te;
         if (lane == 0) {
             s_T = pd.T;
             lda[(b * H + h) * pc.nk + k] = tiles_between(pd.T, -1, 4);
@@ -124,7 +127,11 @@ __global__ __launch_bounds__(kFT) void k_fs_state(const T* __restrict__ x, const
                     for (int p = 0; p < PT; ++p) acc[n][p] = mfma4(ab[n], PT == 4 ? vx[p] : vx[p0 + p], acc[n][p]);
             }
         }
-        const float a = lo > 0 ? fast_exp2(log_decay(s_T, (hi - 1) >> 4, s_cl[hi - 1], (lo - 1) >> 4, s_cl[lo - 1])) : 0.f;
+        float a = 0.f;
+        if (lo > 0)
+            a = fast_exp2((hi - 1) >> 4 == (lo - 1) >> 4
+                              ? log_decay_in(s_cl[hi - 1], s_lo[hi - 1], s_cl[lo - 1], s_lo[lo - 1])
+                              : log_decay_over(s_T, (hi - 1) >> 4, s_cl[hi - 1], (lo - 1) >> 4, s_te[lo - 1]));
         T* mo = pc.S <= kQ ? mem + ((b * Mcap + (t0 + lo) / pc.S) * H + h) * (int64_t)(N * kP) : nullptr;
 #pragma unroll
         for (int n = 0; n < NTW; ++n) {
@@ -230,7 +237,7 @@ __global__ __launch_bounds__(kFT, 2) void k_fs_out(const T* __restrict__ x, cons
                                                    int64_t blocks) {
     constexpr int K = N / 16;
     __shared__ __attribute__((aligned(16))) char s_x[kQ * 256], s_w[N * 256];
-    __shared__ __attribute__((aligned(16))) float s_cl[kQ], s_dt[kQ];
+    __shared__ __attribute__((aligned(16))) float s_cl[kQ], s_lo[kQ], s_te[kQ], s_dt[kQ];
     __shared__ f32x4 s_T;
     const int64_t blk = flat_block();
     if (blk >= blocks) return;
@@ -283,13 +290,15 @@ __global__ __launch_bounds__(kFT, 2) void k_fs_out(const T* __restrict__ x, cons
             PieceDecay pd;
             pd.load(dt, A[h], b, pc.L, H, h, t0, t1, lane);
             s_cl[lane] = pd.cl;
+            s_lo[lane] = pd.lo;
+            s_te[lane] = pd.te;
             s_dt[lane] = pd.d;
             if (lane == 0) s_T = pd.T;
         }
         __syncthreads();
         if (!used) continue;
         const f32x4 tt = s_T;
-        const float cs = s_cl[tl];
+        const float cs = s_cl[tl], cl = s_lo[tl];
         f32x4 yi[4], yw[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) yi[i] = yw[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -304,7 +313,8 @@ __global__ __launch_bounds__(kFT, 2) void k_fs_out(const T* __restrict__ x, cons
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if (j <= w && 16 * j < nt) {
-                const f32x4 ct = *reinterpret_cast<const f32x4*>(s_cl + 16 * j + 4 * g);
+                const f32x4 ct = *reinterpret_cast<const f32x4*>((j == w ? s_cl : s_te) + 16 * j + 4 * g);
+                const f32x4 tlo = *reinterpret_cast<const f32x4*>(s_lo + 16 * j + 4 * g);
                 const f32x4 dtt = *reinterpret_cast<const f32x4*>(s_dt + 16 * j + 4 * g);
                 float bq[4];
                 f32x4 yj[4];
@@ -312,7 +322,8 @@ __global__ __launch_bounds__(kFT, 2) void k_fs_out(const T* __restrict__ x, cons
                 for (int i = 0; i < 4; ++i) yj[i] = yi[i];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float e = fast_exp2(fminf(log_decay(tt, w, cs, j, ct[r]), 0.f)) * dtt[r];
+                    const float l = j == w ? log_decay_in(cs, cl, ct[r], tlo[r]) : log_decay_over(tt, w, cs, j, ct[r]);
+                    const float e = fast_exp2(fminf(l, 0.f)) * dtt[r];
                     bq[r] = j == w && 4 * g + r > m ? 0.f : e * g1[j][r];
                     const f32x4 a = lds4(s_x + j * 4096 + off.op[r]);
 #pragma unroll

@@ -55,3 +55,26 @@ def test_scan_f32_forward(c):
     assert_close_slices(to_np(mem)[:, :M], mem_ref, tol, axes_keep=(0, 1, 2), what="mem")
     assert_close_slices(to_np(hl), hl_ref, 1e-5, axes_keep=(0, 1), what="h_last")
     assert np.all(to_np(mem)[:, M:] == 7.0)
+
+
+@pytest.mark.parametrize("N,S", [(16, 16), (64, 5), (128, 32), (64, 64)])
+def test_strong_decays_keep_their_precision(N, S):
+    """Decays of e^-0.8 to e^-1.6 a token: sums over a tile reach 37 (log2), the decays between
+    tokens that still count are a few, and must not carry the rounding of the
+    sums (2^-24 of 37 is 1.5e-6 of a decay).  A memory and an output are then a few
+    tokens' terms with about four roundings of 2^-24 each, in the 2-norm over
+    all of them at most their sum."""
+    import torch
+    w = synth.Workload("decays", 2, 200, 2, 64, N, S, "fp32")
+    print("\n[gpu-case] scan decays %s" % (w,), flush=True)
+    d = synth.forward_inputs(w, seed=N + S)
+    rng = np.random.default_rng(S)
+    dt = rng.uniform(0.05, 0.1, d["dt"].shape).astype(np.float32)
+    A = np.full(2, -16.0, dtype=np.float32)
+    y, mem, _ = dart.ssd_chunk_scan(*(f32_dev(v) for v in (d["x"], dt, A, d["Bm"], d["Cm"])), S)
+    torch.cuda.synchronize()
+    y_ref, _ = oracle.ssd_recurrence(d["x"], dt, A, d["Bm"], d["Cm"])
+    for what, got, ref in (("mem", mem, oracle.chunk_memories(d["x"], dt, A, d["Bm"], S)), ("y", y, y_ref)):
+        err = float(np.linalg.norm(to_np(got) - ref) / np.linalg.norm(ref))
+        print("  %s 2-norm rel err %.2e" % (what, err), flush=True)
+        assert err <= 4 * 2.0 ** -24, what
