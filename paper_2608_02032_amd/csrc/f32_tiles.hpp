@@ -11,6 +11,12 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 __device__ __forceinline__ f32x4 lds4(const char* p) { return *reinterpret_cast<const f32x4*>(p); }
+// A tile's sum of 16 products (four steps), formed of two sums of 8: rounded at
+// fewer of them than one chain, and the two overlap.
+__device__ __forceinline__ f32x4 mfma16(const f32x4& a, const f32x4& b) {
+    const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+    return mfma4(a[1], b[1], mfma4(a[0], b[0], zero)) + mfma4(a[3], b[3], mfma4(a[2], b[2], zero));
+}
 
 // The scan's pieces of a sequence: at most kQ tokens, nested with the memory
 // chunks (a chunk of S >= kQ tokens is nq pieces, the last one shorter; for

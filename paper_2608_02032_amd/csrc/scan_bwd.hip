@@ -371,8 +371,10 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
             for (int q = 0; q < K; ++q) {
                 float c4[4];
                 load4(cr + 16 * q, c4);
+                f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int s = 0; s < 4; ++s) g1[j] = mfma4(c4[s], bv[q][s], g1[j]);
+                for (int s = 0; s < 4; ++s) a = mfma4(c4[s], bv[q][s], a);
+                g1[j] += a;
             }
         }
     }
@@ -434,11 +436,9 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
                 if (j >= w && 16 * j < nt) {
                     f32x4 g2 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const f32x4 a = lds4(s_y + j * 4096 + off.oc[q]);
-#pragma unroll
-                        for (int s = 0; s < 4; ++s) g2 = mfma4(a[s], xt[q][s], g2);
-                    }
+                    for (int q = 0; q < 4; q += 2)
+                        g2 += mfma16(lds4(s_y + j * 4096 + off.oc[q]), xt[q]) +
+                              mfma16(lds4(s_y + j * 4096 + off.oc[q + 1]), xt[q + 1]);
                     const f32x4 cs = *reinterpret_cast<const f32x4*>(s_cl + 16 * j + 4 * g);
                     const f32x4 slo = *reinterpret_cast<const f32x4*>(s_lo + 16 * j + 4 * g);
                     f32x4 m1, ps;
@@ -597,15 +597,13 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
             for (int qn = 0; qn < NQ; ++qn) {
                 f32x4 acc[NV];
 #pragma unroll
-                for (int i = 0; i < NV; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int i = 0; i < NV; ++i) {
+                    acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-#pragma unroll
-                    for (int i = 0; i < NV; ++i) {
-                        const f32x4 a = off.state_n(s_h, qn * NV + i, q);
-#pragma unroll
-                        for (int s = 0; s < 4; ++s) acc[i] = mfma4(a[s], ys[q][s], acc[i]);
-                    }
+                    for (int q = 0; q < 4; q += 2)
+                        acc[i] += mfma16(off.state_n(s_h, qn * NV + i, q), ys[q]) +
+                                  mfma16(off.state_n(s_h, qn * NV + i, q + 1), ys[q + 1]);
+                }
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     float c4[NV];
@@ -694,26 +692,39 @@ __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
         if (bad && j == w) continue;
         if (j >= w && 16 * j < nt) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
+            for (int qn = 0; qn < NQ; ++qn) {
+                f32x4 t[NV];
 #pragma unroll
-                for (int qn = 0; qn < NQ; ++qn) {
+                for (int i = 0; i < NV; ++i) t[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
                     float a[NV];
                     vec(Cm + (row(16 * j + 4 * g + r) * G + grp) * N + 16 * NV * qn + NV * m, a);
 #pragma unroll
-                    for (int i = 0; i < NV; ++i) aB[qn * NV + i] = mfma4(a[i], mb[j][r], aB[qn * NV + i]);
+                    for (int i = 0; i < NV; ++i) t[i] = mfma4(a[i], mb[j][r], t[i]);
                 }
+#pragma unroll
+                for (int i = 0; i < NV; ++i) aB[qn * NV + i] += t[i];
+            }
         }
         if (j <= w) {
+            float mt[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float mt = s_m[(16 * j + 4 * g + r) * MP + tl];
+            for (int r = 0; r < 4; ++r) mt[r] = s_m[(16 * j + 4 * g + r) * MP + tl];
 #pragma unroll
-                for (int qn = 0; qn < NQ; ++qn) {
+            for (int qn = 0; qn < NQ; ++qn) {
+                f32x4 t[2][NV];
+#pragma unroll
+                for (int i = 0; i < NV; ++i) t[0][i] = t[1][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
                     float a[NV];
                     vec(Bm + (row(16 * j + 4 * g + r) * G + grp) * N + 16 * NV * qn + NV * m, a);
 #pragma unroll
-                    for (int i = 0; i < NV; ++i) aC[qn * NV + i] = mfma4(a[i], mt, aC[qn * NV + i]);
+                    for (int i = 0; i < NV; ++i) t[r >> 1][i] = mfma4(a[i], mt[r], t[r >> 1][i]);
                 }
+#pragma unroll
+                for (int i = 0; i < NV; ++i) aC[qn * NV + i] += t[0][i] + t[1][i];
             }
         }
     }

@@ -78,3 +78,23 @@ def test_strong_decays_keep_their_precision(N, S):
         err = float(np.linalg.norm(to_np(got) - ref) / np.linalg.norm(ref))
         print("  %s 2-norm rel err %.2e" % (what, err), flush=True)
         assert err <= 4 * 2.0 ** -24, what
+
+
+@pytest.mark.parametrize("N,S,dtype", [(16, 16, "fp32"), (64, 16, "fp32"), (128, 32, "fp32"), (64, 5, "fp32")])
+def test_gradient_of_C_keeps_the_precision_of_short_sums(N, S, dtype):
+    """dC_s is 64 products over p with the entering state and up to 64 over the piece's tokens.  Formed of
+    sums of 8, a result carries about 4 roundings of its chains, 3 of the tree
+    over them and 3 of the factors (2^-24, 2.5e-8 in the root mean square each: 8e-8)
+    beside the state's own 9e-8: 1.2e-7 in all, 1.9e-7 in one chain.  The bound
+    lies between."""
+    import torch
+    w = synth.Workload("dC", 2, 500, 4, 64, N, S, dtype)
+    print("\n[gpu-case] scan dC %s" % (w,), flush=True)
+    d = synth.forward_inputs(w, seed=N + S)
+    dy = np.random.default_rng(S).standard_normal((2, 500, 4, 64)).astype(np.float32)
+    got = dart.ssd_bwd(*(f32_dev(d[k]) for k in ("x", "dt", "A", "Bm", "Cm")), S, f32_dev(dy))
+    torch.cuda.synchronize()
+    ref = oracle.ssd_bwd(d["x"], d["dt"], d["A"], d["Bm"], d["Cm"], S, dy)["dC"]
+    err = float(np.linalg.norm(to_np(got["dC"]) - ref) / np.linalg.norm(ref))
+    print("  dC 2-norm rel err %.2e" % err, flush=True)
+    assert err <= 1.5e-7
