@@ -153,6 +153,12 @@ __device__ __forceinline__ float col_dot(const f32x4 (&U)[4], const float (&e)[4
     return row4_sum((s[0] + s[1]) + (s[2] + s[3]));
 }
 
+// e^(a - b) of two logits.  They stay in natural units, and their difference is
+// scaled for the base-2 exponential: scaled each, both would be rounded at their own
+// size (the attention's dC 5.9e-7 to 7.9e-7 from 64 bits at N 16 and 64, where
+// 1/sqrt(N) is exact; 3.2e-7 to 4.6e-7 this way, no slower).
+__device__ __forceinline__ float exp_diff(float a, float b) { return fast_exp2((a - b) * kLog2e); }
+
 // ---- forward -----------------------------------------------------------------------
 // Block order: heaviest (latest) tokens first, and blockIdx % (B H) = (b, h), so
 // that for a multiple of eight (b, h) the blocks that read the same memories
@@ -197,7 +203,7 @@ __global__ __launch_bounds__(kFT, 2) void k_fsma(
     if (jb > 0) st.store(s_h[0], s_r[0], eps, normalize, tid);
     TileOff off;
     off.init(m, g);
-    const float sc = kLog2e / sqrtf((float)N);
+    const float isn = 1.0f / sqrtf((float)N);
     float mx = -INFINITY, d = 0.f;
     f32x4 O[4];
 #pragma unroll
@@ -211,10 +217,10 @@ __global__ __launch_bounds__(kFT, 2) void k_fsma(
 #pragma unroll
             for (int i = 0; i < 4; ++i) U[i] = V[i] = f32x4{0.f, 0.f, 0.f, 0.f};
             read_memory<N>(s_h[buf], s_r[buf], off, g, qv, cv, U, V);
-            const float l = col_dot(U, ev) * sc;
+            const float l = col_dot(U, ev) * isn;
             if (j < jt) {  // the four lanes of a column agree
                 const float mn = fmaxf(mx, l);
-                const float al = fast_exp2(mx - mn), pw = fast_exp2(l - mn);
+                const float al = exp_diff(mx, mn), pw = exp_diff(l, mn);
                 mx = mn;
                 d = d * al + pw;
 #pragma unroll
@@ -239,7 +245,7 @@ __global__ __launch_bounds__(kFT, 2) void k_fsma(
         }
         store4(y + yi + 4 * r, v);
     }
-    if (lse && g == 0) lse[bt * H + h] = jt > 0 ? (mx + log2f(d)) * kLn2 : -INFINITY;
+    if (lse && g == 0) lse[bt * H + h] = jt > 0 ? mx + log2f(d) * kLn2 : -INFINITY;
 }
 
 // ... where those blocks leave the chip idle: 16 tokens per block, wave w on the
@@ -293,7 +299,7 @@ __global__ __launch_bounds__(kFT, 2) void k_fsma_split(
         norm_pieces<K>(qv, qw, 4 * g, 16, eps);
         norm_pieces<4>(ev, ew, 16 * g, 4, eps);
     }
-    const float sc = kLog2e / sqrtf((float)N);
+    const float isn = 1.0f / sqrtf((float)N);
     // finite, so that a wave without memories (or with logits of -inf) merges as 0
     float mx = -__FLT_MAX__, d = 0.f;
     f32x4 O[4];
@@ -329,10 +335,10 @@ __global__ __launch_bounds__(kFT, 2) void k_fsma_split(
                     }
                 }
         }
-        const float l = col_dot(U, ev) * sc;
+        const float l = col_dot(U, ev) * isn;
         if (j < jt) {
             const float mn = fmaxf(mx, l);
-            const float al = fast_exp2(mx - mn), pw = fast_exp2(l - mn);
+            const float al = exp_diff(mx, mn), pw = exp_diff(l, mn);
             mx = mn;
             d = d * al + pw;
 #pragma unroll
@@ -355,7 +361,7 @@ __global__ __launch_bounds__(kFT, 2) void k_fsma_split(
         d = 0.f;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-            const float al = fast_exp2(s_o[w][16][lane] - mx);
+            const float al = exp_diff(s_o[w][16][lane], mx);
             d += al * s_o[w][17][lane];
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[i] += al * s_o[w][4 * wave + i][lane];
@@ -365,7 +371,7 @@ __global__ __launch_bounds__(kFT, 2) void k_fsma_split(
         for (int i = 0; i < 4; ++i) yv[i] += f * v[i];
     }
     store4(y + yi, yv);
-    if (lse && g == 0 && wave == 0) lse[bt * H + h] = jt > 0 ? (mx + log2f(d)) * kLn2 : -INFINITY;
+    if (lse && g == 0 && wave == 0) lse[bt * H + h] = jt > 0 ? mx + log2f(d) * kLn2 : -INFINITY;
 }
 
 // ---- forward, bf16 storage ------------------------------------------------------------
@@ -485,7 +491,7 @@ __global__ __launch_bounds__(2 * kFT, N < 128 ? 4 : 2) void k_bsma(
     for (int k = 0; k < 2; ++k) on[k] = (uint32_t)SwzTile<128>::off(m, (32 * k + 8 * g) * 2);
 #pragma unroll
     for (int pt = 0; pt < 4; ++pt) ot[pt].init(4 * g, 16 + 4 * g, 16 * pt, lane);
-    const float sc = kLog2e / sqrtf((float)N);
+    const float isn = 1.0f / sqrtf((float)N);
     float mx = -INFINITY, d = 0.f;
     f32x4 O[4];
 #pragma unroll
@@ -510,16 +516,16 @@ __global__ __launch_bounds__(2 * kFT, N < 128 ? 4 : 2) void k_bsma(
 #pragma unroll
                 for (int i = 0; i < 4; ++i) l4[n & 1] += qv[n][i] * rn[i] * w[i];
             }
-            const float l = row4_sum(l4[0] + l4[1]) * sc;
+            const float l = row4_sum(l4[0] + l4[1]) * isn;
             const bool at = j < jt, grow = at && l > mx;
             if (__builtin_amdgcn_ballot_w64(grow)) {  // (rare after the first memories)
-                const float mn = grow ? l : mx, al = grow ? fast_exp2(mx - mn) : 1.f;
+                const float mn = grow ? l : mx, al = grow ? exp_diff(mx, mn) : 1.f;
                 mx = mn;
                 d *= al;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) O[i] *= al;
             }
-            const float pw = at ? fast_exp2(l - mx) : 0.f;
+            const float pw = at ? exp_diff(l, mx) : 0.f;
             d += pw;
 #pragma unroll
             for (int pt = 0; pt < 4; ++pt) {
@@ -548,7 +554,7 @@ __global__ __launch_bounds__(2 * kFT, N < 128 ? 4 : 2) void k_bsma(
     if (odd || t >= L) return;
     if (jt > 1) {
         const float m1 = so[16], mn = fmaxf(mx, m1);
-        const float a0 = fast_exp2(mx - mn), a1 = fast_exp2(m1 - mn);
+        const float a0 = exp_diff(mx, mn), a1 = exp_diff(m1, mn);
         mx = mn;
         d = d * a0 + so[17] * a1;
 #pragma unroll
@@ -569,7 +575,7 @@ __global__ __launch_bounds__(2 * kFT, N < 128 ? 4 : 2) void k_bsma(
         }
         store4(y + yi + 16 * pt, v);
     }
-    if (lse && g == 0) lse[bt * H + h] = jt > 0 ? (mx + log2f(d)) * kLn2 : -INFINITY;
+    if (lse && g == 0) lse[bt * H + h] = jt > 0 ? mx + log2f(d) * kLn2 : -INFINITY;
 }
 
 // ---- backward ----------------------------------------------------------------------
@@ -597,7 +603,7 @@ __global__ __launch_bounds__(kFT) void k_fbwd_prep(const T* __restrict__ q, cons
     for (int k = 0; k < 4; ++k) store4(eb + row * kP + 16 * k + 4 * g, ev[k]);
 }
 
-// gp and dl, [b][h][memory][Ls]: pass 1 leaves the logit (log2 units) and
+// gp and dl, [b][h][memory][Ls]: pass 1 leaves the logit and
 // dy . V_j there, pass 2 turns them into g p_j and dl_j / sqrt(N) for the
 // memory kernel.  Blocks as in the forward, without those of chunk 0 alone.
 template <typename T, int N>
@@ -639,7 +645,7 @@ __global__ __launch_bounds__(kFT, 2) void k_fbwd_tok(
     off.init(m, g);
     float qv[K][4];
     load_row<float, K>(qb + row * N, g, qv);
-    const float isn = 1.0f / sqrtf((float)N), sc = kLog2e * isn;
+    const float isn = 1.0f / sqrtf((float)N);
     float mx = -INFINITY, d = 0.f, sd = 0.f;
     {
         float cv[K][4], ev[4][4], dv[4][4];
@@ -656,10 +662,10 @@ __global__ __launch_bounds__(kFT, 2) void k_fbwd_tok(
 #pragma unroll
                 for (int i = 0; i < 4; ++i) U[i] = V[i] = f32x4{0.f, 0.f, 0.f, 0.f};
                 read_memory<N>(s_h[buf], s_r[buf], off, g, qv, cv, U, V);
-                const float l = col_dot(U, ev) * sc, dw = col_dot(V, dv);
+                const float l = col_dot(U, ev) * isn, dw = col_dot(V, dv);
                 if (j < jt) {
                     const float mn = fmaxf(mx, l);
-                    const float al = fast_exp2(mx - mn), pw = fast_exp2(l - mn);
+                    const float al = exp_diff(mx, mn), pw = exp_diff(l, mn);
                     mx = mn;
                     d = d * al + pw;
                     sd = sd * al + pw * dw;
@@ -672,8 +678,7 @@ __global__ __launch_bounds__(kFT, 2) void k_fbwd_tok(
             st.store(s_h[buf ^ 1], s_r[buf ^ 1], eps, normalize, tid);
         }
     }
-    const float l2 = mx + log2f(d), Dy = sd / d;
-    const float gate = silu(to_f(z[z_per_head ? bt * H + h : bt]));
+    const float Dy = sd / d, gd = silu(to_f(z[z_per_head ? bt * H + h : bt])) / d;
     if (jt > 0 && g == 0) rdy[bt * H + h] = Dy;
     float ev[4][4], dv[4][4];
     load_row<float, 4>(eb + row * kP, g, ev);
@@ -691,7 +696,7 @@ __global__ __launch_bounds__(kFT, 2) void k_fbwd_tok(
         if (j < jw) {
             float gpv = 0.f, dlv = 0.f;
             if (j < jt) {
-                gpv = gate * fast_exp2(gp[col + j * Ls] - l2);
+                gpv = gd * exp_diff(gp[col + j * Ls], mx);
                 dlv = gpv * (dl[col + j * Ls] - Dy) * isn;
             }
             // every lane of the column has read them before they are replaced

@@ -91,3 +91,21 @@ def test_bf16_forward_rounds_no_operand(N, S):
         rms = float(np.sqrt(np.mean((to_np(lse)[:, S:] - ref[:, S:]) ** 2)))
         print("  rms of the logits' error %.3e" % rms, flush=True)
         assert rms <= 2 * 8 * 4 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("N,S,dtype", [(16, 16, "fp32"), (64, 16, "fp32"), (64, 5, "fp32")])
+def test_weights_carry_no_rounding_of_a_scaled_logit(N, S, dtype):
+    """With 1/sqrt(N) a power of two a logit is its dot product's rounding alone,
+    and a weight exp(l - max) takes one more of the difference.  Logits scaled by
+    log2(e) before the difference are rounded at their own size as well, and dC,
+    whose terms cancel, shows it: 5.9e-7 to 7.9e-7 against 3.2e-7 to 4.6e-7.  The
+    bound lies between."""
+    import torch
+    w = synth.Workload("logits", 2, 500, 4, 64, N, S, dtype)
+    print("\n[gpu-case] sma logits %s" % (w,), flush=True)
+    d, mem, y_ssd, dy = MB.bwd_case(w, seed=N + S)
+    got = MB.run_gpu(w, d, mem, y_ssd, dy)
+    ref = oracle.sma_bwd(d["q"], d["e"], d["Cm"], mem, d["z"], dy, S)["dC"]
+    err = float(np.linalg.norm(got["dC"] - ref) / np.linalg.norm(ref))
+    print("  dC 2-norm rel err %.2e" % err, flush=True)
+    assert err <= 5.2e-7
