@@ -11,7 +11,7 @@
 // their rounding) small.
 //   k_fs_state  per (b, piece, h): for S <= 64 each chunk's memory, and the
 //               piece's contribution to the state, on MFMA;
-//   k_fs_states per (b, h, 1024 elements): the pass over the pieces; a
+//   k_fs_states per (b, h, 256 elements): the pass over the pieces; a
 //               contribution becomes the state entering its piece, and for
 //               S > 64 the contributions of a chunk's pieces its memory;
 //   k_fs_out    per (b, piece, block of heads of one group): y = (decay o
@@ -23,6 +23,8 @@
 // S 256, fp32 (three MFMA kernels with the Gram tiles through memory, and the
 // state pass) 136 -> 105 us; B 64, L 512, 4 heads, N 64, S 16, fp32 (token by
 // token) 258 -> 107; B 2, L 2048, 8 heads, N 128, S 32, bf16 104 -> 58.
+#include <type_traits>
+
 #include "f32_tiles.hpp"
 
 namespace dart {
@@ -30,6 +32,7 @@ namespace {
 
 constexpr int kP = 64;
 constexpr int kFT = 256;
+constexpr int kPassT = 64;
 
 // The waves split the N rows (WN of them, NTW row tiles each) and, for N < 64,
 // the column tiles (PT each).  HBM-bound: N P floats are written per piece.
@@ -41,8 +44,7 @@ __global__ __launch_bounds__(kFT) void k_fs_state(const T* __restrict__ x, const
                                                   int64_t Mcap, int64_t blocks) {
     constexpr int WN = N / 16 < 4 ? N / 16 : 4, NTW = N / 16 / WN, PT = WN;
     __shared__ __attribute__((aligned(16))) float s_b[kQ][N + 16], s_x[kQ][kP + 16];
-    __shared__ float s_f[kQ], s_cl[kQ], s_lo[kQ], s_te[kQ];
-    __shared__ f32x4 s_T;
+    __shared__ float s_f[kQ], s_a[kQ];
     const int64_t blk = flat_block();
     if (blk >= blocks) return;
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
@@ -73,20 +75,19 @@ __global__ __launch_bounds__(kFT) void k_fs_state(const T* __restrict__ x, const
         // to the last token of this token's chunk inside the piece
         float to = log_to_end(pd.T, lane >> 4, pd.te);
         if (pc.S < kQ) {
-            int e = lane - (int)((t0 + lane) % pc.S) + pc.S - 1;
+            int e = lane - lane % (int)pc.S + (int)pc.S - 1;  // (a piece starts with a chunk)
             e = e < nt ? e : nt - 1;
             const float ce = __shfl(pd.cl, e, 64), le = __shfl(pd.lo, e, 64);
             to = e >> 4 == lane >> 4 ? log_decay_in(ce, le, pd.cl, pd.lo)
                                      : log_decay_over(pd.T, e >> 4, ce, lane >> 4, pd.te);
+            // a chunk's decay, at its first token: from the token before it to its last
+            const int q = lane > 0 ? lane - 1 : 0;
+            const float cq = __shfl(pd.cl, q, 64), lq = __shfl(pd.lo, q, 64), tq = __shfl(pd.te, q, 64);
+            s_a[lane] = fast_exp2(e >> 4 == q >> 4 ? log_decay_in(ce, le, cq, lq)
+                                                   : log_decay_over(pd.T, e >> 4, ce, q >> 4, tq));
         }
         s_f[lane] = lane < nt ? fast_exp2(to) * pd.d : 0.f;
-        s_cl[lane] = pd.cl;
-        s_lo[lane] = pd.lo;
-        s_te[lane] = pd.te;
-        if (lane == 0) {
-            s_T = pd.T;
-            lda[(b * H + h) * pc.nk + k] = tiles_between(pd.T, -1, 4);
-        }
+        if (lane == 0) lda[(b * H + h) * pc.nk + k] = tiles_between(pd.T, -1, 4);
     }
 #pragma unroll
     for (int q = 0; q < N / 16; ++q) {
@@ -102,6 +103,7 @@ __global__ __launch_bounds__(kFT) void k_fs_state(const T* __restrict__ x, const
 #pragma unroll
         for (int p = 0; p < PT; ++p) sum[n][p] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int per = pc.S < kQ ? pc.S : kQ;  // tokens of one memory in the piece
+    T* mo = pc.S <= kQ ? mem + ((b * Mcap + k * (pc.Q / per)) * H + h) * (int64_t)(N * kP) : nullptr;
     for (int lo = 0; lo < nt; lo += per) {
         const int hi = lo + per < nt ? lo + per : nt;
         f32x4 acc[NTW][PT];
@@ -109,30 +111,30 @@ __global__ __launch_bounds__(kFT) void k_fs_state(const T* __restrict__ x, const
         for (int n = 0; n < NTW; ++n)
 #pragma unroll
             for (int p = 0; p < PT; ++p) acc[n][p] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int k16 = lo & ~15; k16 < hi; k16 += 16) {
+        for (int k8 = lo & ~3; k8 < hi; k8 += 8) {
+            // the operands of two products are read before the first: short
+            // memories are a chain of such reads
+            float ab[2][NTW];
+            f32x4 vx[2];
 #pragma unroll
-            for (int ks = 0; ks < 16; ks += 4) {
-                if (k16 + ks >= hi || k16 + ks + 4 <= lo) continue;
+            for (int ks = 0; ks < 2; ++ks) {
                 // tokens of another memory leave no operand, whatever they hold
-                const int t = k16 + ks + g;
+                const int t = k8 + 4 * ks + g, tc = t < kQ ? t : kQ - 1;
                 const bool in = t >= lo && t < hi;
-                const float f = s_f[t];
-                float ab[NTW];
+                const float f = s_f[tc];
 #pragma unroll
-                for (int n = 0; n < NTW; ++n) ab[n] = in ? s_b[t][wn * 16 * NTW + NTW * m + n] * f : 0.f;
-                const f32x4 vx = in ? *reinterpret_cast<const f32x4*>(&s_x[t][4 * m]) : f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int n = 0; n < NTW; ++n) ab[ks][n] = in ? s_b[tc][wn * 16 * NTW + NTW * m + n] * f : 0.f;
+                vx[ks] = in ? *reinterpret_cast<const f32x4*>(&s_x[tc][4 * m]) : f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
                 for (int n = 0; n < NTW; ++n)
 #pragma unroll
-                    for (int p = 0; p < PT; ++p) acc[n][p] = mfma4(ab[n], PT == 4 ? vx[p] : vx[p0 + p], acc[n][p]);
-            }
+                    for (int p = 0; p < PT; ++p)
+                        acc[n][p] = mfma4(ab[ks][n], PT == 4 ? vx[ks][p] : vx[ks][p0 + p], acc[n][p]);
         }
-        float a = 0.f;
-        if (lo > 0)
-            a = fast_exp2((hi - 1) >> 4 == (lo - 1) >> 4
-                              ? log_decay_in(s_cl[hi - 1], s_lo[hi - 1], s_cl[lo - 1], s_lo[lo - 1])
-                              : log_decay_over(s_T, (hi - 1) >> 4, s_cl[hi - 1], (lo - 1) >> 4, s_te[lo - 1]));
-        T* mo = pc.S <= kQ ? mem + ((b * Mcap + (t0 + lo) / pc.S) * H + h) * (int64_t)(N * kP) : nullptr;
+        const float a = lo > 0 ? s_a[lo] : 0.f;
 #pragma unroll
         for (int n = 0; n < NTW; ++n) {
 #pragma unroll
@@ -150,6 +152,7 @@ __global__ __launch_bounds__(kFT) void k_fs_state(const T* __restrict__ x, const
 #pragma unroll
             for (int p = 0; p < PT; ++p) sum[n][p] = sum[n][p] * a + acc[n][p];
         }
+        if (mo) mo += H * (int64_t)(N * kP);
     }
     const int64_t base = blk * (int64_t)(N * kP);
 #pragma unroll
@@ -169,15 +172,18 @@ __global__ __launch_bounds__(kFT) void k_fs_state(const T* __restrict__ x, const
 
 // In place: a piece's contribution becomes the state entering it.  Four pieces'
 // contributions are loaded while the four before them are used, ahead of their
-// stores: the chain over the pieces is short, the loads' latency is what bounds
-// it (memory operations complete in order).
+// stores (memory operations complete in order).  Where few waves run, the
+// instructions of one bound it: no index arithmetic or test per piece, the
+// chunks' sums only where they are wanted, and blocks of one wave, which spread
+// over four times as many CUs (64 pieces of 8 heads, N 32: 8.8 us, 14.0 with
+// 256 threads and an index product and three branches per piece).
 template <typename T>
-__global__ __launch_bounds__(256) void k_fs_states(float* dH, const float* __restrict__ lda,
+__global__ __launch_bounds__(kPassT) void k_fs_states(float* dH, const float* __restrict__ lda,
                                                    const float* __restrict__ h0, float* __restrict__ h_last,
                                                    T* __restrict__ mem, Pieces pc, int H, int NP, int64_t Mcap) {
     const int h = blockIdx.y;
     const int64_t b = blockIdx.z, bh = b * H + h;
-    const int e0 = (blockIdx.x * 256 + threadIdx.x) * 4;
+    const int e0 = (blockIdx.x * kPassT + threadIdx.x) * 4;
     if (e0 >= NP) return;
     const float* ld = lda + bh * pc.nk;
     const int64_t step = (int64_t)H * NP;
@@ -185,44 +191,61 @@ __global__ __launch_bounds__(256) void k_fs_states(float* dH, const float* __res
     T* pm = pc.S > kQ ? mem + (b * Mcap * H + h) * (int64_t)NP + e0 : nullptr;
     float hc[4] = {0.f, 0.f, 0.f, 0.f}, own[4] = {0.f, 0.f, 0.f, 0.f};
     if (h0) load4(h0 + bh * (int64_t)NP + e0, hc);
-    int i = 0;  // piece of its chunk
     constexpr int U = 4;
     struct Part {
         float d[U][4], a[U];
     };
-    auto load = [&](int64_t k0, Part& f) __attribute__((always_inline)) {
+    const float *pl = ph, *al = ld;  // the next piece to load: the last one again past the end, not used
+    const float* const ae = ld + pc.nk - 1;
+    auto load = [&](Part& f) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t k = k0 + u < pc.nk ? k0 + u : pc.nk - 1;
-            load4(ph + k * step, f.d[u]);  // (past the end: read, not used)
-            f.a[u] = fast_exp2(ld[k]);
+            load4(pl, f.d[u]);
+            f.a[u] = fast_exp2(*al);
+            const bool more = al < ae;
+            pl += more ? step : 0;
+            al += more;
         }
     };
-    auto run = [&](int64_t k0, const Part& f) __attribute__((always_inline)) {
+    int64_t left = pc.nk;
+    int i = 0;  // piece of its chunk
+    // OWN: with the sums of a chunk's pieces; TAIL: pieces may have run out
+    auto pass = [&](auto OWN) __attribute__((always_inline)) {
+        auto run = [&](const Part& f, auto TAIL) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t k = k0 + u;
-            if (k >= pc.nk) continue;
-            store4(ph + k * step, hc);
+            for (int u = 0; u < U; ++u) {
+                if (decltype(TAIL)::value && u >= left) break;
+                store4(ph, hc);
+                ph += step;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                hc[q] = f.a[u] * hc[q] + f.d[u][q];
-                own[q] = (i == 0 ? 0.f : f.a[u] * own[q]) + f.d[u][q];
+                for (int q = 0; q < 4; ++q) {
+                    hc[q] = f.a[u] * hc[q] + f.d[u][q];
+                    if constexpr (decltype(OWN)::value) own[q] = (i == 0 ? 0.f : f.a[u] * own[q]) + f.d[u][q];
+                }
+                if (decltype(OWN)::value && (++i == pc.nq || u + 1 == left)) {
+                    store4(pm, own);
+                    pm += step;
+                    i = 0;
+                }
             }
-            if (++i == pc.nq || k == pc.nk - 1) {
-                if (pm) store4(pm + k / pc.nq * step, own);
-                i = 0;
-            }
+            left -= U;
+        };
+        Part f0, f1;
+        load(f0);
+        while (left >= 2 * U) {
+            load(f1);
+            run(f0, std::false_type{});
+            load(f0);
+            run(f1, std::false_type{});
         }
+        load(f1);
+        if (left > 0) run(f0, std::true_type{});
+        if (left > 0) run(f1, std::true_type{});
     };
-    Part f0, f1;
-    load(0, f0);
-    for (int64_t k0 = 0; k0 < pc.nk; k0 += 2 * U) {
-        load(k0 + U, f1);
-        run(k0, f0);
-        load(k0 + 2 * U, f0);
-        run(k0 + U, f1);
-    }
+    if (pm)
+        pass(std::true_type{});
+    else
+        pass(std::false_type{});
     if (h_last) store4(h_last + bh * (int64_t)NP + e0, hc);
 }
 
@@ -396,7 +419,7 @@ hipError_t run_fscan(const Shape& s, const void* x, const float* dt, const float
                                                        w.lda, pc, s.H, s.G, s.Mcap, units);
     prof_end(st);
     prof_begin("k_state_pass", st);
-    k_fs_states<T><<<dim3((NP + 1023) / 1024, (unsigned)s.H, (unsigned)s.B), 256, 0, st>>>(
+    k_fs_states<T><<<dim3((NP + 4 * kPassT - 1) / (4 * kPassT), (unsigned)s.H, (unsigned)s.B), kPassT, 0, st>>>(
         w.dH, w.lda, h0, hl, (T*)mem, pc, s.H, NP, s.Mcap);
     prof_end(st);
     const int hpb = piece_heads_per_block(s, pc.nk);
