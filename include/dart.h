@@ -94,7 +94,10 @@ typedef struct {
                                0: z is [B][L] (one scalar gate per token) */
 } dart_sma_opts;
 
-/* Bytes of workspace dart_ssd_chunk_scan needs for `dims`. */
+/* Bytes of workspace dart_ssd_chunk_scan needs for `dims`.  In bf16 storage at N
+ * in {32, 64, 128} with S in {64, 128, 256} one state per chunk; elsewhere a
+ * float state of N x P per (b, h) and piece of at most 64 tokens, whatever S
+ * (1 GiB at L 65536, 32 heads, N 128), of which dart_ssd_bwd takes two. */
 size_t dart_scan_workspace_bytes(const dart_dims* dims);
 
 /*
@@ -160,10 +163,10 @@ dart_status dart_ssd_bwd(const dart_dims* dims, const void* x, const float* dt, 
                          float* dB, float* dC, float* dh0, void* workspace, size_t workspace_bytes,
                          void* stream);
 
-/* Bytes of workspace dart_sma_fwd needs for `dims`: at N in {32, 64, 128} with
- * S in {64, 128, 256} four bytes per element of memories 0..M-2 (bf16: their
- * key and value sides; the fp32 kernels leave it untouched); 0 at other shapes
- * and when M = 1 (workspace may then be NULL). */
+/* Bytes of workspace dart_sma_fwd needs for `dims`: in bf16 storage at N in
+ * {32, 64, 128} with S in {64, 128, 256} four bytes per element of memories
+ * 0..M-2 (their key and value sides); 0 at other shapes, in fp32 storage and
+ * when M = 1 (workspace may then be NULL). */
 size_t dart_sma_workspace_bytes(const dart_dims* dims);
 
 /*

@@ -985,13 +985,11 @@ hipError_t launch_sma_keys(const Shape& s, const SmaArgs& a, const void* mem, vo
 }
 
 size_t sma_workspace_bytes(const Shape& s) {
-    // key and value sides for the bf16 kernels.  The fp32 kernels stage memories
-    // themselves; callers know this size at the shapes where fp32 storage had a
-    // key side too.
-    const bool tuned = s.N >= 32 && (s.S == 64 || s.S == 128 || s.S == 256);
-    if (!tuned) return 0;
+    // key and value sides for the bf16 kernels; the fp32 kernels stage memories
+    // themselves
+    if (!bf16_shape(s)) return 0;
     const int64_t Mp = s.M > 1 ? s.M - 1 : 0;
-    return 4 * s.B * Mp * s.H * (size_t)s.N * s.P;  // two sides in bf16 or one in float
+    return 4 * s.B * Mp * s.H * (size_t)s.N * s.P;
 }
 
 hipError_t launch_sma(const Shape& s, const SmaArgs& a, const void* q, const void* e,

@@ -83,6 +83,13 @@ def test_workspace_sizes(lib):
     assert lib.dart_scan_workspace_bytes(ctypes.byref(bad)) == 0
 
 
+@pytest.mark.parametrize("kw", [dict(dtype="fp32"), dict(chunk=32), dict(dstate=16)])
+def test_sma_forward_asks_for_no_workspace_it_leaves_untouched(lib, kw):
+    """Only the bf16 kernels write key and value sides; the fp32 ones stage the memories themselves."""
+    assert lib.dart_sma_workspace_bytes(ctypes.byref(dims())) > 0
+    assert lib.dart_sma_workspace_bytes(ctypes.byref(dims(**kw))) == 0
+
+
 NULL = None
 
 
