@@ -6,6 +6,7 @@ import json
 import os
 import re
 import subprocess
+import types
 
 import pytest
 
@@ -81,6 +82,16 @@ def test_workspace_sizes(lib):
     assert lib.dart_decode_workspace_bytes(ctypes.byref(dd)) >= 4 * 2 * 4 * (66 + 64)
     bad = dims(headdim=48)
     assert lib.dart_scan_workspace_bytes(ctypes.byref(bad)) == 0
+
+
+@pytest.mark.parametrize("absent", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_torchs_private_queries(monkeypatch, absent):
+    """The two are not public: a torch without either still gives its current stream."""
+    torch = pytest.importorskip("torch")
+    monkeypatch.delattr(torch._C, absent, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    assert dart._stream(None) == 77
+    assert dart._stream(types.SimpleNamespace(cuda_stream=5)) == 5
 
 
 @pytest.mark.parametrize("kw", [dict(dtype="fp32"), dict(chunk=32), dict(dstate=16)])
