@@ -1,8 +1,8 @@
 """Backward of the block kernels where their launch forms change: four channels
 per thread in the convolution (channel counts and strides that are multiples
 of 4, runs of 32 tokens and their remainders, sequences shorter than the
-filter), rows tiled over few or many heads in the step sizes, and one to four
-register pieces of 512 channels per row in the gated RMSNorm."""
+filter), rows tiled over few or many heads in the step sizes, and two to eight
+register pieces of 256 channels per row in the gated RMSNorm."""
 import numpy as np
 import pytest
 

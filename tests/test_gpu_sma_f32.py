@@ -93,6 +93,31 @@ def test_bf16_forward_rounds_no_operand(N, S):
         assert rms <= 2 * 8 * 4 * 2.0 ** -24
 
 
+@pytest.mark.parametrize("zh", [True, False])
+@pytest.mark.parametrize("N,S,dtype", [(32, 17, "bf16"), (32, 32, "bf16"), (64, 17, "bf16"), (64, 32, "bf16"),
+                                       (128, 17, "bf16"), (128, 32, "bf16"), (16, 30, "bf16"), (64, 30, "fp32")])
+def test_forward_options(N, S, dtype, zh):
+    """normalize = 0, and norm weights with y in place of y_ssd, for one gate per head and
+    one per token, over a last block of 64 tokens cut to 22; at N 16 and in fp32 with
+    more such blocks than CUs, past which the whole-block form runs."""
+    import torch
+
+    many = torch.cuda.get_device_properties(0).multi_processor_count // 4 + 1
+    w = synth.Workload("opts_%d_%d" % (N, S), many if N == 16 or dtype == "fp32" else 1, 214, 2, 64, N, S, dtype,
+                       ngroups=2, z_per_head=zh)
+    print("\n[gpu-case] sma options %s" % (w,), flush=True)
+    d, mem, y_ssd = sma_case(w, seed=S + N)
+    rng = np.random.default_rng(N)
+    qw, ew = (rng.uniform(0.5, 1.5, n).astype(np.float32) for n in (N, 64))
+    for inplace, kw in ((False, dict(normalize=False)), (True, dict(q_norm_w=qw, e_norm_w=ew))):
+        y, lse = run_sma(w, d, mem, y_ssd, inplace=inplace,
+                         **{k: f32_dev(v) if k != "normalize" else v for k, v in kw.items()})
+        y_ref, lse_ref = oracle.sma(d["q"], d["e"], d["Cm"], mem, d["z"], y_ssd, S, **kw)
+        assert_close_slices(to_np(y), y_ref, TOL[dtype] if dtype == "fp32" else 2.0 ** -8, what="y %s" % sorted(kw))
+        assert_lse_close(to_np(lse), lse_ref, "fp32")
+        np.testing.assert_array_equal(to_np(y)[:, :S], y_ssd[:, :S].astype(np.float64))
+
+
 @pytest.mark.parametrize("N,S,dtype", [(16, 16, "fp32"), (64, 16, "fp32"), (64, 5, "fp32")])
 def test_weights_carry_no_rounding_of_a_scaled_logit(N, S, dtype):
     """With 1/sqrt(N) a power of two a logit is its dot product's rounding alone,
