@@ -6,7 +6,7 @@ are already resident in HBM:
   forward   chunked SSD scan (k_chunk_state, k_chunk_gram, k_state_pass, k_chunk_out)
             -> state-memory attention + gated residual (k_sma_prep, k_sma)
             on the L = 8192 workload (batch 4, 32 heads, P = 64, N = 128, S = 256);
-  decode    one token (k_decode_partial, k_decode_merge) for batch 64, 32 heads,
+  decode    one token (k_decode_partial, k_decode_state_merge) for batch 64, 32 heads,
             N = 128, S = 256 over a 65536-token context (256 cached memories).
 `value` is forward tokens/s (batch * L / forward time).  Per-kernel times come
 from HIP events the library records around every launch on the launch stream

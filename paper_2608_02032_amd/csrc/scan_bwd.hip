@@ -318,8 +318,9 @@ __global__ __launch_bounds__(256) void k_fs_pass(float* dH, float* dR,
 // dB, dC and dx.
 // 256 registers and at most 68 KB of LDS: two blocks per CU.  W and H stand in
 // LDS together up to N = 64, so that one wait covers both (the whole backward at
-// B 64, L 512, H 4, N 64, S 16: 266 us with H staged over W, 259 so); at N = 128
-// the second tile would leave one block per CU.  SMALL: S < 64.
+// B 64, L 512, H 4, N 64, S 16 is 3 % faster so, 281 us, than with H staged over W);
+// at N = 128 the second tile would leave one block per CU.  SMALL: S < 64.  The
+// registers don't hold it all: 33 to 67 spill at N 64, 112 to 157 at N 128.
 template <typename T, int N, bool SMALL>
 __global__ __launch_bounds__(kBT, 2) void k_fs_tokens(
     const T* __restrict__ x, const float* __restrict__ dt, const float* __restrict__ A,

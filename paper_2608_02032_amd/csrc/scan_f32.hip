@@ -21,8 +21,8 @@
 //
 // Measured, with the kernels these replaced: B 2, L 2048, 24 heads, N 128,
 // S 256, fp32 (three MFMA kernels with the Gram tiles through memory, and the
-// state pass) 136 -> 105 us; B 64, L 512, 4 heads, N 64, S 16, fp32 (token by
-// token) 258 -> 107; B 2, L 2048, 8 heads, N 128, S 32, bf16 104 -> 58.
+// state pass) 132 -> 102 us; B 64, L 512, 4 heads, N 64, S 16, fp32 (token by
+// token) 234 -> 107; B 2, L 2048, 8 heads, N 128, S 32, bf16 99 -> 47.
 #include <type_traits>
 
 #include "f32_tiles.hpp"

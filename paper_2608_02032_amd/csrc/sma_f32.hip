@@ -25,10 +25,10 @@
 //
 // Measured, with the kernels these replaced (VALU dot products per token, and
 // for fp32 storage at the tuned shapes bf16-style kernels of eight fp32 MFMAs a
-// step): B 64, L 512, 4 heads, N 64, S 16, fp32: forward 3557 -> 326 us (102
-// TFLOP/s), token side 6508 -> 832 (100), memory side 2256 -> 347 (96); B 2,
-// L 2048, 8 heads, N 128, S 32, bf16: forward 5394 -> 466; B 2, L 2048, 24
-// heads, N 128, S 256, fp32: 376 -> 135, 336 -> 307 and 578 -> 166.
+// step): B 64, L 512, 4 heads, N 64, S 16, fp32: forward 3523 -> 354 us (94
+// TFLOP/s), token side 6276 -> 908 (92), memory side 2257 -> 369 (90); B 2,
+// L 2048, 8 heads, N 128, S 32, bf16: forward 5414 -> 96; B 2, L 2048, 24
+// heads, N 128, S 256, fp32: 378 -> 125, 328 -> 294 and 577 -> 155.
 //
 //   k_fsma      per (64 tokens, b, h), 16 tokens a wave: U = dH^T (r . Qbar) and
 //               V = dH^T C from the same reads, l = U . Ebar, the online
@@ -168,14 +168,14 @@ __global__ __launch_bounds__(kFT, 2) void k_fsma(
     const T* __restrict__ q, const T* __restrict__ e, const T* __restrict__ Cm,
     const T* __restrict__ mem, const T* __restrict__ z, const T* y_ssd, T* y, float* __restrict__ lse,
     const float* __restrict__ qw, const float* __restrict__ ew, float eps, int normalize,
-    int z_per_head, int64_t L, int H, int G, int S, int64_t Mcap, int BH, int nblk, int used) {
+    int z_per_head, int64_t L, int H, int G, int S, int64_t Mcap, int BH, int nblk) {
     constexpr int K = N / 16;
     __shared__ __attribute__((aligned(16))) char s_h[2][N * 256];
     __shared__ __attribute__((aligned(16))) float s_r[2][N];
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const unsigned blk = (unsigned)flat_block(), bq = blk / (unsigned)BH;
-    if (bq >= (unsigned)used) return;
+    if (bq >= (unsigned)nblk) return;
     const int bh = (int)(blk % (unsigned)BH);
     const int64_t tb = (int64_t)(nblk - 1 - (int)bq) * kFTok;
     const int64_t b = bh / H;
@@ -386,8 +386,8 @@ __global__ __launch_bounds__(kFT, 2) void k_fsma_split(
 // end, so that the heaviest blocks of a small problem are half as long.
 // Bound by the 64 MFMAs per 16 tokens and memory and the vector work beside them
 // (two operations per W element, and the staging), two waves a SIMD at N = 128.
-// B 2, L 2048, 8 heads, N 128, S 32: 85 us (the VALU kernel before the matrix
-// ones 5394, the fp32 instructions 466); 72 with Ebar cut to two bf16 and the
+// B 2, L 2048, 8 heads, N 128, S 32: 96 us (the VALU kernel before the matrix
+// ones 5414, the fp32 instructions 466); 79 with Ebar cut to two bf16 and the
 // hardware's approximate 1/sqrt, which put the logits 1.9e-5 from 64 bits instead
 // of 1.0e-6 (the VALU kernel 1.4e-6).
 template <int N>
@@ -423,8 +423,7 @@ __global__ __launch_bounds__(2 * kFT, N < 128 ? 4 : 2) void k_bsma(
     const bf16* __restrict__ q, const bf16* __restrict__ e, const bf16* __restrict__ Cm,
     const bf16* __restrict__ mem, const bf16* __restrict__ z, const bf16* y_ssd, bf16* y,
     float* __restrict__ lse, const float* __restrict__ qw, const float* __restrict__ ew, float eps,
-    int normalize, int z_per_head, int64_t L, int H, int G, int S, int64_t Mcap, int BH, int nblk,
-    int used) {
+    int normalize, int z_per_head, int64_t L, int H, int G, int S, int64_t Mcap, int BH, int nblk) {
     constexpr int NT = N / 16, KS = N / 32;
     __shared__ __attribute__((aligned(16))) char s_h[2][2][N < 64 ? 64 * 128 : N * 128];  // [buffer][memory of the step]
     __shared__ __attribute__((aligned(16))) float s_r[2][2][N];
@@ -432,7 +431,7 @@ __global__ __launch_bounds__(2 * kFT, N < 128 ? 4 : 2) void k_bsma(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int odd = __builtin_amdgcn_readfirstlane(threadIdx.x / kFT);
     const unsigned blk = (unsigned)flat_block(), bq = blk / (unsigned)BH;
-    if (bq >= (unsigned)used) return;
+    if (bq >= (unsigned)nblk) return;
     const int bh = (int)(blk % (unsigned)BH);
     const int64_t tb = (int64_t)(nblk - 1 - (int)bq) * kFTok;
     const int64_t b = bh / H;
@@ -957,7 +956,7 @@ hipError_t run_fsma(const Shape& s, const SmaArgs& a, const void* q, const void*
     if constexpr (sizeof(T) == 2 && N >= 32) {
         k_bsma<N><<<flat_grid((int64_t)BH * nblk, 2 * kFT), 2 * kFT, 0, st>>>(
             (const T*)q, (const T*)e, (const T*)Cm, (const T*)mem, (const T*)z, (const T*)ys, (T*)y, lse,
-            a.qw, a.ew, a.eps, a.normalize, a.z_per_head, s.L, s.H, s.G, s.S, s.Mcap, BH, nblk, nblk);
+            a.qw, a.ew, a.eps, a.normalize, a.z_per_head, s.L, s.H, s.G, s.S, s.Mcap, BH, nblk);
     } else if ((int64_t)BH * nblk <= device_cu_count()) {
         // (fp32, blocks of 64 tokens at most one per CU: L 512, 2 heads, N 32, S 64
         // 19.0 -> 12.5 us; L 1024, 8 heads, N 64, S 16 184 -> 91; L 2048, 8 heads,
@@ -971,7 +970,7 @@ hipError_t run_fsma(const Shape& s, const SmaArgs& a, const void* q, const void*
     } else {
         k_fsma<T, N><<<flat_grid((int64_t)BH * nblk, kFT), kFT, 0, st>>>(
             (const T*)q, (const T*)e, (const T*)Cm, (const T*)mem, (const T*)z, (const T*)ys, (T*)y, lse,
-            a.qw, a.ew, a.eps, a.normalize, a.z_per_head, s.L, s.H, s.G, s.S, s.Mcap, BH, nblk, nblk);
+            a.qw, a.ew, a.eps, a.normalize, a.z_per_head, s.L, s.H, s.G, s.S, s.Mcap, BH, nblk);
     }
     prof_end(st);
     return hipGetLastError();

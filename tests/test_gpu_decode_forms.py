@@ -1,8 +1,9 @@
 """The decode step's three forms -- one launch (at most sixteen memories and no
 more (batch, head) pairs than compute units), stream plus merge with the state
-updates among the stream's blocks, and apart from it -- on either side of the lines, uniform and ragged, with a token that closes its chunk, one
-that opens one, no memory at all, a row outside the step, and more splits than
-a merging wave has lanes, against the oracle's step."""
+updates among the stream's blocks, and apart from it -- on either side of the
+lines, uniform and ragged, with a token that closes its chunk, one that opens
+one, no memory at all, a row outside the step, and more splits than a merging
+wave has lanes, against the oracle's step."""
 import numpy as np
 import pytest
 
