@@ -357,16 +357,17 @@ __global__ __launch_bounds__(kThreads, (sizeof(T) == 2 && N == 64 ? 4 : 1)) void
     const int64_t id = flat_block(), nstream = BH * ns;
     if (id >= (STATE ? nstream + BH : nstream)) return;  // (past the last block of the grid's last row)
     // A (b, h)'s splits one after the other (1253 us against 1265 with (b, h)
-    // fastest at B 64, context 65536), except in a ragged batch of a multiple of four
+    // fastest at B 64, context 65536), except in a ragged batch of an even number of
     // splits: its short rows leave the later splits empty, and with the split index
     // fastest (8 XCDs, workgroups dealt in turn) some XCDs would get the empty
-    // ones.  (Other counts deal every split over four or eight XCDs either way: 13
-    // splits, 384 (b, h) of fp32, N 64: 127 us, 137 with (b, h) fastest.)  The
-    // state blocks come last and overlap the stream's end.
+    // ones (2048 (b, h), N 128, 2 splits of 255 memories at most: 808 us, 706
+    // so; 768 (b, h), 6 of 96: 124 and 118).  (An odd number deals every split over
+    // all XCDs either way: 13 splits, 384 (b, h) of fp32, N 64: 127 us, 137 with
+    // (b, h) fastest.)  The state blocks come last and overlap the stream's end.
     const bool state = STATE && id >= nstream;
     int64_t bh = id - nstream, b;
     int s = 0, h;
-    const bool bh_fastest = pos_rows && ns % 4 == 0;
+    const bool bh_fastest = pos_rows && ns % 2 == 0;
     if (!state) split_block(id, bh_fastest ? BH : ns, bh_fastest, bh, s);
     div_mod(bh, H, b, h);
     const int g = (int)((int64_t)h * G / H);
