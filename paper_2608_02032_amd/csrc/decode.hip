@@ -31,7 +31,7 @@
 // us a step).
 // Measured, N 128, S 256, bf16, ragged contexts, against the state update in the
 // merging kernel, the first loads after the set-up and the split index fastest:
-// B 16, 24 heads, up to 16384: 72 -> 57 us; B 64, 32 heads, up to 32768: 436 ->
+// B 16, 24 heads, up to 16384: 74 -> 51 us; B 64, 32 heads, up to 32768: 436 ->
 // 374.  B 1, context 4095: 12.1 -> 10.5 (and one launch instead of two).
 #include "dart_common.hpp"
 #include "dart_internal.hpp"
