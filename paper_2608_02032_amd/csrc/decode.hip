@@ -353,7 +353,7 @@ __global__ __launch_bounds__(kThreads, (sizeof(T) == 2 && N == 64 ? 4 : 1)) void
     const T* __restrict__ Cm, const float* __restrict__ qw, const float* __restrict__ ew,
     float* __restrict__ part, float eps, int normalize, int H, int G, int S, int64_t Mcap,
     int64_t pos, const int64_t* __restrict__ pos_rows, int64_t pos_lim, int nsplit, int mps, int ns,
-    int64_t BH) {
+    int64_t BH, bool bh_fastest) {
     const int64_t id = flat_block(), nstream = BH * ns;
     if (id >= (STATE ? nstream + BH : nstream)) return;  // (past the last block of the grid's last row)
     // A (b, h)'s splits one after the other (1253 us against 1265 with (b, h)
@@ -363,11 +363,14 @@ __global__ __launch_bounds__(kThreads, (sizeof(T) == 2 && N == 64 ? 4 : 1)) void
     // ones (2048 (b, h), N 128, 2 splits of 255 memories at most: 808 us, 706
     // so; 768 (b, h), 6 of 96: 124 and 118).  (An odd number deals every split over
     // all XCDs either way: 13 splits, 384 (b, h) of fp32, N 64: 127 us, 137 with
-    // (b, h) fastest.)  The state blocks come last and overlap the stream's end.
+    // (b, h) fastest.  With fewer (b, h) than half the CUs the last splits, together
+    // and mostly empty, would leave the full ones in front to one round of the chip: 32
+    // (b, h) of fp32, N 128, 10 splits of 78: 19.9 us, 31.0 with (b, h) fastest; 64, bf16, 24
+    // of 190: 33.5 and 36.4; 128, 8 of 62: 28.2 and 25.8.)  The state blocks come
+    // last and overlap the stream's end.
     const bool state = STATE && id >= nstream;
     int64_t bh = id - nstream, b;
     int s = 0, h;
-    const bool bh_fastest = pos_rows && ns % 2 == 0;
     if (!state) split_block(id, bh_fastest ? BH : ns, bh_fastest, bh, s);
     div_mod(bh, H, b, h);
     const int g = (int)((int64_t)h * G / H);
@@ -676,7 +679,7 @@ hipError_t run_decode(const Shape& s, const SmaArgs& a, int64_t pos, const int64
         k_decode_partial<T, N, STATE><<<flat_grid(BH * (STATE ? ns + 1 : ns), kThreads), kThreads, 0, st>>>(
             (const T*)x, dt, A, (const T*)Bm, h_state, chunk_acc, (T*)mem, yssd, (const T*)q, (const T*)e,
             (const T*)Cm, a.qw, a.ew, part, a.eps, a.normalize, s.H, s.G, s.S, s.Mcap, pos, pos_rows, pos,
-            nsplit_cap, mps, ns, BH);
+            nsplit_cap, mps, ns, BH, pos_rows && ns % 2 == 0 && 2 * BH >= device_cu_count());
         prof_end(st);
     };
     if (!apart) stream(std::true_type()); else if (m > 0) stream(std::false_type());
