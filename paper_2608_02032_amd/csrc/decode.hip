@@ -610,7 +610,9 @@ __global__ __launch_bounds__(64 * kOneWaves, 2) void k_decode_one(
 }
 
 // One launch where it is the shorter way: at most two memories per wave (one of
-// fp32 at N = 128, unless the blocks fill the chip) and the blocks resident at
+// fp32 at N = 128, unless the blocks fill the chip; twelve in all of fp32 at N = 64
+// where they fill a quarter of it to all: 128 (b, h), 16 memories 15.7 us against 13.8
+// in two launches, 12 memories 13.3 and 13.4) and the blocks resident at
 // once, one per CU at N = 128, two at 64, four at 32, or soon (eight at 16).  bf16,
 // N 128, 16 memories: 256 (b, h) 20.8 us against 23.3 in two launches, 384 33.3
 // against 31.5.  fp32, N 128, 16 memories: 4 (b, h) 21.1 against 13.8.  At fp32,
@@ -621,7 +623,8 @@ template <typename T, int N>
 inline bool decode_in_one(int64_t bh, int64_t m) {
     const int64_t cus = device_cu_count();
     const bool fills = bh >= cus, wide = sizeof(T) == 4 && N == 128;
-    if (forced_mps() || m < 1 || m > (wide && !fills ? 1 : 2) * kOneWaves) return false;
+    const bool some = sizeof(T) == 4 && N == 64 && !fills && 4 * bh >= cus;
+    if (forced_mps() || m < 1 || m > (wide && !fills ? 2 : some ? 3 : 4) * kOneWaves / 2) return false;
     return (wide && fills) || bh <= cus * (N == 128 ? 1 : 128 / N);
 }
 // Otherwise, or without memories: whether the state updates have their own
