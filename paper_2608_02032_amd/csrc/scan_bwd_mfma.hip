@@ -52,6 +52,8 @@
 //   k_sbwd_bc           per (b, c, g): + Mbar^T C into dB, + Mbar B into dC;
 //   k_sbwd_dA           dA summed over batch and chunks.
 // Deterministic (no atomics).
+#include <type_traits>
+
 #include "dart_common.hpp"
 #include "dart_internal.hpp"
 
@@ -288,6 +290,7 @@ __global__ __launch_bounds__(512) void k_sbwd_contract(
 // partial K_c = e^{lda_c} sum R_c . H_[c-1] of this element block
 // (-> Kp[b][h][c][block]) and R_{c-1} = e^{lda_c} R_c + dR_c; dh0 = R_{-1}.
 // ---------------------------------------------------------------------------
+template <int U, bool ALL>
 __global__ __launch_bounds__(256) void k_sbwd_pass2(
     const bf16* __restrict__ dH, const bf16* __restrict__ dR, const float* __restrict__ lda,
     const float* __restrict__ h0, const float* __restrict__ dmem, const float* __restrict__ dhl,
@@ -298,8 +301,10 @@ __global__ __launch_bounds__(256) void k_sbwd_pass2(
     // of those chunks' stores (memory operations complete in order, so a load
     // issued after a store would wait for it too).  B 2, 47 chunks, 16 heads,
     // N 64: 53 us with one chunk at a time, 24 here; B 8, 16 chunks, 24 heads,
-    // N 128: 60 and 58 (U = 2: 28 and 58, U = 8: 24 and 62).
-    constexpr int U = 4;
+    // N 128: 60 and 58 (U = 2: 28 and 58, U = 8: 24 and 62).  ALL: the chunks are U
+    // at most, and the batches past the last one, loaded for nothing, are left out
+    // (B 16, 2 chunks, 32 heads, N 128: 39 us with them, 23 with one chunk at a
+    // time, 21 here).
     __shared__ float red[2][U][4];
     const int h = blockIdx.y;
     const int64_t b = blockIdx.z;
@@ -335,7 +340,8 @@ __global__ __launch_bounds__(256) void k_sbwd_pass2(
     {
         Fwd f0, f1;
         fload(0, f0);
-        for (int64_t c0 = 0; c0 < M; c0 += 2 * U) {
+        if constexpr (ALL) fstep(0, f0);
+        for (int64_t c0 = 0; !ALL && c0 < M; c0 += 2 * U) {
             fload(c0 + U, f1);
             fstep(c0, f0);
             fload(c0 + 2 * U, f0);
@@ -389,7 +395,8 @@ __global__ __launch_bounds__(256) void k_sbwd_pass2(
     {
         Bwd f0, f1;
         bload(M - 1, f0);
-        for (int64_t c0 = M - 1; c0 >= 0; c0 -= 2 * U) {
+        if constexpr (ALL) bstep(M - 1, 0, f0);
+        for (int64_t c0 = M - 1; !ALL && c0 >= 0; c0 -= 2 * U) {
             bload(c0 - U, f1);
             bstep(c0, 0, f0);
             bload(c0 - 2 * U, f0);
@@ -1163,8 +1170,16 @@ hipError_t run_mfma(const Shape& s, const bf16* x, const float* dt, const float*
     prof_end(st);
     const int NP = s.N * s.P;
     prof_begin("k_sbwd_pass2", st);
-    k_sbwd_pass2<<<dim3((unsigned)w.nkp, (unsigned)s.H, (unsigned)s.B), 256, 0, st>>>(
-        w.dH, w.dR, w.lda, h0, dmem, dhl, w.Hb, w.Wb, w.Kp, dh0, s.H, NP, s.M, s.Mcap);
+    auto pass2 = [&](auto u, auto all) {
+        const dim3 pg((unsigned)w.nkp, (unsigned)s.H, (unsigned)s.B);
+        k_sbwd_pass2<decltype(u)::value, decltype(all)::value><<<pg, 256, 0, st>>>(
+            w.dH, w.dR, w.lda, h0, dmem, dhl, w.Hb, w.Wb, w.Kp, dh0, s.H, NP, s.M, s.Mcap);
+    };
+    using std::integral_constant;
+    if (s.M == 1) pass2(integral_constant<int, 1>(), std::true_type());
+    else if (s.M == 2) pass2(integral_constant<int, 2>(), std::true_type());
+    else if (s.M <= 4) pass2(integral_constant<int, 4>(), std::true_type());
+    else pass2(integral_constant<int, 4>(), std::false_type());
     prof_end(st);
     prof_begin("k_sbwd_group", st);
     k_sbwd_group<N, S><<<(unsigned)(nbcg * (S / 64)), 512, 0, st>>>(x, dt, Cm, dy, w.rec, w.Hb, w.Wb, dB, dC,

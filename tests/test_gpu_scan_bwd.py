@@ -131,3 +131,10 @@ def test_ssd_bwd_full_size_sampled_rows():
                              dmem=dmem[sl])
         row = {k: got[k][sl] for k in ("dx", "ddt", "dB", "dC", "dh0")}
         check(row, ref, TOL["bf16"], keys=tuple(row))
+
+
+@pytest.mark.parametrize("M", [1, 2, 3, 4, 5])
+def test_matrix_form_of_few_chunks(M):
+    """The pass over the chunks takes up to four of them at once, then in batches."""
+    w = synth.Workload("bf16_M%d" % M, 2, 64 * M - 5, 4, 64, 32, 64, "bf16", ngroups=2)
+    run_case(w, seed=M, mcap=M + 1)
