@@ -40,9 +40,9 @@
 //                       dC += g p_j X_j on MFMA; it writes g p_j[t] over the
 //                       logit for the memory kernel and per-head-block partial
 //                       sums of dQbar, dEbar, dC
-//   k_bwd_mem           one workgroup per (b, h, 4 memories): M1 and M2 over
-//                       the later tokens, the token stream copied into LDS by
-//                       DMA once for the four memories, dl_j[t] formed from
+//   k_bwd_mem           one workgroup per (b, h, 4 or 2 memories): M1 and M2
+//                       over the later tokens, the token stream copied into LDS
+//                       by DMA once for these memories, dl_j[t] formed from
 //                       the stored g p_j, dwy_j and Dy and applied to the
 //                       MFMA operand fragments in registers; then the
 //                       epilogue above.  Heavy memories (small j) go first.
@@ -60,7 +60,6 @@ constexpr int kP = 64;
 constexpr int kTokWaves = 4;               // 16-token groups (and copying waves) per
                                            // k_bwd_tokens workgroup; two waves a group
 constexpr int kTokBlock = 16 * kTokWaves;  // tokens per k_bwd_tokens workgroup
-constexpr int kMemJ = 4;                   // memories per k_bwd_mem workgroup
 constexpr int kHeadsPerBlock = 8;
 
 // Sum over the 64 lanes in every lane (DPP within rows, then row swaps); call
@@ -773,14 +772,14 @@ __global__ __launch_bounds__(512) void k_bwd_tokens(
 }
 
 // ---- memory-side gradients -------------------------------------------------------
-// Workgroup (b, h, block of kMemJ memories j0 .. j0 + kMemJ - 1), 8 waves:
+// Workgroup (b, h, block of J = 2 PW memories j0 .. j0 + J - 1), 8 waves:
 //   M1_j = sum_t C_t^T (g p_j[t] dy_t),   M2_j = sum_t Qbar'_t^T (ln2 dl_j[t] Ebar_t)
 // over the tokens t >= (j + 1) S.  The token stream (C, Qbar', dy, Ebar in the
 // storage dtype, unscaled) is read once for all the block's memories: TB
 // tokens per step are copied into LDS by DMA one step ahead, and the
 // per-(memory, token) factors g p_j and ln2 dl_j (zero where memory j is not
-// attended) scale the dy and Ebar fragments in registers.  Wave w owns half of
-// the output columns (p = 32 (w % 2) .. + 31) of memory w / 2 over every n
+// attended) scale the dy and Ebar fragments in registers.  Wave w owns PW of the
+// four column tiles (at PW = 2 p = 32 (w % 2) .. + 31 of memory w / 2) over every n
 // tile, so each scaled fragment feeds N/16 MFMAs of each product, no two waves
 // scale the same fragment, and a wave reads one memory's factors (16 bytes per
 // lane and four tokens, as dear to LDS as the operands: one p tile of two
@@ -804,7 +803,7 @@ __device__ __forceinline__ Frag<T> scale_frag(Frag<T> f, const f32x4& s0, const 
     return r;
 }
 
-template <typename T, int N>
+template <typename T, int N, int PW>
 __global__ __launch_bounds__(512) void k_bwd_mem(const T* __restrict__ qb,
                                                  const T* __restrict__ ebt,
                                                  const T* __restrict__ Cm, const T* __restrict__ dy,
@@ -815,7 +814,7 @@ __global__ __launch_bounds__(512) void k_bwd_mem(const T* __restrict__ qb,
                                                  float* __restrict__ dmem, float eps, int normalize,
                                                  int64_t L, int64_t Ls, int H, int G, int S,
                                                  int64_t Mcap, int64_t Mp, int64_t BH) {
-    constexpr int J = kMemJ;
+    constexpr int J = 2 * PW;  // memories: 4 / PW waves each, of PW p tiles
     constexpr int ES = (int)sizeof(T);
     constexpr int TB = kMemTok;
     constexpr int RBN = N * ES, RBP = kP * ES;
@@ -824,8 +823,7 @@ __global__ __launch_bounds__(512) void k_bwd_mem(const T* __restrict__ qb,
     using SwN = std::conditional_t<(RBN >= 256), SwzTilePair<RBN>, SwzTile<RBN>>;
     constexpr int STAGE = 2 * CT + 2 * DT;
     constexpr int NT = N / 16;  // n tiles per wave
-    constexpr int PW = 2;       // p tiles per wave
-    static_assert(NT >= 1 && J == 4, "a wave per memory and half of the p tiles");
+    static_assert(NT >= 1 && (PW == 1 || PW == 2), "eight waves share J memories' p tiles");
     constexpr int NS = 3;
     // DMA copies per copying wave per step (every tile is a multiple of 256 pieces)
     constexpr int CPW = (2 * TB * RBN / 16 + 2 * TB * RBP / 16) / 256;
@@ -836,8 +834,8 @@ __global__ __launch_bounds__(512) void k_bwd_mem(const T* __restrict__ qb,
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
     const int col = lane & 15, grp = lane >> 4;
-    const int pt0 = PW * (wave & 1);               // first p tile of the wave
-    const int jl = wave >> 1;                      // its memory
+    const int pt0 = PW * (wave % (4 / PW));        // first p tile of the wave
+    const int jl = wave / (4 / PW);                // its memory
     const int64_t jb = (int64_t)blockIdx.x / BH;
     const int64_t bh = (int64_t)blockIdx.x - jb * BH;
     const int64_t b = bh / H;
@@ -895,7 +893,7 @@ __global__ __launch_bounds__(512) void k_bwd_mem(const T* __restrict__ qb,
                             (int64_t)G * RBP, TB, rv, wave, 4, lane);
     };
     // factors of step st: g p_j[t] and ln2 dl_j[t] = ln2 g p_j (dwy_j - Dy),
-    // loaded and stored by waves 4-7 (thread ft = tid - 256 of J * TB = 256)
+    // loaded and stored by waves 4-7 (thread ft = tid - 256 of J * TB)
     static_assert(J * TB <= 256, "one factor per thread of waves 4-7");
     // The loaded values stay raw until the store at the end of the step, so the
     // wait for the loads falls behind the step's MFMA work.
@@ -1233,10 +1231,17 @@ hipError_t run_bwd(const Shape& s, const SmaArgs& a, const void* q, const void* 
     }
     const int64_t BH = s.B * s.H;
     prof_begin("k_bwd_mem", st);
-    const int64_t njb = (s.Mcap + kMemJ - 1) / kMemJ;
-    k_bwd_mem<T, N><<<(unsigned)(BH * njb), 512, 0, st>>>(
-        (const T*)w.qb, (const T*)w.ebt, (const T*)Cm, (const T*)dy, (const T*)mem, w.gp, w.gd, w.rdy, dmem, a.eps,
-        a.normalize, s.L, Ls, s.H, s.G, s.S, s.Mcap, Mp, BH);
+    auto mem_side = [&](auto pw) {
+        constexpr int PW = decltype(pw)::value;
+        const int64_t njb = (s.Mcap + 2 * PW - 1) / (2 * PW);
+        k_bwd_mem<T, N, PW><<<(unsigned)(BH * njb), 512, 0, st>>>(
+            (const T*)w.qb, (const T*)w.ebt, (const T*)Cm, (const T*)dy, (const T*)mem, w.gp, w.gd, w.rdy, dmem,
+            a.eps, a.normalize, s.L, Ls, s.H, s.G, s.S, s.Mcap, Mp, BH);
+    };
+    // one or two memories would leave half or more of the waves of the wider form idle
+    // (B 16, L 500, 32 heads, N 128, S 256, one memory: 81 us, 61 so; 32 heads of N 64,
+    // B 12: 40 and 29)
+    if (Mp <= 2) mem_side(std::integral_constant<int, 1>()); else mem_side(std::integral_constant<int, 2>());
     prof_end(st);
     prof_begin("k_bwd_finish", st);
     k_bwd_finish<T, N><<<rblocks, 256, 0, st>>>((const T*)q, (const T*)e, (const T*)z, a.qw, a.ew,

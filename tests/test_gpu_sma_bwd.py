@@ -156,3 +156,24 @@ def test_sma_bwd_full_size_sampled():
                             axes_keep=(0, 1, 2), what="dmem head %d" % h)
         assert_close_slices(got["dz"][:, :, h:h + 1], r1["dz"], tol, axes_keep=(0, 2),
                             what="dz head %d" % h)
+
+
+@pytest.mark.parametrize("N,S", [(32, 64), (64, 128), (128, 64)])
+@pytest.mark.parametrize("M", [2, 3, 4])
+def test_sma_bwd_few_memories(M, N, S):
+    """Two memories share a workgroup of the memory side up to two attended ones, four
+    beyond; slots past them are zero.  (With one memory the weight is one and dq
+    and de are zero: nothing to compare.)"""
+    w = synth.Workload("few_M%d_N%d" % (M, N), 2, S * M - 9, 2, 64, N, S, "bf16", mem_capacity=M + 2)
+    announce("sma_bwd %s" % (w,))
+    d, mem, y_ssd, dy = bwd_case(w, seed=M + N)
+    got = run_gpu(w, d, mem, y_ssd, dy)
+    ref = oracle.sma_bwd(d["q"], d["e"], d["Cm"], mem, d["z"], dy, S)
+    if M > 2:
+        compare(w, got, ref, TOL["bf16"])
+        return
+    assert_close_slices(got["dC"], ref["dC"], TOL["bf16"], what="dC")
+    assert_close_slices(got["dmem"][:, 0], ref["dmem"][:, 0], TOL["bf16"], what="dmem")
+    assert np.all(got["dmem"][:, 1:] == 0)
+    for k, scale in (("dq", "dC"), ("de", "dC")):
+        assert np.abs(got[k]).max() <= 1e-5 * np.abs(got[scale]).max(), k
