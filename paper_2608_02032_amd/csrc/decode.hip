@@ -609,23 +609,24 @@ __global__ __launch_bounds__(64 * kOneWaves, 2) void k_decode_one(
     y[(b * H + h) * kP + tid] = from_f<T>(ys + silu(zz) * R);
 }
 
-// One launch where it is the shorter way: at most two memories per wave (one of
-// fp32 at N = 128, unless the blocks fill the chip; twelve in all of fp32 at N = 64
-// where they fill a quarter of it to all: 128 (b, h), 16 memories 15.7 us against 13.8
-// in two launches, 12 memories 13.3 and 13.4) and the blocks resident at
-// once, one per CU at N = 128, two at 64, four at 32, or soon (eight at 16).  bf16,
-// N 128, 16 memories: 256 (b, h) 20.8 us against 23.3 in two launches, 384 33.3
-// against 31.5.  fp32, N 128, 16 memories: 4 (b, h) 21.1 against 13.8.  At fp32,
-// N = 128, the streaming kernel has one wave a SIMD and the one launch is the
-// shorter way for any number of blocks (2048 (b, h): 1 memory 76 us against 84,
-// 16 272 against 297).
+// One launch where it is the shorter way: at most two memories per wave and the
+// blocks resident at once, one per CU at N = 128, two at 64, four at 32, or soon
+// (eight at 16).  bf16, N 128, 16 memories: 256 (b, h) 20.8 us against 23.3 in two
+// launches, 384 33.3 against 31.5.  In fp32 twelve memories and more are better
+// spread over the chip where two splits of each (b, h) fit on it (N = 128: 32 (b, h)
+// of 12 memories 19.3 us against 16.1, of 10 15.8 and 15.1; 128 of 9 19.3 and 22.0;
+// 240 of 16 33.0 and 39.0), or the blocks fill a quarter of it to all (N = 64: 128
+// (b, h) of 16 memories 15.7 against 13.8, of 12 13.3 and 13.4).  At fp32, N = 128,
+// the streaming kernel has one wave a SIMD and the one launch is the shorter way
+// for any number of blocks (2048 (b, h): 1 memory 76 us against 84, 16 272 against
+// 297).
 template <typename T, int N>
 inline bool decode_in_one(int64_t bh, int64_t m) {
     const int64_t cus = device_cu_count();
-    const bool fills = bh >= cus, wide = sizeof(T) == 4 && N == 128;
-    const bool some = sizeof(T) == 4 && N == 64 && !fills && 4 * bh >= cus;
-    if (forced_mps() || m < 1 || m > (wide && !fills ? 2 : some ? 3 : 4) * kOneWaves / 2) return false;
-    return (wide && fills) || bh <= cus * (N == 128 ? 1 : 128 / N);
+    const bool wide = sizeof(T) == 4 && N == 128;
+    const bool spread = wide ? 2 * bh <= cus : sizeof(T) == 4 && N == 64 && 4 * bh >= cus && bh < cus;
+    if (forced_mps() || m < 1 || m > 2 * kOneWaves || (spread && m >= 12)) return false;
+    return wide || bh <= cus * (N == 128 ? 1 : 128 / N);
 }
 // Otherwise, or without memories: whether the state updates have their own
 // kernel.  In the stream they save a pass over the chip (context 20000, B 8, 24

@@ -89,9 +89,9 @@ def test_forced_split_size_takes_the_step_in_splits():
 @pytest.mark.parametrize("c", [
     # (b, h) pairs in CUs, N, dtype, memories: either side of each line between the forms
     (1.0, 128, "bf16", 1), (1.5, 128, "bf16", 1), (1.5, 128, "bf16", 2), (1.5, 128, "bf16", 3), (0.1, 128, "fp32", 8),
-    (0.1, 128, "fp32", 9), (1.0, 128, "fp32", 16), (1.5, 128, "fp32", 17), (2.0, 64, "fp32", 1), (2.1, 64, "fp32", 1),
+    (0.1, 128, "fp32", 9), (0.5, 128, "fp32", 11), (0.5, 128, "fp32", 12), (0.6, 128, "fp32", 12), (1.0, 128, "fp32", 16), (1.5, 128, "fp32", 17), (2.0, 64, "fp32", 1), (2.1, 64, "fp32", 1),
     (2.1, 64, "bf16", 3), (4.1, 32, "fp32", 2), (4.0, 32, "bf16", 16), (8.0, 16, "fp32", 16), (8.1, 16, "bf16", 1),
-    (1.5, 64, "bf16", 0), (0.5, 64, "fp32", 12), (0.5, 64, "fp32", 13)], ids=lambda c: "cus%s_N%d_%s_m%d" % c)
+    (1.5, 64, "bf16", 0), (0.5, 64, "fp32", 11), (0.5, 64, "fp32", 12)], ids=lambda c: "cus%s_N%d_%s_m%d" % c)
 @pytest.mark.parametrize("ragged", [False, True])
 def test_decode_step_forms_by_blocks(c, ragged):
     """Every form of the step (one launch; state updates in the stream; in their own kernel),
