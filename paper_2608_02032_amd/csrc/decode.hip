@@ -356,18 +356,8 @@ __global__ __launch_bounds__(kThreads, (sizeof(T) == 2 && N == 64 ? 4 : 1)) void
     int64_t BH, bool bh_fastest) {
     const int64_t id = flat_block(), nstream = BH * ns;
     if (id >= (STATE ? nstream + BH : nstream)) return;  // (past the last block of the grid's last row)
-    // A (b, h)'s splits one after the other (1253 us against 1265 with (b, h)
-    // fastest at B 64, context 65536), except in a ragged batch of an even number of
-    // splits: its short rows leave the later splits empty, and with the split index
-    // fastest (8 XCDs, workgroups dealt in turn) some XCDs would get the empty
-    // ones (2048 (b, h), N 128, 2 splits of 255 memories at most: 808 us, 706
-    // so; 768 (b, h), 6 of 96: 124 and 118).  (An odd number deals every split over
-    // all XCDs either way: 13 splits, 384 (b, h) of fp32, N 64: 127 us, 137 with
-    // (b, h) fastest.  With fewer (b, h) than half the CUs the last splits, together
-    // and mostly empty, would leave the full ones in front to one round of the chip: 32
-    // (b, h) of fp32, N 128, 10 splits of 78: 19.9 us, 31.0 with (b, h) fastest; 64, bf16, 24
-    // of 190: 33.5 and 36.4; 128, 8 of 62: 28.2 and 25.8.)  The state blocks come
-    // last and overlap the stream's end.
+    // A (b, h)'s splits one after the other, or with (b, h) fastest where the host says
+    // so.  The state blocks come last and overlap the stream's end.
     const bool state = STATE && id >= nstream;
     int64_t bh = id - nstream, b;
     int s = 0, h;
@@ -615,8 +605,8 @@ __global__ __launch_bounds__(64 * kOneWaves, 2) void k_decode_one(
 // launches, 384 33.3 against 31.5.  In fp32 twelve memories and more are better
 // spread over the chip where two splits of each (b, h) fit on it (N = 128: 32 (b, h)
 // of 12 memories 19.3 us against 16.1, of 10 15.8 and 15.1; 128 of 9 19.3 and 22.0;
-// 240 of 16 33.0 and 39.0), or the blocks fill a quarter of it to all (N = 64: 128
-// (b, h) of 16 memories 15.7 against 13.8, of 12 13.3 and 13.4).  At fp32, N = 128,
+// 240 of 16 33.0 and 39.0), or they are a quarter to half of its CUs (N = 64: 128
+// (b, h) of 16 memories 15.7 against 13.8, of 12 13.3 and 13.4; 160 of 16 17.2 and 19.8).  At fp32, N = 128,
 // the streaming kernel has one wave a SIMD and the one launch is the shorter way
 // for any number of blocks (2048 (b, h): 1 memory 76 us against 84, 16 272 against
 // 297).
@@ -624,7 +614,7 @@ template <typename T, int N>
 inline bool decode_in_one(int64_t bh, int64_t m) {
     const int64_t cus = device_cu_count();
     const bool wide = sizeof(T) == 4 && N == 128;
-    const bool spread = wide ? 2 * bh <= cus : sizeof(T) == 4 && N == 64 && 4 * bh >= cus && bh < cus;
+    const bool spread = wide ? 2 * bh <= cus : sizeof(T) == 4 && N == 64 && 4 * bh >= cus && 2 * bh <= cus;
     if (forced_mps() || m < 1 || m > 2 * kOneWaves || (spread && m >= 12)) return false;
     return wide || bh <= cus * (N == 128 ? 1 : 128 / N);
 }
@@ -641,6 +631,24 @@ inline bool state_apart(int64_t bh, int64_t m) {
     const int64_t cus = device_cu_count();
     return m == 0 || bh * m * N * kP * (int64_t)sizeof(T) >= (int64_t)4 << 30 ||
            (bh > cus && m * (int64_t)sizeof(T) <= 4) || (sizeof(T) == 4 && N == 128 && bh >= cus);
+}
+
+// Whether the stream's blocks go with (b, h) fastest, not a (b, h)'s splits one after
+// the other (1253 us against 1265 at B 64, context 65536).  In a ragged batch of an
+// even number of splits: its short rows leave the later splits empty, and with the
+// split index fastest (8 XCDs, workgroups dealt in turn) a split falls to 8 / k of
+// the XCDs only, k the common factor of 8 and the number, some of which then get the
+// empty ones (2048 (b, h), N 128, 2 splits of 255 memories at most: 808 us, 706 so;
+// 240, 8 of 64: 73 and 53).  Odd numbers deal every split over all of them (13
+// splits, 384 (b, h) of fp32, N 64: 127 us, 137 with (b, h) fastest), and with few
+// blocks the last splits, together and mostly empty, would leave the full ones in
+// front to one round of the chip (32 (b, h) of fp32, N 128, 10 splits: 19.9 and
+// 31.0).  Over 526 shapes, bf16 and fp32, N 64 and 128, 8 to 960 (b, h), the
+// line lies at CUs / k (b, h): 0.90 to 1.00 of the time below it, up
+// to 1.75 times past it.
+inline bool stream_bh_fastest(int64_t bh, int ns) {
+    const int k = ns % 8 == 0 ? 8 : ns % 4 == 0 ? 4 : ns % 2 == 0 ? 2 : 1;
+    return k > 1 && bh * k > device_cu_count();
 }
 
 // Number of splits of a step that attends m memories.
@@ -683,7 +691,7 @@ hipError_t run_decode(const Shape& s, const SmaArgs& a, int64_t pos, const int64
         k_decode_partial<T, N, STATE><<<flat_grid(BH * (STATE ? ns + 1 : ns), kThreads), kThreads, 0, st>>>(
             (const T*)x, dt, A, (const T*)Bm, h_state, chunk_acc, (T*)mem, yssd, (const T*)q, (const T*)e,
             (const T*)Cm, a.qw, a.ew, part, a.eps, a.normalize, s.H, s.G, s.S, s.Mcap, pos, pos_rows, pos,
-            nsplit_cap, mps, ns, BH, pos_rows && ns % 2 == 0 && 2 * BH >= device_cu_count());
+            nsplit_cap, mps, ns, BH, pos_rows && stream_bh_fastest(BH, ns));
         prof_end(st);
     };
     if (!apart) stream(std::true_type()); else if (m > 0) stream(std::false_type());
